@@ -126,7 +126,7 @@ Tuning tuning_from_env() {
     t.attn_min_split = env_int("D3_ATTN_MIN_SPLIT", 64, 65536, 128) / 64 * 64;
     const int pc = env_int("D3_PREFILL_COLS", 64, kPassCols, 0);
     t.prefill_cols = pc % 64 == 0 ? pc : 0;
-    t.prompt_ks = env_int("D3_PROMPT_KS", 1, 4, 0);
+    t.prompt_ks = env_int("D3_PROMPT_KS", 1, 8, 0);
     return t;
 }
 }  // namespace d3

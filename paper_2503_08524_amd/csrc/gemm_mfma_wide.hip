@@ -384,26 +384,38 @@ namespace {
 
 int launch_config(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups, int force_ct);
 
+// The launch for columns [first, first + n) of a pass.
+GemvArgs columns_of(const GemvArgs& a, int first, int n) {
+    GemvArgs g = a;
+    g.ncols = n;
+    g.x_hi += (size_t)first * a.x_stride; g.x_lo += (size_t)first * a.x_stride;
+    if (g.out) g.out += (size_t)first * a.out_stride;
+    if (g.out_hi) { g.out_hi += (size_t)first * a.out_stride; g.out_lo += (size_t)first * a.out_stride; }
+    if (g.ssq_in) g.ssq_in += (size_t)first * kSsqStride;
+    if (g.ssq_out) g.ssq_out += (size_t)first * kSsqStride;
+    return g;
+}
+
 // Column halves of a pass of more than 64 columns, both with the 64-column kernel (the same row groups, so the partial
 // sums of squares of all columns have one layout).
 int launch_halves(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {
-    GemvArgs lo = a;
-    lo.ncols = 64;
-    int rc = launch_config(lo, mode, n_cu, tn, s, n_groups, 4);
+    int rc = launch_config(columns_of(a, 0, 64), mode, n_cu, tn, s, n_groups, 4);
     if (rc != 0) return rc;
-    GemvArgs hi = a;
-    hi.ncols = a.ncols - 64;
-    hi.x_hi += (size_t)64 * a.x_stride; hi.x_lo += (size_t)64 * a.x_stride;
-    if (hi.out) hi.out += (size_t)64 * a.out_stride;
-    if (hi.out_hi) { hi.out_hi += (size_t)64 * a.out_stride; hi.out_lo += (size_t)64 * a.out_stride; }
-    if (hi.ssq_in) hi.ssq_in += (size_t)64 * kSsqStride;
-    if (hi.ssq_out) hi.ssq_out += (size_t)64 * kSsqStride;
-    return launch_config(hi, mode, n_cu, tn, s, nullptr, 4);
+    return launch_config(columns_of(a, 64, a.ncols - 64), mode, n_cu, tn, s, nullptr, 4);
 }
 
 }  // namespace
 
 int launch_gemm_mfma_wide(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {
+    // A prompt chunk whose contraction is too short for the LDS-tiled kernel: 64 columns at a time, one layout of the partial
+    // sums of squares for all of them
+    if (a.ncols > 128) {
+        for (int c0 = 0; c0 < a.ncols; c0 += 64) {
+            const int rc = launch_config(columns_of(a, c0, a.ncols - c0 < 64 ? a.ncols - c0 : 64), mode, n_cu, tn, s, n_groups, 4);
+            if (rc != 0) return rc;
+        }
+        return 0;
+    }
     // More than 64 columns: one launch of the 128-column kernel (four waves per workgroup) when the matrix is small enough
     // for its fixed costs to matter, else two of the 64-column kernel, whose eight-wave workgroups stream a large matrix
     // faster (70B shape, per 128 columns: gate/up 940 MB 396 against 330 us, down 470 MB 252 against 224 us; QKV 168 MB 85

@@ -1,43 +1,44 @@
-// Tiled GEMM on the matrix cores for the prompt pass, 129..2048 activation columns per launch:
+// Tiled GEMM on the matrix cores for the prompt pass, up to 2048 activation columns per launch:
 // out[col][row] = sum_k W[row][k] * x[col][k], bf16 weights, activations x = hi + lo (two bf16 halves).
 //
 // With hundreds of columns the contraction is compute-bound (the prompt pass is the one part of the path that is), so
-// the design is the opposite of the skinny kernels': operands are staged in LDS and re-used from there.  A workgroup
-// owns a tile of 256 weight rows x 128 columns whose accumulators never leave registers, and walks K in stages of 32 (one
-// MFMA k-step): the stage's weight slab (256 rows x 64 bytes) and activation slab (128 columns, hi plane and lo plane)
-// go from global memory straight into LDS with global_load_lds_dwordx4 (16 bytes per lane, lane l of the wave lands at
-// base + 16 l, so one instruction fills sixteen 64-byte slab rows; no staging registers, no ds_write instructions).
-// The four 16-byte segments of a slab row are swizzled by the row number, which keeps the fragment reads free of bank
-// conflicts (sixteen consecutive rows x one segment touch each of the sixteen 16-byte bank groups once); since the
-// direct load fixes where a lane's bytes land, the swizzle is applied on the global side: lane l fetches segment
-// (l % 4) ^ ((l / 16) % 4) of row l / 4 of its sixteen-row block.
+// the design is the opposite of the skinny kernels': operands are staged in LDS and re-used from there.  A workgroup of
+// eight waves owns a tile of 256 weight rows x 128 columns and walks K in stages of 64: the stage's weight slab (256 rows x
+// 128 bytes) and activation slab (128 columns, hi plane and lo plane) go from global memory straight into LDS
+// (buffer_load_dwordx4 ... lds: 16 bytes per lane, lane l of the wave lands at base + 16 l, one instruction fills eight
+// 128-byte slab rows).  Two LDS buffers of 64 KB, one workgroup per compute unit.
 //
-// The LDS pipe delivers 128 bytes per cycle and a 16 x 16 x 32 MFMA takes 16 cycles, so with 64 x 64 per wave (12
-// fragment reads for 32 MFMAs) the reads and writes of a stage occupy LDS for as many cycles as its MFMAs occupy the
-// matrix cores, and any time the two do not overlap is lost.  Two kernels:
-//  * gemm_prompt_w4_kernel (QKV, gate/up): four waves (2 x 2), 128 x 64 per wave = 8 x 4 MFMA tiles (16 fragment reads
-//    for 64 MFMAs: a third fewer LDS bytes per MFMA), two LDS buffers of 32 KB, two workgroups per compute unit whose
-//    stage barriers are independent: one multiplies while the other waits for its loads or reads its fragments.
-//  * gemm_prompt_w8_kernel (the residual projections, whose 256 tiles are one per compute unit): eight waves (4 x 2), 64 x
-//    64 per wave, four LDS buffers, and two sets of fragments in registers: while the MFMAs of stage t run from one set,
-//    the LDS reads of stage t + 1 fill the other.
-//    A long residual contraction is cut into K parts instead, one workgroup each on the four-wave kernel (see the launcher).
+// What bounds it, and what set the design (measured on a 8192 x 4096 x 2048 product, 256 tiles = one per compute unit):
+//  * Whole cache lines.  A stage of 32 k reads 64-byte pieces of rows, every one of them pulling a 128-byte line through the
+//    compute unit's L1: the loads alone then held a stage at 0.82 us (40 GB/s per compute unit) whatever their spacing and
+//    however many buffers were in flight.  With 64 k per stage a row's piece is one line: 207 -> 196 us.
+//  * The two wave groups (waves 0-3, 4-7) share the slabs and split the stage's k: group g multiplies k-step g of every
+//    stage (32 k each), each wave a 128 x 64 piece of the tile (8 x 4 MFMA tiles, 16 fragment reads for 64 MFMAs), so there
+//    are two waves per SIMD without a second set of slabs or smaller pieces.  At the end the groups exchange halves of their
+//    accumulators through LDS (64 KB each way, once per tile) and each finishes two of the four column tiles.
+//  * Nothing is issued in bursts.  A stage is 4 slots of 16 MFMAs (one per column tile).  The barrier sits at the start of
+//    slot 2, when every wave has read all of the stage's fragments: behind it the slots' MFMAs are interleaved with the loads
+//    of the stage after next (into the buffer just freed) and with the reads of the next stage's first fragments, and slot 0
+//    consumes the weight fragments as they arrive.  Reads and loads issued ahead of the MFMAs instead cost 15-20 %.
+// Measured (bf16 operands drawn from a normal distribution; the matrix cores alone sustain 1.9-2.0 PFLOP/s on such data, the
+// clock drops with the toggling of the operands; the loop without its global loads runs at 1.5-1.65): 1.37 PFLOP/s as issued on
+// the product above; 7B shape, 2048 columns: QKV 350 -> 300 us, gate/up 657 -> 600, O 165 -> 102, down 362 -> 254; 512 columns:
+// QKV 139 -> 94, 256 columns: gate/up 139 -> 92 (before: 32 k per stage, 128 x 64 per wave with two workgroups per compute
+// unit, or eight waves of 64 x 64).
+//
 // The LDS reads are inline assembly: the compiler orders every LDS read it knows of behind ALL outstanding direct-to-LDS
 // loads, which would drain the prefetch at every stage.  Here the vmcnt / lgkmcnt waits are written out (a wave's loads
-// complete in issue order, NL per stage), and empty asm statements that name the fragments as operands keep the MFMAs
-// behind the waits.  7B shape, 2048 columns: QKV 432 -> 350 us, gate/up 805 -> 660, O 167 -> 158, down 402 -> 382
-// against the version that staged the slabs through registers (global -> VGPR -> ds_write, 64 x 64 per wave, fragments
-// read and multiplied in turns).  Measured with the operands' loads taken out, the stage loop of the eight-wave kernel
-// (LDS reads, MFMAs, barrier) takes 68 % of the full time; the matrix cores alone sustain 2.06-2.23 PFLOP/s on this chip
-// (82-89 % of the nominal peak: the clock drops under MFMA load), 1.92-2.06 with the LDS reads of this loop beside them
-// (mfma_yardstick_kernel below).
+// complete in issue order, kLoads per stage), and empty asm statements that name the fragments as operands keep the MFMAs
+// behind the waits.  A fragment in flight must not be moved or spilled: it is only across the stage loop's back edge, where the
+// loop fits its registers exactly; at every other change of control flow the reads are waited for.
 //
-// Workgroup order: the column blocks of one row block are 8 apart in the launch order, which puts them on one XCD at the
-// same time (workgroups go to the XCDs round-robin), so a weight slab pulled into that XCD's L2 serves all of them.  The
-// activation slabs are shared by the few row blocks resident on an XCD only and are re-read through the fabric by every
-// later one (they fit the 256 MB memory-side cache, not the 4 MB L2): the L2 misses of a 2048-column gate/up launch add up
-// to 3.2 GB, 17 times the weight matrix.  A launch order in chunks of 8 row blocks x 4 column blocks per XCD cut that to
-// 1.9 GB and was slower (its padded grid delays the residual projections); not kept.
+// LDS layout: a slab row is eight 16-byte segments, segment s at position s ^ ((row / 2) % 8): sixteen consecutive rows x one
+// segment then touch each of the sixteen 16-byte bank groups once.  The direct load fixes where a lane's bytes land, so the
+// swizzle is applied on the global side.
+//
+// Workgroup order: ids go to the XCDs round-robin; XCD x owns the row blocks x, x + 8, ... and walks them in groups of 4 row
+// blocks x 8 column blocks, so the 32 tiles it works on at a time share 12 slabs in its L2 (16 column blocks of 2 row
+// blocks: 18 slabs; gate/up at 2048 columns 640 -> 600 us, the smaller launches unchanged).
 //
 // SwiGLU: a workgroup's 256 slab rows are 128 gate rows and the 128 up rows of the same outputs, four tiles of each per
 // wave, so a wave finishes silu(gate) * up from its own accumulators.  Operand layouts, RMSNorm folding (1/rms from the
@@ -55,39 +56,31 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) char lds_char;
-typedef const __attribute__((address_space(1))) void global_cvoid;
 
-constexpr int kBK = 32;                        // k per stage = one MFMA k-step
-constexpr int kPitch = 2 * kBK;                // bytes per staged row: four 16-byte segments, no padding
-constexpr int kTileN = 128;                    // columns of a workgroup tile
-constexpr int kBBytes = 2 * kTileN * kPitch;   // activation slab of a stage: hi plane, lo plane
-constexpr int kLo = kTileN * kPitch;           // the lo plane follows the hi plane
+constexpr int kBK = 64;                        // k per stage: one MFMA k-step per wave group
+constexpr int kPitch = 2 * kBK;                // bytes per staged row: eight 16-byte segments = one cache line
+constexpr int kTileM = 256, kTileN = 128;      // weight rows and columns of a workgroup tile
+constexpr int kThreads = 512, kWaves = 8;
+constexpr int kABytes = kTileM * kPitch;       // weight slab of a stage
+constexpr int kPlane = kTileN * kPitch;        // one plane of its activation slab (hi, then lo)
+constexpr int kStage = kABytes + 2 * kPlane;   // 64 KB
+[[maybe_unused]] constexpr int kLoads = kStage / 1024 / kWaves;   // direct loads per wave and stage
+constexpr int RW = 8;                          // 16-row tiles per wave
+constexpr int CW = 2;                          // column tiles a wave finishes (it multiplies 2 CW)
+constexpr int kAccWords = RW * CW * 4;         // accumulator words per lane of a finished (half) wave tile
 
-// RW: 16-row weight tiles per wave; WY waves along the rows (x 2 along the columns).
-template <int RW, int WY> struct PromptTile {
-    static constexpr int kThreads = WY * 2 * 64;
-    static constexpr int kWaves = WY * 2;
-    static constexpr int kTileM = 16 * RW * WY;             // slab rows (256 in both kernels)
-    static constexpr int kABytes = kTileM * kPitch;         // weight slab of a stage
-    static constexpr int kStage = kABytes + kBBytes;        // 32 KB
-    static constexpr int kBlocks = kStage / 1024;           // sixteen-row blocks of a stage: weights first, then activations hi, lo
-    static constexpr int NL = kBlocks / kWaves;             // direct loads per wave and stage
-    static constexpr int kAJ = kTileM / 16 / kWaves;        // the first kAJ of them fetch weight rows
-    static_assert(kBlocks % kWaves == 0 && (kTileM / 16) % kWaves == 0 && RW % 2 == 0, "slab blocks divide evenly over the waves");
-};
-
-// The epilogue of both kernels, from the accumulators: lane (i, g) holds column i of a column tile, rows 4g..4g+3 of each tile.
-template <int MODE, int RW, int WY>
-__device__ __forceinline__ void prompt_epilogue(const GemvArgs& a, f32x4 (&acc)[RW][4], int rb, int cb, int tiles,
+// The epilogue, from the summed accumulators: lane (i, g) holds column i of a column tile, rows 4g..4g+3 of each row tile.
+// Wave (wy, wx) of group grp finishes slab rows 128 wy .. + 128 of the columns 64 wx + 32 grp .. + 32.
+template <int MODE>
+__device__ __forceinline__ void prompt_epilogue(const GemvArgs& a, const f32x4 (&acc)[RW][CW], int rb, int cb, int tiles, int grp, int wy, int wx,
                                                 const float* inv_rms, float (*ssq_w)[kTileN]) {
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
-    constexpr int kWavesY = WY, OT = WY * RW / SW;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wy = wave >> 1, wx = wave & 1;
+    constexpr int OT = 2 * RW / SW;                    // output row tiles per workgroup
+    const int tid = threadIdx.x, lane = tid & 63;
     const int li = lane & 15, lg = lane >> 4;
-    float sq[4];
+    float sq[CW];
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) sq[tt] = 0.f;
+    for (int tt = 0; tt < CW; ++tt) sq[tt] = 0.f;
 #pragma unroll
     for (int r = 0; r < RW / SW; ++r) {
         // tiles and columns past the matrix compute on clamped addresses and store nothing (no divergent control flow around the loads)
@@ -97,8 +90,8 @@ __device__ __forceinline__ void prompt_epilogue(const GemvArgs& a, f32x4 (&acc)[
         float4 gn = make_float4(1.f, 1.f, 1.f, 1.f);
         if (MODE == MODE_RESID && a.ssq_out) gn = *reinterpret_cast<const float4*>(a.gain_next + row);
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-            const int cl = wx * 64 + tt * 16 + li, col_raw = cb * kTileN + cl;
+        for (int tt = 0; tt < CW; ++tt) {
+            const int cl = wx * 64 + grp * 32 + tt * 16 + li, col_raw = cb * kTileN + cl;
             const bool live = otile_raw < tiles && col_raw < a.ncols;
             const int col = col_raw < a.ncols ? col_raw : a.ncols - 1;
             const size_t oi = (size_t)col * a.out_stride + row;
@@ -140,209 +133,281 @@ __device__ __forceinline__ void prompt_epilogue(const GemvArgs& a, f32x4 (&acc)[
     }
     if (MODE == MODE_RESID && a.ssq_out) {             // rows of a column: the 4 lane groups by butterfly, then the two row halves in order
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
+        for (int tt = 0; tt < CW; ++tt) {
             sq[tt] += __shfl_xor(sq[tt], 16, 64);
             sq[tt] += __shfl_xor(sq[tt], 32, 64);
-            if (lg == 0) ssq_w[wy][wx * 64 + tt * 16 + li] = sq[tt];
+            if (lg == 0) ssq_w[wy][wx * 64 + grp * 32 + tt * 16 + li] = sq[tt];
         }
         __syncthreads();
-        if (tid < kTileN && cb * kTileN + tid < a.ncols) {
-            float ss = 0.f;
-#pragma unroll
-            for (int w = 0; w < kWavesY; ++w) ss += ssq_w[w][tid];
-            a.ssq_out[(size_t)(cb * kTileN + tid) * kSsqStride + rb] = ss;
-        }
+        if (tid < kTileN && cb * kTileN + tid < a.ncols) a.ssq_out[(size_t)(cb * kTileN + tid) * kSsqStride + rb] = ssq_w[0][tid] + ssq_w[1][tid];
     }
 }
 
 extern __shared__ __attribute__((aligned(16))) char prompt_lds[];
 
 template <int OFF>
-__device__ __forceinline__ bf16x8 lds_read_frag(uint32_t addr) {
+__device__ __forceinline__ u32x4 lds_read_frag(uint32_t addr) {
     u32x4 v;
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
-    return __builtin_bit_cast(bf16x8, v);
+    return v;
+}
+// Fragments are kept as four words and become bf16 vectors at the MFMA: a vector of bf16 that lives across the loop's back
+// edge is taken apart and put together again there, while it may still be in flight.
+__device__ __forceinline__ f32x4 mfma(const u32x4& fa, const u32x4& fb, const f32x4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa), __builtin_bit_cast(bf16x8, fb), c, 0, 0, 0);
 }
 template <int N> __device__ __forceinline__ void vm_loads_left() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 template <int N> __device__ __forceinline__ void lds_reads_left() { asm volatile("s_waitcnt lgkmcnt(%0)" :: "n"(N) : "memory"); }
 // Nothing that uses the fragment moves above this statement, and volatile statements keep their order: after a wait it
-// keeps the MFMAs behind the wait; after the reads of the next stage it keeps this stage's MFMAs behind those reads.
-__device__ __forceinline__ void pin_frag(bf16x8& v) { asm volatile("" : "+v"(v)); }
+// keeps the MFMAs behind the wait.
+__device__ __forceinline__ void pin_frag(u32x4& v) { asm volatile("" : "+v"(v)); }
+// all LDS reads have arrived, these among them
+__device__ __forceinline__ void all_arrived(u32x4 (&f)[RW]) {
+    lds_reads_left<0>();
+#pragma unroll
+    for (int r = 0; r < RW; ++r) pin_frag(f[r]);
+}
+// Instructions stay on their side of this point: what interleaves the MFMAs with loads and reads as written.
+__device__ __forceinline__ void fixed_here() { __builtin_amdgcn_sched_barrier(0); }
 
-template <int RW> struct PromptFrags { bf16x8 a[RW], bh[4], bl[4]; };
-template <int RW, int... R>
-__device__ __forceinline__ void read_a_frags(PromptFrags<RW>& f, uint32_t A, std::integer_sequence<int, R...>) {
-    ((f.a[R] = lds_read_frag<R * 1024>(A)), ...);
+struct PromptB { u32x4 h, l; };                       // one column tile's activation fragments: hi and lo plane
+__device__ __forceinline__ void all_arrived(PromptB& f) { lds_reads_left<0>(); pin_frag(f.h); pin_frag(f.l); }
+template <int... R>
+__device__ __forceinline__ void read_a_frags(u32x4 (&f)[RW], uint32_t A, std::integer_sequence<int, R...>) {
+    ((f[R] = lds_read_frag<R * 16 * kPitch>(A)), ...);
 }
-// all fragments of a stage: weight tiles 0 .. RW - 1, then hi and lo of column tile 0, of column tile 1, ...
-template <int RW>
-__device__ __forceinline__ void read_frags(PromptFrags<RW>& f, uint32_t A, uint32_t B) {
-    read_a_frags<RW>(f, A, std::make_integer_sequence<int, RW>{});
-    f.bh[0] = lds_read_frag<0>(B);      f.bl[0] = lds_read_frag<kLo>(B);
-    f.bh[1] = lds_read_frag<1024>(B);   f.bl[1] = lds_read_frag<kLo + 1024>(B);
-    f.bh[2] = lds_read_frag<2048>(B);   f.bl[2] = lds_read_frag<kLo + 2048>(B);
-    f.bh[3] = lds_read_frag<3072>(B);   f.bl[3] = lds_read_frag<kLo + 3072>(B);
+// column tile tt of a stage whose activation fragments start at B
+template <int TT>
+__device__ __forceinline__ void read_b_frags(PromptB& f, uint32_t B) {
+    f.h = lds_read_frag<TT * 16 * kPitch>(B);
+    f.l = lds_read_frag<kPlane + TT * 16 * kPitch>(B);
 }
-template <int RW>
-__device__ __forceinline__ void pin_frags(PromptFrags<RW>& f) {
+// N MFMAs: row tiles R0 .. R0 + N - 1 of one column tile
+template <int R0, int N>
+__device__ __forceinline__ void mma(f32x4 (&acc)[RW][2 * CW], int tt, const u32x4 (&fa)[RW], const u32x4& fb) {
 #pragma unroll
-    for (int r = 0; r < RW; ++r) pin_frag(f.a[r]);
-#pragma unroll
-    for (int tt = 0; tt < 4; ++tt) { pin_frag(f.bh[tt]); pin_frag(f.bl[tt]); }
-}
-template <int RW>
-__device__ __forceinline__ void mma_column_tile(f32x4 (&acc)[RW][4], const PromptFrags<RW>& f, int tt) {
-#pragma unroll
-    for (int r = 0; r < RW; ++r) acc[r][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[r], f.bh[tt], acc[r][tt], 0, 0, 0);
-#pragma unroll
-    for (int r = 0; r < RW; ++r) acc[r][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[r], f.bl[tt], acc[r][tt], 0, 0, 0);
+    for (int r = R0; r < R0 + N; ++r) acc[r][tt] = mfma(fa[r], fb, acc[r][tt]);
 }
 
-// What both kernels do before their stage loops.  Launch order -> (row block, column block): ids 8m .. 8m + 7 are eight
-// row blocks of one column block, the next eight ids the same row blocks of the next column block.
-template <int MODE, int RW, int WY>
-struct PromptSetup {
-    typedef PromptTile<RW, WY> Tile;
-    static constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
-    static constexpr int OT = WY * RW / SW;            // output row tiles per workgroup (half as many gate/up pairs)
-    int rb, cb, tiles, slice;                          // slice: which of the ks parts of K this workgroup walks
-    const bf16_t* src[Tile::NL];                       // this lane's piece of each of the wave's sixteen-row blocks, at k = 0
-    uint32_t a_off, b_off;                             // LDS addresses of this lane's first weight / activation fragment in buffer 0
-
-    __device__ __forceinline__ bool init(const GemvArgs& a, int n_rb, int n_cb, int ks, int wave, int lane, float* inv_rms) {
-        const int per_group = 8 * n_cb;
-        const int v = (blockIdx.x / per_group) * 8 + (blockIdx.x % per_group) % 8;   // row block x K part
-        cb = (blockIdx.x % per_group) / 8;
-        rb = v / ks; slice = v - rb * ks;
-        if (rb >= n_rb) return false;
-        const int K = a.K;
-        tiles = a.total_rows / 16;                     // output row tiles of the whole matrix
-        // slab row -> weight row.  Slab tile st (0 .. WY RW - 1): wave row wy owns st = RW wy .. RW wy + RW - 1.  Plain modes:
-        // output tile OT rb + st.  SwiGLU: the first RW / 2 tiles of a wave are gate rows, the others the up rows of the same
-        // outputs OT rb + (RW / 2) wy + (st % (RW / 2)).  Tiles past the matrix re-read the last tile (result dropped).
-        auto slab_row = [&](int s) -> const bf16_t* {
-            const int st = s >> 4, i = s & 15;
-            if (MODE == MODE_SWIGLU) {
-                const int t = st % RW;
-                int otile = rb * OT + (st / RW) * (RW / 2) + t % (RW / 2);
-                otile = otile < tiles ? otile : tiles - 1;
-                return static_cast<const bf16_t*>(a.w[t / (RW / 2)]) + (size_t)(otile * 16 + i) * K;
-            }
-            int otile = rb * OT + st;
-            otile = otile < tiles ? otile : tiles - 1;
-            int m = 0, local = otile * 16;
-            if (local >= a.rows[0]) { local -= a.rows[0]; m = 1; if (local >= a.rows[1]) { local -= a.rows[1]; m = 2; } }
-            return static_cast<const bf16_t*>(a.w[m]) + (size_t)(local + i) * K;
-        };
-        const int prow = lane >> 2, pseg = (lane & 3) ^ ((lane >> 4) & 3);
-#pragma unroll
-        for (int j = 0; j < Tile::NL; ++j) {
-            const int s = 16 * (wave + Tile::kWaves * j) + prow;
-            if (j < Tile::kAJ) src[j] = slab_row(s) + pseg * 8;
-            else {
-                const int b = s - Tile::kTileM, plane = b >> 7, col = cb * kTileN + (b & 127);
-                src[j] = (plane ? a.x_lo : a.x_hi) + (size_t)col * a.x_stride + pseg * 8;
-            }
-        }
-        // fragment reads: lane (i, g) takes segment g of row i of a tile, at slot g ^ ((i / 4) % 4) (tile bases are
-        // multiples of 16 rows, so the swizzle depends on i alone)
-        const int wy = wave >> 1, wx = wave & 1, li = lane & 15, lg = lane >> 4;
-        const uint32_t slot = (uint32_t)((lg ^ ((li >> 2) & 3)) << 4);
-        const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)prompt_lds;
-        a_off = lds0 + (wy * 16 * RW + li) * kPitch + slot;
-        b_off = lds0 + Tile::kABytes + (wx * 64 + li) * kPitch + slot;
-        // 16 threads add up one column's partial sums of squares, in a fixed order (before the direct loads: vmcnt counts these loads too)
-        if (MODE != MODE_RESID && a.ssq_in) {
-            const int tid = threadIdx.x;
-            for (int c = tid >> 4; c < kTileN; c += Tile::kThreads / 16) {
-                const int col = cb * kTileN + c;
-                float ss = 0.f;
-                if (col < a.ncols) {
-                    const float* p = a.ssq_in + (size_t)col * kSsqStride;
-                    for (int i0 = tid & 15; i0 < a.ssq_parts; i0 += 16) ss += p[i0];
-                }
-#pragma unroll
-                for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
-                if ((tid & 15) == 0) inv_rms[c] = 1.0f / sqrtf(ss / (float)K + a.eps);
-            }
-        }
-        vm_loads_left<0>();
-        return true;
-    }
-    // stage t -> LDS buffer buf (its 1 KB blocks in slab order; this wave's are wave, wave + kWaves, ...)
-    __device__ __forceinline__ void dma(int t, int buf, int wave) const {
-        lds_char* dst = (lds_char*)prompt_lds + buf * Tile::kStage + wave * 1024;
-#pragma unroll
-        for (int j = 0; j < Tile::NL; ++j)
-            __builtin_amdgcn_global_load_lds((global_cvoid*)(src[j] + (size_t)t * kBK),
-                                             (__attribute__((address_space(3))) void*)(dst + j * Tile::kWaves * 1024), 16, 0, 0);
-    }
-};
-
-// ---------------- four waves, 128 x 64 per wave, two workgroups per compute unit ----------------
-// One set of fragments, two LDS buffers.  Stage t: wait for the wave's own loads of the stage, barrier (everybody's have
-// landed, nobody still reads stage t - 1), request stage t + 1 into the other buffer, read the 16 fragments, and
-// multiply column tile by column tile as its fragments arrive.
+// ks: parts of K, one workgroup each.  (The buffer resource type exists in device code only.)
 template <int MODE>
-__global__ __launch_bounds__(256, 2) void gemm_prompt_w4_kernel(GemvArgs a, int n_rb, int n_cb, int ks) {
-    constexpr int RW = 8, WY = 2;
-    typedef PromptTile<RW, WY> Tile;
+__global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, int n_rb, int n_cb, int ks) {
+#ifdef __HIP_DEVICE_COMPILE__
+    constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
+    constexpr int OT = 2 * RW / SW;                    // output row tiles per workgroup (half as many gate/up pairs)
     __shared__ float inv_rms[kTileN];
-    __shared__ float ssq_w[WY][kTileN];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __shared__ float ssq_w[2][kTileN];
     __shared__ int is_last;
-    PromptSetup<MODE, RW, WY> su;
-    if (!su.init(a, n_rb, n_cb, ks, wave, lane, inv_rms)) return;
-    const int all_stages = a.K / kBK;
-    const int s0 = (int)((long long)all_stages * su.slice / ks), n_stages = (int)((long long)all_stages * (su.slice + 1) / ks) - s0;
-    su.dma(s0, 0, wave);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = wave8 >> 2, wave = wave8 & 3, wy = wave >> 1, wx = wave & 1;
+    const int li = lane & 15, lg = lane >> 4;
 
-    f32x4 acc[RW][4];                                  // [slab tile of the wave][column tile of the wave]
+    // ---- launch order -> (row block, column block, K part); the virtual row blocks of the order are (row block, part) pairs ----
+    int rb, cb, slice;
+    {
+        constexpr int GR = 4, GC = 8;
+        const int n_v = n_rb * ks, xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+        const int own = (n_v - xcd + 7) / 8;           // virtual row blocks of this XCD
+        if (idx >= own * n_cb) return;
+        const int group = idx / (GR * n_cb), rem = idx - group * GR * n_cb;
+        const int in_group = min(GR, own - GR * group);
+        const int chunk = rem / (in_group * GC), r2 = rem - chunk * in_group * GC;
+        const int v = (GR * group + r2 % in_group) * 8 + xcd;
+        cb = chunk * GC + r2 / in_group;
+        rb = v / ks; slice = v - rb * ks;
+    }
+    const int K = a.K, tiles = a.total_rows / 16;      // output row tiles of the whole matrix
+    // whole stages go to the parts in pairs; the last part takes what is over: an odd stage, and the half stage of K % 64 == 32
+    const int pairs = K / (2 * kBK), pair0 = (int)((long long)pairs * slice / ks);
+    const int s0 = 2 * pair0, n_stages = 2 * ((int)((long long)pairs * (slice + 1) / ks) - pair0);
+    const int s_end = (K + kBK - 1) / kBK, n_single = slice == ks - 1 ? s_end - 2 * pairs : 0;      // 0, 1 or 2
+    // (the launcher sees to at least two whole stages per part)
+
+    // ---- this wave's eight-row blocks of a stage (wave8, wave8 + 8, ...): the first 32 are weight rows, then hi, then lo ----
+    // Slab tile st = 8 wy + t is wave row wy's tile t.  Plain modes: output tile OT rb + st.  SwiGLU: tiles t < 4 are gate rows,
+    // the others the up rows of the same outputs OT rb + 4 wy + t % 4.  Tiles past the matrix re-read the last one (result dropped).
+    __amdgpu_buffer_rsrc_t src[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+        const int blk = wave8 + kWaves * j;
+        const bf16_t* p;
+        if (blk < kTileM / 8) {
+            const int st = blk >> 1, t = st % RW;
+            int otile = MODE == MODE_SWIGLU ? rb * OT + (st / RW) * (RW / 2) + t % (RW / 2) : rb * OT + st;
+            otile = otile < tiles ? otile : tiles - 1;
+            int m = MODE == MODE_SWIGLU ? t / (RW / 2) : 0, local = otile * 16;
+            if (MODE != MODE_SWIGLU && local >= a.rows[0]) { local -= a.rows[0]; m = 1; if (local >= a.rows[1]) { local -= a.rows[1]; m = 2; } }
+            p = static_cast<const bf16_t*>(a.w[m]) + (size_t)(local + 8 * (blk & 1)) * K;
+        } else {
+            const int b = 8 * (blk - kTileM / 8), plane = b / kTileN;
+            p = (plane ? a.x_lo : a.x_hi) + (size_t)(cb * kTileN + b % kTileN) * a.x_stride;
+        }
+        const int row_elems = blk < kTileM / 8 ? K : a.x_stride;
+        src[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 2 * (7 * row_elems + K), 0x00027000);   // eight rows
+    }
+    // lane l of a load: row l / 8 of the block, LDS position l % 8, i.e. segment (l % 8) ^ ((slab row / 2) % 8) of that row
+    const int prow = lane >> 3, pseg = (lane & 7) ^ ((lane >> 4) | (4 * (wave8 & 1)));
+    const int voff_w = 2 * (prow * K + pseg * 8), voff_x = 2 * (prow * a.x_stride + pseg * 8);
+    auto load1 = [&](int j, int t, int buf) {         // t: stage of the whole K
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src[j], (__attribute__((address_space(3))) void*)((lds_char*)prompt_lds + buf * kStage + (wave8 + kWaves * j) * 1024),
+                                                 16, j < kTileM / 8 / kWaves ? voff_w : voff_x, t * kPitch, 0, 0);
+    };
+    // fragment reads: lane (i, g) takes segment 4 grp + g of row i of a tile (tile bases are multiples of 16 rows, so the
+    // swizzle depends on i alone)
+    const uint32_t slot = (uint32_t)(((grp * 4 + lg) ^ ((li >> 1) & 7)) << 4);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)prompt_lds;
+    const uint32_t a_off = lds0 + (wy * 16 * RW + li) * kPitch + slot, b_off = lds0 + kABytes + (wx * 64 + li) * kPitch + slot;
+
+    // 16 threads add up one column's partial sums of squares, in a fixed order (before the direct loads: vmcnt counts these loads too)
+    if (MODE != MODE_RESID && a.ssq_in) {
+        for (int c = tid >> 4; c < kTileN; c += kThreads / 16) {
+            const int col = cb * kTileN + c;
+            float ss = 0.f;
+            if (col < a.ncols) {
+                const float* p = a.ssq_in + (size_t)col * kSsqStride;
+                for (int i0 = tid & 15; i0 < a.ssq_parts; i0 += 16) ss += p[i0];
+            }
+#pragma unroll
+            for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
+            if ((tid & 15) == 0) inv_rms[c] = 1.0f / sqrtf(ss / (float)K + a.eps);
+        }
+    }
+    vm_loads_left<0>();
+
+    f32x4 acc[RW][2 * CW];                             // [row tile of the wave][column tile of the wave]
 #pragma unroll
     for (int r = 0; r < RW; ++r)
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) acc[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    PromptFrags<RW> f;
-    for (int t = 0; t < n_stages; ++t) {
-        vm_loads_left<0>();                            // this wave's part of stage t has landed ...
-        __syncthreads();                               // ... and everybody's; nobody still reads stage t - 1 (and inv_rms is written)
-        if (t + 1 < n_stages) su.dma(s0 + t + 1, (t + 1) & 1, wave);
-        read_frags<RW>(f, su.a_off + (t & 1) * Tile::kStage, su.b_off + (t & 1) * Tile::kStage);
-        lds_reads_left<6>();                           // the weight tiles and column tile 0
+        for (int tt = 0; tt < 2 * CW; ++tt) acc[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 A0[RW], A1[RW];                             // weight fragments of this stage and the next
+    PromptB f0, f1, f2;                                // activation fragments of three column tiles
+    // Stage t, in buffer BUF, on the weight fragments A; X holds column tile 0 when it starts (requested, like A, by the stage
+    // before) and column tile 3 in the end, Y the next stage's column tile 0.  MORE: a stage follows; loads: so do
+    // two.  A wave's LDS reads return
+    // in order, so "at most n outstanding" names the oldest ones that have arrived.
+    auto stage = [&](int t, auto buf_c, auto more_c, auto loads_c, u32x4 (&A)[RW], u32x4 (&An)[RW], PromptB& X, PromptB& Y, PromptB& Z) {
+        constexpr int BUF = decltype(buf_c)::value;
+        constexpr bool MORE = decltype(more_c)::value;
+        const uint32_t B = b_off + BUF * kStage, Bn = b_off + (BUF ^ 1) * kStage, Wn = a_off + (BUF ^ 1) * kStage;
+        constexpr bool loads = decltype(loads_c)::value;
+        const int k2 = s0 + t + 2;
+        // slot 0: the weight fragments are used in the order of their arrival
+        read_b_frags<1>(Y, B);
+        lds_reads_left<8>(); pin_frag(A[0]); pin_frag(A[1]); pin_frag(X.h); pin_frag(X.l);
+        mma<0, 2>(acc, 0, A, X.h); mma<0, 2>(acc, 0, A, X.l); fixed_here();
+        lds_reads_left<6>(); pin_frag(A[2]); pin_frag(A[3]);
+        mma<2, 2>(acc, 0, A, X.h); mma<2, 2>(acc, 0, A, X.l); fixed_here();
+        lds_reads_left<4>(); pin_frag(A[4]); pin_frag(A[5]);
+        mma<4, 2>(acc, 0, A, X.h); mma<4, 2>(acc, 0, A, X.l); fixed_here();
+        lds_reads_left<2>(); pin_frag(A[6]); pin_frag(A[7]);
+        mma<6, 2>(acc, 0, A, X.h); mma<6, 2>(acc, 0, A, X.l); fixed_here();
+        // slot 1
+        read_b_frags<2>(Z, B);
+        lds_reads_left<2>(); pin_frag(Y.h); pin_frag(Y.l);
+        mma<0, 4>(acc, 1, A, Y.h); fixed_here();
+        read_b_frags<3>(X, B); fixed_here();
+        mma<4, 4>(acc, 1, A, Y.h); mma<0, 8>(acc, 1, A, Y.l); fixed_here();
+        // slots 2 and 3: this wave has read all of stage t
+        lds_reads_left<0>(); pin_frag(Z.h); pin_frag(Z.l); pin_frag(X.h); pin_frag(X.l);
+        if constexpr (MORE) {
+            vm_loads_left<0>();                        // this wave's part of stage t + 1 has landed ...
+            __builtin_amdgcn_s_barrier();              // ... and everybody's; nobody still reads stage t
+            mma<0, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(0, k2, BUF); fixed_here();
+            mma<2, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(1, k2, BUF); fixed_here();
+            mma<4, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(2, k2, BUF); fixed_here();
+            mma<6, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(3, k2, BUF); fixed_here();
+            mma<0, 2>(acc, 2, A, Z.l); fixed_here(); if (loads) load1(4, k2, BUF); fixed_here();
+            mma<2, 2>(acc, 2, A, Z.l); fixed_here(); if (loads) load1(5, k2, BUF); fixed_here();
+            mma<4, 2>(acc, 2, A, Z.l); fixed_here(); if (loads) load1(6, k2, BUF); read_b_frags<0>(Y, Bn); fixed_here();
+            mma<6, 2>(acc, 2, A, Z.l); fixed_here(); if (loads) load1(7, k2, BUF); An[0] = lds_read_frag<0>(Wn); fixed_here();
+            mma<0, 2>(acc, 3, A, X.h); fixed_here(); An[1] = lds_read_frag<1 * 16 * kPitch>(Wn); fixed_here();
+            mma<2, 2>(acc, 3, A, X.h); fixed_here(); An[2] = lds_read_frag<2 * 16 * kPitch>(Wn); fixed_here();
+            mma<4, 2>(acc, 3, A, X.h); fixed_here(); An[3] = lds_read_frag<3 * 16 * kPitch>(Wn); fixed_here();
+            mma<6, 2>(acc, 3, A, X.h); fixed_here(); An[4] = lds_read_frag<4 * 16 * kPitch>(Wn); fixed_here();
+            mma<0, 2>(acc, 3, A, X.l); fixed_here(); An[5] = lds_read_frag<5 * 16 * kPitch>(Wn); fixed_here();
+            mma<2, 2>(acc, 3, A, X.l); fixed_here(); An[6] = lds_read_frag<6 * 16 * kPitch>(Wn); fixed_here();
+            mma<4, 2>(acc, 3, A, X.l); fixed_here(); An[7] = lds_read_frag<7 * 16 * kPitch>(Wn); fixed_here();
+            mma<6, 2>(acc, 3, A, X.l); fixed_here();
+        } else {
+            mma<0, 8>(acc, 2, A, Z.h); mma<0, 8>(acc, 2, A, Z.l); mma<0, 8>(acc, 3, A, X.h); mma<0, 8>(acc, 3, A, X.l); fixed_here();
+        }
+    };
+    static_assert(kLoads == 8 && RW == 8 && CW == 2, "the stage is written out for these");
+    constexpr std::integral_constant<int, 0> b0{};
+    constexpr std::integral_constant<int, 1> b1{};
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
 #pragma unroll
-        for (int r = 0; r < RW; ++r) pin_frag(f.a[r]);
-        pin_frag(f.bh[0]); pin_frag(f.bl[0]);
-        mma_column_tile<RW>(acc, f, 0);
-        __builtin_amdgcn_sched_barrier(0);             // the scheduler moves nothing across: the next wait stays behind these MFMAs
-        lds_reads_left<4>();
-        pin_frag(f.bh[1]); pin_frag(f.bl[1]);
-        mma_column_tile<RW>(acc, f, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        lds_reads_left<2>();
-        pin_frag(f.bh[2]); pin_frag(f.bl[2]);
-        mma_column_tile<RW>(acc, f, 2);
-        __builtin_amdgcn_sched_barrier(0);
-        lds_reads_left<0>();
-        pin_frag(f.bh[3]); pin_frag(f.bl[3]);
-        mma_column_tile<RW>(acc, f, 3);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int j = 0; j < kLoads; ++j) load1(j, s0, 0);
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) load1(j, s0 + 1, 1);
+    vm_loads_left<kLoads>();
+    __syncthreads();                                   // stage 0 is in LDS (and inv_rms is written)
+    read_b_frags<0>(f0, b_off);
+    read_a_frags(A0, a_off, std::make_integer_sequence<int, RW>{});
+    all_arrived(A0); all_arrived(f0);
+    int t = 0;
+    for (; t + 2 < n_stages; t += 2) {
+        stage(t, b0, yes, yes, A0, A1, f0, f1, f2);
+        stage(t + 1, b1, yes, yes, A1, A0, f1, f0, f2);
     }
-    asm volatile("" ::: "memory");                     // the epilogue's loads stay behind the last stage
-    // ---- K parts: publish, count arrivals, the last one adds the parts up in order (independent of arrival order) ----
-    if (ks > 1) {
-        constexpr int ACC = RW * 4 * 4;
-        const int tile_id = su.rb * n_cb + su.cb;
-        float* mine = a.part + (((size_t)tile_id * ks + su.slice) * 4 + wave) * (ACC * 64) + lane;
+    all_arrived(A0); all_arrived(f0);                  // nothing in flight where the compiler may move registers
+    stage(t, b0, yes, no, A0, A1, f0, f1, f2);
+    stage(t + 1, b1, no, no, A1, A0, f1, f0, f2);
+    __syncthreads();
+    // the stages over, one at a time (K % 64 == 32: the last holds one k-step, which is group 0's; what group 1 finds there belongs to the next row)
+    for (int u = s_end - n_single; u < s_end; ++u) {
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) load1(j, u, 1);
+        vm_loads_left<0>();
+        __syncthreads();
+        if (grp == 0 || (u + 1) * kBK <= K) {
+            read_a_frags(A0, a_off + kStage, std::make_integer_sequence<int, RW>{});
+            read_b_frags<0>(f0, b_off + kStage); read_b_frags<1>(f1, b_off + kStage); read_b_frags<2>(f2, b_off + kStage);
+            all_arrived(A0); all_arrived(f0); all_arrived(f1); all_arrived(f2);
+            mma<0, 8>(acc, 0, A0, f0.h); mma<0, 8>(acc, 0, A0, f0.l); mma<0, 8>(acc, 1, A0, f1.h); mma<0, 8>(acc, 1, A0, f1.l);
+            mma<0, 8>(acc, 2, A0, f2.h); mma<0, 8>(acc, 2, A0, f2.l); fixed_here();
+            read_b_frags<3>(f0, b_off + kStage);
+            all_arrived(f0);
+            mma<0, 8>(acc, 3, A0, f0.h); mma<0, 8>(acc, 3, A0, f0.l); fixed_here();
+        }
+        __syncthreads();
+    }
+
+    // ---- the groups exchange halves: group g finishes the column tiles 2g, 2g + 1 ----
+    f32x4 fin[RW][CW];
+    {
+        f32x4* mine = reinterpret_cast<f32x4*>(prompt_lds) + (size_t)wave8 * (RW * CW * 64) + lane;
+        const f32x4* theirs = reinterpret_cast<const f32x4*>(prompt_lds) + (size_t)(wave8 ^ 4) * (RW * CW * 64) + lane;
 #pragma unroll
         for (int r = 0; r < RW; ++r)
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt)
+            for (int tt = 0; tt < CW; ++tt) mine[(r * CW + tt) * 64] = grp ? acc[r][tt] : acc[r][CW + tt];
+        __syncthreads();
 #pragma unroll
-                for (int e = 0; e < 4; ++e) st_agent(mine + ((r * 4 + tt) * 4 + e) * 64, acc[r][tt][e]);
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int tt = 0; tt < CW; ++tt) {
+                const f32x4 o = theirs[(r * CW + tt) * 64];
+                fin[r][tt] = grp ? o + acc[r][CW + tt] : acc[r][tt] + o;      // k-step 0's sum first
+            }
+    }
+
+    // ---- K parts: publish, count arrivals, the last one adds the parts up in order (independent of arrival order) ----
+    if (ks > 1) {
+        const int tile_id = rb * n_cb + cb;
+        float* mine = a.part + ((size_t)tile_id * ks + slice) * (kAccWords * kThreads) + 2 * tid;
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int tt = 0; tt < CW; ++tt) {
+                st_agent2(mine + ((r * CW + tt) * 2 + 0) * 2 * kThreads, fin[r][tt][0], fin[r][tt][1]);
+                st_agent2(mine + ((r * CW + tt) * 2 + 1) * 2 * kThreads, fin[r][tt][2], fin[r][tt][3]);
+            }
         wait_stores();                                 // this part's partials have reached the coherence point
         __syncthreads();
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             int* ticket = &a.part_tickets[tile_id];
             const int done = atomicAdd(ticket, 1);
             is_last = done == ks - 1;
@@ -353,136 +418,82 @@ __global__ __launch_bounds__(256, 2) void gemm_prompt_w4_kernel(GemvArgs a, int 
 #pragma unroll
         for (int r = 0; r < RW; ++r)
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) acc[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int tt = 0; tt < CW; ++tt) fin[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int part = 0; part < ks; ++part) {
-            const float* p = a.part + (((size_t)tile_id * ks + part) * 4 + wave) * (ACC * 64) + lane;
+            const float* p = a.part + ((size_t)tile_id * ks + part) * (kAccWords * kThreads) + 2 * tid;
+            float2 v[RW * CW * 2];
+#pragma unroll
+            for (int i = 0; i < RW * CW * 2; ++i) v[i] = ld_agent2(p + i * 2 * kThreads);
 #pragma unroll
             for (int r = 0; r < RW; ++r)
 #pragma unroll
-                for (int tt = 0; tt < 4; ++tt) {
-                    float v[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = ld_agent(p + ((r * 4 + tt) * 4 + e) * 64);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[r][tt][e] += v[e];
+                for (int tt = 0; tt < CW; ++tt) {
+                    const float2 u = v[(r * CW + tt) * 2], w = v[(r * CW + tt) * 2 + 1];
+                    fin[r][tt][0] += u.x; fin[r][tt][1] += u.y; fin[r][tt][2] += w.x; fin[r][tt][3] += w.y;
                 }
         }
     }
-    prompt_epilogue<MODE, RW, WY>(a, acc, su.rb, su.cb, su.tiles, inv_rms, ssq_w);
+    prompt_epilogue<MODE>(a, fin, rb, cb, tiles, grp, wy, wx, inv_rms, ssq_w);
+#endif
 }
 
-// ---------------- eight waves, 64 x 64 per wave, fragments double-buffered in registers ----------------
-// Four LDS buffers: stage t + 1 is being read, t + 2 .. t + 4 are in flight or landed.  Stage t: the fragments of stage
-// t are in registers (read during stage t - 1).  Loads are issued in the order 0 1 2 3 | 4 5 (at stage 1) | 6 7 (at stage
-// 3) | ...: the two stages of a pair are the two halves of the rows' cache lines, requested together so that a line is
-// fetched into the compute unit's L1 once.  When stage t + 1 must have landed, the stages issued after it are t + 2, t + 3
-// (t even) or t + 2 (t odd).  The steady state has no branch; the last four stages issue nothing and wait for everything.
-// Needs an even number of stages, at least four.
-template <int MODE>
-__global__ __launch_bounds__(512, 2) void gemm_prompt_w8_kernel(GemvArgs a, int n_rb, int n_cb) {
-    constexpr int RW = 4, WY = 4, NB = 4;
-    typedef PromptTile<RW, WY> Tile;
-    constexpr int NL = Tile::NL, kStage = Tile::kStage;
-    static_assert(3 * NL < 64, "vmcnt holds 6 bits");
-    __shared__ float inv_rms[kTileN];
-    __shared__ float ssq_w[WY][kTileN];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    PromptSetup<MODE, RW, WY> su;
-    if (!su.init(a, n_rb, n_cb, 1, wave, lane, inv_rms)) return;
-    const int n_stages = a.K / kBK;
-    su.dma(0, 0, wave); su.dma(1, 1, wave); su.dma(2, 2, wave); su.dma(3, 3, wave);
-
-    f32x4 acc[RW][4];
-#pragma unroll
-    for (int r = 0; r < RW; ++r)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) acc[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto read = [&](PromptFrags<RW>& f, int t) { read_frags<RW>(f, su.a_off + (t & (NB - 1)) * kStage, su.b_off + (t & (NB - 1)) * kStage); };
-    // the reads of the next stage are in flight while this stage's MFMAs run, and the MFMAs stay above the next stage's waits
-    auto mma = [&](PromptFrags<RW>& f) {
-        pin_frags<RW>(f);
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) mma_column_tile<RW>(acc, f, tt);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    PromptFrags<RW> f0, f1;
-    vm_loads_left<3 * NL>();
-    __syncthreads();                                   // stage 0 is in LDS (and inv_rms is written)
-    read(f0, 0);
-    int t = 0;
-    for (; t + 4 < n_stages; t += 2) {
-        vm_loads_left<2 * NL>();
-        lds_reads_left<0>();
-        __syncthreads();                               // stage t + 1 is complete in LDS; nobody still reads stages <= t
-        read(f1, t + 1);
-        mma(f0);
-        vm_loads_left<NL>();
-        lds_reads_left<0>();
-        __syncthreads();
-        su.dma(t + 4, t & (NB - 1), wave); su.dma(t + 5, (t + 1) & (NB - 1), wave);
-        read(f0, t + 2);
-        mma(f1);
-    }
-    // t = n_stages - 4
-    vm_loads_left<0>();
-    lds_reads_left<0>();
-    __syncthreads();
-    read(f1, t + 1);
-    mma(f0);
-    lds_reads_left<0>();
-    __syncthreads();
-    read(f0, t + 2);
-    mma(f1);
-    lds_reads_left<0>();
-    __syncthreads();
-    read(f1, t + 3);
-    mma(f0);
-    lds_reads_left<0>();
-    mma(f1);
-    asm volatile("" ::: "memory");
-    prompt_epilogue<MODE, RW, WY>(a, acc, su.rb, su.cb, su.tiles, inv_rms, ssq_w);
+// ---------------- yardstick: what the matrix cores sustain ----------------
+// A stage loop of eight waves, 64 x 64 per wave (32 MFMAs per wave and stage), on fragments that (mode >= 1) are re-read from
+// a fixed LDS buffer every stage, (mode 2) with a workgroup barrier per stage.  One workgroup per launched block, no global
+// memory traffic but one word per wave at the end.
+constexpr int kYardRows = 4, kYardPitch = 64, kYardPlane = 128 * kYardPitch, kYardA = 256 * kYardPitch, kYardStage = kYardA + 2 * kYardPlane;
+struct YardFrags { u32x4 a[kYardRows], bh[4], bl[4]; };
+__device__ __forceinline__ void yard_read(YardFrags& f, uint32_t A, uint32_t B) {
+    f.a[0] = lds_read_frag<0>(A); f.a[1] = lds_read_frag<1024>(A); f.a[2] = lds_read_frag<2048>(A); f.a[3] = lds_read_frag<3072>(A);
+    f.bh[0] = lds_read_frag<0>(B);      f.bl[0] = lds_read_frag<kYardPlane>(B);
+    f.bh[1] = lds_read_frag<1024>(B);   f.bl[1] = lds_read_frag<kYardPlane + 1024>(B);
+    f.bh[2] = lds_read_frag<2048>(B);   f.bl[2] = lds_read_frag<kYardPlane + 2048>(B);
+    f.bh[3] = lds_read_frag<3072>(B);   f.bl[3] = lds_read_frag<kYardPlane + 3072>(B);
 }
-
-// ---------------- yardstick: what the matrix cores sustain with this file's stage loop ----------------
-// The stage loop of the eight-wave kernel without its operands' loads: 32 MFMAs per wave and stage on fragments that
-// (mode >= 1) are re-read from a fixed LDS buffer every stage as in the kernel, (mode 2) with the stage barrier.  One
-// workgroup per launched block, no global memory traffic but one word per wave at the end.
+__device__ __forceinline__ void yard_pin(YardFrags& f) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) { pin_frag(f.a[r]); pin_frag(f.bh[r]); pin_frag(f.bl[r]); }
+}
 template <int V>
 __global__ __launch_bounds__(512, 2) void mfma_yardstick_kernel(float* __restrict__ sink, int stages) {
-    constexpr int RW = 4;
+    constexpr int RWY = kYardRows;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lg = lane >> 4;
     unsigned* words = reinterpret_cast<unsigned*>(prompt_lds);
-    for (int i = tid; i < PromptTile<4, 4>::kStage / 4; i += 512) words[i] = 0x3c003c00u ^ ((unsigned)i * 2654435761u & 0x00ff00ffu);   // bf16 values near 1
+    for (int i = tid; i < kYardStage / 4; i += 512) words[i] = 0x3c003c00u ^ ((unsigned)i * 2654435761u & 0x00ff00ffu);   // bf16 values near 1
     __syncthreads();
     const uint32_t slot = (uint32_t)((lg ^ ((li >> 2) & 3)) << 4);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)prompt_lds;
-    const uint32_t A = lds0 + ((wave >> 1) * 16 * RW + li) * kPitch + slot, B = lds0 + PromptTile<4, 4>::kABytes + ((wave & 1) * 64 + li) * kPitch + slot;
-    f32x4 acc[RW][4];
+    const uint32_t A = lds0 + ((wave >> 1) * 16 * RWY + li) * kYardPitch + slot, B = lds0 + kYardA + ((wave & 1) * 64 + li) * kYardPitch + slot;
+    f32x4 acc[RWY][4];
 #pragma unroll
-    for (int r = 0; r < RW; ++r)
+    for (int r = 0; r < RWY; ++r)
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) acc[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    PromptFrags<RW> f0, f1;
-    read_frags<RW>(f0, A, B);
+    YardFrags f0, f1;
+    yard_read(f0, A, B);
     lds_reads_left<0>();
-    pin_frags<RW>(f0);
+    yard_pin(f0);
     f1 = f0;
-    auto half = [&](PromptFrags<RW>& cur, PromptFrags<RW>& nxt) {
+    auto half = [&](YardFrags& cur, YardFrags& nxt) {
         if (V >= 1) lds_reads_left<0>();
         if (V >= 2) __syncthreads();
-        if (V >= 1) read_frags<RW>(nxt, A, B);
-        pin_frags<RW>(cur);
+        if (V >= 1) yard_read(nxt, A, B);
+        yard_pin(cur);
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) mma_column_tile<RW>(acc, cur, tt);
+        for (int tt = 0; tt < 4; ++tt) {
+#pragma unroll
+            for (int r = 0; r < RWY; ++r) acc[r][tt] = mfma(cur.a[r], cur.bh[tt], acc[r][tt]);
+#pragma unroll
+            for (int r = 0; r < RWY; ++r) acc[r][tt] = mfma(cur.a[r], cur.bl[tt], acc[r][tt]);
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     for (int t = 0; t < stages; t += 2) { half(f0, f1); half(f1, f0); }
     lds_reads_left<0>();
-    pin_frags<RW>(f0);
-    float sum = (float)f0.a[0][0];
+    yard_pin(f0);
+    float sum = __uint_as_float(f0.a[0][0]);
 #pragma unroll
-    for (int r = 0; r < RW; ++r)
+    for (int r = 0; r < RWY; ++r)
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) sum += acc[r][tt][0] + acc[r][tt][3];
 #pragma unroll
@@ -490,60 +501,57 @@ __global__ __launch_bounds__(512, 2) void mfma_yardstick_kernel(float* __restric
     if (lane == 0) sink[blockIdx.x * 8 + wave] = sum;
 }
 
-template <int MODE>
-int launch_w4(const GemvArgs& a, int n_rb, int n_cb, int ks, hipStream_t s) {
-    constexpr int lds = 2 * PromptTile<8, 2>::kStage;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_prompt_w4_kernel<MODE>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (attr != hipSuccess) return (int)attr;
-    hipLaunchKernelGGL(gemm_prompt_w4_kernel<MODE>, dim3((n_rb * ks + 7) / 8 * 8 * n_cb), dim3(256), lds, s, a, n_rb, n_cb, ks);
-    return (int)hipGetLastError();
+// K parts of a launch.  A workgroup occupies a compute unit, so a launch takes ceil(workgroups / compute units) rounds of
+// stages / parts stages of 1.6 us each; a part more costs every round the publication of its accumulators (128 KB per
+// workgroup) and the last arriver the reading of all parts: 16 us + 3 us per part.  Measured at the 7B shape (us, 1 / 2 / 3 / 4 / 8
+// parts): O at 203 columns (32 tiles) 104 / 69 / 58 / 53 / 58, at 616 (80 tiles) 104 / 76 / 63 / 103 / 103 (four parts need a
+// second round), at 1280 (160 tiles) 118 / 145 / 136 / - / -; down at 512 (64 tiles) 247 / 149 / 118 / 104 / 161.
+int prompt_k_parts(int tiles_wg, int n_stages, int n_cu, int forced, bool can_split) {
+    auto fits = [&](int ks) { return can_split && 2 * ks <= n_stages && tiles_wg <= kGemmPartTickets && (size_t)tiles_wg * ks * kAccWords * kThreads * sizeof(float) <= kPromptPartBytes; };
+    if (forced >= 1) return fits(forced) ? forced : 1;
+    int best = 1;
+    long long best_cost = 0;
+    for (int ks = 1; ks <= 8; ++ks) {
+        if (ks > 1 && (!fits(ks) || n_stages / ks < 8)) break;
+        const long long rounds = ((long long)tiles_wg * ks + n_cu - 1) / n_cu;
+        const long long cost = rounds * ((n_stages + ks - 1) / ks + (ks > 1 ? 10 + 2 * ks : 0));     // in stages
+        if (ks == 1 || cost < best_cost) { best = ks; best_cost = cost; }
+    }
+    return best;
 }
-int launch_w8_resid(const GemvArgs& a, int n_rb, int n_cb, hipStream_t s) {
-    constexpr int lds = 4 * PromptTile<4, 4>::kStage;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_prompt_w8_kernel<MODE_RESID>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+
+template <int MODE>
+int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, int ks, hipStream_t s) {
+    constexpr int lds = 2 * kStage;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_prompt_kernel<MODE>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return (int)attr;
-    hipLaunchKernelGGL(gemm_prompt_w8_kernel<MODE_RESID>, dim3((n_rb + 7) / 8 * 8 * n_cb), dim3(512), lds, s, a, n_rb, n_cb);
+    hipLaunchKernelGGL(gemm_prompt_kernel<MODE>, dim3((n_rb * ks + 7) / 8 * 8 * n_cb), dim3(kThreads), lds, s, a, n_rb, n_cb, ks);
     return (int)hipGetLastError();
 }
 
 }  // namespace
 
-// Requirements: those of launch_gemm_mfma (bf16 weights, K % 32 == 0, row counts multiples of 16), 1 <= ncols <=
+// Requirements: those of launch_gemm_mfma (bf16 weights, K % 32 == 0, row counts multiples of 16), K >= 128, 1 <= ncols <=
 // kPassCols (x_hi / x_lo hold ncols rounded up to 128 rows); with ssq_out at most kSsqStride row blocks.
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {
     const int tiles = a.total_rows / 16;
     const int n_cb = (a.ncols + kTileN - 1) / kTileN;
-    if (a.ncols < 1 || a.ncols > kPassCols || a.K % kBK != 0 || a.K < kBK) return (int)hipErrorInvalidValue;
-    const int ot = mode == MODE_SWIGLU ? 8 : 16;       // output row tiles per workgroup: 256 slab rows in both kernels
+    if (a.ncols < 1 || a.ncols > kPassCols || a.K % 32 != 0 || a.K < 2 * kBK) return (int)hipErrorInvalidValue;
+    const int ot = mode == MODE_SWIGLU ? 8 : 16;       // output row tiles per workgroup: 256 slab rows
     const int n_rb = (tiles + ot - 1) / ot;
     if (a.ssq_out && n_rb > kSsqStride) return (int)hipErrorInvalidValue;
     if (n_groups) *n_groups = n_rb;
-    const int n_stages = a.K / kBK;
-    if (mode == MODE_STORE) return launch_w4<MODE_STORE>(a, n_rb, n_cb, 1, s);
-    if (mode == MODE_SWIGLU) return launch_w4<MODE_SWIGLU>(a, n_rb, n_cb, 1, s);
-    // A residual projection has few tiles (4096 rows x 2048 columns: 256, one per compute unit).  With room for a second
-    // workgroup per compute unit K is cut into parts, one workgroup each on the four-wave kernel; the parts publish their
-    // accumulators (128 KB) and the one that arrives last at the tile's counter adds them up in part order.  That costs
-    // 40-65 us per launch (7B shape), so a part must keep enough stages: 96, or 48 when the tiles alone would leave a quarter
-    // of the compute units idle (7B shape, 2048 columns: down 395 -> 362 us in two parts, O 166 -> 185 and left whole; 13B
-    // shape, 1024 columns, 160 tiles: down 447 -> 314 in three parts, O 192 -> 173).
-    const int tiles_wg = n_rb * n_cb;
-    int ks = 2 * n_cu / tiles_wg;
-    if (ks > 4) ks = 4;
-    const int min_part = 4 * tiles_wg < 3 * n_cu ? 48 : 96;
-    while (ks > 1 && n_stages / ks < min_part) --ks;
-    if (tn.prompt_ks >= 1 && tn.prompt_ks <= n_stages) ks = tn.prompt_ks;
-    if (ks < 1) ks = 1;
-    if (ks > 1 && a.part && a.part_tickets && tiles_wg <= kGemmPartTickets && (size_t)tiles_wg * ks * 4 * 128 * 64 * sizeof(float) <= kPromptPartBytes)
-        return launch_w4<MODE_RESID>(a, n_rb, n_cb, ks, s);
-    if (n_stages >= 4 && n_stages % 2 == 0) return launch_w8_resid(a, n_rb, n_cb, s);
-    return launch_w4<MODE_RESID>(a, n_rb, n_cb, 1, s);
+    const int n_stages = a.K / (2 * kBK) * 2, tiles_wg = n_rb * n_cb;
+    const int ks = prompt_k_parts(tiles_wg, n_stages, n_cu, tn.prompt_ks, a.part && a.part_tickets);
+    if (mode == MODE_STORE) return launch_prompt<MODE_STORE>(a, n_rb, n_cb, ks, s);
+    if (mode == MODE_SWIGLU) return launch_prompt<MODE_SWIGLU>(a, n_rb, n_cb, ks, s);
+    return launch_prompt<MODE_RESID>(a, n_rb, n_cb, ks, s);
 }
 
 // mode 0: MFMAs alone; 1: with the fragment reads of the stage loop; 2: with the stage barrier as well.  n_wg workgroups of
 // eight waves; sink holds 8 floats per workgroup.  Flops issued: n_wg * 8 waves * stages * 32 MFMAs * 16384.
 int launch_mfma_yardstick(int mode, int stages, int n_wg, float* sink, hipStream_t s) {
-    constexpr int lds = PromptTile<4, 4>::kStage;
+    constexpr int lds = kYardStage;
     if (mode < 0 || mode > 2 || stages < 2 || stages % 2 != 0) return (int)hipErrorInvalidValue;
     if (mode == 0) hipLaunchKernelGGL(mfma_yardstick_kernel<0>, dim3(n_wg), dim3(512), lds, s, sink, stages);
     else if (mode == 1) hipLaunchKernelGGL(mfma_yardstick_kernel<1>, dim3(n_wg), dim3(512), lds, s, sink, stages);

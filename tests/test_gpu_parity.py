@@ -132,10 +132,10 @@ def test_prompt_chunks_of_a_forced_width(monkeypatch, cols):
 
 @pytest.mark.parametrize("ks", [2, 3, 4])
 def test_prompt_residual_projections_in_k_parts(monkeypatch, ks):
-    # the residual projections of a prompt chunk with K cut into 2, 3 and 4 parts (one workgroup each; the part that arrives
-    # last at the tile's counter adds the published accumulators in part order): K of 16 and 43 stages (uneven parts),
-    # then 8 and 22 stages; by itself the launcher cuts K only for long contractions (the 7B / 13B / 70B widths, which
-    # the all-block and full-size tests run)
+    # the projections of a prompt chunk with K cut into 2, 3 and 4 parts (one workgroup each; the part that arrives
+    # last at the tile's counter adds the published accumulators in part order): K of 8 and 21.5 stages (uneven parts, the
+    # last with the stages over), then 4 and 11 stages; by itself the launcher cuts K only for long contractions (the 7B / 13B /
+    # 70B widths, which the all-block and full-size tests run)
     monkeypatch.setenv("D3_PROMPT_KS", str(ks))
     _run(SMALL_GQA, 1, 300, 3, 0.8, 1, forced_seed=21)
     _run(SMALL_BF16, 2, 200, 3, 0.9, 2, forced_seed=21)
@@ -143,14 +143,26 @@ def test_prompt_residual_projections_in_k_parts(monkeypatch, ks):
 
 def test_lds_tiled_prompt_kernel_shapes():
     # rows that do not fill the last row block (d_ffn 1376 = 10.75 blocks of 128 gate/up pairs, vocab 2000), five and a half
-    # column blocks; K of 16 stages (four-wave kernel) and 43 stages (odd: the residual projection cannot pair its stages
-    # and takes the four-wave kernel too); then head_dim 64 (vector-ALU attention per column) with 1100 tokens, a chunk of
-    # 1024 columns and one of 76, K of 8 and 22 stages (even: the residual projections run the eight-wave kernel, whose
-    # steady-state loop runs twice and nine times before its four-stage tail)
+    # column blocks; K of 8 stages and of 21.5 (10 pairs, then a whole and a half stage one at a time); then head_dim 64
+    # (vector-ALU attention per column) with 1100 tokens, K of 4 and 11 stages
     _run(SMALL_GQA, 1, 700, 3, 0.8, 1, forced_seed=19)
     _run(SMALL_BF16, 1, 1100, 3, 0.9, 2, forced_seed=19)
-    # the shortest contractions: K of 4 stages (the eight-wave kernel is all prologue and tail) and of 6 (one steady-state turn)
+    # the shortest contractions: K of one pair of stages (prologue and tail) and of three stages
     _run(ModelShape("narrow", L=2, d=128, H=2, H_kv=1, hd=64, F=192, V=512, dtype="bf16"), 1, 300, 3, 0.9, 1, forced_seed=19)
+
+
+@pytest.mark.parametrize("d,F,P,ks", [(128, 128, 129, 0), (160, 224, 255, 0), (192, 352, 257, 1), (256, 608, 384, 2), (512, 1120, 130, 3),
+                                      (288, 96, 140, 0), (512, 2048, 513, 8)])
+def test_prompt_kernel_contractions_and_parts(monkeypatch, d, F, P, ks):
+    # the LDS-tiled kernel walks K in pairs of 64-wide stages: contractions that are one pair, that leave 32, 64 and 96 over,
+    # that are too short for it (96: the panel kernel in blocks of 64 columns), and K parts of uneven length; column blocks of
+    # 1, 2, 127 and 128 live columns.  Rows of the last row block are missing throughout.  With an fp32 cache only fp32 sums and the 16 bits
+    # of an activation's two bf16 halves are left: 2^-17 per product, far below the bound of 1e-4.
+    if ks:
+        monkeypatch.setenv("D3_PROMPT_KS", str(ks))
+    s = ModelShape("odd-k", L=2, d=d, H=2, H_kv=1, hd=128, F=F, V=512, dtype="bf16")
+    gpu, gens = _run(s, 1, P, 2, 1.0, 1, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
 @pytest.mark.parametrize("B,kv", [(1, "f16"), (3, "f16"), (2, "f32")])
