@@ -127,6 +127,7 @@ Tuning tuning_from_env() {
     const int pc = env_int("D3_PREFILL_COLS", 64, kPassCols, 0);
     t.prefill_cols = pc % 64 == 0 ? pc : 0;
     t.prompt_ks = env_int("D3_PROMPT_KS", 1, 8, 0);
+    t.prompt_attn_wgs = env_int("D3_PROMPT_ATTN_WGS", 1, 1 << 20, 96);
     return t;
 }
 }  // namespace d3
@@ -407,6 +408,12 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     const int grp = d.n_heads / d.n_kv_heads;
     const bool qtile = c->prefill_by_seq && mfma && cm.B == 1 && ncols >= 2 && hd == 128 &&
                        (grp == 1 || grp == 2 || grp == 4 || grp == 8);
+    // with enough workgroups to go round, one of 128 (query, head) pairs that walks its whole context beats the short query
+    // tiles with a split context (7B shape, us: 512 queries = 128 workgroups 21 against 25, 2048 = 512 workgroups 88 against 199; 203
+    // on 1024 cached rows = 64 workgroups 39 against 41; 128 = 32 workgroups 12 against 7, 77 on 1024 34 against 31)
+    SeqRuns runs{};
+    runs.n = 1; runs.seq0 = cm.seq(0); runs.col[1] = ncols; runs.pos[0] = cm.pos(0);
+    const bool prompt_attn = qtile && c->tn.attn_mfma && (ncols * grp + 127) / 128 * d.n_kv_heads >= c->tn.prompt_attn_wgs;
     int split_len, n_splits;
     pick_splits(c, ncols, cm.pos(ncols - 1) + 1, c->attn_wgs_per_cu * c->n_cu, &split_len, &n_splits, qtile);
 
@@ -467,7 +474,8 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         at.row0 = row0;
         {
             Timed t(c, D3_K_ATTN, s);
-            D3_HIP(launch_attention(at, d.kv_dtype, c->tn.attn_mfma, s));
+            if (prompt_attn) D3_HIP(launch_attention_prompt(at, runs, d.kv_dtype, s));
+            else D3_HIP(launch_attention(at, d.kv_dtype, c->tn.attn_mfma, s));
         }
 
         GemvArgs o{};

@@ -125,7 +125,8 @@ struct GemvArgs {
 // D3_MFMA_WIDE=0: no panel kernel (passes are limited to kMaxCols columns); D3_WIDE_RT, D3_WIDE_KS: row tiles per wave
 // and K slices of the panel kernel; D3_WIDE_SPLIT_MB: matrix size above which a pass of more than 64 columns runs as
 // two 64-column launches; D3_ATTN_MFMA=0: grouped-query and query-tile attention on the vector ALUs;
-// D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most 2048); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8); D3_GEMV_WGS_PER_CU: workgroups
+// D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most 2048); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8);
+// D3_PROMPT_ATTN_WGS: fewest workgroups (128 (query, head) pairs each) for which a prompt chunk takes the whole-context attention kernel; D3_GEMV_WGS_PER_CU: workgroups
 // per compute unit of the vector-ALU GEMV (default 3).
 struct Tuning {
     int gemv_wgs_per_cu = 3;
@@ -137,6 +138,7 @@ struct Tuning {
     int attn_min_split = 128;
     int prefill_cols = 0;
     int prompt_ks = 0;
+    int prompt_attn_wgs = 96;
 };
 Tuning tuning_from_env();
 
@@ -187,6 +189,14 @@ struct AttnArgs {
     bf16_t* out_lo;
 };
 int launch_attention(const AttnArgs& a, int kv_dtype, bool use_mfma, hipStream_t s);
+
+// The columns of a prompt pass as runs of consecutive positions: run r is sequence seq0 + r, columns [col[r], col[r + 1]), the
+// first of them at cache row pos[r].
+struct SeqRuns {
+    int n, seq0;
+    int col[kMaxCols + 1], pos[kMaxCols];
+};
+int launch_attention_prompt(const AttnArgs& a, const SeqRuns& runs, int kv_dtype, hipStream_t s);   // attention_prompt.hip
 
 int launch_argmax(const float* logits, int vocab, int ncols, int32_t* out, hipStream_t s);
 

@@ -165,6 +165,19 @@ def test_prompt_kernel_contractions_and_parts(monkeypatch, d, F, P, ks):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("H,H_kv,kv,P", [(2, 2, "f16", 130), (2, 2, "f16", 257), (3, 3, "f32", 65), (4, 2, "f16", 193), (4, 2, "f32", 129),
+                                         (8, 2, "f16", 161), (8, 1, "f16", 150), (8, 1, "f32", 97), (8, 8, "f16", 64)])
+def test_prompt_attention_over_the_whole_context(monkeypatch, H, H_kv, kv, P):
+    # the kernel of long prompt chunks (128 (query, head) pairs per workgroup), forced on short ones: group sizes 1, 2, 4 and 8, KV heads that
+    # do and do not divide over the XCDs, last query tiles of 1 to 128 pairs, row tiles (64 rows fp16, 32 fp32) that end on, before
+    # and past a boundary, one and several steps of the two wave groups, and a group that sees no row of some entries
+    monkeypatch.setenv("D3_PROMPT_ATTN_WGS", "1")
+    s = ModelShape("prompt-attn", L=2, d=256, H=H, H_kv=H_kv, hd=128, F=384, V=512, dtype="bf16")
+    gpu, gens = _run(s, 2, P, 2, 1.0, 1, forced_seed=19, kv_dtype=kv)
+    if kv == "f32":     # only arithmetic rounding is left (16 bits of an activation's two bf16 halves, 21 of the fp16 pairs)
+        helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
 @pytest.mark.parametrize("B,kv", [(1, "f16"), (3, "f16"), (2, "f32")])
 def test_small_gqa(B, kv):
     _run(SMALL_GQA, B, 37, 6, 0.8, 1, forced_seed=8, kv_dtype=kv)
