@@ -22,7 +22,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {          // byte offsets into the workspace
-    size_t x, qkv, attn_o, act, part_o, part_ml, tickets, logits, s_hi, s_lo, f_hi, f_lo, inv_freq, rope_cs, n_hi, n_lo, ssq, h_skip, gemm_part, gemm_tickets, row0, total;
+    size_t x, qkv, attn_o, act, part_o, part_ml, tickets, logits, s_hi, s_lo, f_hi, f_lo, inv_freq, rope_cs, n_hi, n_lo, ssq, h_skip, gemm_part, gemm_tickets, row0, col_at, h_last, total;
 };
 
 // The vector-ALU GEMV stages one column of its input in LDS.
@@ -89,14 +89,22 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
     l.gemm_part = take(with_gemm_part ? (C > 128 ? kPromptPartBytes : kGemmPartBytes) : 0);   // passes of more than 128 columns are prompt chunks
     l.gemm_tickets = take((size_t)kGemmPartTickets * 4);
     l.row0 = take(kMaxCols * 4);
+    l.col_at = take(C * 8);                                           // (sequence, cache row) of a prompt pass's columns
+    l.h_last = take(PC * d.d_model * 4);                              // residual of every sequence's last prompt position
     l.total = o;
     return l;
 }
 // Columns of a prompt chunk: a whole sequence if it fits kPassCols (one pass over the weights per sequence, and enough
 // column blocks for the 4096-row projections to fill the chip), never more than the cache can hold.
+// Sequences share a pass where the matrix-core attention takes runs of several of them.
+bool shares_passes(const d3_model_desc& d) {
+    const int grp = d.n_heads / d.n_kv_heads;
+    return mfma_fits(d) && d.head_dim == 128 && (grp == 1 || grp == 2 || grp == 4 || grp == 8);
+}
 int pass_cols(const d3_model_desc& d) {
-    const int need = (d.max_seq + 127) / 128 * 128;
-    return need < kPassCols ? need : kPassCols;
+    const long long rows = (long long)d.max_seq * (shares_passes(d) ? d.max_batch : 1);
+    const long long need = (rows + 127) / 128 * 128;
+    return (int)(need < kPassCols ? need : kPassCols);
 }
 // The caller's workspace serves prompt chunks of up to pass_cols() columns.
 Layout make_layout(const d3_model_desc& d) { return make_layout(d, pass_cols(d), pass_cols(d), true); }
@@ -368,11 +376,13 @@ int alu_projection(d3_ctx* c, GemvArgs g, int first, int count, int mode, bool n
 
 // One pass of `ncols` columns through the listed blocks.  hidden_dump (or NULL): dev
 // [(n_ids+1)][dump_cols][d], fed from columns [dump_first, dump_first + dump_cols).
+// shared: a prompt pass whose columns are runs of several sequences (cm then gives P and
+// pos_begin only, and there is no head); picks: its last positions, which hidden_dump takes.
 // save_before >= 0: the residual that enters the first listed block >= save_before (the one after the last, if none)
 // is copied to the workspace's h_skip: it is what the blocks of the drop window would have seen.
 int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_t* ids, int n_ids,
             float* hidden_dump, int dump_first, int dump_cols, const HeadOut* head, hipStream_t s, int save_before = -1,
-            int dump_total = -1, int dump_dst = 0) {
+            int dump_total = -1, int dump_dst = 0, const SeqRuns* shared = nullptr, const RowPick* picks = nullptr) {
     const d3_model_desc& d = c->desc;
     const int dm = d.d_model, hd = d.head_dim, qdim = d.n_heads * hd, kvdim = d.n_kv_heads * hd, qkv_dim = qdim + 2 * kvdim, F = d.d_ffn;
     float* x = c->at<float>(c->lay.x);
@@ -381,21 +391,31 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     float* act = c->at<float>(c->lay.act);
     bf16_t *s_hi = c->at<bf16_t>(c->lay.s_hi), *s_lo = c->at<bf16_t>(c->lay.s_lo);
     bf16_t *f_hi = c->at<bf16_t>(c->lay.f_hi), *f_lo = c->at<bf16_t>(c->lay.f_lo);
-    const bool mfma = c->mfma_ok && (ncols >= 2 || !c->alu_ok);
+    const bool mfma = c->mfma_ok && (ncols >= 2 || shared || !c->alu_ok);
     // a decode pass (every column a different sequence) leaves the rotary embedding and the cache append to the
     // attention kernel (batch 1, 7B shape: the projection's rotate-and-scatter epilogue cost it 1.5 us, the attention
     // kernel does the same for 0.5 us with whole-row stores); a prompt chunk holds several positions of one sequence
     // and needs the rows in the cache before attention starts
-    const bool rope_in_attn = ncols <= cm.B;
+    const bool rope_in_attn = !shared && ncols <= cm.B;
 
     float2* rope_cs = c->at<float2>(c->lay.rope_cs);
     const int* row0 = c->ragged ? c->at<int>(c->lay.row0) : nullptr;
     bf16_t *n_hi = c->at<bf16_t>(c->lay.n_hi), *n_lo = c->at<bf16_t>(c->lay.n_lo);   // split of residual * next norm's gain
     float* ssq = c->at<float>(c->lay.ssq);
     int ssq_parts = 1;
-    D3_HIP(launch_embed(c->tok_emb, d.weight_dtype, tokens, cm, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, s));
+    // a prompt chunk of one sequence (consecutive positions) or of several: tiles of queries share the cache rows they read
+    const int grp = d.n_heads / d.n_kv_heads;
+    const bool qtile = shared || (c->prefill_by_seq && mfma && cm.B == 1 && ncols >= 2 && hd == 128 &&
+                                  (grp == 1 || grp == 2 || grp == 4 || grp == 8));
+    SeqRuns one{};
+    one.n = 1; one.seq0 = cm.seq(0); one.col[1] = ncols; one.pos[0] = cm.pos(0);
+    const SeqRuns& runs = shared ? *shared : one;
+    int2* col_at = qtile ? c->at<int2>(c->lay.col_at) : nullptr;
+    if (qtile) D3_HIP(launch_embed_runs(c->tok_emb, tokens, runs, cm.P, cm.pos_begin, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, col_at, s));
+    else D3_HIP(launch_embed(c->tok_emb, d.weight_dtype, tokens, cm, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, s));
     auto dump = [&](int slot) -> int {
         if (!hidden_dump) return 0;
+        if (shared) return launch_pick_rows(x, dm, *picks, hidden_dump + (size_t)slot * dump_total * dm, s);
         // destination slot layout [dump_total columns][d]; this pass fills columns dump_dst .. dump_dst + dump_cols - 1
         return (int)hipMemcpyAsync(hidden_dump + ((size_t)slot * (dump_total < 0 ? dump_cols : dump_total) + dump_dst) * dm, x + (size_t)dump_first * dm,
                                    (size_t)dump_cols * dm * sizeof(float), hipMemcpyDeviceToDevice, s);
@@ -404,18 +424,12 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
 
     auto alu = [&](GemvArgs g, int first, int count, int mode, bool norm) -> int { return alu_projection(c, g, first, count, mode, norm, s); };
 
-    // a prompt chunk of one sequence (consecutive positions): tiles of queries share the cache rows they read
-    const int grp = d.n_heads / d.n_kv_heads;
-    const bool qtile = c->prefill_by_seq && mfma && cm.B == 1 && ncols >= 2 && hd == 128 &&
-                       (grp == 1 || grp == 2 || grp == 4 || grp == 8);
     // with enough workgroups to go round, one of 128 (query, head) pairs that walks its whole context beats the short query
     // tiles with a split context (7B shape, us: 512 queries = 128 workgroups 21 against 25, 2048 = 512 workgroups 88 against 199; 203
     // on 1024 cached rows = 64 workgroups 39 against 41; 128 = 32 workgroups 12 against 7, 77 on 1024 34 against 31)
-    SeqRuns runs{};
-    runs.n = 1; runs.seq0 = cm.seq(0); runs.col[1] = ncols; runs.pos[0] = cm.pos(0);
-    const bool prompt_attn = qtile && c->tn.attn_mfma && (ncols * grp + 127) / 128 * d.n_kv_heads >= c->tn.prompt_attn_wgs;
-    int split_len, n_splits;
-    pick_splits(c, ncols, cm.pos(ncols - 1) + 1, c->attn_wgs_per_cu * c->n_cu, &split_len, &n_splits, qtile);
+    const bool prompt_attn = shared || (qtile && c->tn.attn_mfma && (ncols * grp + 127) / 128 * d.n_kv_heads >= c->tn.prompt_attn_wgs);
+    int split_len = 0, n_splits = 0;
+    if (!prompt_attn) pick_splits(c, ncols, cm.pos(ncols - 1) + 1, c->attn_wgs_per_cu * c->n_cu, &split_len, &n_splits, qtile);
 
     // Matrix-core path: RMSNorm lives inside the projections.  Whoever writes the residual also writes the split of
     // residual * (gain of the norm that reads it next) and partial sums of squares; the reading projection scales its
@@ -445,14 +459,19 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         void* v_layer = c->v_cache + (size_t)l * c->kv_layer_bytes();
         if (mfma) {
             g.x_hi = n_hi; g.x_lo = n_lo; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = ssq_parts;
+            const bool rope_in_qkv = qtile && gemm_prompt_takes(g, c->tn);
             {
                 Timed t(c, D3_K_QKV, s);
-                D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s));
+                if (rope_in_qkv) {
+                    g.rope_cs = rope_cs; g.k_cache = k_layer; g.v_cache = v_layer; g.col_at = col_at;
+                    g.H = d.n_heads; g.H_kv = d.n_kv_heads; g.hd = hd; g.max_seq = d.max_seq; g.kv_dtype = d.kv_dtype;
+                }
+                D3_HIP(launch_gemm_mfma(g, rope_in_qkv ? MODE_QKV_ROPE : MODE_STORE, c->n_cu, c->tn, s));
             }
-            if (!rope_in_attn) {
+            if (!rope_in_attn && !rope_in_qkv) {
                 RopeArgs r{};
                 r.qkv = qkv; r.k_cache = k_layer; r.v_cache = v_layer; r.rope_cs = rope_cs;
-                r.cm = cm; r.ncols = ncols; r.H = d.n_heads; r.H_kv = d.n_kv_heads; r.hd = hd; r.max_seq = d.max_seq;
+                r.cm = cm; r.col_at = col_at; r.ncols = ncols; r.H = d.n_heads; r.H_kv = d.n_kv_heads; r.hd = hd; r.max_seq = d.max_seq;
                 D3_HIP(launch_rope_append(r, d.kv_dtype, s));
             }
         } else {
@@ -542,6 +561,52 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
 
 namespace {
 
+// Prompts of several sequences, their tokens laid end to end and cut into passes of chunk_cols columns: the weights are streamed
+// once per pass and not once per sequence, and short prompts fill the projections' column tiles together (8 x 77 tokens at the 7B
+// shape, 8 blocks: eight passes 17.4 ms, one pass 4.2 ms;
+// 4 x 203 tokens on 1024 cached rows 12.0 -> 5.9 ms; 4 x 1024 at the 13B widths, two passes instead of four, 20.7 -> 18.8 ms).  The head runs once, on every sequence's last position.
+int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin, int chunk_cols, const std::vector<int32_t>& all, int32_t* next_tok,
+                   float* logits, float* hidden_dump, hipStream_t s) {
+    const d3_model_desc& d = c->desc;
+    const int dm = d.d_model;
+    float* h_last = c->at<float>(c->lay.h_last);
+    const ColMap cm{0, 1, P, pos_begin};
+    auto first_of = [&](int b) { return pos_begin == 0 ? c->row0[b] : 0; };          // padding columns are not computed
+    int b = 0, at = first_of(0);                       // next token: sequence b, prompt column `at`
+    while (b < B) {
+        SeqRuns runs{};
+        RowPick picks{};
+        runs.seq0 = b;
+        int ncols = 0;
+        while (b < B && ncols < chunk_cols) {
+            const int n = P - at < chunk_cols - ncols ? P - at : chunk_cols - ncols;
+            runs.pos[runs.n] = pos_begin + at;
+            runs.n += 1;
+            ncols += n; at += n;
+            runs.col[runs.n] = ncols;
+            if (at == P) {
+                picks.col[picks.n] = ncols - 1; picks.row[picks.n] = b;
+                picks.n += 1;
+                if (++b < B) at = first_of(b);
+            }
+        }
+        const int rc = forward(c, tokens, cm, ncols, all.data(), d.n_layers, picks.n ? hidden_dump : nullptr, 0, 0, nullptr, s, -1, B, 0, &runs, &picks);
+        if (rc != D3_OK) return rc;
+        if (picks.n) D3_HIP(launch_pick_rows(c->at<float>(c->lay.x), dm, picks, h_last, s));
+    }
+    bf16_t *n_hi = c->at<bf16_t>(c->lay.n_hi), *n_lo = c->at<bf16_t>(c->lay.n_lo);
+    float* ssq = c->at<float>(c->lay.ssq);
+    D3_HIP(launch_gain_split(h_last, dm, static_cast<const float*>(c->final_norm), dm, B, n_hi, n_lo, ssq, s));
+    GemvArgs g{};
+    g.part = c->at<float>(c->lay.gemm_part); g.part_tickets = c->at<int>(c->lay.gemm_tickets);
+    g.K = dm; g.eps = d.rms_eps; g.w[0] = c->lm_head; g.rows[0] = d.vocab; g.total_rows = d.vocab;
+    g.out = logits; g.out_stride = d.vocab; g.ncols = B;
+    g.x_hi = n_hi; g.x_lo = n_lo; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1;
+    { Timed t(c, D3_K_LM_HEAD, s); D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s)); }
+    D3_HIP(launch_argmax(logits, d.vocab, B, next_tok, s));
+    return D3_OK;
+}
+
 // Prompt pass.  lengths (host, optional): a left-padded batch, sequence b holds lengths[b] tokens in columns
 // [P - lengths[b], P) of its row of `tokens` and in the cache rows of the same numbers.
 int prefill_impl(d3_ctx* ctx, const int32_t* tokens, int32_t B, int32_t P, int32_t pos_begin, const int32_t* lengths,
@@ -576,14 +641,16 @@ int prefill_impl(d3_ctx* ctx, const int32_t* tokens, int32_t B, int32_t P, int32
     for (int l = 0; l < d.n_layers; ++l) all[l] = l;
     float* lg = logits ? logits : ctx->at<float>(ctx->lay.logits);
     if (ctx->prefill_by_seq || (ctx->ragged && pos_begin == 0)) {
-        // one sequence at a time, 32 consecutive positions per pass: the attention of such a chunk reads every cache
-        // row once per tile of queries instead of once per query
-        // the matrix-core path takes 128 columns a pass (the weights are streamed once per pass); D3_PREFILL_COLS=64 halves that
-        // (projections of large matrices split such a pass into two launches of 64 columns by themselves)
+        // consecutive positions of a sequence per pass: the attention of such a chunk reads every cache row once per tile of
+        // queries instead of once per query.  The matrix-core path takes pass_cols() columns (the weights are streamed once per
+        // pass), of several sequences if its attention kernel can; else one sequence at a time
         const int fit = pass_cols(d);
         const int wide_cols = ctx->tn.prefill_cols && ctx->tn.prefill_cols < fit ? ctx->tn.prefill_cols : fit;
         const int chunk_cols = ctx->mfma_ok && ctx->tn.mfma_wide ? wide_cols : kMaxCols;
-        for (int b = 0; b < B; ++b) {
+        if (B > 1 && ctx->prefill_by_seq && shares_passes(d) && ctx->tn.mfma_wide && ctx->tn.attn_mfma) {
+            const int rc = prefill_shared(ctx, tokens, B, P, pos_begin, chunk_cols, all, next_tok, lg, hidden_dump, s);
+            if (rc != D3_OK) return rc;
+        } else for (int b = 0; b < B; ++b) {
             for (int base = pos_begin == 0 ? ctx->row0[b] : 0; base < P;) {     // padding columns are not computed
                 const int ncols = P - base < chunk_cols ? P - base : chunk_cols;
                 const bool last = base + ncols == P;

@@ -33,6 +33,21 @@ struct ColMap {
     __host__ __device__ int tok_index(int c) const { return seq(c) * P + (base + c) / B; }
 };
 
+// The columns of a prompt pass on the matrix-core path as runs of consecutive positions, one run per sequence: run r is sequence
+// seq0 + r, columns [col[r], col[r + 1]), the first of them at cache row pos[r].
+struct SeqRuns {
+    int n, seq0;
+    int col[kMaxCols + 1], pos[kMaxCols];
+    __host__ __device__ int of(int c) const {          // the run that column c belongs to
+        int lo = 0, hi = n - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (col[mid] <= c) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    }
+};
+
 // 16-byte streaming load of weights that are read exactly once (non-temporal: do not
 // displace the activations that live in L2)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -104,6 +119,7 @@ struct GemvArgs {
     void* v_cache;
     ColMap cm;
     int col0;                // pass column of this launch's column 0
+    const int2* col_at;      // prompt pass on the matrix cores, instead of cm: (sequence, cache row) of every column
     int H, H_kv, hd, max_seq, kv_dtype;
     // MFMA path, RMSNorm folded into the projections around it.  A projection whose input is a normalised
     // residual (STORE, SWIGLU) gets x * gain pre-split in x_hi/x_lo and scales its sums by
@@ -147,6 +163,7 @@ int launch_gemv_alu(const GemvArgs& a, int weight_dtype, int mode, bool norm, in
 // n_groups: workgroups launched (= parts written to ssq_out)
 int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups = nullptr);
 int launch_gemm_mfma_wide(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // 17..128 columns
+bool gemm_prompt_takes(const GemvArgs& a, const Tuning& tn);   // launch_gemm_mfma sends the launch to launch_gemm_prompt
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // 129..kPassCols columns: LDS-tiled, compute-bound
 size_t gemv_alu_max_cols(int K, int weight_dtype);   // columns one ALU launch can take (LDS bound)
 
@@ -157,6 +174,12 @@ int launch_gain_split(const float* x, int x_stride, const float* gain, int K, in
 // ---------------- the rest of a block ----------------
 // x[c][:] = E[token(c)][:], and the pass's rotary table rope_cs[c][j] = (cos, sin)((pos(c) - row0[seq(c)]) * inv_freq[j])
 // (row0 optional: the first cache row of each sequence of a left-padded batch)
+// The columns of `runs`: tokens [B][P] of the cache rows from pos_begin on; also col_at[c] = (sequence, cache row) of every column.
+int launch_embed_runs(const void* tok_emb, const int32_t* tokens, const SeqRuns& runs, int P, int pos_begin, int ncols, int d, int vocab,
+                      float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, int2* col_at, hipStream_t s);   // bf16 table
+// dst[row[r]][:] = x[col[r]][:], r < n: the last position of every sequence that a prompt pass finishes
+struct RowPick { int n, col[kMaxCols], row[kMaxCols]; };
+int launch_pick_rows(const float* x, int d, const RowPick& pick, float* dst, hipStream_t s);
 int launch_embed(const void* tok_emb, int weight_dtype, const int32_t* tokens, ColMap cm, int ncols, int d,
                  int vocab, float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, hipStream_t s);
 
@@ -166,6 +189,7 @@ struct RopeArgs {
     void* v_cache;
     const float2* rope_cs;   // [ncols][hd/2] (cos, sin) of this pass
     ColMap cm;
+    const int2* col_at;      // instead of cm: (sequence, cache row) of every column
     int ncols, H, H_kv, hd, max_seq;
 };
 int launch_rope_append(const RopeArgs& a, int kv_dtype, hipStream_t s);
@@ -190,12 +214,6 @@ struct AttnArgs {
 };
 int launch_attention(const AttnArgs& a, int kv_dtype, bool use_mfma, hipStream_t s);
 
-// The columns of a prompt pass as runs of consecutive positions: run r is sequence seq0 + r, columns [col[r], col[r + 1]), the
-// first of them at cache row pos[r].
-struct SeqRuns {
-    int n, seq0;
-    int col[kMaxCols + 1], pos[kMaxCols];
-};
 int launch_attention_prompt(const AttnArgs& a, const SeqRuns& runs, int kv_dtype, hipStream_t s);   // attention_prompt.hip
 
 int launch_argmax(const float* logits, int vocab, int ncols, int32_t* out, hipStream_t s);

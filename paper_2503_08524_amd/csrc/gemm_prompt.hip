@@ -143,6 +143,56 @@ __device__ __forceinline__ void prompt_epilogue(const GemvArgs& a, const f32x4 (
     }
 }
 
+// QKV of a prompt pass at head_dim 128: a wave's 128 rows are one head, and row tiles r and r + 4 hold the dims j and j + 64 that one
+// rotation pairs, so q and k are rotated and k and v appended to the cache straight from the accumulators (as a launch of its own
+// over fp32 q, k, v that took 24 us of a 2048-column block at the 7B shape).
+template <typename T>
+__device__ __forceinline__ void store_row4(T* p, const float (&v)[4]);
+template <> __device__ __forceinline__ void store_row4<float>(float* p, const float (&v)[4]) { *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]); }
+template <> __device__ __forceinline__ void store_row4<f16_t>(f16_t* p, const float (&v)[4]) {
+    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+    half4 h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = (f16_t)fminf(fmaxf(v[e], -65504.f), 65504.f);
+    *reinterpret_cast<half4*>(p) = h;
+}
+template <typename T>
+__device__ __forceinline__ void qkv_rope_epilogue(const GemvArgs& a, const f32x4 (&acc)[RW][CW], int rb, int cb, int grp, int wy, int wx, const float* inv_rms) {
+    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+    const int head = 2 * rb + wy;
+    if (head >= a.H + 2 * a.H_kv) return;
+    const bool is_q = head < a.H, is_v = head >= a.H + a.H_kv;
+    const int kvh = is_v ? head - a.H - a.H_kv : head - a.H;
+#pragma unroll
+    for (int tt = 0; tt < CW; ++tt) {
+        const int cl = wx * 64 + grp * 32 + tt * 16 + li, col = cb * kTileN + cl;
+        if (col >= a.ncols) continue;
+        const float sc = inv_rms[cl];
+        const int2 at = a.col_at[col];                 // (sequence, cache row)
+        float* q = a.out + (size_t)col * a.out_stride + head * 128;
+        T* row = nullptr;
+        if (!is_q) row = static_cast<T*>(is_v ? a.v_cache : a.k_cache) + (((size_t)at.x * a.H_kv + kvh) * a.max_seq + at.y) * 128;
+#pragma unroll
+        for (int r = 0; r < RW / 2; ++r) {
+            const int j = 16 * r + 4 * lg;
+            float lo[4], hi[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { lo[e] = acc[r][tt][e] * sc; hi[e] = acc[r + RW / 2][tt][e] * sc; }
+            if (!is_v) {
+                const float4 c0 = *reinterpret_cast<const float4*>(a.rope_cs + (size_t)col * 64 + j), c1 = *reinterpret_cast<const float4*>(a.rope_cs + (size_t)col * 64 + j + 2);
+                const float cs[4] = {c0.x, c0.z, c1.x, c1.z}, sn[4] = {c0.y, c0.w, c1.y, c1.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float y0 = lo[e] * cs[e] - hi[e] * sn[e], y1 = lo[e] * sn[e] + hi[e] * cs[e];
+                    lo[e] = y0; hi[e] = y1;
+                }
+            }
+            if (is_q) { store_row4<float>(q + j, lo); store_row4<float>(q + j + 64, hi); }
+            else { store_row4<T>(row + j, lo); store_row4<T>(row + j + 64, hi); }
+        }
+    }
+}
+
 extern __shared__ __attribute__((aligned(16))) char prompt_lds[];
 
 template <int OFF>
@@ -433,7 +483,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
                 }
         }
     }
-    prompt_epilogue<MODE>(a, fin, rb, cb, tiles, grp, wy, wx, inv_rms, ssq_w);
+    if constexpr (MODE == MODE_QKV_ROPE) {
+        if (a.kv_dtype == 0) qkv_rope_epilogue<float>(a, fin, rb, cb, grp, wy, wx, inv_rms);
+        else qkv_rope_epilogue<f16_t>(a, fin, rb, cb, grp, wy, wx, inv_rms);
+    } else prompt_epilogue<MODE>(a, fin, rb, cb, tiles, grp, wy, wx, inv_rms, ssq_w);
 #endif
 }
 
@@ -532,7 +585,10 @@ int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, int ks, hipStream_t s) 
 }  // namespace
 
 // Requirements: those of launch_gemm_mfma (bf16 weights, K % 32 == 0, row counts multiples of 16), K >= 128, 1 <= ncols <=
-// kPassCols (x_hi / x_lo hold ncols rounded up to 128 rows); with ssq_out at most kSsqStride row blocks.
+// kPassCols (x_hi / x_lo hold ncols rounded up to 128 rows); with ssq_out at most kSsqStride row blocks.  MODE_QKV_ROPE: head_dim
+// 128, ssq_in, col_at and rope_cs set, only q is written to out.
+bool gemm_prompt_takes(const GemvArgs& a, const Tuning& tn) { return a.ncols > 128 && a.K >= 2 * kBK && a.part && tn.mfma_wide; }
+
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {
     const int tiles = a.total_rows / 16;
     const int n_cb = (a.ncols + kTileN - 1) / kTileN;
@@ -544,6 +600,10 @@ int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, 
     const int n_stages = a.K / (2 * kBK) * 2, tiles_wg = n_rb * n_cb;
     const int ks = prompt_k_parts(tiles_wg, n_stages, n_cu, tn.prompt_ks, a.part && a.part_tickets);
     if (mode == MODE_STORE) return launch_prompt<MODE_STORE>(a, n_rb, n_cb, ks, s);
+    if (mode == MODE_QKV_ROPE) {
+        if (a.hd != 128 || !a.ssq_in || !a.col_at || !a.rope_cs || (a.kv_dtype != 0 && a.kv_dtype != 2)) return (int)hipErrorInvalidValue;
+        return launch_prompt<MODE_QKV_ROPE>(a, n_rb, n_cb, ks, s);
+    }
     if (mode == MODE_SWIGLU) return launch_prompt<MODE_SWIGLU>(a, n_rb, n_cb, ks, s);
     return launch_prompt<MODE_RESID>(a, n_rb, n_cb, ks, s);
 }

@@ -7,19 +7,16 @@ namespace d3 {
 namespace {
 
 // ---------------- embedding gather: x[c][:] = E[token(c)][:] ----------------
+// A workgroup per column: the column's row of the rotary table (the rotation angles depend on the position only, not on the
+// block) and its row of the residual stream.
 template <typename W>
-__global__ __launch_bounds__(256) void embed_kernel(const W* __restrict__ emb, const int32_t* __restrict__ tokens,
-                                                    ColMap cm, int d, int vocab, float* __restrict__ x,
-                                                    const double* __restrict__ inv_freq, int half_hd,
-                                                    float2* __restrict__ rope_cs, const int* __restrict__ row0) {
-    const int c = blockIdx.x;
-    if ((int)threadIdx.x < half_hd) {       // the rotation angles depend on the position only, not on the block
+__device__ __forceinline__ void embed_column(const W* __restrict__ emb, int tok, int angle_pos, int c, int d, int vocab, float* __restrict__ x,
+                                             const double* __restrict__ inv_freq, int half_hd, float2* __restrict__ rope_cs) {
+    if ((int)threadIdx.x < half_hd) {
         double sn, cs;
-        const int pos = cm.pos(c) - (row0 ? row0[cm.seq(c)] : 0);      // a left-padded sequence counts from its first token
-        sincos((double)pos * inv_freq[threadIdx.x], &sn, &cs);
+        sincos((double)angle_pos * inv_freq[threadIdx.x], &sn, &cs);
         rope_cs[(size_t)c * half_hd + threadIdx.x] = make_float2((float)cs, (float)sn);
     }
-    int tok = tokens[cm.tok_index(c)];
     tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);   // stay inside the table whatever the caller fed
     const W* row = emb + (size_t)tok * d;
     float* xo = x + (size_t)c * d;
@@ -33,6 +30,30 @@ __global__ __launch_bounds__(256) void embed_kernel(const W* __restrict__ emb, c
             *reinterpret_cast<float4*>(xo + j + 4) = make_float4(bf16_lo(v.z), bf16_hi(v.z), bf16_lo(v.w), bf16_hi(v.w));
         }
     }
+}
+template <typename W>
+__global__ __launch_bounds__(256) void embed_kernel(const W* __restrict__ emb, const int32_t* __restrict__ tokens,
+                                                    ColMap cm, int d, int vocab, float* __restrict__ x,
+                                                    const double* __restrict__ inv_freq, int half_hd,
+                                                    float2* __restrict__ rope_cs, const int* __restrict__ row0) {
+    const int c = blockIdx.x;
+    embed_column<W>(emb, tokens[cm.tok_index(c)], cm.pos(c) - (row0 ? row0[cm.seq(c)] : 0),      // a left-padded sequence counts from its first token
+                    c, d, vocab, x, inv_freq, half_hd, rope_cs);
+}
+__global__ __launch_bounds__(256) void embed_runs_kernel(const bf16_t* __restrict__ emb, const int32_t* __restrict__ tokens, SeqRuns runs, int P,
+                                                         int pos_begin, int d, int vocab, float* __restrict__ x,
+                                                         const double* __restrict__ inv_freq, int half_hd, float2* __restrict__ rope_cs,
+                                                         const int* __restrict__ row0, int2* __restrict__ col_at) {
+    const int c = blockIdx.x, r = runs.of(c), seq = runs.seq0 + r, pos = runs.pos[r] + (c - runs.col[r]);
+    if (threadIdx.x == 0) col_at[c] = make_int2(seq, pos);
+    embed_column<bf16_t>(emb, tokens[(size_t)seq * P + (pos - pos_begin)], pos - (row0 ? row0[seq] : 0), c, d, vocab, x, inv_freq, half_hd, rope_cs);
+}
+
+// ---------------- the last positions of a prompt pass ----------------
+__global__ __launch_bounds__(256) void pick_rows_kernel(const float* __restrict__ x, int d, RowPick pick, float* __restrict__ dst) {
+    const float* src = x + (size_t)pick.col[blockIdx.x] * d;
+    float* out = dst + (size_t)pick.row[blockIdx.x] * d;
+    for (int j = threadIdx.x * 4; j < d; j += blockDim.x * 4) *reinterpret_cast<float4*>(out + j) = *reinterpret_cast<const float4*>(src + j);
 }
 
 // ---------------- gain + split into bf16 hi/lo, sum of squares ----------------
@@ -96,7 +117,8 @@ __global__ __launch_bounds__(64) void rope_append_kernel(RopeArgs a) {
     const int head = blockIdx.x, c = blockIdx.y, j = threadIdx.x;
     const int half = a.hd / 2;
     if (j >= half) return;
-    const int seq = a.cm.seq(c), pos = a.cm.pos(c);
+    const int2 at = a.col_at ? a.col_at[c] : make_int2(a.cm.seq(c), a.cm.pos(c));
+    const int seq = at.x, pos = at.y;
     float* row = a.qkv + (size_t)c * (a.H + 2 * a.H_kv) * a.hd + (size_t)head * a.hd;
     if (head < a.H + a.H_kv) {
         const float2 cs = a.rope_cs[(size_t)c * half + j];
@@ -236,6 +258,18 @@ int launch_embed(const void* tok_emb, int weight_dtype, const int32_t* tokens, C
     else
         hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(ncols), dim3(256), 0, s, static_cast<const bf16_t*>(tok_emb), tokens, cm, d, vocab, x,
                            inv_freq, half_hd, rope_cs, row0);
+    return (int)hipGetLastError();
+}
+
+int launch_embed_runs(const void* tok_emb, const int32_t* tokens, const SeqRuns& runs, int P, int pos_begin, int ncols, int d, int vocab,
+                      float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, int2* col_at, hipStream_t s) {
+    hipLaunchKernelGGL(embed_runs_kernel, dim3(ncols), dim3(256), 0, s, static_cast<const bf16_t*>(tok_emb), tokens, runs, P, pos_begin, d, vocab, x,
+                       inv_freq, half_hd, rope_cs, row0, col_at);
+    return (int)hipGetLastError();
+}
+
+int launch_pick_rows(const float* x, int d, const RowPick& pick, float* dst, hipStream_t s) {
+    hipLaunchKernelGGL(pick_rows_kernel, dim3(pick.n), dim3(256), 0, s, x, d, pick, dst);
     return (int)hipGetLastError();
 }
 

@@ -130,6 +130,20 @@ def test_prompt_chunks_of_a_forced_width(monkeypatch, cols):
     _run(SMALL_GQA, 2, 150 if cols == 64 else 700, 4, 0.8, 1, forced_seed=9)
 
 
+@pytest.mark.parametrize("B,P,cols,lengths,kv", [(2, 32, 64, None, "f16"), (5, 13, 64, None, "f32"), (3, 43, 128, None, "f16"), (3, 150, 256, None, "f16"),
+                                                (32, 7, 0, None, "f32"), (4, 90, 128, (90, 1, 37, 2), "f32"), (3, 260, 320, (64, 260, 65), "f16")])
+def test_sequences_share_prompt_passes(monkeypatch, B, P, cols, lengths, kv):
+    # prompts laid end to end and cut into passes: passes that end between sequences, inside one and one column into the next (65 = 64
+    # + 1 and 129 = 128 + 1 columns: a pass of a single column), runs of one column, 32 sequences in a pass, and unequal prompts padded on the left; hidden states of the
+    # last positions from every pass, logits from the one head at the end
+    if cols:
+        monkeypatch.setenv("D3_PREFILL_COLS", str(cols))
+    s = ModelShape("shared", L=2, d=256, H=4, H_kv=2, hd=128, F=384, V=512, dtype="bf16")
+    gpu, gens = _run(s, B, P, 2, 1.0, 1, forced_seed=19, kv_dtype=kv, lengths=None if lengths is None else np.array(lengths, np.int32), max_seq=P + 2)
+    if kv == "f32":     # only arithmetic rounding is left
+        helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
 @pytest.mark.parametrize("ks", [2, 3, 4])
 def test_prompt_residual_projections_in_k_parts(monkeypatch, ks):
     # the projections of a prompt chunk with K cut into 2, 3 and 4 parts (one workgroup each; the part that arrives
