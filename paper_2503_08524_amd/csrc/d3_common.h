@@ -142,6 +142,7 @@ struct GemvArgs {
 // and K slices of the panel kernel; D3_WIDE_SPLIT_MB: matrix size above which a pass of more than 64 columns runs as
 // two 64-column launches; D3_ATTN_MFMA=0: grouped-query and query-tile attention on the vector ALUs;
 // D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most 2048); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8);
+// D3_PROMPT_CUS: compute units a round of its tiles is taken to have;
 // D3_PROMPT_ATTN_WGS: fewest workgroups (128 (query, head) pairs each) for which a prompt chunk takes the whole-context attention kernel; D3_GEMV_WGS_PER_CU: workgroups
 // per compute unit of the vector-ALU GEMV (default 3).
 struct Tuning {
@@ -153,7 +154,7 @@ struct Tuning {
     bool attn_mfma = true;
     int attn_min_split = 128;
     int prefill_cols = 0;
-    int prompt_ks = 0;
+    int prompt_ks = 0, prompt_cus = 0;
     int prompt_attn_wgs = 96;
 };
 Tuning tuning_from_env();

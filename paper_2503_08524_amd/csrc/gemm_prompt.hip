@@ -38,7 +38,8 @@
 //
 // Workgroup order: ids go to the XCDs round-robin; XCD x owns the row blocks x, x + 8, ... and walks them in groups of 4 row
 // blocks x 8 column blocks, so the 32 tiles it works on at a time share 12 slabs in its L2 (16 column blocks of 2 row
-// blocks: 18 slabs; gate/up at 2048 columns 640 -> 600 us, the smaller launches unchanged).
+// blocks: 18 slabs; gate/up at 2048 columns 640 -> 600 us, the smaller launches unchanged).  Tiles that do not fill a round of
+// all compute units are cut into K parts (prompt_split).
 //
 // SwiGLU: a workgroup's 256 slab rows are 128 gate rows and the 128 up rows of the same outputs, four tiles of each per
 // wave, so a wave finishes silu(gate) * up from its own accumulators.  Operand layouts, RMSNorm folding (1/rms from the
@@ -239,9 +240,10 @@ __device__ __forceinline__ void mma(f32x4 (&acc)[RW][2 * CW], int tt, const u32x
     for (int r = R0; r < R0 + N; ++r) acc[r][tt] = mfma(fa[r], fb, acc[r][tt]);
 }
 
-// ks: parts of K, one workgroup each.  (The buffer resource type exists in device code only.)
+// Tiles [0, n_whole) of the launch order have a workgroup each, the others ks of them, one per part of K.  (The buffer resource type
+// exists in device code only.)
 template <int MODE>
-__global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, int n_rb, int n_cb, int ks) {
+__global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, int n_rb, int n_cb, int n_whole, int ks) {
 #ifdef __HIP_DEVICE_COMPILE__
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
     constexpr int OT = 2 * RW / SW;                    // output row tiles per workgroup (half as many gate/up pairs)
@@ -253,25 +255,36 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     const int grp = wave8 >> 2, wave = wave8 & 3, wy = wave >> 1, wx = wave & 1;
     const int li = lane & 15, lg = lane >> 4;
 
-    // ---- launch order -> (row block, column block, K part); the virtual row blocks of the order are (row block, part) pairs ----
-    int rb, cb, slice;
+    // ---- launch order -> tile, K part; tile -> (row block, column block) ----
+    int tile_id = blockIdx.x, slice = 0, parts = 1;
+    if (tile_id >= n_whole) {                          // part by part: neighbours in the order share the part's columns of K
+        const int rest = n_rb * n_cb - n_whole;
+        slice = (tile_id - n_whole) / rest;
+        tile_id -= slice * rest;
+        parts = ks;
+    }
+    int rb, cb;
     {
         constexpr int GR = 4, GC = 8;
-        const int n_v = n_rb * ks, xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-        const int own = (n_v - xcd + 7) / 8;           // virtual row blocks of this XCD
-        if (idx >= own * n_cb) return;
-        const int group = idx / (GR * n_cb), rem = idx - group * GR * n_cb;
-        const int in_group = min(GR, own - GR * group);
-        const int chunk = rem / (in_group * GC), r2 = rem - chunk * in_group * GC;
-        const int v = (GR * group + r2 % in_group) * 8 + xcd;
-        cb = chunk * GC + r2 / in_group;
-        rb = v / ks; slice = v - rb * ks;
+        const int own = n_rb / 8, even = own * 8 * n_cb;       // row blocks per XCD; what is left of them comes last, in plain order
+        if (tile_id < even) {
+            const int xcd = tile_id & 7, idx = tile_id >> 3;
+            const int group = idx / (GR * n_cb), rem = idx - group * GR * n_cb;
+            const int in_group = min(GR, own - GR * group);
+            const int chunk = rem / (in_group * GC), r2 = rem - chunk * in_group * GC;
+            rb = (GR * group + r2 % in_group) * 8 + xcd;
+            cb = chunk * GC + r2 / in_group;
+        } else {
+            const int left = n_rb - own * 8;
+            rb = own * 8 + (tile_id - even) % left;
+            cb = (tile_id - even) / left;
+        }
     }
     const int K = a.K, tiles = a.total_rows / 16;      // output row tiles of the whole matrix
     // whole stages go to the parts in pairs; the last part takes what is over: an odd stage, and the half stage of K % 64 == 32
-    const int pairs = K / (2 * kBK), pair0 = (int)((long long)pairs * slice / ks);
-    const int s0 = 2 * pair0, n_stages = 2 * ((int)((long long)pairs * (slice + 1) / ks) - pair0);
-    const int s_end = (K + kBK - 1) / kBK, n_single = slice == ks - 1 ? s_end - 2 * pairs : 0;      // 0, 1 or 2
+    const int pairs = K / (2 * kBK), pair0 = (int)((long long)pairs * slice / parts);
+    const int s0 = 2 * pair0, n_stages = 2 * ((int)((long long)pairs * (slice + 1) / parts) - pair0);
+    const int s_end = (K + kBK - 1) / kBK, n_single = slice == parts - 1 ? s_end - 2 * pairs : 0;      // 0, 1 or 2
     // (the launcher sees to at least two whole stages per part)
 
     // ---- this wave's eight-row blocks of a stage (wave8, wave8 + 8, ...): the first 32 are weight rows, then hi, then lo ----
@@ -445,9 +458,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     }
 
     // ---- K parts: publish, count arrivals, the last one adds the parts up in order (independent of arrival order) ----
-    if (ks > 1) {
-        const int tile_id = rb * n_cb + cb;
-        float* mine = a.part + ((size_t)tile_id * ks + slice) * (kAccWords * kThreads) + 2 * tid;
+    if (parts > 1) {
+        const int part_id = tile_id - n_whole;
+        float* mine = a.part + ((size_t)part_id * parts + slice) * (kAccWords * kThreads) + 2 * tid;
 #pragma unroll
         for (int r = 0; r < RW; ++r)
 #pragma unroll
@@ -458,9 +471,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
         wait_stores();                                 // this part's partials have reached the coherence point
         __syncthreads();
         if (tid == 0) {
-            int* ticket = &a.part_tickets[tile_id];
+            int* ticket = &a.part_tickets[part_id];
             const int done = atomicAdd(ticket, 1);
-            is_last = done == ks - 1;
+            is_last = done == parts - 1;
             if (is_last) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // all arrived: leave it clean
         }
         __syncthreads();
@@ -469,8 +482,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
         for (int r = 0; r < RW; ++r)
 #pragma unroll
             for (int tt = 0; tt < CW; ++tt) fin[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int part = 0; part < ks; ++part) {
-            const float* p = a.part + ((size_t)tile_id * ks + part) * (kAccWords * kThreads) + 2 * tid;
+        for (int part = 0; part < parts; ++part) {
+            const float* p = a.part + ((size_t)part_id * parts + part) * (kAccWords * kThreads) + 2 * tid;
             float2 v[RW * CW * 2];
 #pragma unroll
             for (int i = 0; i < RW * CW * 2; ++i) v[i] = ld_agent2(p + i * 2 * kThreads);
@@ -554,31 +567,34 @@ __global__ __launch_bounds__(512, 2) void mfma_yardstick_kernel(float* __restric
     if (lane == 0) sink[blockIdx.x * 8 + wave] = sum;
 }
 
-// K parts of a launch.  A workgroup occupies a compute unit, so a launch takes ceil(workgroups / compute units) rounds of
-// stages / parts stages of 1.6 us each; a part more costs every round the publication of its accumulators (128 KB per
-// workgroup) and the last arriver the reading of all parts: 16 us + 3 us per part.  Measured at the 7B shape (us, 1 / 2 / 3 / 4 / 8
-// parts): O at 203 columns (32 tiles) 104 / 69 / 58 / 53 / 58, at 616 (80 tiles) 104 / 76 / 63 / 103 / 103 (four parts need a
-// second round), at 1280 (160 tiles) 118 / 145 / 136 / - / -; down at 512 (64 tiles) 247 / 149 / 118 / 104 / 161.
-int prompt_k_parts(int tiles_wg, int n_stages, int n_cu, int forced, bool can_split) {
-    auto fits = [&](int ks) { return can_split && 2 * ks <= n_stages && tiles_wg <= kGemmPartTickets && (size_t)tiles_wg * ks * kAccWords * kThreads * sizeof(float) <= kPromptPartBytes; };
-    if (forced >= 1) return fits(forced) ? forced : 1;
-    int best = 1;
-    long long best_cost = 0;
-    for (int ks = 1; ks <= 8; ++ks) {
-        if (ks > 1 && (!fits(ks) || n_stages / ks < 8)) break;
-        const long long rounds = ((long long)tiles_wg * ks + n_cu - 1) / n_cu;
-        const long long cost = rounds * ((n_stages + ks - 1) / ks + (ks > 1 ? 10 + 2 * ks : 0));     // in stages
-        if (ks == 1 || cost < best_cost) { best = ks; best_cost = cost; }
+// Which tiles of a launch are cut into K parts, and how many.  A workgroup occupies a compute unit, so whole tiles take rounds of
+// one tile per compute unit; the tiles of the last, partly filled round are cut so that their parts fill it.  A part costs
+// every round of parts the publication of its accumulators (128 KB per workgroup) and the last arriver the reading of all parts:
+// 16 us + 3 us per part, against 1.6 us per stage of 64 k.  Measured (us, whole / in parts): 13B shape, 2048 columns, 320 tiles: O 280 /
+// 221, down 667 / 484 (the last 64 tiles in 4 parts); 7B, 812 columns, QKV 336 tiles 176 / 157; 512 columns, gate/up 344 tiles 200 / 171; fewer tiles than
+// compute units: 7B O at 203 columns (32 tiles, 1 / 2 / 3 / 4 / 8 parts) 104 / 69 / 58 / 53 / 58, at 616 (80 tiles) 104 / 76 / 63 / 103 / 103.
+struct PromptSplit { int n_whole, ks; };
+PromptSplit prompt_split(int tiles_wg, int n_stages, int n_cu, int forced, bool can_split) {
+    auto fits = [&](int n, int ks) { return can_split && 2 * ks <= n_stages && n <= kGemmPartTickets && (size_t)n * ks * kAccWords * kThreads * sizeof(float) <= kPromptPartBytes; };
+    if (forced >= 1) return forced > 1 && fits(tiles_wg, forced) ? PromptSplit{0, forced} : PromptSplit{tiles_wg, 1};
+    const int rest = tiles_wg % n_cu;
+    PromptSplit best{tiles_wg, 1};
+    int best_cost = n_stages;                          // of the last round, in stages
+    for (int ks = 2; ks <= 8 && rest > 0; ++ks) {
+        if (!fits(rest, ks) || n_stages / ks < 8) break;
+        const int rounds = (rest * ks + n_cu - 1) / n_cu, cost = rounds * ((n_stages + ks - 1) / ks + 10 + 2 * ks);
+        if (cost < best_cost) { best = PromptSplit{tiles_wg - rest, ks}; best_cost = cost; }
     }
     return best;
 }
 
 template <int MODE>
-int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, int ks, hipStream_t s) {
+int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, PromptSplit sp, hipStream_t s) {
     constexpr int lds = 2 * kStage;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_prompt_kernel<MODE>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return (int)attr;
-    hipLaunchKernelGGL(gemm_prompt_kernel<MODE>, dim3((n_rb * ks + 7) / 8 * 8 * n_cb), dim3(kThreads), lds, s, a, n_rb, n_cb, ks);
+    const int grid = sp.n_whole + (n_rb * n_cb - sp.n_whole) * sp.ks;
+    hipLaunchKernelGGL(gemm_prompt_kernel<MODE>, dim3(grid), dim3(kThreads), lds, s, a, n_rb, n_cb, sp.n_whole, sp.ks);
     return (int)hipGetLastError();
 }
 
@@ -598,14 +614,14 @@ int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, 
     if (a.ssq_out && n_rb > kSsqStride) return (int)hipErrorInvalidValue;
     if (n_groups) *n_groups = n_rb;
     const int n_stages = a.K / (2 * kBK) * 2, tiles_wg = n_rb * n_cb;
-    const int ks = prompt_k_parts(tiles_wg, n_stages, n_cu, tn.prompt_ks, a.part && a.part_tickets);
-    if (mode == MODE_STORE) return launch_prompt<MODE_STORE>(a, n_rb, n_cb, ks, s);
+    const PromptSplit sp = prompt_split(tiles_wg, n_stages, tn.prompt_cus ? tn.prompt_cus : n_cu, tn.prompt_ks, a.part && a.part_tickets);
+    if (mode == MODE_STORE) return launch_prompt<MODE_STORE>(a, n_rb, n_cb, sp, s);
     if (mode == MODE_QKV_ROPE) {
         if (a.hd != 128 || !a.ssq_in || !a.col_at || !a.rope_cs || (a.kv_dtype != 0 && a.kv_dtype != 2)) return (int)hipErrorInvalidValue;
-        return launch_prompt<MODE_QKV_ROPE>(a, n_rb, n_cb, ks, s);
+        return launch_prompt<MODE_QKV_ROPE>(a, n_rb, n_cb, sp, s);
     }
-    if (mode == MODE_SWIGLU) return launch_prompt<MODE_SWIGLU>(a, n_rb, n_cb, ks, s);
-    return launch_prompt<MODE_RESID>(a, n_rb, n_cb, ks, s);
+    if (mode == MODE_SWIGLU) return launch_prompt<MODE_SWIGLU>(a, n_rb, n_cb, sp, s);
+    return launch_prompt<MODE_RESID>(a, n_rb, n_cb, sp, s);
 }
 
 // mode 0: MFMAs alone; 1: with the fragment reads of the stage loop; 2: with the stage barrier as well.  n_wg workgroups of

@@ -179,6 +179,16 @@ def test_prompt_kernel_contractions_and_parts(monkeypatch, d, F, P, ks):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("cus,F,P", [(4, 2048, 700), (7, 2080, 1100), (4, 2144, 513), (7, 4096, 900)])
+def test_prompt_tiles_whole_and_in_parts_in_one_launch(monkeypatch, cus, F, P):
+    # the down projection's row block x 5 to 9 column blocks, in rounds of 4 or 7 tiles: whole tiles first, then 1 or 2 tiles in 2 to 5
+    # parts each, of 32 stages and of 32.5, 33.5 and 64 (uneven parts, single stages in the last)
+    monkeypatch.setenv("D3_PROMPT_CUS", str(cus))
+    s = ModelShape("mixed", L=2, d=256, H=2, H_kv=1, hd=128, F=F, V=512, dtype="bf16")
+    gpu, gens = _run(s, 1, P, 2, 1.0, 1, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
 @pytest.mark.parametrize("H,H_kv,kv,P", [(2, 2, "f16", 130), (2, 2, "f16", 257), (3, 3, "f32", 65), (4, 2, "f16", 193), (4, 2, "f32", 129),
                                          (8, 2, "f16", 161), (8, 1, "f16", 150), (8, 1, "f32", 97), (8, 8, "f16", 64)])
 def test_prompt_attention_over_the_whole_context(monkeypatch, H, H_kv, kv, P):
