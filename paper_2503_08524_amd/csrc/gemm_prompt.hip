@@ -70,109 +70,93 @@ constexpr int RW = 8;                          // 16-row tiles per wave
 constexpr int CW = 2;                          // column tiles a wave finishes (it multiplies 2 CW)
 constexpr int kAccWords = RW * CW * 4;         // accumulator words per lane of a finished (half) wave tile
 
-// The epilogue, from the summed accumulators: lane (i, g) holds column i of a column tile, rows 4g..4g+3 of each row tile.
-// Wave (wy, wx) of group grp finishes slab rows 128 wy .. + 128 of the columns 64 wx + 32 grp .. + 32.
-template <int MODE>
-__device__ __forceinline__ void prompt_epilogue(const GemvArgs& a, const f32x4 (&acc)[RW][CW], int rb, int cb, int tiles, int grp, int wy, int wx,
-                                                const float* inv_rms, float (*ssq_w)[kTileN]) {
-    constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
-    constexpr int OT = 2 * RW / SW;                    // output row tiles per workgroup
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int li = lane & 15, lg = lane >> 4;
-    float sq[CW];
-#pragma unroll
-    for (int tt = 0; tt < CW; ++tt) sq[tt] = 0.f;
-#pragma unroll
-    for (int r = 0; r < RW / SW; ++r) {
-        // tiles and columns past the matrix compute on clamped addresses and store nothing (no divergent control flow around the loads)
-        const int otile_raw = rb * OT + wy * (RW / SW) + r;
-        const int otile = otile_raw < tiles ? otile_raw : tiles - 1;
-        const int row = otile * 16 + 4 * lg;
-        float4 gn = make_float4(1.f, 1.f, 1.f, 1.f);
-        if (MODE == MODE_RESID && a.ssq_out) gn = *reinterpret_cast<const float4*>(a.gain_next + row);
-#pragma unroll
-        for (int tt = 0; tt < CW; ++tt) {
-            const int cl = wx * 64 + grp * 32 + tt * 16 + li, col_raw = cb * kTileN + cl;
-            const bool live = otile_raw < tiles && col_raw < a.ncols;
-            const int col = col_raw < a.ncols ? col_raw : a.ncols - 1;
-            const size_t oi = (size_t)col * a.out_stride + row;
-            const f32x4 s0 = acc[r][tt];
-            float v[4], split[4];
-            if (MODE == MODE_STORE) {
-                const float sc = a.ssq_in ? inv_rms[cl] : 1.0f;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = s0[e] * sc;
-            } else if (MODE == MODE_RESID) {
-                const float4 o = *reinterpret_cast<const float4*>(a.out + oi);
-                v[0] = o.x + s0[0]; v[1] = o.y + s0[1]; v[2] = o.z + s0[2]; v[3] = o.w + s0[3];
-            } else {
-                const f32x4 s1 = acc[r + RW / 2][tt];
-                const float sc = a.ssq_in ? inv_rms[cl] : 1.0f;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { const float gt = s0[e] * sc; v[e] = gt / (1.0f + expf(-gt)) * (s1[e] * sc); }
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) split[e] = v[e];
-            if (MODE == MODE_RESID && a.ssq_out) {     // the consumer is a normalised projection: hand it x * gain and sum(x^2)
-                if (live) sq[tt] += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
-                split[0] = v[0] * gn.x; split[1] = v[1] * gn.y; split[2] = v[2] * gn.z; split[3] = v[3] * gn.w;
-            }
-            uint32_t hb[4], lb[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                hb[e] = f32_to_bf16(split[e]);
-                lb[e] = f32_to_bf16(split[e] - bf16_to_f32(hb[e]));
-            }
-            if (live) {
-                if (a.out) *reinterpret_cast<float4*>(a.out + oi) = make_float4(v[0], v[1], v[2], v[3]);
-                if (a.out_hi) {
-                    *reinterpret_cast<uint2*>(a.out_hi + oi) = make_uint2(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16));
-                    *reinterpret_cast<uint2*>(a.out_lo + oi) = make_uint2(lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16));
-                }
-            }
-        }
-    }
-    if (MODE == MODE_RESID && a.ssq_out) {             // rows of a column: the 4 lane groups by butterfly, then the two row halves in order
-#pragma unroll
-        for (int tt = 0; tt < CW; ++tt) {
-            sq[tt] += __shfl_xor(sq[tt], 16, 64);
-            sq[tt] += __shfl_xor(sq[tt], 32, 64);
-            if (lg == 0) ssq_w[wy][wx * 64 + grp * 32 + tt * 16 + li] = sq[tt];
-        }
-        __syncthreads();
-        if (tid < kTileN && cb * kTileN + tid < a.ncols) a.ssq_out[(size_t)(cb * kTileN + tid) * kSsqStride + rb] = ssq_w[0][tid] + ssq_w[1][tid];
-    }
-}
+// Instructions stay on their side of this point: what interleaves the MFMAs with loads and reads as written.
+__device__ __forceinline__ void fixed_here() { __builtin_amdgcn_sched_barrier(0); }
 
-// QKV of a prompt pass at head_dim 128: a wave's 128 rows are one head, and row tiles r and r + 4 hold the dims j and j + 64 that one
-// rotation pairs, so q and k are rotated and k and v appended to the cache straight from the accumulators (as a launch of its own
-// over fp32 q, k, v that took 24 us of a 2048-column block at the 7B shape).
-template <typename T>
-__device__ __forceinline__ void store_row4(T* p, const float (&v)[4]);
-template <> __device__ __forceinline__ void store_row4<float>(float* p, const float (&v)[4]) { *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]); }
-template <> __device__ __forceinline__ void store_row4<f16_t>(f16_t* p, const float (&v)[4]) {
+__device__ __forceinline__ void store_split(const GemvArgs& a, size_t oi, const float (&v)[4]) {
+    uint32_t hb[4], lb[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        hb[e] = f32_to_bf16(v[e]);
+        lb[e] = f32_to_bf16(v[e] - bf16_to_f32(hb[e]));
+    }
+    *reinterpret_cast<uint2*>(a.out_hi + oi) = make_uint2(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16));
+    *reinterpret_cast<uint2*>(a.out_lo + oi) = make_uint2(lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16));
+}
+// the cache's element type from four fp32 values
+__device__ __forceinline__ void store_row4(float* p, const float (&v)[4]) { *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void store_row4(f16_t* p, const float (&v)[4]) {
     typedef _Float16 half4 __attribute__((ext_vector_type(4)));
     half4 h;
 #pragma unroll
     for (int e = 0; e < 4; ++e) h[e] = (f16_t)fminf(fmaxf(v[e], -65504.f), 65504.f);
     *reinterpret_cast<half4*>(p) = h;
 }
+
+// ---- epilogues of the projections that only store (STORE, SWIGLU), from the summed accumulators: lane (i, g) holds column i of a column
+// tile, rows 4g..4g+3 of each row tile.  Wave (wy, wx) of group grp finishes slab rows 128 wy .. + 128 of the columns 64 wx + 32 grp .. + 32. ----
+template <int MODE>
+__device__ __forceinline__ void store_tiles(const GemvArgs& a, const f32x4 (&acc)[RW][CW], int rb, int cb, int tiles, int grp, int wy, int wx,
+                                            const float* inv_rms) {
+    constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
+    constexpr int OT = 2 * RW / SW;                    // output row tiles per workgroup
+    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+#pragma unroll
+    for (int r = 0; r < RW / SW; ++r) {
+        const int otile = rb * OT + wy * (RW / SW) + r, row = otile * 16 + 4 * lg;
+#pragma unroll
+        for (int tt = 0; tt < CW; ++tt) {
+            const int cl = wx * 64 + grp * 32 + tt * 16 + li, col = cb * kTileN + cl;
+            const float sc = a.ssq_in ? inv_rms[cl] : 1.0f;
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] = acc[r][tt][e] * sc;
+                if (MODE == MODE_SWIGLU) v[e] = v[e] / (1.0f + expf(-v[e])) * (acc[r + RW / 2][tt][e] * sc);
+            }
+            if (otile < tiles && col < a.ncols) {
+                const size_t oi = (size_t)col * a.out_stride + row;
+                if (a.out) *reinterpret_cast<float4*>(a.out + oi) = make_float4(v[0], v[1], v[2], v[3]);
+                if (a.out_hi) store_split(a, oi, v);
+            }
+        }
+    }
+}
+
+// ---- QKV of a prompt pass at head_dim 128: a wave's 128 rows are one head, and row tiles r and r + 4 hold the dims j and j + 64 that one
+// rotation pairs, so q and k are rotated and k and v appended to the cache straight from the accumulators (as a launch of its own
+// over fp32 q, k, v that took 24 us of a 2048-column block at the 7B shape). ----
 template <typename T>
-__device__ __forceinline__ void qkv_rope_epilogue(const GemvArgs& a, const f32x4 (&acc)[RW][CW], int rb, int cb, int grp, int wy, int wx, const float* inv_rms) {
+__device__ __forceinline__ void store_qkv(const GemvArgs& a, const f32x4 (&acc)[RW][CW], int rb, int cb, int grp, int wy, int wx, const float* inv_rms) {
     const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
     const int head = 2 * rb + wy;
     if (head >= a.H + 2 * a.H_kv) return;
     const bool is_q = head < a.H, is_v = head >= a.H + a.H_kv;
     const int kvh = is_v ? head - a.H - a.H_kv : head - a.H;
+    int2 at[CW];                                       // (sequence, cache row) of this lane's columns
+    float4 c0[CW][RW / 2], c1[CW][RW / 2];             // (cos, sin) of dims j, j + 1 and j + 2, j + 3
+#pragma unroll
+    for (int tt = 0; tt < CW; ++tt) {                  // all requested before the first store, which they might alias
+        const int col_raw = cb * kTileN + wx * 64 + grp * 32 + tt * 16 + li, col = col_raw < a.ncols ? col_raw : a.ncols - 1;
+        at[tt] = a.col_at[col];
+        if (!is_v) {
+#pragma unroll
+            for (int r = 0; r < RW / 2; ++r) {
+                const float2* cs = a.rope_cs + (size_t)col * 64 + 16 * r + 4 * lg;
+                c0[tt][r] = *reinterpret_cast<const float4*>(cs);
+                c1[tt][r] = *reinterpret_cast<const float4*>(cs + 2);
+            }
+        }
+    }
+    fixed_here();
 #pragma unroll
     for (int tt = 0; tt < CW; ++tt) {
         const int cl = wx * 64 + grp * 32 + tt * 16 + li, col = cb * kTileN + cl;
         if (col >= a.ncols) continue;
         const float sc = inv_rms[cl];
-        const int2 at = a.col_at[col];                 // (sequence, cache row)
         float* q = a.out + (size_t)col * a.out_stride + head * 128;
         T* row = nullptr;
-        if (!is_q) row = static_cast<T*>(is_v ? a.v_cache : a.k_cache) + (((size_t)at.x * a.H_kv + kvh) * a.max_seq + at.y) * 128;
+        if (!is_q) row = static_cast<T*>(is_v ? a.v_cache : a.k_cache) + (((size_t)at[tt].x * a.H_kv + kvh) * a.max_seq + at[tt].y) * 128;
 #pragma unroll
         for (int r = 0; r < RW / 2; ++r) {
             const int j = 16 * r + 4 * lg;
@@ -180,17 +164,69 @@ __device__ __forceinline__ void qkv_rope_epilogue(const GemvArgs& a, const f32x4
 #pragma unroll
             for (int e = 0; e < 4; ++e) { lo[e] = acc[r][tt][e] * sc; hi[e] = acc[r + RW / 2][tt][e] * sc; }
             if (!is_v) {
-                const float4 c0 = *reinterpret_cast<const float4*>(a.rope_cs + (size_t)col * 64 + j), c1 = *reinterpret_cast<const float4*>(a.rope_cs + (size_t)col * 64 + j + 2);
-                const float cs[4] = {c0.x, c0.z, c1.x, c1.z}, sn[4] = {c0.y, c0.w, c1.y, c1.w};
+                const float cs[4] = {c0[tt][r].x, c0[tt][r].z, c1[tt][r].x, c1[tt][r].z}, sn[4] = {c0[tt][r].y, c0[tt][r].w, c1[tt][r].y, c1[tt][r].w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float y0 = lo[e] * cs[e] - hi[e] * sn[e], y1 = lo[e] * sn[e] + hi[e] * cs[e];
                     lo[e] = y0; hi[e] = y1;
                 }
             }
-            if (is_q) { store_row4<float>(q + j, lo); store_row4<float>(q + j + 64, hi); }
-            else { store_row4<T>(row + j, lo); store_row4<T>(row + j + 64, hi); }
+            if (is_q) { store_row4(q + j, lo); store_row4(q + j + 64, hi); }
+            else { store_row4(row + j, lo); store_row4(row + j + 64, hi); }
         }
+    }
+}
+
+// ---- residual projections.  The finished sums go through LDS, [128 columns][256 rows] of fp32, so that a wave then takes whole columns and
+// its loads and stores are 512 bytes to 1 KB in a row.  From the accumulators' own layout an instruction touches 16 columns' rows of 32
+// or 64 bytes each, which stores only (above) leave behind but the reading of the old residual waits for: 7B shape, O 137 -> 124 us at
+// 2048 columns, 63 -> 59 at 512, down 110 -> 102 at 512; 13B down 489 -> 474 at 2048.  (QKV through LDS as well: 310 -> 320.)
+// Rows 4 u .. + 3 of column c are float4 u ^ (c % 16) of the column: the writes of 16 columns' rows u and the reads of one column both
+// spread over all banks. ----
+__device__ __forceinline__ f32x4* staged(char* lds, int c, int u) { return reinterpret_cast<f32x4*>(lds) + c * 64 + (u ^ (c & 15)); }
+constexpr int kWaveCols = kTileN / kWaves;             // columns a wave finishes: 16; lane l takes rows 4 l .. + 3 of each
+__device__ __forceinline__ void add_residual(const GemvArgs& a, char* lds, int rb, int cb, int wave8, int lane) {
+    const int row_raw = rb * kTileM + 4 * lane, c0 = wave8 * kWaveCols;
+    const bool live_row = row_raw < a.total_rows;
+    const int row = live_row ? row_raw : a.total_rows - 4;         // rows past the matrix compute on clamped addresses and store nothing
+    float4 old[kWaveCols], gain = make_float4(1.f, 1.f, 1.f, 1.f);
+    if (a.ssq_out) gain = *reinterpret_cast<const float4*>(a.gain_next + row);
+#pragma unroll
+    for (int i = 0; i < kWaveCols; ++i) {              // all requested before the first store, which they might alias
+        const int col_raw = cb * kTileN + c0 + i, col = col_raw < a.ncols ? col_raw : a.ncols - 1;
+        old[i] = *reinterpret_cast<const float4*>(a.out + (size_t)col * a.out_stride + row);
+    }
+    float sq[kWaveCols];
+#pragma unroll
+    for (int i = 0; i < kWaveCols; ++i) {
+        const int c = c0 + i, col = cb * kTileN + c;
+        const bool live = live_row && col < a.ncols;
+        const f32x4 sum = *staged(lds, c, lane);
+        const float v[4] = {old[i].x + sum[0], old[i].y + sum[1], old[i].z + sum[2], old[i].w + sum[3]};
+        sq[i] = live ? (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]) : 0.f;
+        if (live) {
+            const size_t oi = (size_t)col * a.out_stride + row;
+            store_row4(a.out + oi, v);
+            if (a.out_hi) {                            // a normalised projection reads it next: hand it x * gain (and sum(x^2) below)
+                const float w[4] = {v[0] * gain.x, v[1] * gain.y, v[2] * gain.z, v[3] * gain.w};
+                store_split(a, oi, w);
+            }
+        }
+    }
+    if (a.ssq_out) {                                   // sixteen sums over 64 lanes: halve the columns a lane carries at every step
+#pragma unroll
+        for (int o = 32, n = kWaveCols / 2; o >= 4; o >>= 1, n >>= 1) {
+            const bool up = lane & o;
+#pragma unroll
+            for (int i = 0; i < n; ++i) {
+                const float mine = up ? sq[i + n] : sq[i], theirs = up ? sq[i] : sq[i + n];
+                sq[i] = mine + __shfl_xor(theirs, o, 64);
+            }
+        }
+        sq[0] += __shfl_xor(sq[0], 2, 64);
+        sq[0] += __shfl_xor(sq[0], 1, 64);
+        const int col = cb * kTileN + c0 + (lane >> 2);            // lane bits 5..2 name the column that is left
+        if ((lane & 3) == 0 && col < a.ncols) a.ssq_out[(size_t)col * kSsqStride + rb] = sq[0];
     }
 }
 
@@ -218,9 +254,6 @@ __device__ __forceinline__ void all_arrived(u32x4 (&f)[RW]) {
 #pragma unroll
     for (int r = 0; r < RW; ++r) pin_frag(f[r]);
 }
-// Instructions stay on their side of this point: what interleaves the MFMAs with loads and reads as written.
-__device__ __forceinline__ void fixed_here() { __builtin_amdgcn_sched_barrier(0); }
-
 struct PromptB { u32x4 h, l; };                       // one column tile's activation fragments: hi and lo plane
 __device__ __forceinline__ void all_arrived(PromptB& f) { lds_reads_left<0>(); pin_frag(f.h); pin_frag(f.l); }
 template <int... R>
@@ -248,7 +281,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
     constexpr int OT = 2 * RW / SW;                    // output row tiles per workgroup (half as many gate/up pairs)
     __shared__ float inv_rms[kTileN];
-    __shared__ float ssq_w[2][kTileN];
     __shared__ int is_last;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -322,22 +354,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)prompt_lds;
     const uint32_t a_off = lds0 + (wy * 16 * RW + li) * kPitch + slot, b_off = lds0 + kABytes + (wx * 64 + li) * kPitch + slot;
 
-    // 16 threads add up one column's partial sums of squares, in a fixed order (before the direct loads: vmcnt counts these loads too)
-    if (MODE != MODE_RESID && a.ssq_in) {
-        for (int c = tid >> 4; c < kTileN; c += kThreads / 16) {
-            const int col = cb * kTileN + c;
-            float ss = 0.f;
-            if (col < a.ncols) {
-                const float* p = a.ssq_in + (size_t)col * kSsqStride;
-                for (int i0 = tid & 15; i0 < a.ssq_parts; i0 += 16) ss += p[i0];
-            }
-#pragma unroll
-            for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
-            if ((tid & 15) == 0) inv_rms[c] = 1.0f / sqrtf(ss / (float)K + a.eps);
-        }
-    }
-    vm_loads_left<0>();
-
     f32x4 acc[RW][2 * CW];                             // [row tile of the wave][column tile of the wave]
 #pragma unroll
     for (int r = 0; r < RW; ++r)
@@ -405,7 +421,23 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     for (int j = 0; j < kLoads; ++j) load1(j, s0, 0);
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) load1(j, s0 + 1, 1);
-    vm_loads_left<kLoads>();
+    // 16 threads add up one column's partial sums of squares, in a fixed order, behind the direct loads of the first two stages
+    // (reading them ahead of those put a round trip more in front of every tile)
+    if (MODE != MODE_RESID && a.ssq_in) {
+        for (int c = tid >> 4; c < kTileN; c += kThreads / 16) {
+            const int col = cb * kTileN + c;
+            float ss = 0.f;
+            if (col < a.ncols) {
+                const float* p = a.ssq_in + (size_t)col * kSsqStride;
+                for (int i0 = tid & 15; i0 < a.ssq_parts; i0 += 16) ss += p[i0];
+            }
+#pragma unroll
+            for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
+            if ((tid & 15) == 0) inv_rms[c] = 1.0f / sqrtf(ss / (float)K + a.eps);
+        }
+    }
+    if (MODE != MODE_RESID && a.ssq_in) vm_loads_left<0>();
+    else vm_loads_left<kLoads>();
     __syncthreads();                                   // stage 0 is in LDS (and inv_rms is written)
     read_b_frags<0>(f0, b_off);
     read_a_frags(A0, a_off, std::make_integer_sequence<int, RW>{});
@@ -496,10 +528,18 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
                 }
         }
     }
-    if constexpr (MODE == MODE_QKV_ROPE) {
-        if (a.kv_dtype == 0) qkv_rope_epilogue<float>(a, fin, rb, cb, grp, wy, wx, inv_rms);
-        else qkv_rope_epilogue<f16_t>(a, fin, rb, cb, grp, wy, wx, inv_rms);
-    } else prompt_epilogue<MODE>(a, fin, rb, cb, tiles, grp, wy, wx, inv_rms, ssq_w);
+    if constexpr (MODE == MODE_RESID) {
+        __syncthreads();                               // the exchanged halves have been read
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int tt = 0; tt < CW; ++tt) *staged(prompt_lds, wx * 64 + grp * 32 + tt * 16 + li, wy * 32 + 4 * r + lg) = fin[r][tt];
+        __syncthreads();
+        add_residual(a, prompt_lds, rb, cb, wave8, lane);
+    } else if constexpr (MODE == MODE_QKV_ROPE) {
+        if (a.kv_dtype == 0) store_qkv<float>(a, fin, rb, cb, grp, wy, wx, inv_rms);
+        else store_qkv<f16_t>(a, fin, rb, cb, grp, wy, wx, inv_rms);
+    } else store_tiles<MODE>(a, fin, rb, cb, tiles, grp, wy, wx, inv_rms);
 #endif
 }
 
