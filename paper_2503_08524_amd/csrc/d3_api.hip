@@ -86,7 +86,7 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
     l.n_lo = take(CS * d.d_model * 2);
     l.ssq = take(C * kSsqStride * 4);
     l.h_skip = take(PC * d.d_model * 4);                              // decode passes only
-    l.gemm_part = take(with_gemm_part ? (C > 128 ? kPromptPartBytes : kGemmPartBytes) : 0);   // passes of more than 128 columns are prompt chunks
+    l.gemm_part = take(with_gemm_part ? (C > (size_t)kMaxCols ? kPromptPartBytes : kGemmPartBytes) : 0);   // passes of more than 32 columns are prompt chunks
     l.gemm_tickets = take((size_t)kGemmPartTickets * 4);
     l.row0 = take(kMaxCols * 4);
     l.col_at = take(C * 8);                                           // (sequence, cache row) of a prompt pass's columns
@@ -135,6 +135,7 @@ Tuning tuning_from_env() {
     const int pc = env_int("D3_PREFILL_COLS", 64, kPassCols, 0);
     t.prefill_cols = pc % 64 == 0 ? pc : 0;
     t.prompt_ks = env_int("D3_PROMPT_KS", 1, 8, 0);
+    t.prompt_row_blocks = env_int("D3_PROMPT_ROW_BLOCKS", 1, 1 << 20, 24);
     t.prompt_cus = env_int("D3_PROMPT_CUS", 1, 4096, 0);
     t.prompt_attn_wgs = env_int("D3_PROMPT_ATTN_WGS", 1, 1 << 20, 96);
     return t;
@@ -460,7 +461,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         void* v_layer = c->v_cache + (size_t)l * c->kv_layer_bytes();
         if (mfma) {
             g.x_hi = n_hi; g.x_lo = n_lo; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = ssq_parts;
-            const bool rope_in_qkv = qtile && gemm_prompt_takes(g, c->tn);
+            const bool rope_in_qkv = qtile && gemm_prompt_takes(g, MODE_QKV_ROPE, c->tn);
             {
                 Timed t(c, D3_K_QKV, s);
                 if (rope_in_qkv) {

@@ -142,6 +142,7 @@ struct GemvArgs {
 // and K slices of the panel kernel; D3_WIDE_SPLIT_MB: matrix size above which a pass of more than 64 columns runs as
 // two 64-column launches; D3_ATTN_MFMA=0: grouped-query and query-tile attention on the vector ALUs;
 // D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most 2048); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8);
+// D3_PROMPT_ROW_BLOCKS: fewest blocks of 256 rows for which 65..128 columns take the LDS-tiled kernel;
 // D3_PROMPT_CUS: compute units a round of its tiles is taken to have;
 // D3_PROMPT_ATTN_WGS: fewest workgroups (128 (query, head) pairs each) for which a prompt chunk takes the whole-context attention kernel; D3_GEMV_WGS_PER_CU: workgroups
 // per compute unit of the vector-ALU GEMV (default 3).
@@ -154,7 +155,7 @@ struct Tuning {
     bool attn_mfma = true;
     int attn_min_split = 128;
     int prefill_cols = 0;
-    int prompt_ks = 0, prompt_cus = 0;
+    int prompt_ks = 0, prompt_cus = 0, prompt_row_blocks = 24;
     int prompt_attn_wgs = 96;
 };
 Tuning tuning_from_env();
@@ -164,7 +165,7 @@ int launch_gemv_alu(const GemvArgs& a, int weight_dtype, int mode, bool norm, in
 // n_groups: workgroups launched (= parts written to ssq_out)
 int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups = nullptr);
 int launch_gemm_mfma_wide(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // 17..128 columns
-bool gemm_prompt_takes(const GemvArgs& a, const Tuning& tn);   // launch_gemm_mfma sends the launch to launch_gemm_prompt
+bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn);   // launch_gemm_mfma sends the launch to launch_gemm_prompt
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // 129..kPassCols columns: LDS-tiled, compute-bound
 size_t gemv_alu_max_cols(int K, int weight_dtype);   // columns one ALU launch can take (LDS bound)
 

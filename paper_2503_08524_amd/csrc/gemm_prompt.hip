@@ -643,7 +643,14 @@ int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, PromptSplit sp, hipStre
 // Requirements: those of launch_gemm_mfma (bf16 weights, K % 32 == 0, row counts multiples of 16), K >= 128, 1 <= ncols <=
 // kPassCols (x_hi / x_lo hold ncols rounded up to 128 rows); with ssq_out at most kSsqStride row blocks.  MODE_QKV_ROPE: head_dim
 // 128, ssq_in, col_at and rope_cs set, only q is written to out.
-bool gemm_prompt_takes(const GemvArgs& a, const Tuning& tn) { return a.ncols > 128 && a.K >= 2 * kBK && a.part && tn.mfma_wide; }
+// Up to 128 columns the panel kernel is the other choice.  It slows down past 64 (its LDS pipe, or two launches of 64), the LDS-tiled
+// kernel takes one column block whatever its width and wants row blocks.  Measured at 77 columns (us, panel / LDS-tiled): 48 or more row blocks: 7B QKV
+// 60 / 54, gate/up 100 / 76, 13B 74 / 60 and 126 / 96, 70B gate/up 354 / 277; 40 and 32: 70B QKV 78 / 71, O 78 / 68, down 211 / 163; 20: 13B O 40 / 53,
+// down 86 / 82; 16: 7B O 28 / 48, down 57 / 70.  At 64 columns the panel kernel is ahead everywhere (7B gate/up 50 / 75, 70B 181 / 279).
+bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn) {
+    const int row_blocks = a.total_rows / (mode == MODE_SWIGLU ? kTileM / 2 : kTileM);
+    return a.K >= 2 * kBK && a.part && tn.mfma_wide && (a.ncols > 128 || (a.ncols > 64 && row_blocks >= tn.prompt_row_blocks));
+}
 
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {
     const int tiles = a.total_rows / 16;

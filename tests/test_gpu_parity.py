@@ -179,6 +179,16 @@ def test_prompt_kernel_contractions_and_parts(monkeypatch, d, F, P, ks):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("P,blocks", [(65, 1), (100, 2), (128, 4)])
+def test_short_prompts_on_the_prompt_kernel(monkeypatch, P, blocks):
+    # 65 to 128 columns: the LDS-tiled kernel takes the projections with enough row blocks (all, then gate/up and QKV, then gate/up
+    # alone), the panel kernel the others; each reads the other's partial sums of squares and activations
+    monkeypatch.setenv("D3_PROMPT_ROW_BLOCKS", str(blocks))
+    s = ModelShape("short", L=2, d=256, H=2, H_kv=1, hd=128, F=608, V=512, dtype="bf16")
+    gpu, gens = _run(s, 1, P, 2, 1.0, 1, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
 @pytest.mark.parametrize("cus,F,P", [(4, 2048, 700), (7, 2080, 1100), (4, 2144, 513), (7, 4096, 900)])
 def test_prompt_tiles_whole_and_in_parts_in_one_launch(monkeypatch, cus, F, P):
     # the down projection's row block x 5 to 9 column blocks, in rounds of 4 or 7 tiles: whole tiles first, then 1 or 2 tiles in 2 to 5
