@@ -405,6 +405,14 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     bf16_t *n_hi = c->at<bf16_t>(c->lay.n_hi), *n_lo = c->at<bf16_t>(c->lay.n_lo);   // split of residual * next norm's gain
     float* ssq = c->at<float>(c->lay.ssq);
     int ssq_parts = 1;
+    // Matrix-core path: RMSNorm lives inside the projections.  Whoever writes the residual (the embedding first) also writes the split of
+    // residual * (gain of the norm that reads it next) and partial sums of squares; the reading projection scales its
+    // sums by 1/rms.  The norm after block e is the next executed block's, or the final one.
+    auto gain_after = [&](int e) -> const float* {
+        return static_cast<const float*>(e + 1 < n_ids ? c->layers[ids[e + 1]].attn_norm : c->final_norm);
+    };
+    const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_hi, n_lo, ssq};
+
     // a prompt chunk of one sequence (consecutive positions) or of several: tiles of queries share the cache rows they read
     const int grp = d.n_heads / d.n_kv_heads;
     const bool qtile = shared || (c->prefill_by_seq && mfma && cm.B == 1 && ncols >= 2 && hd == 128 &&
@@ -413,8 +421,8 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     one.n = 1; one.seq0 = cm.seq(0); one.col[1] = ncols; one.pos[0] = cm.pos(0);
     const SeqRuns& runs = shared ? *shared : one;
     int2* col_at = qtile ? c->at<int2>(c->lay.col_at) : nullptr;
-    if (qtile) D3_HIP(launch_embed_runs(c->tok_emb, tokens, runs, cm.P, cm.pos_begin, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, col_at, s));
-    else D3_HIP(launch_embed(c->tok_emb, d.weight_dtype, tokens, cm, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, s));
+    if (qtile) D3_HIP(launch_embed_runs(c->tok_emb, tokens, runs, cm.P, cm.pos_begin, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, col_at, split, s));
+    else D3_HIP(launch_embed(c->tok_emb, d.weight_dtype, tokens, cm, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, split, s));
     auto dump = [&](int slot) -> int {
         if (!hidden_dump) return 0;
         if (shared) return launch_pick_rows(x, dm, *picks, hidden_dump + (size_t)slot * dump_total * dm, s);
@@ -432,14 +440,6 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     const bool prompt_attn = shared || (qtile && c->tn.attn_mfma && (ncols * grp + 127) / 128 * d.n_kv_heads >= c->tn.prompt_attn_wgs);
     int split_len = 0, n_splits = 0;
     if (!prompt_attn) pick_splits(c, ncols, cm.pos(ncols - 1) + 1, c->attn_wgs_per_cu * c->n_cu, &split_len, &n_splits, qtile);
-
-    // Matrix-core path: RMSNorm lives inside the projections.  Whoever writes the residual also writes the split of
-    // residual * (gain of the norm that reads it next) and partial sums of squares; the reading projection scales its
-    // sums by 1/rms.  The norm after block e is the next executed block's, or the final one.
-    auto gain_after = [&](int e) -> const float* {
-        return static_cast<const float*>(e + 1 < n_ids ? c->layers[ids[e + 1]].attn_norm : c->final_norm);
-    };
-    if (mfma) D3_HIP(launch_gain_split(x, dm, gain_after(-1), dm, ncols, n_hi, n_lo, ssq, s));
 
     bool saved = save_before < 0;
     auto save_skip = [&]() -> int {

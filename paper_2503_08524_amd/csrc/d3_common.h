@@ -169,21 +169,23 @@ bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn);   // laun
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // 129..kPassCols columns: LDS-tiled, compute-bound
 size_t gemv_alu_max_cols(int K, int weight_dtype);   // columns one ALU launch can take (LDS bound)
 
-// first step of a pass on the MFMA path: hi + lo = x * gain (bf16 halves), ssq[col * kSsqStride] = sum(x^2)
+// hi + lo = x * gain (bf16 halves), ssq[col * kSsqStride] = sum(x^2)
 int launch_gain_split(const float* x, int x_stride, const float* gain, int K, int ncols,
                       bf16_t* hi, bf16_t* lo, float* ssq, hipStream_t s);
 
 // ---------------- the rest of a block ----------------
 // x[c][:] = E[token(c)][:], and the pass's rotary table rope_cs[c][j] = (cos, sin)((pos(c) - row0[seq(c)]) * inv_freq[j])
 // (row0 optional: the first cache row of each sequence of a left-padded batch)
+// What a pass on the matrix-core path starts from, beside x (gain NULL: not wanted; bf16 tables only): launch_gain_split's outputs.
+struct EmbedSplit { const float* gain; bf16_t *hi, *lo; float* ssq; };
 // The columns of `runs`: tokens [B][P] of the cache rows from pos_begin on; also col_at[c] = (sequence, cache row) of every column.
 int launch_embed_runs(const void* tok_emb, const int32_t* tokens, const SeqRuns& runs, int P, int pos_begin, int ncols, int d, int vocab,
-                      float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, int2* col_at, hipStream_t s);   // bf16 table
+                      float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, int2* col_at, const EmbedSplit& split, hipStream_t s);   // bf16 table
 // dst[row[r]][:] = x[col[r]][:], r < n: the last position of every sequence that a prompt pass finishes
 struct RowPick { int n, col[kMaxCols], row[kMaxCols]; };
 int launch_pick_rows(const float* x, int d, const RowPick& pick, float* dst, hipStream_t s);
 int launch_embed(const void* tok_emb, int weight_dtype, const int32_t* tokens, ColMap cm, int ncols, int d,
-                 int vocab, float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, hipStream_t s);
+                 int vocab, float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, const EmbedSplit& split, hipStream_t s);
 
 struct RopeArgs {
     float* qkv;            // [ncols][(H + 2 H_kv) * hd] fp32: q rotated in place

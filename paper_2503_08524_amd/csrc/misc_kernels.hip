@@ -8,10 +8,11 @@ namespace {
 
 // ---------------- embedding gather: x[c][:] = E[token(c)][:] ----------------
 // A workgroup per column: the column's row of the rotary table (the rotation angles depend on the position only, not on the
-// block) and its row of the residual stream.
+// block) and its row of the residual stream; on the matrix-core path (split.gain set) also what gain_split_kernel hands to the first
+// projection, from the registers that hold the row anyway (as a launch of its own that was 5 us of a decode step, 13 us of 2048 columns).
 template <typename W>
 __device__ __forceinline__ void embed_column(const W* __restrict__ emb, int tok, int angle_pos, int c, int d, int vocab, float* __restrict__ x,
-                                             const double* __restrict__ inv_freq, int half_hd, float2* __restrict__ rope_cs) {
+                                             const double* __restrict__ inv_freq, int half_hd, float2* __restrict__ rope_cs, const EmbedSplit& split) {
     if ((int)threadIdx.x < half_hd) {
         double sn, cs;
         sincos((double)angle_pos * inv_freq[threadIdx.x], &sn, &cs);
@@ -20,33 +21,72 @@ __device__ __forceinline__ void embed_column(const W* __restrict__ emb, int tok,
     tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);   // stay inside the table whatever the caller fed
     const W* row = emb + (size_t)tok * d;
     float* xo = x + (size_t)c * d;
+    float ss = 0.f;
     if (sizeof(W) == 4) {
         for (int j = threadIdx.x * 4; j < d; j += blockDim.x * 4)
             *reinterpret_cast<float4*>(xo + j) = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(row) + j);
     } else {
-        for (int j = threadIdx.x * 8; j < d; j += blockDim.x * 8) {       // d % 8 == 0: eight bf16 per load
-            const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(row) + j);
-            *reinterpret_cast<float4*>(xo + j) = make_float4(bf16_lo(v.x), bf16_hi(v.x), bf16_lo(v.y), bf16_hi(v.y));
-            *reinterpret_cast<float4*>(xo + j + 4) = make_float4(bf16_lo(v.z), bf16_hi(v.z), bf16_lo(v.w), bf16_hi(v.w));
+        // d % 8 == 0: eight bf16 per load; up to R pieces per thread and their gains are requested together, wider rows go round again
+        constexpr int R = 4;
+        for (int base = threadIdx.x * 8; base < d; base += R * 2048) {
+            uint4 v[R];
+            float4 g0[R], g1[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int at = base + r * 2048, j = at < d ? at : base;
+                v[r] = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(row) + j);
+                if (split.gain) {
+                    g0[r] = *reinterpret_cast<const float4*>(split.gain + j);
+                    g1[r] = *reinterpret_cast<const float4*>(split.gain + j + 4);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int j = base + r * 2048;
+                if (j >= d) break;
+                const float f[8] = {bf16_lo(v[r].x), bf16_hi(v[r].x), bf16_lo(v[r].y), bf16_hi(v[r].y), bf16_lo(v[r].z), bf16_hi(v[r].z), bf16_lo(v[r].w), bf16_hi(v[r].w)};
+                *reinterpret_cast<float4*>(xo + j) = make_float4(f[0], f[1], f[2], f[3]);
+                *reinterpret_cast<float4*>(xo + j + 4) = make_float4(f[4], f[5], f[6], f[7]);
+                if (split.gain) {
+                    const float g[8] = {g0[r].x, g0[r].y, g0[r].z, g0[r].w, g1[r].x, g1[r].y, g1[r].z, g1[r].w};
+                    uint32_t h[8], l[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        ss += f[e] * f[e];
+                        const float w = f[e] * g[e];
+                        h[e] = f32_to_bf16(w);
+                        l[e] = f32_to_bf16(w - bf16_to_f32(h[e]));
+                    }
+                    *reinterpret_cast<uint4*>(split.hi + (size_t)c * d + j) = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+                    *reinterpret_cast<uint4*>(split.lo + (size_t)c * d + j) = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
+                }
+            }
         }
+    }
+    if (split.gain) {                                  // the same for the whole workgroup
+        __shared__ float red[4];
+        ss = wave_sum(ss);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+        __syncthreads();
+        if (threadIdx.x == 0) split.ssq[(size_t)c * kSsqStride] = (red[0] + red[1]) + (red[2] + red[3]);
     }
 }
 template <typename W>
 __global__ __launch_bounds__(256) void embed_kernel(const W* __restrict__ emb, const int32_t* __restrict__ tokens,
                                                     ColMap cm, int d, int vocab, float* __restrict__ x,
                                                     const double* __restrict__ inv_freq, int half_hd,
-                                                    float2* __restrict__ rope_cs, const int* __restrict__ row0) {
+                                                    float2* __restrict__ rope_cs, const int* __restrict__ row0, EmbedSplit split) {
     const int c = blockIdx.x;
     embed_column<W>(emb, tokens[cm.tok_index(c)], cm.pos(c) - (row0 ? row0[cm.seq(c)] : 0),      // a left-padded sequence counts from its first token
-                    c, d, vocab, x, inv_freq, half_hd, rope_cs);
+                    c, d, vocab, x, inv_freq, half_hd, rope_cs, split);
 }
 __global__ __launch_bounds__(256) void embed_runs_kernel(const bf16_t* __restrict__ emb, const int32_t* __restrict__ tokens, SeqRuns runs, int P,
                                                          int pos_begin, int d, int vocab, float* __restrict__ x,
                                                          const double* __restrict__ inv_freq, int half_hd, float2* __restrict__ rope_cs,
-                                                         const int* __restrict__ row0, int2* __restrict__ col_at) {
+                                                         const int* __restrict__ row0, int2* __restrict__ col_at, EmbedSplit split) {
     const int c = blockIdx.x, r = runs.of(c), seq = runs.seq0 + r, pos = runs.pos[r] + (c - runs.col[r]);
     if (threadIdx.x == 0) col_at[c] = make_int2(seq, pos);
-    embed_column<bf16_t>(emb, tokens[(size_t)seq * P + (pos - pos_begin)], pos - (row0 ? row0[seq] : 0), c, d, vocab, x, inv_freq, half_hd, rope_cs);
+    embed_column<bf16_t>(emb, tokens[(size_t)seq * P + (pos - pos_begin)], pos - (row0 ? row0[seq] : 0), c, d, vocab, x, inv_freq, half_hd, rope_cs, split);
 }
 
 // ---------------- the last positions of a prompt pass ----------------
@@ -59,7 +99,7 @@ __global__ __launch_bounds__(256) void pick_rows_kernel(const float* __restrict_
 // ---------------- gain + split into bf16 hi/lo, sum of squares ----------------
 // The matrix-core projections fold the RMSNorm scale 1/rms into their epilogue; what they need from the
 // residual is hi + lo = x * gain and sum(x^2).  Inside a pass the residual projections produce both; this
-// kernel does it for the embedding output.  One workgroup per column; a thread keeps up to 8 float4 of the
+// kernel does it for the residual that a head or a fill starts from (the embedding kernel does it itself).  One workgroup per column; a thread keeps up to 8 float4 of the
 // column in registers (all loads issued together); wider columns fall back to a second read.
 __global__ __launch_bounds__(256) void gain_split_kernel(const float* __restrict__ x, int x_stride,
                                                          const float* __restrict__ gain, int K,
@@ -251,20 +291,20 @@ int launch_stream_read(const void* src, size_t bytes, unsigned* sink, int n_wg, 
 }
 
 int launch_embed(const void* tok_emb, int weight_dtype, const int32_t* tokens, ColMap cm, int ncols, int d,
-                 int vocab, float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, hipStream_t s) {
+                 int vocab, float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, const EmbedSplit& split, hipStream_t s) {
     if (weight_dtype == 0)
         hipLaunchKernelGGL(embed_kernel<float>, dim3(ncols), dim3(256), 0, s, static_cast<const float*>(tok_emb), tokens, cm, d, vocab, x,
-                           inv_freq, half_hd, rope_cs, row0);
+                           inv_freq, half_hd, rope_cs, row0, split);
     else
         hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(ncols), dim3(256), 0, s, static_cast<const bf16_t*>(tok_emb), tokens, cm, d, vocab, x,
-                           inv_freq, half_hd, rope_cs, row0);
+                           inv_freq, half_hd, rope_cs, row0, split);
     return (int)hipGetLastError();
 }
 
 int launch_embed_runs(const void* tok_emb, const int32_t* tokens, const SeqRuns& runs, int P, int pos_begin, int ncols, int d, int vocab,
-                      float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, int2* col_at, hipStream_t s) {
+                      float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, int2* col_at, const EmbedSplit& split, hipStream_t s) {
     hipLaunchKernelGGL(embed_runs_kernel, dim3(ncols), dim3(256), 0, s, static_cast<const bf16_t*>(tok_emb), tokens, runs, P, pos_begin, d, vocab, x,
-                       inv_freq, half_hd, rope_cs, row0, col_at);
+                       inv_freq, half_hd, rope_cs, row0, col_at, split);
     return (int)hipGetLastError();
 }
 
