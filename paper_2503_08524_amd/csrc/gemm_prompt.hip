@@ -510,11 +510,19 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
         }
         __syncthreads();
         if (!is_last) return;
+        f32x4 sum[RW][CW];                             // (its own part it still has in registers)
 #pragma unroll
         for (int r = 0; r < RW; ++r)
 #pragma unroll
-            for (int tt = 0; tt < CW; ++tt) fin[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int tt = 0; tt < CW; ++tt) sum[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int part = 0; part < parts; ++part) {
+            if (part == slice) {
+#pragma unroll
+                for (int r = 0; r < RW; ++r)
+#pragma unroll
+                    for (int tt = 0; tt < CW; ++tt) sum[r][tt] += fin[r][tt];
+                continue;
+            }
             const float* p = a.part + ((size_t)part_id * parts + part) * (kAccWords * kThreads) + 2 * tid;
             float2 v[RW * CW * 2];
 #pragma unroll
@@ -524,9 +532,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
 #pragma unroll
                 for (int tt = 0; tt < CW; ++tt) {
                     const float2 u = v[(r * CW + tt) * 2], w = v[(r * CW + tt) * 2 + 1];
-                    fin[r][tt][0] += u.x; fin[r][tt][1] += u.y; fin[r][tt][2] += w.x; fin[r][tt][3] += w.y;
+                    sum[r][tt][0] += u.x; sum[r][tt][1] += u.y; sum[r][tt][2] += w.x; sum[r][tt][3] += w.y;
                 }
         }
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int tt = 0; tt < CW; ++tt) fin[r][tt] = sum[r][tt];
     }
     if constexpr (MODE == MODE_RESID) {
         __syncthreads();                               // the exchanged halves have been read
