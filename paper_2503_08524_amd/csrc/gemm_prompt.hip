@@ -6,7 +6,7 @@
 // eight waves owns a tile of 256 weight rows x 128 columns and walks K in stages of 64: the stage's weight slab (256 rows x
 // 128 bytes) and activation slab (128 columns, hi plane and lo plane) go from global memory straight into LDS
 // (buffer_load_dwordx4 ... lds: 16 bytes per lane, lane l of the wave lands at base + 16 l, one instruction fills eight
-// 128-byte slab rows).  Two LDS buffers of 64 KB, one workgroup per compute unit.
+// 128-byte slab rows).  LDS holds three weight slabs and two activation slabs, 160 KB; one workgroup per compute unit.
 //
 // What bounds it, and what set the design (measured on a 8192 x 4096 x 2048 product, 256 tiles = one per compute unit):
 //  * Whole cache lines.  A stage of 32 k reads 64-byte pieces of rows, every one of them pulling a 128-byte line through the
@@ -16,15 +16,20 @@
 //    stage (32 k each), each wave a 128 x 64 piece of the tile (8 x 4 MFMA tiles, 16 fragment reads for 64 MFMAs), so there
 //    are two waves per SIMD without a second set of slabs or smaller pieces.  At the end the groups exchange halves of their
 //    accumulators through LDS (64 KB each way, once per tile) and each finishes two of the four column tiles.
+//  * Weights come from HBM, activations mostly from a cache.  A slab requested one stage ahead has 1 us to arrive, which the loaded
+//    memory's latency exceeds: a stage then took 1.42 us even with three compute units in four idle.  So the weight slabs have a third
+//    buffer and are requested two stages ahead (behind the activations of the stage before, so that a wait for all but a wave's
+//    last four loads covers both): 1.15 us.  7B shape, between events, 203 / 512 / 812 / 2048 columns: gate/up 110 / 173 / 260 / 571 -> 94 /
+//    158 / 246 / 555 us, down 77 / 97 / 150 / 305 -> 71 / 87 / 131 / 263, O 46 / 48 / 68 / 121 -> 44 / 46 / 64 / 115.
 //  * Nothing is issued in bursts.  A stage is 4 slots of 16 MFMAs (one per column tile).  The barrier sits at the start of
 //    slot 2, when every wave has read all of the stage's fragments: behind it the slots' MFMAs are interleaved with the loads
-//    of the stage after next (into the buffer just freed) and with the reads of the next stage's first fragments, and slot 0
+//    into the buffers just freed and with the reads of the next stage's first fragments, and slot 0
 //    consumes the weight fragments as they arrive.  Reads and loads issued ahead of the MFMAs instead cost 15-20 %.
-// Measured (bf16 operands drawn from a normal distribution; the matrix cores alone sustain 1.9-2.0 PFLOP/s on such data, the
-// clock drops with the toggling of the operands; the loop without its global loads runs at 1.5-1.65): 1.37 PFLOP/s as issued on
-// the product above; 7B shape, 2048 columns: QKV 350 -> 300 us, gate/up 657 -> 600, O 165 -> 102, down 362 -> 254; 512 columns:
-// QKV 139 -> 94, 256 columns: gate/up 139 -> 92 (before: 32 k per stage, 128 x 64 per wave with two workgroups per compute
-// unit, or eight waves of 64 x 64).
+// The bound is the matrix cores at the clock that their power leaves them: on operands drawn from a normal distribution they
+// alone sustain 1.9-2.0 PFLOP/s (the clock drops with the toggling of the operands), the loop without its global loads 1.5-1.65, and
+// the launches at 2048 columns 1.35-1.45 as issued.  7B shape, 2048 columns, the kernel with stages of 32 k (128 x 64 per wave with two workgroups per
+// compute unit, or eight waves of 64 x 64) -> this one: QKV 350 -> 308 us (rotation and cache append now included), gate/up
+// 657 -> 555, O 165 -> 115, down 362 -> 263.
 //
 // The LDS reads are inline assembly: the compiler orders every LDS read it knows of behind ALL outstanding direct-to-LDS
 // loads, which would drain the prefetch at every stage.  Here the vmcnt / lgkmcnt waits are written out (a wave's loads
@@ -64,8 +69,10 @@ constexpr int kTileM = 256, kTileN = 128;      // weight rows and columns of a w
 constexpr int kThreads = 512, kWaves = 8;
 constexpr int kABytes = kTileM * kPitch;       // weight slab of a stage
 constexpr int kPlane = kTileN * kPitch;        // one plane of its activation slab (hi, then lo)
-constexpr int kStage = kABytes + 2 * kPlane;   // 64 KB
-[[maybe_unused]] constexpr int kLoads = kStage / 1024 / kWaves;   // direct loads per wave and stage
+constexpr int kXBytes = 2 * kPlane;
+constexpr int kLdsX = 3 * kABytes;             // LDS: three weight slabs, two activation slabs
+constexpr int kPromptLds = kLdsX + 2 * kXBytes;        // 160 KB, all there is
+[[maybe_unused]] constexpr int kLoadsW = kABytes / 1024 / kWaves, kLoadsX = kXBytes / 1024 / kWaves, kLoads = kLoadsW + kLoadsX;   // direct loads per wave and stage
 constexpr int RW = 8;                          // 16-row tiles per wave
 constexpr int CW = 2;                          // column tiles a wave finishes (it multiplies 2 CW)
 constexpr int kAccWords = RW * CW * 4;         // accumulator words per lane of a finished (half) wave tile
@@ -345,8 +352,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
 #ifdef __HIP_DEVICE_COMPILE__
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
     constexpr int OT = 2 * RW / SW;                    // output row tiles per workgroup (half as many gate/up pairs)
-    __shared__ float inv_rms[kTileN];
-    __shared__ int last_at[8];                         // [0]: of the tile; residual projections: of each run of columns
+    // behind the 128 KB that the epilogues exchange sums in, once the slabs are done with:
+    float* inv_rms = reinterpret_cast<float*>(prompt_lds + kPartBytes);                            // [kTileN]
+    int* last_at = reinterpret_cast<int*>(prompt_lds + kPartBytes + kTileN * sizeof(float));       // [0]: of the tile; residual projections: of each run of columns
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave8 >> 2, wave = wave8 & 3, wy = wave >> 1, wx = wave & 1;
@@ -409,15 +417,23 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     // lane l of a load: row l / 8 of the block, LDS position l % 8, i.e. segment (l % 8) ^ ((slab row / 2) % 8) of that row
     const int prow = lane >> 3, pseg = (lane & 7) ^ ((lane >> 4) | (4 * (wave8 & 1)));
     const int voff_w = 2 * (prow * K + pseg * 8), voff_x = 2 * (prow * a.x_stride + pseg * 8);
-    auto load1 = [&](int j, int t, int buf) {         // t: stage of the whole K
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(src[j], (__attribute__((address_space(3))) void*)((lds_char*)prompt_lds + buf * kStage + (wave8 + kWaves * j) * 1024),
-                                                 16, j < kTileM / 8 / kWaves ? voff_w : voff_x, t * kPitch, 0, 0);
+    auto load1 = [&](int j, int t, int lds) {         // t: stage of the whole K; lds: where its slab (weights j < kLoadsW, or activations) lies
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src[j], (__attribute__((address_space(3))) void*)((lds_char*)prompt_lds + lds + (wave8 + kWaves * (j < kLoadsW ? j : j - kLoadsW)) * 1024),
+                                                 16, j < kLoadsW ? voff_w : voff_x, t * kPitch, 0, 0);
+    };
+    auto load_w = [&](int t, int lds) {
+#pragma unroll
+        for (int j = 0; j < kLoadsW; ++j) load1(j, t, lds);
+    };
+    auto load_x = [&](int t, int buf) {
+#pragma unroll
+        for (int j = kLoadsW; j < kLoads; ++j) load1(j, t, kLdsX + buf * kXBytes);
     };
     // fragment reads: lane (i, g) takes segment 4 grp + g of row i of a tile (tile bases are multiples of 16 rows, so the
     // swizzle depends on i alone)
     const uint32_t slot = (uint32_t)(((grp * 4 + lg) ^ ((li >> 1) & 7)) << 4);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)prompt_lds;
-    const uint32_t a_off = lds0 + (wy * 16 * RW + li) * kPitch + slot, b_off = lds0 + kABytes + (wx * 64 + li) * kPitch + slot;
+    const uint32_t a_off = lds0 + (wy * 16 * RW + li) * kPitch + slot, b_off = lds0 + kLdsX + (wx * 64 + li) * kPitch + slot;
 
     f32x4 acc[RW][2 * CW];                             // [row tile of the wave][column tile of the wave]
 #pragma unroll
@@ -426,16 +442,16 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
         for (int tt = 0; tt < 2 * CW; ++tt) acc[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
     u32x4 A0[RW], A1[RW];                             // weight fragments of this stage and the next
     PromptB f0, f1, f2;                                // activation fragments of three column tiles
-    // Stage t, in buffer BUF, on the weight fragments A; X holds column tile 0 when it starts (requested, like A, by the stage
-    // before) and column tile 3 in the end, Y the next stage's column tile 0.  MORE: a stage follows; loads: so do
-    // two.  A wave's LDS reads return
-    // in order, so "at most n outstanding" names the oldest ones that have arrived.
-    auto stage = [&](int t, auto buf_c, auto more_c, auto loads_c, u32x4 (&A)[RW], u32x4 (&An)[RW], PromptB& X, PromptB& Y, PromptB& Z) {
+    int w0 = 0, w1 = kABytes, w2 = 2 * kABytes;        // the weight slabs of this stage and the next two
+    // Stage t, activations in buffer BUF, on the weight fragments A; X holds column tile 0 when it starts (requested, like A, by the stage
+    // before) and column tile 3 in the end, Y the next stage's column tile 0.  MORE: a stage follows; loads: so do two; loads_w: three.
+    // A wave's LDS reads return in order, so "at most n outstanding" names the oldest ones that have arrived.
+    auto stage = [&](int t, auto buf_c, auto more_c, auto loads_c, auto loads_w_c, u32x4 (&A)[RW], u32x4 (&An)[RW], PromptB& X, PromptB& Y, PromptB& Z) {
         constexpr int BUF = decltype(buf_c)::value;
         constexpr bool MORE = decltype(more_c)::value;
-        const uint32_t B = b_off + BUF * kStage, Bn = b_off + (BUF ^ 1) * kStage, Wn = a_off + (BUF ^ 1) * kStage;
-        constexpr bool loads = decltype(loads_c)::value;
-        const int k2 = s0 + t + 2;
+        const uint32_t B = b_off + BUF * kXBytes, Bn = b_off + (BUF ^ 1) * kXBytes, Wn = a_off + w1;
+        constexpr bool loads = decltype(loads_c)::value, loads_w = decltype(loads_w_c)::value;
+        const int k2 = s0 + t + 2, k3 = k2 + 1, xb = kLdsX + BUF * kXBytes;
         // slot 0: the weight fragments are used in the order of their arrival
         read_b_frags<1>(Y, B);
         lds_reads_left<8>(); pin_frag(A[0]); pin_frag(A[1]); pin_frag(X.h); pin_frag(X.l);
@@ -455,16 +471,16 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
         // slots 2 and 3: this wave has read all of stage t
         lds_reads_left<0>(); pin_frag(Z.h); pin_frag(Z.l); pin_frag(X.h); pin_frag(X.l);
         if constexpr (MORE) {
-            vm_loads_left<0>();                        // this wave's part of stage t + 1 has landed ...
+            vm_loads_left<loads ? kLoadsW : 0>();      // this wave's part of stage t + 1 has landed (stage t + 2's weights may be on their way) ...
             __builtin_amdgcn_s_barrier();              // ... and everybody's; nobody still reads stage t
-            mma<0, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(0, k2, BUF); fixed_here();
-            mma<2, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(1, k2, BUF); fixed_here();
-            mma<4, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(2, k2, BUF); fixed_here();
-            mma<6, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(3, k2, BUF); fixed_here();
-            mma<0, 2>(acc, 2, A, Z.l); fixed_here(); if (loads) load1(4, k2, BUF); fixed_here();
-            mma<2, 2>(acc, 2, A, Z.l); fixed_here(); if (loads) load1(5, k2, BUF); fixed_here();
-            mma<4, 2>(acc, 2, A, Z.l); fixed_here(); if (loads) load1(6, k2, BUF); read_b_frags<0>(Y, Bn); fixed_here();
-            mma<6, 2>(acc, 2, A, Z.l); fixed_here(); if (loads) load1(7, k2, BUF); An[0] = lds_read_frag<0>(Wn); fixed_here();
+            mma<0, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(4, k2, xb); fixed_here();
+            mma<2, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(5, k2, xb); fixed_here();
+            mma<4, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(6, k2, xb); fixed_here();
+            mma<6, 2>(acc, 2, A, Z.h); fixed_here(); if (loads) load1(7, k2, xb); fixed_here();
+            mma<0, 2>(acc, 2, A, Z.l); fixed_here(); if (loads_w) load1(0, k3, w0); fixed_here();
+            mma<2, 2>(acc, 2, A, Z.l); fixed_here(); if (loads_w) load1(1, k3, w0); fixed_here();
+            mma<4, 2>(acc, 2, A, Z.l); fixed_here(); if (loads_w) load1(2, k3, w0); read_b_frags<0>(Y, Bn); fixed_here();
+            mma<6, 2>(acc, 2, A, Z.l); fixed_here(); if (loads_w) load1(3, k3, w0); An[0] = lds_read_frag<0>(Wn); fixed_here();
             mma<0, 2>(acc, 3, A, X.h); fixed_here(); An[1] = lds_read_frag<1 * 16 * kPitch>(Wn); fixed_here();
             mma<2, 2>(acc, 3, A, X.h); fixed_here(); An[2] = lds_read_frag<2 * 16 * kPitch>(Wn); fixed_here();
             mma<4, 2>(acc, 3, A, X.h); fixed_here(); An[3] = lds_read_frag<3 * 16 * kPitch>(Wn); fixed_here();
@@ -476,16 +492,17 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
         } else {
             mma<0, 8>(acc, 2, A, Z.h); mma<0, 8>(acc, 2, A, Z.l); mma<0, 8>(acc, 3, A, X.h); mma<0, 8>(acc, 3, A, X.l); fixed_here();
         }
+        const int done = w0;
+        w0 = w1; w1 = w2; w2 = done;
     };
     static_assert(kLoads == 8 && RW == 8 && CW == 2, "the stage is written out for these");
     constexpr std::integral_constant<int, 0> b0{};
     constexpr std::integral_constant<int, 1> b1{};
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) load1(j, s0, 0);
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) load1(j, s0 + 1, 1);
+    load_w(s0, w0); load_x(s0, 0);
+    load_w(s0 + 1, w1); load_x(s0 + 1, 1);
+    float inv = 0.f;                                   // of column tid / 16 + 32 (tid % 16), for tid % 16 < 4
     // 16 threads add up one column's partial sums of squares, in a fixed order, behind the direct loads of the first two stages
     // (reading them ahead of those put a round trip more in front of every tile)
     if (MODE != MODE_RESID && a.ssq_in) {
@@ -498,37 +515,42 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
             }
 #pragma unroll
             for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
-            if ((tid & 15) == 0) inv_rms[c] = 1.0f / sqrtf(ss / (float)K + a.eps);
+            if ((tid & 15) == c / (kThreads / 16)) inv = 1.0f / sqrtf(ss / (float)K + a.eps);
         }
     }
-    if (MODE != MODE_RESID && a.ssq_in) vm_loads_left<0>();
+    if (n_stages > 2) { load_w(s0 + 2, w2); vm_loads_left<kLoads + kLoadsW>(); }
     else vm_loads_left<kLoads>();
-    __syncthreads();                                   // stage 0 is in LDS (and inv_rms is written)
+    __syncthreads();                                   // stage 0 is in LDS
     read_b_frags<0>(f0, b_off);
     read_a_frags(A0, a_off, std::make_integer_sequence<int, RW>{});
     all_arrived(A0); all_arrived(f0);
     int t = 0;
-    for (; t + 2 < n_stages; t += 2) {
-        stage(t, b0, yes, yes, A0, A1, f0, f1, f2);
-        stage(t + 1, b1, yes, yes, A1, A0, f1, f0, f2);
+    for (; t + 4 < n_stages; t += 2) {
+        stage(t, b0, yes, yes, yes, A0, A1, f0, f1, f2);
+        stage(t + 1, b1, yes, yes, yes, A1, A0, f1, f0, f2);
     }
     all_arrived(A0); all_arrived(f0);                  // nothing in flight where the compiler may move registers
-    stage(t, b0, yes, no, A0, A1, f0, f1, f2);
-    stage(t + 1, b1, no, no, A1, A0, f1, f0, f2);
+    if (n_stages > 2) {
+        stage(t, b0, yes, yes, yes, A0, A1, f0, f1, f2);
+        stage(t + 1, b1, yes, yes, no, A1, A0, f1, f0, f2);
+        all_arrived(A0); all_arrived(f0);
+        t += 2;
+    }
+    stage(t, b0, yes, no, no, A0, A1, f0, f1, f2);
+    stage(t + 1, b1, no, no, no, A1, A0, f1, f0, f2);
     __syncthreads();
     // the stages over, one at a time (K % 64 == 32: the last holds one k-step, which is group 0's; what group 1 finds there belongs to the next row)
     for (int u = s_end - n_single; u < s_end; ++u) {
-#pragma unroll
-        for (int j = 0; j < kLoads; ++j) load1(j, u, 1);
+        load_w(u, 0); load_x(u, 0);
         vm_loads_left<0>();
         __syncthreads();
         if (grp == 0 || (u + 1) * kBK <= K) {
-            read_a_frags(A0, a_off + kStage, std::make_integer_sequence<int, RW>{});
-            read_b_frags<0>(f0, b_off + kStage); read_b_frags<1>(f1, b_off + kStage); read_b_frags<2>(f2, b_off + kStage);
+            read_a_frags(A0, a_off, std::make_integer_sequence<int, RW>{});
+            read_b_frags<0>(f0, b_off); read_b_frags<1>(f1, b_off); read_b_frags<2>(f2, b_off);
             all_arrived(A0); all_arrived(f0); all_arrived(f1); all_arrived(f2);
             mma<0, 8>(acc, 0, A0, f0.h); mma<0, 8>(acc, 0, A0, f0.l); mma<0, 8>(acc, 1, A0, f1.h); mma<0, 8>(acc, 1, A0, f1.l);
             mma<0, 8>(acc, 2, A0, f2.h); mma<0, 8>(acc, 2, A0, f2.l); fixed_here();
-            read_b_frags<3>(f0, b_off + kStage);
+            read_b_frags<3>(f0, b_off);
             all_arrived(f0);
             mma<0, 8>(acc, 3, A0, f0.h); mma<0, 8>(acc, 3, A0, f0.l); fixed_here();
         }
@@ -539,6 +561,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     f32x4 fin[RW][CW];
     {
         f32x4* mine = reinterpret_cast<f32x4*>(prompt_lds) + (size_t)wave8 * (RW * CW * 64) + lane;
+        if (MODE != MODE_RESID && (tid & 15) < 4) inv_rms[(tid >> 4) + 32 * (tid & 15)] = inv;
         const f32x4* theirs = reinterpret_cast<const f32x4*>(prompt_lds) + (size_t)(wave8 ^ 4) * (RW * CW * 64) + lane;
 #pragma unroll
         for (int r = 0; r < RW; ++r)
@@ -686,12 +709,12 @@ __global__ __launch_bounds__(512, 2) void mfma_yardstick_kernel(float* __restric
 
 // Which tiles of a launch are cut into K parts, and how many.  A workgroup occupies a compute unit, so whole tiles take rounds of
 // one tile per compute unit; the tiles of the last, partly filled round are cut so that their parts fill it.  What a part costs
-// beside its stages (1.6 us each): its start, the exchange of the accumulators (128 KB per workgroup each way) and a share of the
-// finishing, counted as 10 + 2 ks stages.  Measured (us between events): 13B shape, 2048 columns, 320 tiles, whole / the last 64 in
-// 4 parts: O 280 / 221, down 667 / 484; 7B, 812 columns, QKV 336 tiles 177 / 155; 512 columns, gate/up 344 tiles 203 / 171; fewer
-// tiles than compute units, whole / 2 / 3 / 4 / 5 / 6 / 8 parts: 7B O at 203 columns (32 tiles) 104 / 62 / 53 / 43 / 46 / 49 / 50, down 250 /
-// 137 / 104 / 88 / 83 / 80 / 79, at 700 (96 tiles) O 105 / 65 / 89 / 86 / 82 / 105 / 104, 70B O at 203 (64 tiles) 201 / 116 / 94 / 81 / 118 /
-// 112 / 109: the rule's choice is within 3 us of the best of each.
+// beside its stages (1.15 us each, 1.4 with all compute units busy): its start, the exchange of the accumulators (128 KB per workgroup each
+// way) and a share of the finishing, counted as 10 + 2 ks stages.  Measured (us between events), whole / the last round in parts: 7B
+// shape, 812 columns, QKV 336 tiles 172 / 153, gate/up 602 tiles 269 / 246; 512 columns, gate/up 344 tiles 183 / 158; fewer tiles than compute
+// units, whole / 2 / 3 / 4 / 5 / 6 / 8 parts: 7B O at 203 columns (32 tiles) 88 / 55 / 48 / 39 / 44 / 47 / 45, down 203 / 116 / 88 / 77 /
+// 74 / 71 / 70, at 700 (96 tiles) O 91 / 60 / 88 / 82 / 80 / 91 / 92, 70B O at 203 (64 tiles) 170 / 99 / 85 / 74 / 110 / 106 / 106: the rule's
+// choice is within 4 us of the best of each.
 struct PromptSplit { int n_whole, ks; };
 PromptSplit prompt_split(int tiles_wg, int n_stages, int n_cu, int forced, bool can_split) {
     auto fits = [&](int n, int ks) { return can_split && 2 * ks <= n_stages && n * ks <= kGemmPartTickets && (size_t)n * ks * kAccWords * kThreads * sizeof(float) <= kPromptPartBytes; };
@@ -709,7 +732,7 @@ PromptSplit prompt_split(int tiles_wg, int n_stages, int n_cu, int forced, bool 
 
 template <int MODE>
 int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, PromptSplit sp, hipStream_t s) {
-    constexpr int lds = 2 * kStage;
+    constexpr int lds = kPromptLds;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_prompt_kernel<MODE>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return (int)attr;
     const int grid = sp.n_whole + (n_rb * n_cb - sp.n_whole) * sp.ks;
