@@ -157,7 +157,7 @@ int launch_gemv_alu(const GemvArgs& a, int weight_dtype, int mode, bool norm, in
 int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups = nullptr);
 int launch_gemm_mfma_wide(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // 17..128 columns
 bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn);   // launch_gemm_mfma sends the launch to launch_gemm_prompt
-int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // 129..kPassCols columns: LDS-tiled, compute-bound
+int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // up to kPassCols columns: LDS-tiled, compute-bound
 size_t gemv_alu_max_cols(int K, int weight_dtype);   // columns one ALU launch can take (LDS bound)
 
 // hi + lo = x * gain (bf16 halves), ssq[col * kSsqStride] = sum(x^2)
