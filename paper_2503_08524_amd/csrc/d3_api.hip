@@ -135,7 +135,7 @@ Tuning tuning_from_env() {
     const int pc = env_int("D3_PREFILL_COLS", 64, kPassCols, 0);
     t.prefill_cols = pc % 64 == 0 ? pc : 0;
     t.prompt_ks = env_int("D3_PROMPT_KS", 1, 8, 0);
-    t.prompt_row_blocks = env_int("D3_PROMPT_ROW_BLOCKS", 1, 1 << 20, 24);
+    t.prompt_row_blocks = env_int("D3_PROMPT_ROW_BLOCKS", 1, 1 << 20, t.prompt_row_blocks);
     t.prompt_cus = env_int("D3_PROMPT_CUS", 1, 4096, 0);
     t.prompt_attn_wgs = env_int("D3_PROMPT_ATTN_WGS", 1, 1 << 20, 96);
     return t;

@@ -146,7 +146,7 @@ struct Tuning {
     bool attn_mfma = true;
     int attn_min_split = 128;
     int prefill_cols = 0;
-    int prompt_ks = 0, prompt_cus = 0, prompt_row_blocks = 24;
+    int prompt_ks = 0, prompt_cus = 0, prompt_row_blocks = 20;
     int prompt_attn_wgs = 96;
 };
 Tuning tuning_from_env();

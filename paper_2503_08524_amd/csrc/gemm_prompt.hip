@@ -746,9 +746,11 @@ int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, PromptSplit sp, hipStre
 // kPassCols (x_hi / x_lo hold ncols rounded up to 128 rows); with ssq_out at most kSsqStride row blocks.  MODE_QKV_ROPE: head_dim
 // 128, ssq_in, col_at and rope_cs set, only q is written to out.
 // Up to 128 columns the panel kernel is the other choice.  It slows down past 64 (its LDS pipe, or two launches of 64), the LDS-tiled
-// kernel takes one column block whatever its width and wants row blocks.  Measured at 77 columns (us, panel / LDS-tiled): 48 or more row blocks: 7B QKV
-// 60 / 54, gate/up 100 / 76, 13B 74 / 60 and 126 / 96, 70B gate/up 354 / 277; 40 and 32: 70B QKV 78 / 71, O 78 / 68, down 211 / 163; 20: 13B O 40 / 53,
-// down 86 / 82; 16: 7B O 28 / 48, down 57 / 70.  At 64 columns the panel kernel is ahead everywhere (7B gate/up 50 / 75, 70B 181 / 279).
+// kernel takes one column block whatever its width and wants row blocks.  Measured at 65 / 77 / 128 columns (us between events, panel -> LDS-tiled): 48 or
+// more row blocks: 7B QKV 64 / 66 / 69 -> 47 / 48 / 54, gate/up 105 / 105 / 109 -> 71 / 72 / 73, 13B QKV 79 / 79 / 85 -> 59 / 61 / 65, 70B gate/up 316 /
+// 316 / 326 -> 232 / 235 / 241; 32: 70B O 84 / 86 / 90 -> 71 / 74 / 79, down 216 / 218 / 225 -> 158 / 159 / 166; 20: 13B O 44 / 45 / 48 -> 42 /
+// 41 / 45, down 90 / 91 / 93 -> 82 / 84 / 90; 16: 7B O 32 / 33 / 36 -> 42 / 42 / 43, down 61 / 61 / 64 -> 68 / 66 / 70.  At 64 columns the
+// panel kernel needs half its time at 65 (one launch) and is ahead everywhere.
 bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn) {
     const int row_blocks = a.total_rows / (mode == MODE_SWIGLU ? kTileM / 2 : kTileM);
     return a.K >= 2 * kBK && a.part && tn.mfma_wide && (a.ncols > 128 || (a.ncols > 64 && row_blocks >= tn.prompt_row_blocks));
