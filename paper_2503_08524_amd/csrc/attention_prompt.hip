@@ -104,7 +104,7 @@ __global__ __launch_bounds__(512, 2) void attn_prompt_kernel(AttnArgs a, SeqRuns
         ++run;
     }
     const int c_begin = runs.col[run] + left * QT, c_end = min(c_begin + QT, runs.col[run + 1]);   // this workgroup's columns
-    const int seq = runs.seq0 + run;
+    const int seq = runs.seq[run];
     const int row0 = a.row0 ? a.row0[seq] : 0;         // left-padded batch: rows are counted from the sequence's first row
     const int pos_begin = runs.pos[run] + left * QT - row0;      // local row of column c_begin
     const int ctx_max = pos_begin + (c_end - c_begin);           // rows visible to the last query

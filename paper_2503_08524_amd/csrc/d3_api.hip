@@ -380,11 +380,12 @@ int alu_projection(d3_ctx* c, GemvArgs g, int first, int count, int mode, bool n
 // [(n_ids+1)][dump_cols][d], fed from columns [dump_first, dump_first + dump_cols).
 // shared: a prompt pass whose columns are runs of several sequences (cm then gives P and
 // pos_begin only, and there is no head); picks: its last positions, which hidden_dump takes.
+// fp32_projections: fp32 activations on the vector ALUs also where the pass has several columns.
 // save_before >= 0: the residual that enters the first listed block >= save_before (the one after the last, if none)
 // is copied to the workspace's h_skip: it is what the blocks of the drop window would have seen.
 int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_t* ids, int n_ids,
             float* hidden_dump, int dump_first, int dump_cols, const HeadOut* head, hipStream_t s, int save_before = -1,
-            int dump_total = -1, int dump_dst = 0, const SeqRuns* shared = nullptr, const RowPick* picks = nullptr) {
+            int dump_total = -1, int dump_dst = 0, const SeqRuns* shared = nullptr, const RowPick* picks = nullptr, bool fp32_projections = false) {
     const d3_model_desc& d = c->desc;
     const int dm = d.d_model, hd = d.head_dim, qdim = d.n_heads * hd, kvdim = d.n_kv_heads * hd, qkv_dim = qdim + 2 * kvdim, F = d.d_ffn;
     float* x = c->at<float>(c->lay.x);
@@ -393,7 +394,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     float* act = c->at<float>(c->lay.act);
     bf16_t *s_hi = c->at<bf16_t>(c->lay.s_hi), *s_lo = c->at<bf16_t>(c->lay.s_lo);
     bf16_t *f_hi = c->at<bf16_t>(c->lay.f_hi), *f_lo = c->at<bf16_t>(c->lay.f_lo);
-    const bool mfma = c->mfma_ok && (ncols >= 2 || shared || !c->alu_ok);
+    const bool mfma = c->mfma_ok && !fp32_projections && (ncols >= 2 || shared || !c->alu_ok);
     // a decode pass (every column a different sequence) leaves the rotary embedding and the cache append to the
     // attention kernel (batch 1, 7B shape: the projection's rotate-and-scatter epilogue cost it 1.5 us, the attention
     // kernel does the same for 0.5 us with whole-row stores); a prompt chunk holds several positions of one sequence
@@ -418,7 +419,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     const bool qtile = shared || (c->prefill_by_seq && mfma && cm.B == 1 && ncols >= 2 && hd == 128 &&
                                   (grp == 1 || grp == 2 || grp == 4 || grp == 8));
     SeqRuns one{};
-    one.n = 1; one.seq0 = cm.seq(0); one.col[1] = ncols; one.pos[0] = cm.pos(0);
+    one.n = 1; one.seq[0] = cm.seq(0); one.col[1] = ncols; one.pos[0] = cm.pos(0);
     const SeqRuns& runs = shared ? *shared : one;
     int2* col_at = qtile ? c->at<int2>(c->lay.col_at) : nullptr;
     if (qtile) D3_HIP(launch_embed_runs(c->tok_emb, tokens, runs, cm.P, cm.pos_begin, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, col_at, split, s));
@@ -567,6 +568,11 @@ namespace {
 // once per pass and not once per sequence, and short prompts fill the projections' column tiles together (8 x 77 tokens at the 7B
 // shape, 8 blocks: eight passes 17.4 ms, one pass 4.2 ms;
 // 4 x 203 tokens on 1024 cached rows 12.0 -> 5.9 ms; 4 x 1024 at the 13B widths, two passes instead of four, 20.7 -> 18.8 ms).  The head runs once, on every sequence's last position.
+//
+// A last token that passes of its sequence alone would leave in a pass of its own (a prompt of one token, or of a multiple of
+// chunk_cols and one) is not shared: a single column runs on the fp32 projections, as it does at batch 1, and joining a pass of
+// bf16 hi + lo activations would cost it precision (7B widths, fp32 cache, two prompts of one token: logits 5.7e-7 off float64 on
+// the fp32 projections, 7.6e-6 in a shared pass).  Where every sequence has such a token they go through in one pass.
 int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin, int chunk_cols, const std::vector<int32_t>& all, int32_t* next_tok,
                    float* logits, float* hidden_dump, hipStream_t s) {
     const d3_model_desc& d = c->desc;
@@ -574,27 +580,36 @@ int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin
     float* h_last = c->at<float>(c->lay.h_last);
     const ColMap cm{0, 1, P, pos_begin};
     auto first_of = [&](int b) { return pos_begin == 0 ? c->row0[b] : 0; };          // padding columns are not computed
+    auto last_alone = [&](int b) { return c->alu_ok && (P - first_of(b)) % chunk_cols == 1; };
+    auto end_of = [&](int b) { return last_alone(b) ? P - 1 : P; };
+    int n_alone = 0;
+    for (int b = 0; b < B; ++b) n_alone += last_alone(b);
     int b = 0, at = first_of(0);                       // next token: sequence b, prompt column `at`
-    while (b < B) {
+    auto skip_done = [&] { while (b < B && at == end_of(b)) if (++b < B) at = first_of(b); };
+    for (skip_done(); b < B;) {
         SeqRuns runs{};
         RowPick picks{};
-        runs.seq0 = b;
         int ncols = 0;
         while (b < B && ncols < chunk_cols) {
-            const int n = P - at < chunk_cols - ncols ? P - at : chunk_cols - ncols;
-            runs.pos[runs.n] = pos_begin + at;
+            const int left = end_of(b) - at, n = left < chunk_cols - ncols ? left : chunk_cols - ncols;
+            runs.seq[runs.n] = b; runs.pos[runs.n] = pos_begin + at;
             runs.n += 1;
             ncols += n; at += n;
             runs.col[runs.n] = ncols;
             if (at == P) {
                 picks.col[picks.n] = ncols - 1; picks.row[picks.n] = b;
                 picks.n += 1;
-                if (++b < B) at = first_of(b);
             }
+            skip_done();
         }
         const int rc = forward(c, tokens, cm, ncols, all.data(), d.n_layers, picks.n ? hidden_dump : nullptr, 0, 0, nullptr, s, -1, B, 0, &runs, &picks);
         if (rc != D3_OK) return rc;
         if (picks.n) D3_HIP(launch_pick_rows(c->at<float>(c->lay.x), dm, picks, h_last, s));
+    }
+    if (n_alone == B) {                                // column b of the pass is the last position of sequence b
+        const ColMap last{(P - 1) * B, B, P, pos_begin};
+        const HeadOut head{0, B, logits, next_tok};
+        return forward(c, tokens, last, B, all.data(), d.n_layers, hidden_dump, 0, B, &head, s, -1, B, 0, nullptr, nullptr, true);
     }
     bf16_t *n_hi = c->at<bf16_t>(c->lay.n_hi), *n_lo = c->at<bf16_t>(c->lay.n_lo);
     float* ssq = c->at<float>(c->lay.ssq);
@@ -606,6 +621,13 @@ int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin
     g.x_hi = n_hi; g.x_lo = n_lo; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1;
     { Timed t(c, D3_K_LM_HEAD, s); D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s)); }
     D3_HIP(launch_argmax(logits, d.vocab, B, next_tok, s));
+    for (int a = 0; a < B && n_alone > 0; ++a) {       // unequal prompts: these sequences' rows of the head are written again
+        if (!last_alone(a)) continue;
+        const ColMap last{P - 1, 1, P, pos_begin, a};
+        const HeadOut head{0, 1, logits + (size_t)a * d.vocab, next_tok + a};
+        const int rc = forward(c, tokens, last, 1, all.data(), d.n_layers, hidden_dump, 0, 1, &head, s, -1, B, a);
+        if (rc != D3_OK) return rc;
+    }
     return D3_OK;
 }
 

@@ -34,10 +34,10 @@ struct ColMap {
 };
 
 // The columns of a prompt pass on the matrix-core path as runs of consecutive positions, one run per sequence: run r is sequence
-// seq0 + r, columns [col[r], col[r + 1]), the first of them at cache row pos[r].
+// seq[r], columns [col[r], col[r + 1]), the first of them at cache row pos[r].
 struct SeqRuns {
-    int n, seq0;
-    int col[kMaxCols + 1], pos[kMaxCols];
+    int n;
+    int col[kMaxCols + 1], seq[kMaxCols], pos[kMaxCols];
     __host__ __device__ int of(int c) const {          // the run that column c belongs to
         int lo = 0, hi = n - 1;
         while (lo < hi) {

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(256) void embed_runs_kernel(const bf16_t* __restric
                                                          int pos_begin, int d, int vocab, float* __restrict__ x,
                                                          const double* __restrict__ inv_freq, int half_hd, float2* __restrict__ rope_cs,
                                                          const int* __restrict__ row0, int2* __restrict__ col_at, EmbedSplit split) {
-    const int c = blockIdx.x, r = runs.of(c), seq = runs.seq0 + r, pos = runs.pos[r] + (c - runs.col[r]);
+    const int c = blockIdx.x, r = runs.of(c), seq = runs.seq[r], pos = runs.pos[r] + (c - runs.col[r]);
     if (threadIdx.x == 0) col_at[c] = make_int2(seq, pos);
     embed_column<bf16_t>(emb, tokens[(size_t)seq * P + (pos - pos_begin)], pos - (row0 ? row0[seq] : 0), c, d, vocab, x, inv_freq, half_hd, rope_cs, split);
 }

@@ -144,6 +144,26 @@ def test_sequences_share_prompt_passes(monkeypatch, B, P, cols, lengths, kv):
         helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("B,P,cols,lengths,alone", [(3, 1, 0, None, (0, 1, 2)), (7, 1, 0, None, range(7)), (2, 65, 64, None, (0, 1)), (2, 129, 64, None, (0, 1)),
+                                                     (4, 90, 128, (90, 1, 37, 1), (1, 3)), (3, 65, 64, (65, 64, 1), (0, 2))])
+def test_last_columns_that_stand_alone_keep_the_fp32_projections(monkeypatch, B, P, cols, lengths, alone):
+    # a prompt of one token, or of whole chunks and one, ends in a pass of a single column on the fp32 projections; in a batch
+    # it must not join the shared pass of bf16 hi + lo activations (2^-17 per activation).  What that column computes itself stays in
+    # fp32: sums of up to 384 products of 24 bits, rounded at most 2^-24 x sqrt(384) = 1.2e-6 off; with a prompt before it, block 0
+    # (slot 1) also sees cache rows of the shared passes through softmax weights that sum to one.
+    if cols:
+        monkeypatch.setenv("D3_PREFILL_COLS", str(cols))
+    s = ModelShape("alone", L=2, d=256, H=4, H_kv=2, hd=128, F=384, V=512, dtype="bf16")
+    gpu, gens = _run(s, B, P, 2, 1.0, 1, forced_seed=19, kv_dtype="f32", lengths=None if lengths is None else np.array(lengths, np.int32), max_seq=P + 2)
+    for b in range(B):
+        hr, hg = gens[b].hidden[0], gpu["hidden"][0][:, b].astype(np.float64)
+        rel = np.linalg.norm(hg - hr, axis=1) / np.linalg.norm(hr, axis=1)
+        lg = np.abs(gpu["logits"][0][b] - gens[b].logits[0]).max() / np.abs(gens[b].logits[0]).max()
+        print(f"  seq {b} {'alone' if b in alone else 'shared'} hidden {rel} logits {lg:.2e}", flush=True)
+        if b in alone:
+            assert rel.max() <= 1.2e-6 and lg <= 1.2e-6, f"seq {b}"
+
+
 @pytest.mark.parametrize("ks", [2, 3, 4])
 def test_prompt_residual_projections_in_k_parts(monkeypatch, ks):
     # the projections of a prompt chunk with K cut into 2, 3 and 4 parts (one workgroup each; the part that arrives
