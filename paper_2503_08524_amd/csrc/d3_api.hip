@@ -58,9 +58,16 @@ int check_desc(const d3_model_desc* d) {
     return D3_OK;
 }
 
+// Sequences share a pass where the matrix-core attention takes runs of several of them.
+bool shares_passes(const d3_model_desc& d) {
+    const int grp = d.n_heads / d.n_kv_heads;
+    return mfma_fits(d) && d.head_dim == 128 && (grp == 1 || grp == 2 || grp == 4 || grp == 8);
+}
+
 // C columns of fp32 activations, CS columns of bf16 hi/lo splits (the matrix-core projections read whole column tiles:
-// at least 32 of them must exist), the K-slice partials of the panel kernel only when a pass can have more than 16 columns.
-Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_part) {
+// at least 32 of them must exist), the K-slice partials of the panel kernel only when a pass can have more than 16 columns,
+// what only prompt passes use only for those.
+Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_part, bool prompt_passes) {
     const size_t qdim = (size_t)d.n_heads * d.head_dim;
     const size_t qkv_dim = (size_t)(d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
     const size_t s_dim = qdim > (size_t)d.d_model ? qdim : (size_t)d.d_model;
@@ -89,25 +96,21 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
     l.gemm_part = take(with_gemm_part ? (C > (size_t)kMaxCols ? kPromptPartBytes : kGemmPartBytes) : 0);   // passes of more than 32 columns are prompt chunks
     l.gemm_tickets = take((size_t)kGemmPartTickets * 4);
     l.row0 = take(kMaxCols * 4);
-    l.col_at = take(C * 8);                                           // (sequence, cache row) of a prompt pass's columns
-    l.h_last = take(PC * d.d_model * 4);                              // residual of every sequence's last prompt position
+    const bool runs = prompt_passes && shares_passes(d);
+    l.col_at = take(runs ? C * 8 : 0);                                // (sequence, cache row) of a prompt pass's columns
+    l.h_last = take(runs ? PC * d.d_model * 4 : 0);                   // residual of every sequence's last prompt position
     l.total = o;
     return l;
 }
 // Columns of a prompt chunk: a whole sequence if it fits kPassCols (one pass over the weights per sequence, and enough
-// column blocks for the 4096-row projections to fill the chip), never more than the cache can hold.
-// Sequences share a pass where the matrix-core attention takes runs of several of them.
-bool shares_passes(const d3_model_desc& d) {
-    const int grp = d.n_heads / d.n_kv_heads;
-    return mfma_fits(d) && d.head_dim == 128 && (grp == 1 || grp == 2 || grp == 4 || grp == 8);
-}
+// column blocks for the 4096-row projections to fill the chip), or several sequences that share it; never more than the cache can hold.
 int pass_cols(const d3_model_desc& d) {
     const long long rows = (long long)d.max_seq * (shares_passes(d) ? d.max_batch : 1);
     const long long need = (rows + 127) / 128 * 128;
     return (int)(need < kPassCols ? need : kPassCols);
 }
 // The caller's workspace serves prompt chunks of up to pass_cols() columns.
-Layout make_layout(const d3_model_desc& d) { return make_layout(d, pass_cols(d), pass_cols(d), true); }
+Layout make_layout(const d3_model_desc& d) { return make_layout(d, pass_cols(d), pass_cols(d), true, true); }
 
 }  // namespace
 
@@ -743,7 +746,7 @@ int decode_step_impl(d3_ctx* ctx, const int32_t* tok_in, int32_t step_i, int32_t
         // written there by one small kernel first, because the array keeps whatever the last call on this GPU left
         if (ctx->fill_mode == D3_FILL_RECOMPUTE)
             return fail(D3_ESTATE, "d3_decode_step_static: the RECOMPUTE fill keeps a residual in the context's workspace; use d3_decode_step");
-        const Layout sl = make_layout(ctx->desc, ctx->desc.max_batch, kMaxCols, ctx->desc.max_batch > 16);
+        const Layout sl = make_layout(ctx->desc, ctx->desc.max_batch, kMaxCols, ctx->desc.max_batch > 16, false);
         if (sl.total > kStaticScratchBytes)
             return fail(D3_ESHAPE, "d3_decode_step_static: a step of this model at max_batch %d needs %zu bytes of scratch, the static array holds %zu",
                         ctx->desc.max_batch, sl.total, kStaticScratchBytes);

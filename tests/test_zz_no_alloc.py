@@ -71,6 +71,27 @@ def test_static_scratch_step_equals_the_workspace_step_on_two_requests_in_a_row(
     _same(third, _request(SMALL, 3, 20, 5, static=False, lengths=np.array([20, 4, 11], np.int32)))
 
 
+def test_static_scratch_step_takes_what_just_fits():
+    # 16 columns, most of the 32 MiB their logits: 33 546 240 bytes of step buffers, 8 KB below the limit.  Buffers that only prompt
+    # passes use (8 bytes and a row of the residual per column: 16.6 KB here) are no part of it.
+    import torch
+    from paper_2503_08524_amd import binding
+    dev, B, V = "cuda:0", 16, 511728
+    shape = ModelShape("static-edge", L=1, d=256, H=2, H_kv=2, hd=128, F=256, V=V, dtype="bf16")
+    print("case static scratch: 16 columns of a vocabulary that just fits", flush=True)
+    dec = binding.Decoder(shape, binding.random_weights_on_device(shape, 0, dev), B, 8, device=dev)
+    dec.set_plan(1.0, 0, 0, 4)
+    cur = dec.prefill(torch.arange(2 * B, dtype=torch.int32, device=dev).reshape(B, 2))
+    out = []
+    for step in (dec.decode_step_static, dec.decode_step):
+        nxt, logits = torch.zeros_like(cur), torch.zeros(B, V, dtype=torch.float32, device=dev)
+        dec.truncate(2)
+        step(cur, 1, nxt, logits=logits)
+        out.append((nxt, logits))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    dec.close()
+
+
 def test_static_scratch_step_refuses_what_does_not_fit_and_the_recompute_fill():
     import torch
     from paper_2503_08524_amd import binding
