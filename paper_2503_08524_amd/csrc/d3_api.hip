@@ -1,6 +1,7 @@
 // C ABI of the D^3 decode path: context, argument checks, and the per-step orchestration
 // that launches only the blocks the schedule keeps (Section 3.4).  All device memory is the
 // caller's; this file owns host state only.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
@@ -64,6 +65,16 @@ bool shares_passes(const d3_model_desc& d) {
     return mfma_fits(d) && d.head_dim == 128 && (grp == 1 || grp == 2 || grp == 4 || grp == 8);
 }
 
+// Partial accumulators of K-sliced projections: of the panel kernel, and of the prompt pass's tiles (all of a small model's cut
+// into the most parts, at most what a launch may publish).  The head's columns, one per sequence, are too few for that kernel.
+size_t gemm_part_bytes(const d3_model_desc& d, size_t C, bool prompt_passes) {
+    if (!mfma_fits(d)) return 0;
+    if (!prompt_passes) return kGemmPartBytes;
+    const size_t qkv = (size_t)(d.n_heads + 2 * d.n_kv_heads) * d.head_dim, residual = d.d_model, pairs = d.d_ffn;
+    const size_t row_blocks = std::max(std::max((qkv + 255) / 256, (residual + 255) / 256), (pairs + 127) / 128);
+    return std::min(std::max(row_blocks * ((C + 127) / 128) * kPromptMaxParts * kPromptPartTile, kGemmPartBytes), kPromptPartBytes);
+}
+
 // C columns of fp32 activations, CS columns of bf16 hi/lo splits (the matrix-core projections read whole column tiles:
 // at least 32 of them must exist), the K-slice partials of the panel kernel only when a pass can have more than 16 columns,
 // what only prompt passes use only for those.
@@ -93,7 +104,7 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
     l.n_lo = take(CS * d.d_model * 2);
     l.ssq = take(C * kSsqStride * 4);
     l.h_skip = take(PC * d.d_model * 4);                              // decode passes only
-    l.gemm_part = take(with_gemm_part ? (C > (size_t)kMaxCols ? kPromptPartBytes : kGemmPartBytes) : 0);   // passes of more than 32 columns are prompt chunks
+    l.gemm_part = take(with_gemm_part ? gemm_part_bytes(d, C, prompt_passes) : 0);
     l.gemm_tickets = take((size_t)kGemmPartTickets * 4);
     l.row0 = take(kMaxCols * 4);
     const bool runs = prompt_passes && shares_passes(d);
@@ -137,7 +148,7 @@ Tuning tuning_from_env() {
     t.attn_min_split = env_int("D3_ATTN_MIN_SPLIT", 64, 65536, 128) / 64 * 64;
     const int pc = env_int("D3_PREFILL_COLS", 64, kPassCols, 0);
     t.prefill_cols = pc % 64 == 0 ? pc : 0;
-    t.prompt_ks = env_int("D3_PROMPT_KS", 1, 8, 0);
+    t.prompt_ks = env_int("D3_PROMPT_KS", 1, kPromptMaxParts, 0);
     t.prompt_row_blocks = env_int("D3_PROMPT_ROW_BLOCKS", 1, 1 << 20, t.prompt_row_blocks);
     t.prompt_cus = env_int("D3_PROMPT_CUS", 1, 4096, 0);
     t.prompt_attn_wgs = env_int("D3_PROMPT_ATTN_WGS", 1, 1 << 20, 96);

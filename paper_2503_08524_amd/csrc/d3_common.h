@@ -11,7 +11,9 @@ constexpr int kMaxCols = 32;       // largest batch; columns of a decode pass
 constexpr int kPassCols = 2048;    // most columns of a prompt chunk on the matrix-core path (a context holds min(this, max_seq rounded up to 128))
 constexpr int kMaxSplits = 32;     // context splits of one attention head
 constexpr size_t kGemmPartBytes = 16u << 20;   // partial accumulators of a K-sliced wide MFMA projection
-constexpr size_t kPromptPartBytes = 64u << 20; // ... and of a K-sliced residual projection of the prompt pass (at most 512 workgroups of 128 KB)
+constexpr size_t kPromptPartTile = 128u << 10;  // ... of one K part of a tile (256 rows x 128 columns) of a prompt pass's projection
+constexpr int kPromptMaxParts = 8;             // most K parts of such a tile
+constexpr size_t kPromptPartBytes = 64u << 20; // most of them that a launch may publish (512 parts)
 constexpr int kGemmPartTickets = 2048;         // row groups such a projection may have
 constexpr int kSsqStride = 512;    // partial sums of squares kept per column (one per workgroup of the producing projection)
 

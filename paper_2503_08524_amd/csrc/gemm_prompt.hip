@@ -194,6 +194,7 @@ __device__ __forceinline__ f32x4* staged(char* lds, int c, int u) { return reint
 // The columns [lo, hi) of the tile, at most 8 N of them: N per wave, lane l takes rows 4 l .. + 3 of each.  sums(i, c) is the finished
 // sum of the wave's i-th column; it is called when the loads of the old residual are on their way.
 [[maybe_unused]] constexpr int kPartBytes = kTileM * kTileN * 4;
+static_assert(kPartBytes == (int)kPromptPartTile && kAccWords * kThreads * 4 == kPartBytes, "the workspace is laid out for these");
 #ifdef __HIP_DEVICE_COMPILE__
 struct PartRef { __amdgpu_buffer_rsrc_t buf; int parts, slice; };      // a tile's parts [part][128 columns][256 rows], and which one this is
 // 16 bytes per lane and access, at agent scope (past the XCD's own L2, like st_agent / ld_agent)
@@ -717,12 +718,12 @@ __global__ __launch_bounds__(512, 2) void mfma_yardstick_kernel(float* __restric
 // choice is within 4 us of the best of each.
 struct PromptSplit { int n_whole, ks; };
 PromptSplit prompt_split(int tiles_wg, int n_stages, int n_cu, int forced, bool can_split) {
-    auto fits = [&](int n, int ks) { return can_split && 2 * ks <= n_stages && n * ks <= kGemmPartTickets && (size_t)n * ks * kAccWords * kThreads * sizeof(float) <= kPromptPartBytes; };
+    auto fits = [&](int n, int ks) { return can_split && 2 * ks <= n_stages && n * ks <= kGemmPartTickets && n * ks * kPromptPartTile <= kPromptPartBytes; };
     if (forced >= 1) return forced > 1 && fits(tiles_wg, forced) ? PromptSplit{0, forced} : PromptSplit{tiles_wg, 1};
     const int rest = tiles_wg % n_cu;
     PromptSplit best{tiles_wg, 1};
     int best_cost = n_stages;                          // of the last round, in stages
-    for (int ks = 2; ks <= 8 && rest > 0; ++ks) {
+    for (int ks = 2; ks <= kPromptMaxParts && rest > 0; ++ks) {
         if (!fits(rest, ks) || n_stages / ks < 8) break;
         const int rounds = (rest * ks + n_cu - 1) / n_cu, cost = rounds * ((n_stages + ks - 1) / ks + 10 + 2 * ks);
         if (cost < best_cost) { best = PromptSplit{tiles_wg - rest, ks}; best_cost = cost; }

@@ -105,6 +105,22 @@ def test_workspace_size_and_shape_checks(lib):
     assert "D3_BF16" in lib.d3_last_error().decode()
 
 
+def test_workspace_holds_partial_sums_only_where_a_kernel_can_write_them(lib):
+    MiB = 1 << 20
+    shape = d3_inputs.ModelShape("small", L=2, d=256, H=4, H_kv=4, hd=64, F=704, V=1024, dtype="bf16")
+    # fp32 models never run K-sliced: 32 columns of activations, attention partials and logits are a few MiB
+    assert d3.d3_workspace_size(d3_inputs.TINY, "f32", 4, 128) < 12 * MiB
+    # a small bf16 model in one column block: the panel kernel's 16 MiB; 6 row blocks in 8 parts of 128 KiB would be 6
+    small = d3.d3_workspace_size(shape, "f16", 1, 128)
+    assert 16 * MiB < small < 16 * MiB + 12 * MiB
+    # in sixteen column blocks: 6 x 16 tiles in 8 parts are more than a launch may publish, 64 MiB
+    long = d3.d3_workspace_size(shape, "f16", 1, 2048)
+    activations = lambda C: C * (4 * (256 + 768 + 256 + 704) + 2 * 2 * (256 + 704 + 256) + 8 * 32 + 4 * 512 + 4 * 4)
+    assert abs((long - small) - (48 * MiB + activations(2048) - activations(128))) < MiB
+    # 7B widths, 48 QKV and 86 gate/up row blocks: one column block can already publish 64 MiB (86 x 8 parts)
+    assert d3.d3_workspace_size(d3_inputs.LLAMA_7B, "f16", 1, 64) > 64 * MiB
+
+
 def test_null_context_is_an_error_not_a_crash(lib):
     assert lib.d3_set_plan(None, 0.9, 0, 0, 4) == -1
     assert lib.d3_decode_step(None, None, 1, None, None, None, None) == -1
