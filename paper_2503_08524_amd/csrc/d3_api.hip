@@ -151,7 +151,7 @@ Tuning tuning_from_env() {
     t.prompt_ks = env_int("D3_PROMPT_KS", 1, kPromptMaxParts, 0);
     t.prompt_row_blocks = env_int("D3_PROMPT_ROW_BLOCKS", 1, 1 << 20, t.prompt_row_blocks);
     t.prompt_cus = env_int("D3_PROMPT_CUS", 1, 4096, 0);
-    t.prompt_attn_wgs = env_int("D3_PROMPT_ATTN_WGS", 1, 1 << 20, 96);
+    t.prompt_attn_wgs = env_int("D3_PROMPT_ATTN_WGS", 1, 1 << 20, 0);
     return t;
 }
 }  // namespace d3
@@ -374,6 +374,50 @@ void pick_splits(const d3_ctx* c, int ncols, int ctx, int target_wgs, int* split
     *n_splits = n;
 }
 
+// Attention of a prompt pass on the matrix cores (head_dim 128): one launch of the whole-context kernel (a workgroup takes 128 (query,
+// head) pairs and walks all of their context), or the query-tile kernel (16 pairs, the context split over the chip), one launch per run.
+//
+// One sequence: the whole-context kernel from 96 workgroups on (7B shape, us: 512 queries = 128 workgroups 21 against 25, 2048 = 512
+// workgroups 88 against 199; 203 on 1024 cached rows = 64 workgroups 39 against 41; 128 = 32 workgroups 12 against 7, 77 on 1024 34
+// against 31).
+//
+// Several: one launch for all of them saves a launch per sequence, but a short turn behind a long cache fills a sixteenth of the
+// pairs and few workgroups, and its chain of steps is as long as the cache.  So both are estimated, in us.  Whole context: 2.85 a step
+// of 128 fp16 or 64 fp32 rows along the longest context, or 3.3 per step and compute unit where the workgroups are many.  Query tiles:
+// 15 a run, and per row the larger of its tiles' work (4.1e-5 each, 1.2e-4 on fp32 rows) and its bytes at 5.2 TB/s.  Measured, whole
+// context / query tiles, us a block:
+//   7B  fp16, 2 x 16 tokens behind 1024, 2048, 8192, 32768 rows   29 / 38    51 / 45    186 / 81    727 / 229
+//             2 x 203                                             41 / 84    65 / 115   222 / 311   827 / 1194
+//             4 x 16 behind 1024, 4096, 8192, 32768               30 / 78   102 / 122   199 / 185   755 / 457
+//             16 x 16                                             73 / 347  226 / 549   420 / 758  1563 / 1839
+//   70B fp32, 2 x 16 behind 128, 1024, 8192, 32768                17 / 25    53 / 43    359 / 145  1435 / 563
+//             2 x 64                                              17 / 29    55 / 88    364 / 543  1452 / 2100
+//             8 x 2                                               14 / 105   51 / 142   357 / 304  1416 / 589
+// and over 2 to 16 turns of 2 to 203 tokens behind 128 to 32768 rows, at these widths, the 13B ones and with fp16 rows at the 70B ones,
+// the estimate's choice costs a call at most 8 % over the better of the two.
+bool whole_context_attention(const d3_ctx* c, const SeqRuns& runs, bool shared) {
+    if (!c->tn.attn_mfma) return false;
+    const d3_model_desc& d = c->desc;
+    const int grp = d.n_heads / d.n_kv_heads;
+    const bool f16 = d.kv_dtype == D3_F16;
+    const double step_rows = f16 ? 128 : 64, tile_row = f16 ? 4.1e-5 : 1.2e-4;
+    const double read_row = (double)d.n_kv_heads * 2 * d.head_dim * kv_elem_bytes(d.kv_dtype) / 5.2e6;
+    int workgroups = 0;
+    double longest = 0, steps = 0, tiles_us = 0;
+    for (int r = 0; r < runs.n; ++r) {
+        const int n = runs.col[r + 1] - runs.col[r];
+        const int wgs = (n * grp + 127) / 128 * d.n_kv_heads, tiles = (n * grp + 15) / 16 * d.n_kv_heads;
+        const double rows = runs.pos[r] + n - (c->ragged ? c->row0[runs.seq[r]] : 0), mean_rows = rows - 0.5 * n;
+        workgroups += wgs;
+        longest = std::max(longest, rows / step_rows);
+        steps += wgs * mean_rows / step_rows;
+        tiles_us += 15 + mean_rows * std::max(tiles * tile_row, read_row);
+    }
+    if (c->tn.prompt_attn_wgs) return workgroups >= c->tn.prompt_attn_wgs;
+    if (!shared) return workgroups >= 96;
+    return std::max(2.85 * longest, 3.3 * steps / c->n_cu) <= tiles_us;
+}
+
 // ALU path: a projection takes as many columns per launch as its input fits in LDS
 int alu_projection(d3_ctx* c, GemvArgs g, int first, int count, int mode, bool norm, hipStream_t s) {
     const int per = (int)gemv_alu_max_cols(g.K, c->desc.weight_dtype);
@@ -449,12 +493,9 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
 
     auto alu = [&](GemvArgs g, int first, int count, int mode, bool norm) -> int { return alu_projection(c, g, first, count, mode, norm, s); };
 
-    // with enough workgroups to go round, one of 128 (query, head) pairs that walks its whole context beats the short query
-    // tiles with a split context (7B shape, us: 512 queries = 128 workgroups 21 against 25, 2048 = 512 workgroups 88 against 199; 203
-    // on 1024 cached rows = 64 workgroups 39 against 41; 128 = 32 workgroups 12 against 7, 77 on 1024 34 against 31)
-    const bool prompt_attn = shared || (qtile && c->tn.attn_mfma && (ncols * grp + 127) / 128 * d.n_kv_heads >= c->tn.prompt_attn_wgs);
+    const bool prompt_attn = qtile && whole_context_attention(c, runs, shared != nullptr);
     int split_len = 0, n_splits = 0;
-    if (!prompt_attn) pick_splits(c, ncols, cm.pos(ncols - 1) + 1, c->attn_wgs_per_cu * c->n_cu, &split_len, &n_splits, qtile);
+    if (!prompt_attn && !shared) pick_splits(c, ncols, cm.pos(ncols - 1) + 1, c->attn_wgs_per_cu * c->n_cu, &split_len, &n_splits, qtile);
 
     bool saved = save_before < 0;
     auto save_skip = [&]() -> int {
@@ -508,7 +549,19 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         at.rope_cs = rope_in_attn ? rope_cs : nullptr;
         at.qtile = qtile ? 1 : 0;
         at.row0 = row0;
-        {
+        if (shared && !prompt_attn) {
+            for (int r = 0; r < runs.n; ++r) {         // one after the other: the partials and the counters are the launch's own
+                const int col = runs.col[r];
+                AttnArgs own = at;
+                own.ncols = runs.col[r + 1] - col;
+                own.cm = ColMap{0, 1, own.ncols, runs.pos[r], runs.seq[r]};
+                own.q += (size_t)col * qkv_dim;
+                own.out += (size_t)col * qdim; own.out_hi += (size_t)col * qdim; own.out_lo += (size_t)col * qdim;
+                pick_splits(c, own.ncols, runs.pos[r] + own.ncols, c->attn_wgs_per_cu * c->n_cu, &own.split_len, &own.n_splits, true);
+                Timed t(c, D3_K_ATTN, s);
+                D3_HIP(launch_attention(own, d.kv_dtype, true, s));
+            }
+        } else {
             Timed t(c, D3_K_ATTN, s);
             if (prompt_attn) D3_HIP(launch_attention_prompt(at, runs, d.kv_dtype, s));
             else D3_HIP(launch_attention(at, d.kv_dtype, c->tn.attn_mfma, s));

@@ -137,7 +137,7 @@ struct GemvArgs {
 // D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most 2048); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8);
 // D3_PROMPT_ROW_BLOCKS: fewest blocks of 256 rows for which 65..128 columns take the LDS-tiled kernel;
 // D3_PROMPT_CUS: compute units a round of its tiles is taken to have;
-// D3_PROMPT_ATTN_WGS: fewest workgroups (128 (query, head) pairs each) for which a prompt chunk takes the whole-context attention kernel; D3_GEMV_WGS_PER_CU: workgroups
+// D3_PROMPT_ATTN_WGS: fewest workgroups (128 (query, head) pairs each) for which a prompt pass, shared or not, takes the whole-context attention kernel; D3_GEMV_WGS_PER_CU: workgroups
 // per compute unit of the vector-ALU GEMV (default 3).
 struct Tuning {
     int gemv_wgs_per_cu = 3;
@@ -149,7 +149,7 @@ struct Tuning {
     int attn_min_split = 128;
     int prefill_cols = 0;
     int prompt_ks = 0, prompt_cus = 0, prompt_row_blocks = 20;
-    int prompt_attn_wgs = 96;
+    int prompt_attn_wgs = 0;
 };
 Tuning tuning_from_env();
 

@@ -232,6 +232,49 @@ def test_prompt_attention_over_the_whole_context(monkeypatch, H, H_kv, kv, P):
         helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("B,P,H,H_kv,cols,lengths,kv", [(2, 37, 2, 2, 0, None, "f32"), (3, 150, 4, 2, 256, None, "f16"), (2, 700, 4, 1, 512, None, "f32"),
+                                                         (5, 19, 8, 1, 0, None, "f16"), (4, 300, 4, 2, 256, (300, 1, 37, 2), "f32"),
+                                                         (3, 700, 8, 1, 320, (129, 700, 66), "f16"), (2, 260, 3, 3, 128, (65, 260), "f32")])
+def test_shared_passes_with_query_tiles_run_by_run(monkeypatch, B, P, H, H_kv, cols, lengths, kv):
+    # what short turns behind long caches take, forced on prompts: the query-tile kernel, a launch per sequence of a shared pass, over
+    # its own columns of q and of the outputs, with the context split where it is long; group sizes 1, 2, 4 and 8, passes that end inside a
+    # sequence, runs of one column, sequences that begin inside a later split (left-padded batches)
+    monkeypatch.setenv("D3_PROMPT_ATTN_WGS", str(1 << 20))
+    if cols:
+        monkeypatch.setenv("D3_PREFILL_COLS", str(cols))
+    s = ModelShape("by-run", L=2, d=256, H=H, H_kv=H_kv, hd=128, F=384, V=512, dtype="bf16")
+    gpu, gens = _run(s, B, P, 2, 1.0, 1, forced_seed=19, kv_dtype=kv, lengths=None if lengths is None else np.array(lengths, np.int32), max_seq=P + 2)
+    if kv == "f32":     # only arithmetic rounding is left
+        helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
+@pytest.mark.parametrize("kv,past,n,launches", [("f16", 4096, 16, 2), ("f32", 4096, 16, 2), ("f16", 64, 16, 1), ("f16", 4096, 1000, 1)])
+def test_short_turns_behind_a_long_cache_split_their_context(monkeypatch, kv, past, n, launches):
+    # the whole-context kernel walks a cache of 4096 rows in 32 (fp16) or 64 (fp32) steps on the two workgroups that 16 tokens make, so these
+    # turns take the query tiles with a split context, one launch per sequence and block; a short cache or a long turn takes one launch.
+    # Either route computes the same: the bound is that of the fp32-cache cases here, with an fp16 cache its 11 bits.
+    import torch
+    from paper_2503_08524_amd import binding
+    s = ModelShape("long-cache", L=2, d=256, H=4, H_kv=2, hd=128, F=384, V=512, dtype="bf16")
+    w = binding.random_weights_on_device(s, 3)
+    toks = torch.from_numpy(d3_inputs.make_prompt(2, past + n, s.V, seed=1)).to("cuda:0")
+    print(f"case {n} tokens behind {past} rows, kv={kv}", flush=True)
+    got = []
+    for wgs in (None, 1, 1 << 20):
+        if wgs:
+            monkeypatch.setenv("D3_PROMPT_ATTN_WGS", str(wgs))
+        dec = binding.Decoder(s, w, 2, past + n, kv_dtype=kv)
+        dec.prefill(toks[:, :past].contiguous())
+        logits = torch.zeros(2, s.V, dtype=torch.float32, device="cuda:0")
+        dec.profile_select(binding.D3_K_ATTN)
+        dec.prefill(toks[:, past:].contiguous(), pos_begin=past, logits=logits)
+        got.append((dec.profile_read()[1] / s.L, logits))
+        dec.close()
+    assert [k for k, _ in got] == [launches, 1, 2]
+    for _, other in got[1:]:
+        assert float((got[0][1] - other).abs().max()) <= (2e-4 if kv == "f32" else 5e-3)
+
+
 @pytest.mark.parametrize("B,kv", [(1, "f16"), (3, "f16"), (2, "f32")])
 def test_small_gqa(B, kv):
     _run(SMALL_GQA, B, 37, 6, 0.8, 1, forced_seed=8, kv_dtype=kv)
