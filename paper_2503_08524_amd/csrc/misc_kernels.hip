@@ -90,10 +90,11 @@ __global__ __launch_bounds__(256) void embed_runs_kernel(const bf16_t* __restric
 }
 
 // ---------------- the last positions of a prompt pass ----------------
+// dst may be the caller's hidden_dump, which is aligned to its floats and no more.
 __global__ __launch_bounds__(256) void pick_rows_kernel(const float* __restrict__ x, int d, RowPick pick, float* __restrict__ dst) {
     const float* src = x + (size_t)pick.col[blockIdx.x] * d;
     float* out = dst + (size_t)pick.row[blockIdx.x] * d;
-    for (int j = threadIdx.x * 4; j < d; j += blockDim.x * 4) *reinterpret_cast<float4*>(out + j) = *reinterpret_cast<const float4*>(src + j);
+    for (int j = threadIdx.x; j < d; j += blockDim.x) out[j] = src[j];
 }
 
 // ---------------- gain + split into bf16 hi/lo, sum of squares ----------------

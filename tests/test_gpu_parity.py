@@ -164,6 +164,24 @@ def test_last_columns_that_stand_alone_keep_the_fp32_projections(monkeypatch, B,
             assert rel.max() <= 1.2e-6 and lg <= 1.2e-6, f"seq {b}"
 
 
+def test_hidden_states_of_shared_passes_into_a_buffer_aligned_to_floats_only():
+    # hidden_dump is a float pointer: 4, 8 and 12 bytes past a 16-byte boundary it takes the same rows, and nothing beside them
+    import torch
+    from paper_2503_08524_amd import binding
+    s = ModelShape("dump", L=2, d=256, H=2, H_kv=2, hd=128, F=384, V=512, dtype="bf16")
+    dec = binding.Decoder(s, binding.random_weights_on_device(s, 5), 3, 40)
+    toks = torch.from_numpy(d3_inputs.make_prompt(3, 40, s.V, seed=1)).to("cuda:0")
+    n = (s.L + 1) * 3 * s.d
+    want = torch.zeros(n, device="cuda:0")
+    print("case hidden_dump alignment", flush=True)
+    dec.prefill(toks, hidden_dump=want)
+    for off in (1, 2, 3):
+        buf = torch.full((n + 8,), 7.0, device="cuda:0")
+        dec.prefill(toks, hidden_dump=buf[off:off + n])
+        assert torch.equal(buf[off:off + n], want) and bool((buf[:off] == 7).all()) and bool((buf[off + n:] == 7).all())
+    dec.close()
+
+
 @pytest.mark.parametrize("ks", [2, 3, 4])
 def test_prompt_residual_projections_in_k_parts(monkeypatch, ks):
     # the projections of a prompt chunk with K cut into 2, 3 and 4 parts (one workgroup each; the part that arrives
