@@ -35,7 +35,8 @@
 // loads, which would drain the prefetch at every stage.  Here the vmcnt / lgkmcnt waits are written out (a wave's loads
 // complete in issue order, kLoads per stage), and empty asm statements that name the fragments as operands keep the MFMAs
 // behind the waits.  A fragment in flight must not be moved or spilled: it is only across the stage loop's back edge, where the
-// loop fits its registers exactly; at every other change of control flow the reads are waited for.
+// loop fits its registers exactly; at every other change of control flow the reads are waited for.  That depends on the compiler, so
+// tests/test_prompt_kernel_registers.py follows every such read through the compiled code.
 //
 // LDS layout: a slab row is eight 16-byte segments, segment s at position s ^ ((row / 2) % 8): sixteen consecutive rows x one
 // segment then touch each of the sixteen 16-byte bank groups once.  The direct load fixes where a lane's bytes land, so the
