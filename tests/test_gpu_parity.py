@@ -56,14 +56,23 @@ def test_batched_linear_decay_on_the_matrix_cores():
 
 @pytest.mark.parametrize("shape,lengths,kv", [
     (d3_inputs.TINY, (16, 5, 11), "f32"),                 # fp32 weights: vector-ALU projections, one column per launch group
-    (SMALL_BF16, (9, 70, 1, 33, 64), None),               # head_dim 64: vector-ALU attention; chunks of 64 + 6 columns
-    (SMALL_GQA, (130, 17, 77, 130), "f16"),               # head_dim 128, f16 cache: query tiles in the prompt, MFMA attention in decode
+    (SMALL_BF16, (9, 70, 1, 33, 64), None),               # head_dim 64: vector-ALU attention; one sequence a pass
+    (SMALL_GQA, (130, 17, 77, 130), "f16"),               # head_dim 128, f16 cache: one pass for all of them, MFMA attention in decode
     (SMALL_GQA, (40, 3), "f32"),
 ])
 def test_left_padded_batch_of_unequal_prompts(shape, lengths, kv):
     # every sequence of a ragged batch must behave as if it had run alone: its own positions, its own context
     B, P = len(lengths), max(lengths)
     _run(shape, B, P, 9, 0.8, 1, kv_dtype=kv, forced_seed=21, lengths=np.array(lengths, np.int32), max_seq=P + 9)
+
+
+@pytest.mark.parametrize("lengths,kv", [((130, 17, 77), "f16"), ((40, 300, 1), "f32")])
+def test_left_padded_batch_one_sequence_a_pass(monkeypatch, lengths, kv):
+    # without the panel and LDS-tiled kernels a pass is 32 columns of one sequence: query tiles whose rows begin above row 0
+    monkeypatch.setenv("D3_MFMA_WIDE", "0")
+    gpu, gens = _run(SMALL_GQA, len(lengths), max(lengths), 3, 0.8, 1, kv_dtype=kv, forced_seed=21, lengths=np.array(lengths, np.int32), max_seq=max(lengths) + 3)
+    if kv == "f32":     # only arithmetic rounding is left
+        helpers.compare(gpu, gens, 3, logit_atol=2e-4, hidden_tol=1e-4)
 
 
 def test_left_padded_batch_spans_attention_splits():
@@ -106,28 +115,48 @@ def test_small_bf16_matrix_core_path(B, P):
 
 @pytest.mark.parametrize("shape,B,P", [(SMALL_BF16, 2, 24), (SMALL_BF16, 2, 97), (SMALL_BF16, 1, 81), (SMALL_GQA, 1, 80),
                                        (SMALL_GQA, 2, 72), (SMALL_GQA, 1, 128), (SMALL_BF16, 2, 50), (SMALL_GQA, 1, 168),
-                                       (SMALL_GQA, 1, 136), (SMALL_BF16, 1, 144), (SMALL_GQA, 2, 145)])
+                                       (SMALL_GQA, 1, 136), (SMALL_BF16, 1, 144), (SMALL_GQA, 2, 145), (SMALL_GQA, 1, 72), (SMALL_GQA, 1, 145),
+                                       (SMALL_GQA, 1, 7), (SMALL_GQA, 1, 13)])
 def test_prompt_lengths_that_end_in_every_chunk_width(shape, B, P):
-    # the prompt pass takes one sequence at a time in chunks of up to 1024 columns; the chunks here have 24, 97, 81, 80, 72,
-    # 128, 50, 168, 136, 144 and 145 columns, which ends in each of the projection kernels (packed, 16-column, the panel
-    # kernel with two, four and eight column tiles, and the LDS-tiled kernel with a ragged second column block) and in both
-    # attention paths of a prompt chunk (per column on the vector ALUs at head_dim 64, query tiles on the matrix cores at 128)
+    # a pass is one sequence at batch 1 and at head_dim 64, both sequences end to end at batch 2 and head_dim 128: passes of 24, 97,
+    # 81, 80, 72, 128, 50, 168, 136, 144, 145, 7 and 13 columns, and of 144 and 290 shared ones.  They end in each of the projection
+    # kernels (packed, 16-column, the panel kernel with two, four and eight column tiles, and the LDS-tiled kernel with a ragged second
+    # or third column block) and of the attention paths of a prompt pass (per column on the vector ALUs at head_dim 64; at 128 query tiles for one
+    # sequence of so few columns, the whole-context kernel for several)
     _run(shape, B, P, 4, 0.8, 1, forced_seed=9)
 
 
 def test_wide_prompt_chunks_as_two_launches_of_64_columns(monkeypatch):
-    # what the projections of large matrices (hundreds of MB) do with a chunk of more than 64 columns, forced on small ones
+    # what the panel kernel does with a pass of more than 64 columns on large matrices (hundreds of MB), forced on small ones: 100 columns of
+    # one sequence, 2 x 50 shared ones, 97 at head_dim 64; 2 x 150 columns are the LDS-tiled kernel's, whatever the matrix
     monkeypatch.setenv("D3_WIDE_SPLIT_MB", "0")
+    _run(SMALL_GQA, 1, 100, 4, 0.8, 1, forced_seed=9)
+    _run(SMALL_GQA, 2, 50, 4, 0.8, 1, forced_seed=9)
     _run(SMALL_GQA, 2, 150, 4, 0.8, 1, forced_seed=9)
     _run(SMALL_BF16, 1, 97, 4, 0.8, 1, forced_seed=9)
 
 
+@pytest.mark.parametrize("B", [1, 2])
 @pytest.mark.parametrize("cols", [64, 128, 256])
-def test_prompt_chunks_of_a_forced_width(monkeypatch, cols):
-    # a prompt of 700 tokens in chunks of 64 or 128 columns (panel kernel) and of 256 (LDS-tiled kernel: two full chunks
-    # and one of 188 columns, whose second column block is ragged)
+def test_prompt_chunks_of_a_forced_width(monkeypatch, cols, B):
+    # prompts in passes of 64 or 128 columns (panel kernel) and of 256 (LDS-tiled kernel).  One sequence: 150 tokens in 64 + 64 + 22, 700 in
+    # five passes of 128 and one of 60, or two of 256 and one of 188 (second column block ragged); all but the first begin above row 0.
+    # Two sequences end to end: 300 columns in four passes of 64 and one of 44, 1400 in ten of 128 and one of 120, or five of 256 and one of 120
     monkeypatch.setenv("D3_PREFILL_COLS", str(cols))
-    _run(SMALL_GQA, 2, 150 if cols == 64 else 700, 4, 0.8, 1, forced_seed=9)
+    _run(SMALL_GQA, B, 150 if cols == 64 else 700, 4, 0.8, 1, forced_seed=9)
+
+
+@pytest.mark.parametrize("wgs", [1, 1 << 20])
+@pytest.mark.parametrize("B,P,cols", [(1, 300, 128), (1, 470, 256), (2, 300, 128)])
+@pytest.mark.parametrize("kv", ["f16", "f32"])
+def test_prompt_of_several_passes_on_either_attention_kernel(monkeypatch, kv, B, P, cols, wgs):
+    # passes whose first position lies above row 0, on the whole-context kernel (wgs 1) and on query tiles: one sequence a pass, and two
+    # that share passes
+    monkeypatch.setenv("D3_PROMPT_ATTN_WGS", str(wgs))
+    monkeypatch.setenv("D3_PREFILL_COLS", str(cols))
+    gpu, gens = _run(SMALL_GQA, B, P, 2, 0.8, 1, forced_seed=9, kv_dtype=kv)
+    if kv == "f32":     # only arithmetic rounding is left
+        helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
 @pytest.mark.parametrize("B,P,cols,lengths,kv", [(2, 32, 64, None, "f16"), (5, 13, 64, None, "f32"), (3, 43, 128, None, "f16"), (3, 150, 256, None, "f16"),
@@ -184,13 +213,22 @@ def test_hidden_states_of_shared_passes_into_a_buffer_aligned_to_floats_only():
 
 @pytest.mark.parametrize("ks", [2, 3, 4])
 def test_prompt_residual_projections_in_k_parts(monkeypatch, ks):
-    # the projections of a prompt chunk with K cut into 2, 3 and 4 parts (one workgroup each; the part that arrives
-    # last at the tile's counter adds the published accumulators in part order): K of 8 and 21.5 stages (uneven parts, the
-    # last with the stages over), then 4 and 11 stages; by itself the launcher cuts K only for long contractions (the 7B / 13B /
-    # 70B widths, which the all-block and full-size tests run)
+    # the projections of a prompt pass with K cut into 2, 3 and 4 parts (one workgroup each), which takes two whole stages for
+    # every part (contractions too short for that stay whole): K of 8 stages (QKV, gate/up), 16 (O) and 21.5 (down; uneven parts, the last
+    # with the stages over); at head_dim 64 8 and 11 stages; then 4 and 11, where 3 and 4 parts cut the down projection alone.  By itself the
+    # launcher cuts K only for long contractions (the 7B / 13B / 70B widths, which the all-block and full-size tests run)
     monkeypatch.setenv("D3_PROMPT_KS", str(ks))
     _run(SMALL_GQA, 1, 300, 3, 0.8, 1, forced_seed=21)
+    _run(ModelShape("parts-hd64", L=2, d=512, H=8, H_kv=8, hd=64, F=704, V=512, dtype="bf16"), 2, 200, 3, 0.9, 1, forced_seed=21)
     _run(SMALL_BF16, 2, 200, 3, 0.9, 2, forced_seed=21)
+
+
+def test_every_projection_in_the_most_k_parts(monkeypatch):
+    # 16 stages (QKV, O, gate/up) and 17.5 (down) in 8 parts: one pair of stages each, the last of the down projection with the stages over
+    monkeypatch.setenv("D3_PROMPT_KS", "8")
+    s = ModelShape("most-parts", L=2, d=1024, H=8, H_kv=2, hd=128, F=1120, V=512, dtype="bf16")
+    gpu, gens = _run(s, 1, 150, 2, 1.0, 1, forced_seed=21, kv_dtype="f32")
+    helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
 def test_lds_tiled_prompt_kernel_shapes():
@@ -207,8 +245,8 @@ def test_lds_tiled_prompt_kernel_shapes():
                                       (288, 96, 140, 0), (512, 2048, 513, 8)])
 def test_prompt_kernel_contractions_and_parts(monkeypatch, d, F, P, ks):
     # the LDS-tiled kernel walks K in pairs of 64-wide stages: contractions that are one pair, that leave 32, 64 and 96 over,
-    # that are too short for it (96: the panel kernel in blocks of 64 columns), and K parts of uneven length; column blocks of
-    # 1, 2, 127 and 128 live columns.  Rows of the last row block are missing throughout.  With an fp32 cache only fp32 sums and the 16 bits
+    # that are too short for it (96: the panel kernel in blocks of 64 columns), and K parts of uneven length where the contraction has two
+    # whole stages for every part (8 parts: the down projection's 32 stages alone); column blocks of 1, 2, 127 and 128 live columns.  Rows of the last row block are missing throughout.  With an fp32 cache only fp32 sums and the 16 bits
     # of an activation's two bf16 halves are left: 2^-17 per product, far below the bound of 1e-4.
     if ks:
         monkeypatch.setenv("D3_PROMPT_KS", str(ks))
@@ -237,15 +275,16 @@ def test_prompt_tiles_whole_and_in_parts_in_one_launch(monkeypatch, cus, F, P):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("B", [1, 2])
 @pytest.mark.parametrize("H,H_kv,kv,P", [(2, 2, "f16", 130), (2, 2, "f16", 257), (3, 3, "f32", 65), (4, 2, "f16", 193), (4, 2, "f32", 129),
                                          (8, 2, "f16", 161), (8, 1, "f16", 150), (8, 1, "f32", 97), (8, 8, "f16", 64)])
-def test_prompt_attention_over_the_whole_context(monkeypatch, H, H_kv, kv, P):
-    # the kernel of long prompt chunks (128 (query, head) pairs per workgroup), forced on short ones: group sizes 1, 2, 4 and 8, KV heads that
+def test_prompt_attention_over_the_whole_context(monkeypatch, H, H_kv, kv, P, B):
+    # the kernel of long prompt chunks (128 (query, head) pairs per workgroup), forced on short ones, one sequence or two: group sizes 1, 2, 4 and 8, KV heads that
     # do and do not divide over the XCDs, last query tiles of 1 to 128 pairs, row tiles (64 rows fp16, 32 fp32) that end on, before
     # and past a boundary, one and several steps of the two wave groups, and a group that sees no row of some entries
     monkeypatch.setenv("D3_PROMPT_ATTN_WGS", "1")
     s = ModelShape("prompt-attn", L=2, d=256, H=H, H_kv=H_kv, hd=128, F=384, V=512, dtype="bf16")
-    gpu, gens = _run(s, 2, P, 2, 1.0, 1, forced_seed=19, kv_dtype=kv)
+    gpu, gens = _run(s, B, P, 2, 1.0, 1, forced_seed=19, kv_dtype=kv)
     if kv == "f32":     # only arithmetic rounding is left (16 bits of an activation's two bf16 halves, 21 of the fp16 pairs)
         helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
@@ -301,7 +340,7 @@ def test_small_gqa(B, kv):
 @pytest.mark.parametrize("B,P", [(2, 300), (1, 700)])
 def test_fp32_cache_on_the_matrix_core_attention_kernels(B, P):
     # grouped-query attention at head_dim 128 with an fp32 cache (what models deeper than 48 blocks get): the cache rows go
-    # to the matrix cores as fp16 hi + lo planes; prompt chunks of 128 + 128 + 44 columns (query tiles), decode contexts
+    # to the matrix cores as fp16 hi + lo planes; prompts of 2 x 300 columns in one pass (whole context) and of 700 (query tiles), decode contexts
     # that span three and six splits, batch 1 (vector-ALU projections) and batch 2 (matrix-core projections).  The fp32
     # rows leave nothing but arithmetic rounding: the logits must agree 100 times closer than the acceptance bound.
     gpu, gens = _run(SMALL_GQA, B, P, 5, 0.8, 1, forced_seed=8, kv_dtype="f32")
