@@ -206,7 +206,8 @@ def measure_config(name, steps, warmup, fill, kv_arg=None, with_yardsticks=False
                       "frac_issued": 2 * flops / prefill_s / 1e12 / MFMA_BF16_PEAK_TFLOPS}
 
     if with_yardsticks:
-        # what the matrix cores sustain on this chip: the stage loop of the prompt GEMM on fixed operands (d3_mfma_yardstick)
+        # what the matrix cores sustain on this chip: a plain loop on fixed operands, alone, with LDS fragment reads, and with a barrier per
+        # 32 instructions as well (d3_mfma_yardstick; 12 reads for 32 instructions, where the prompt GEMM's loop has 16 for 64)
         n_cu = torch.cuda.get_device_properties(dev).multi_processor_count
         sustained = {}
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -221,7 +222,7 @@ def measure_config(name, steps, warmup, fill, kv_arg=None, with_yardsticks=False
             sustained[label] = 3 * n_cu * 8 * 4096 * 32 * 16384 / (e0.elapsed_time(e1) * 1e-3) / 1e12
         res["prefill"]["sustained_TFLOPs"] = sustained
         res["prefill"]["frac_issued_of_sustained_mfma_alone"] = res["prefill"]["issued_TFLOPs_hi_lo"] / sustained["mfma_alone"]
-        progress(f"{name}: matrix cores sustain {sustained['mfma_alone']:.0f} TFLOP/s alone, {sustained['with_reads_and_stage_barrier']:.0f} in the prompt GEMM's stage loop")
+        progress(f"{name}: matrix cores sustain {sustained['mfma_alone']:.0f} TFLOP/s alone, {sustained['with_reads_and_stage_barrier']:.0f} in a loop with LDS fragment reads and barriers")
 
     kv_bytes = 4 if kv == "f32" else 2
     results = {}

@@ -248,8 +248,8 @@ class Decoder:
         _check(self.lib.d3_stream_read(self.ctx, tensor.data_ptr(), tensor.numel() * tensor.element_size(), self._stream()))
 
     def mfma_yardstick(self, mode: int, stages: int) -> None:
-        """Matrix-core yardstick of the prompt pass (one launch, asynchronous): mode 0 MFMAs alone, 1 with the stage loop's
-        LDS reads, 2 with its barrier too; n_cu workgroups x 8 waves x stages x 32 instructions of 16384 flops."""
+        """Matrix-core yardstick of the prompt pass (one launch, asynchronous): mode 0 MFMAs alone, 1 with LDS
+        fragment reads, 2 with a barrier per stage too; n_cu workgroups x 8 waves x stages x 32 instructions of 16384 flops."""
         _check(self.lib.d3_mfma_yardstick(self.ctx, mode, stages, self._stream()))
 
     def profile_select(self, kernel_class: int) -> None:

@@ -715,7 +715,7 @@ __device__ __forceinline__ void attn_split_mfma(const AttnArgs& a, int split, in
 // read the whole context once per query; here the 16 entries of the matrix dimension are QT = 16 / GH consecutive
 // queries (columns c0 .. c0 + QT - 1) times the GH query heads of one KV head, so a cache row is read once per QT
 // queries.  Entry e = query e / GH, head h0 + e % GH; its context ends at its own position (causal mask per
-// entry).  The K/V rows of the chunk are already in the cache (rope_append_kernel ran before), q is rotated.
+// entry).  The K/V rows of the chunk are already in the cache (the QKV projection or rope_append_kernel put them there), q is rotated.
 template <typename T, int NW, int GH>
 __device__ __forceinline__ void attn_qtile_mfma(const AttnArgs& a, int split, int h0, int c0, AttnMfmaShared<NW, 16, AttnStage<T>::PL>& sh) {
     constexpr int HD = 128;

@@ -39,7 +39,7 @@ typedef _Float16 pa_half2 __attribute__((ext_vector_type(2)));
 constexpr int kPaEntries = 128;                // entries of a workgroup
 constexpr int kPaBuf = 32 * 1024;              // a tile of K and V
 constexpr float kPaFloor = -3.0e38f;           // running maximum before the first row: below every score, and finite
-constexpr float kPaSlack = 8.0f;               // a running maximum may lag behind by this much (log2): weights up to 256, no rescaling
+constexpr float kPaSlack = 8.0f;               // a running maximum may lag behind by this much (log2): weights up to 256, no rescaling (the conditional rescaling published with FlashAttention-4)
 
 template <typename T> struct PaTile;
 template <> struct PaTile<f16_t> {
@@ -85,8 +85,8 @@ __global__ __launch_bounds__(512, 2) void attn_prompt_kernel(AttnArgs a, SeqRuns
     const int tid = threadIdx.x & 255, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3, grp = wave8 >> 2;
     const int e = lane & 31, h = lane >> 5;
 
-    // ---- launch order -> (KV head, tile of queries): the tiles with the longest contexts first, all heads' of them; a head's
-    // tiles stay on one XCD when the heads divide over them (its L2 then serves the rows to all of them) ----
+    // ---- launch order -> (KV head, tile of queries): a run's tiles with the longest contexts first, all heads' of them, the last run's
+    // ahead of the first's (whatever their contexts); a head's tiles stay on one XCD when the heads divide over them (its L2 then serves the rows to all of them) ----
     int kvh, tile;
     if (a.H_kv % 8 == 0) {
         const int per_xcd = a.H_kv / 8, i = blockIdx.x >> 3;

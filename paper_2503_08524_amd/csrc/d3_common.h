@@ -8,7 +8,7 @@ namespace d3 {
 
 constexpr int kWave = 64;          // CDNA wavefront
 constexpr int kMaxCols = 32;       // largest batch; columns of a decode pass
-constexpr int kPassCols = 2048;    // most columns of a prompt chunk on the matrix-core path (a context holds min(this, max_seq rounded up to 128))
+constexpr int kPassCols = 2048;    // most columns of a prompt pass on the matrix-core path (a context holds min(this, n rounded up to 128), n = the cache rows of one sequence, or of all where they share passes)
 constexpr int kMaxSplits = 32;     // context splits of one attention head
 constexpr size_t kGemmPartBytes = 16u << 20;   // partial accumulators of a K-sliced wide MFMA projection
 constexpr size_t kPromptPartTile = 128u << 10;  // ... of one K part of a tile (256 rows x 128 columns) of a prompt pass's projection
@@ -134,7 +134,7 @@ struct GemvArgs {
 // D3_MFMA_WIDE=0: no panel kernel (passes are limited to kMaxCols columns); D3_WIDE_RT, D3_WIDE_KS: row tiles per wave
 // and K slices of the panel kernel; D3_WIDE_SPLIT_MB: matrix size above which a pass of more than 64 columns runs as
 // two 64-column launches; D3_ATTN_MFMA=0: grouped-query and query-tile attention on the vector ALUs;
-// D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most 2048); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8);
+// D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most 2048); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8; a contraction without two stages for every part stays whole);
 // D3_PROMPT_ROW_BLOCKS: fewest blocks of 256 rows for which 65..128 columns take the LDS-tiled kernel;
 // D3_PROMPT_CUS: compute units a round of its tiles is taken to have;
 // D3_PROMPT_ATTN_WGS: fewest workgroups (128 (query, head) pairs each) for which a prompt pass, shared or not, takes the whole-context attention kernel; D3_GEMV_WGS_PER_CU: workgroups

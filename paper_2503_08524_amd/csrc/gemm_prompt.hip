@@ -27,7 +27,7 @@
 //    consumes the weight fragments as they arrive.  Reads and loads issued ahead of the MFMAs instead cost 15-20 %.
 // The bound is the matrix cores at the clock that their power leaves them: on operands drawn from a normal distribution they
 // alone sustain 1.9-2.0 PFLOP/s (the clock drops with the toggling of the operands), the loop without its global loads 1.5-1.65, and
-// the launches at 2048 columns 1.35-1.45 as issued.  7B shape, 2048 columns, the kernel with stages of 32 k (128 x 64 per wave with two workgroups per
+// the launches at 2048 columns 1.2 (O) to 1.4 (down) as issued, QKV and gate/up 1.33.  7B shape, 2048 columns, the kernel with stages of 32 k (128 x 64 per wave with two workgroups per
 // compute unit, or eight waves of 64 x 64) -> this one: QKV 350 -> 308 us (rotation and cache append now included), gate/up
 // 657 -> 555, O 165 -> 115, down 362 -> 263.
 //
@@ -646,8 +646,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
 }
 
 // ---------------- yardstick: what the matrix cores sustain ----------------
-// A stage loop of eight waves, 64 x 64 per wave (32 MFMAs per wave and stage), on fragments that (mode >= 1) are re-read from
-// a fixed LDS buffer every stage, (mode 2) with a workgroup barrier per stage.  One workgroup per launched block, no global
+// A loop of eight waves, 64 x 64 per wave (32 MFMAs per wave and stage), on fragments that (mode >= 1) are re-read from a fixed LDS
+// buffer every stage, (mode 2) with a workgroup barrier per stage: plainer than the kernel's loop above, with 12 reads for 32 MFMAs
+// where that has 16 for 64.  One workgroup per launched block, no global
 // memory traffic but one word per wave at the end.
 constexpr int kYardRows = 4, kYardPitch = 64, kYardPlane = 128 * kYardPitch, kYardA = 256 * kYardPitch, kYardStage = kYardA + 2 * kYardPlane;
 struct YardFrags { u32x4 a[kYardRows], bh[4], bl[4]; };
@@ -777,7 +778,7 @@ int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, 
     return launch_prompt<MODE_RESID>(a, n_rb, n_cb, sp, s);
 }
 
-// mode 0: MFMAs alone; 1: with the fragment reads of the stage loop; 2: with the stage barrier as well.  n_wg workgroups of
+// mode 0: MFMAs alone; 1: with LDS fragment reads, 12 for 32 MFMAs; 2: with a workgroup barrier per stage as well.  n_wg workgroups of
 // eight waves; sink holds 8 floats per workgroup.  Flops issued: n_wg * 8 waves * stages * 32 MFMAs * 16384.
 int launch_mfma_yardstick(int mode, int stages, int n_wg, float* sink, hipStream_t s) {
     constexpr int lds = kYardStage;

@@ -9,7 +9,8 @@ namespace {
 // ---------------- embedding gather: x[c][:] = E[token(c)][:] ----------------
 // A workgroup per column: the column's row of the rotary table (the rotation angles depend on the position only, not on the
 // block) and its row of the residual stream; on the matrix-core path (split.gain set) also what gain_split_kernel hands to the first
-// projection, from the registers that hold the row anyway (as a launch of its own that was 5 us of a decode step, 13 us of 2048 columns).
+// projection, from the registers that hold the row anyway (as a launch of its own 5 us of a decode step, less than the step's
+// noise, and 13 us of 2048 columns).
 template <typename W>
 __device__ __forceinline__ void embed_column(const W* __restrict__ emb, int tok, int angle_pos, int c, int d, int vocab, float* __restrict__ x,
                                              const double* __restrict__ inv_freq, int half_hd, float2* __restrict__ rope_cs, const EmbedSplit& split) {
