@@ -95,7 +95,10 @@ __global__ __launch_bounds__(256) void embed_runs_kernel(const bf16_t* __restric
 __global__ __launch_bounds__(256) void pick_rows_kernel(const float* __restrict__ x, int d, RowPick pick, float* __restrict__ dst) {
     const float* src = x + (size_t)pick.col[blockIdx.x] * d;
     float* out = dst + (size_t)pick.row[blockIdx.x] * d;
-    for (int j = threadIdx.x; j < d; j += blockDim.x) out[j] = src[j];
+    for (int j = threadIdx.x * 4; j < d; j += blockDim.x * 4) {
+        const float4 v = *reinterpret_cast<const float4*>(src + j);
+        out[j] = v.x; out[j + 1] = v.y; out[j + 2] = v.z; out[j + 3] = v.w;
+    }
 }
 
 // ---------------- gain + split into bf16 hi/lo, sum of squares ----------------
