@@ -298,6 +298,29 @@ def test_left_padded_batch_fill_and_continuation(mode):
     print(f"  continuation logit abs err {wl:.3e}, hidden {wh:.3e}", flush=True)
 
 
+@pytest.mark.parametrize("P2,wgs", [(1, 0), (9, 1), (9, 1 << 20), (150, 1), (150, 1 << 20)])
+def test_left_padded_continuation_on_shared_passes(monkeypatch, P2, wgs):
+    """Equal tails behind a ragged batch at head_dim 128: one pass for all sequences, whose rows begin at different places, on the
+    whole-context kernel and on query tiles; a tail of one token on the fp32 projections.  fp32 cache: the fp32 bounds."""
+    if wgs:
+        monkeypatch.setenv("D3_PROMPT_ATTN_WGS", str(wgs))
+    shape = ModelShape("ragged-tail", L=2, d=256, H=4, H_kv=2, hd=128, F=384, V=512, dtype="bf16")
+    lengths = np.array([140, 2, 77], np.int32)
+    B, P, G2 = 3, 140, 2
+    w = d3_inputs.make_weights(shape, 2)
+    prompts = d3_inputs.make_prompt(B, P, shape.V, seed=1)
+    prompts2 = d3_inputs.make_prompt(B, P2, shape.V, seed=5)
+    forced2 = d3_inputs.make_prompt(B, G2 - 1, shape.V, seed=6)
+    max_seq = P + P2 + G2
+    print(f"case ragged tail of {P2}, wgs {wgs}", flush=True)
+    gpu = helpers.gpu_generate(shape, w, prompts, 1, 1.0, 1, kv_dtype="f32", max_seq=max_seq, lengths=lengths)
+    model, gens = helpers.oracle_generate(shape, w, prompts, 1, 1.0, 1, max_seq=max_seq, lengths=lengths)
+    gpu2 = helpers.gpu_generate(shape, w, prompts2, G2, 1.0, 1, forced=forced2, decoder=gpu["decoder"], pos_begin=P)
+    gens2 = [oracle.generate(model, prompts2[b], G2, 1.0, 1, seq=gen.seq, pos_begin=int(lengths[b]), forced=forced2[b]) for b, gen in enumerate(gens)]
+    wl, wh = helpers.compare(gpu2, gens2, G2, logit_atol=2e-4, hidden_tol=1e-4)
+    print(f"  logit abs err {wl:.3e}, hidden {wh:.3e}", flush=True)
+
+
 @pytest.mark.parametrize("name,B", [("llama-7b", 1), ("llama-70b", 2)])
 def test_recompute_fill_at_real_widths(name, B):
     import torch
@@ -349,12 +372,13 @@ def test_recompute_fill_call_rules():
 
 
 @pytest.mark.parametrize("P2,B,wgs,kv", [(10, 1, 0, "f16"), (150, 1, 0, "f32"), (10, 2, 1 << 20, "f32"), (150, 2, 1 << 20, "f16"),
-                                         (10, 1, 1, "f32"), (150, 1, 1, "f16"), (10, 2, 0, "f16"), (150, 2, 0, "f16")])
+                                         (10, 1, 1, "f32"), (150, 1, 1, "f16"), (10, 2, 0, "f16"), (150, 2, 0, "f16"),
+                                         (1, 1, 0, "f32"), (1, 2, 0, "f32")])
 def test_continuation_prompt_whose_query_tiles_straddle_an_attention_split(monkeypatch, P2, B, wgs, kv):
     """A second prompt that starts at row 125: its pass's query tiles (4 queries x 4 heads of a KV head at this shape) are
     not aligned with the context splits (multiples of 64 rows, 128 by default), so some queries of a tile have no row in
     the last split while others do.  One sequence takes query tiles by itself; two are made to, a launch each; the other cases are the same
-    continuation on the whole-context kernel."""
+    continuation on the whole-context kernel, and a single token on the fp32 projections."""
     if wgs:
         monkeypatch.setenv("D3_PROMPT_ATTN_WGS", str(wgs))
     shape = ModelShape("small-gqa", L=3, d=512, H=8, H_kv=2, hd=128, F=1376, V=2000, dtype="bf16")

@@ -193,6 +193,37 @@ def test_last_columns_that_stand_alone_keep_the_fp32_projections(monkeypatch, B,
             assert rel.max() <= 1.2e-6 and lg <= 1.2e-6, f"seq {b}"
 
 
+@pytest.mark.parametrize("B,P,wgs", [(3, 150, 1), (2, 700, 1 << 20), (5, 1, 0)])
+def test_prompt_pass_of_a_batch_replays_from_a_graph(monkeypatch, B, P, wgs):
+    # shared passes on the whole-context kernel and on query tiles run by run (arrival counters of splits and K parts must be left
+    # zero by every replay), and lone tokens on the fp32 projections: each replay equals the eager call, bit for bit
+    import torch
+    from paper_2503_08524_amd import binding
+    if wgs:
+        monkeypatch.setenv("D3_PROMPT_ATTN_WGS", str(wgs))
+    monkeypatch.setenv("D3_PROMPT_KS", "2")
+    s = ModelShape("graph", L=2, d=256, H=4, H_kv=2, hd=128, F=704, V=512, dtype="bf16")
+    dec = binding.Decoder(s, binding.random_weights_on_device(s, 5), B, P + 2)
+    toks = [torch.from_numpy(d3_inputs.make_prompt(B, P, s.V, seed=k)).to("cuda:0") for k in (1, 2)]
+    fed, out, logits = toks[0].clone(), torch.zeros(B, dtype=torch.int32, device="cuda:0"), torch.zeros(B, s.V, device="cuda:0")
+    print(f"case graph B={B} P={P} wgs={wgs}", flush=True)
+    want = []
+    for t in toks:
+        dec.prefill(t, next_tok=out, logits=logits)
+        want.append((out.clone(), logits.clone(), dec.k_cache.clone()))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dec.prefill(fed, next_tok=out, logits=logits)
+    for k in (0, 1, 1, 0, 1):
+        fed.copy_(toks[k])
+        logits.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[k][0]) and torch.equal(logits, want[k][1]) and torch.equal(dec.k_cache, want[k][2])
+    dec.close()
+
+
 def test_hidden_states_of_shared_passes_into_a_buffer_aligned_to_floats_only():
     # hidden_dump is a float pointer: 4, 8 and 12 bytes past a 16-byte boundary it takes the same rows, and nothing beside them
     import torch
