@@ -76,6 +76,7 @@ constexpr int kPromptLds = kLdsX + 2 * kXBytes;        // 160 KB, all there is
 [[maybe_unused]] constexpr int kLoadsW = kABytes / 1024 / kWaves, kLoadsX = kXBytes / 1024 / kWaves, kLoads = kLoadsW + kLoadsX;   // direct loads per wave and stage
 constexpr int RW = 8;                          // 16-row tiles per wave
 constexpr int CW = 2;                          // column tiles a wave finishes (it multiplies 2 CW)
+[[maybe_unused]] constexpr int kSsqCols = kTileN * 16 / kThreads;   // columns a group of 16 threads takes the sums of squares of
 constexpr int kAccWords = RW * CW * 4;         // accumulator words per lane of a finished (half) wave tile
 
 // Instructions stay on their side of this point: what interleaves the MFMAs with loads and reads as written.
@@ -508,25 +509,39 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
     load_w(s0, w0); load_x(s0, 0);
+    fixed_here();
+    // 16 threads take one column's partial sums of squares (thread tid: columns tid / 16 + 32 u), requested between the first stage's loads and
+    // the second's: they arrive with the first stage
+    const bool norm = MODE != MODE_RESID && a.ssq_in;
+    float sq[kSsqCols][2];
+    if (norm) {
+#pragma unroll
+        for (int u = 0; u < kSsqCols; ++u) {
+            const float* p = a.ssq_in + (size_t)min(cb * kTileN + (tid >> 4) + kThreads / 16 * u, a.ncols - 1) * kSsqStride;
+            sq[u][0] = p[min(tid & 15, a.ssq_parts - 1)];
+            sq[u][1] = p[min(16 + (tid & 15), a.ssq_parts - 1)];
+        }
+    }
+    fixed_here();
     load_w(s0 + 1, w1); load_x(s0 + 1, 1);
+    if (n_stages > 2) { load_w(s0 + 2, w2); vm_loads_left<kLoads + kLoadsW>(); }
+    else vm_loads_left<kLoads>();
     float inv = 0.f;                                   // of column tid / 16 + 32 (tid % 16), for tid % 16 < 4
-    // 16 threads add up one column's partial sums of squares, in a fixed order, behind the direct loads of the first two stages
-    // (reading them ahead of those put a round trip more in front of every tile)
-    if (MODE != MODE_RESID && a.ssq_in) {
-        for (int c = tid >> 4; c < kTileN; c += kThreads / 16) {
-            const int col = cb * kTileN + c;
+    if (norm) {
+#pragma unroll
+        for (int u = 0; u < kSsqCols; ++u) {           // in a fixed order
             float ss = 0.f;
-            if (col < a.ncols) {
-                const float* p = a.ssq_in + (size_t)col * kSsqStride;
-                for (int i0 = tid & 15; i0 < a.ssq_parts; i0 += 16) ss += p[i0];
+            if ((tid & 15) < a.ssq_parts) ss += sq[u][0];
+            if (16 + (tid & 15) < a.ssq_parts) ss += sq[u][1];
+            if (a.ssq_parts > 32) {                    // a producer of few rows per workgroup
+                const float* p = a.ssq_in + (size_t)min(cb * kTileN + (tid >> 4) + kThreads / 16 * u, a.ncols - 1) * kSsqStride;
+                for (int i0 = 32 + (tid & 15); i0 < a.ssq_parts; i0 += 16) ss += p[i0];
             }
 #pragma unroll
             for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
-            if ((tid & 15) == c / (kThreads / 16)) inv = 1.0f / sqrtf(ss / (float)K + a.eps);
+            if ((tid & 15) == u) inv = 1.0f / sqrtf(ss / (float)K + a.eps);
         }
     }
-    if (n_stages > 2) { load_w(s0 + 2, w2); vm_loads_left<kLoads + kLoadsW>(); }
-    else vm_loads_left<kLoads>();
     __syncthreads();                                   // stage 0 is in LDS
     read_b_frags<0>(f0, b_off);
     read_a_frags(A0, a_off, std::make_integer_sequence<int, RW>{});
