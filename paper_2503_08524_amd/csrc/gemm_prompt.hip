@@ -142,6 +142,8 @@ __device__ __forceinline__ void store_qkv(const GemvArgs& a, const f32x4 (&acc)[
     if (head >= a.H + 2 * a.H_kv) return;
     const bool is_q = head < a.H, is_v = head >= a.H + a.H_kv;
     const int kvh = is_v ? head - a.H - a.H_kv : head - a.H;
+    void *kc = a.k_cache, *vc = a.v_cache;
+    asm volatile("" : "+s"(kc), "+s"(vc));             // two values: the compiler would choose between their places, in a copy on the stack
     int2 at[CW];                                       // (sequence, cache row) of this lane's columns
     float4 c0[CW][RW / 2], c1[CW][RW / 2];             // (cos, sin) of dims j, j + 1 and j + 2, j + 3
 #pragma unroll
@@ -165,7 +167,7 @@ __device__ __forceinline__ void store_qkv(const GemvArgs& a, const f32x4 (&acc)[
         const float sc = inv_rms[cl];
         float* q = a.out + (size_t)col * a.out_stride + head * 128;
         T* row = nullptr;
-        if (!is_q) row = static_cast<T*>(is_v ? a.v_cache : a.k_cache) + (((size_t)at[tt].x * a.H_kv + kvh) * a.max_seq + at[tt].y) * 128;
+        if (!is_q) row = static_cast<T*>(is_v ? vc : kc) + (((size_t)at[tt].x * a.H_kv + kvh) * a.max_seq + at[tt].y) * 128;
 #pragma unroll
         for (int r = 0; r < RW / 2; ++r) {
             const int j = 16 * r + 4 * lg;
@@ -353,10 +355,29 @@ __device__ __forceinline__ void mma_hl(f32x4 (&acc)[RW][2 * CW], int tt, const u
     }
 }
 
-// Tiles [0, n_whole) of the launch order have a workgroup each, the others ks of them, one per part of K.  (The buffer resource type
-// exists in device code only.)
+// Division by a number that the host knows: one multiplication instead of the 25 dependent instructions of a division.  m = ceil(2^32 / d);
+// exact while x * d < 2^32.
+struct Divisor {
+    int d = 1;
+    uint32_t m = 0;
+    Divisor() = default;
+    explicit Divisor(int v) : d(v), m(v > 1 ? (uint32_t)(((1ull << 32) + v - 1) / v) : 0) {}
+    __device__ __forceinline__ int of(int x) const { return d == 1 ? x : (int)__umulhi((uint32_t)x, m); }
+};
+// Launch order of the tiles.  Tiles [0, n_whole) have a workgroup each, the others ks of them, one per part of K.  n_rb row blocks: each
+// XCD owns n_rb / 8 of them and walks them in groups of kGroupR, the last group may hold fewer; n_rb % 8 are left over.
+constexpr int kGroupR = 4, kGroupC = 8;
+struct TileOrder {
+    int n_rb, n_cb, n_whole;
+    Divisor ks, rest, group_tiles, last_group, last_chunk, left;
+    TileOrder(int rb, int cb, int whole, int parts)
+        : n_rb(rb), n_cb(cb), n_whole(whole), ks(parts), rest(rb * cb - whole > 0 ? rb * cb - whole : 1), group_tiles(kGroupR * cb),
+          last_group(rb / 8 % kGroupR ? rb / 8 % kGroupR : kGroupR), last_chunk(last_group.d * kGroupC), left(rb % 8 ? rb % 8 : 1) {}
+};
+
+// (The buffer resource type exists in device code only.)
 template <int MODE>
-__global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, int n_rb, int n_cb, int n_whole, int ks) {
+__global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, TileOrder order) {
 #ifdef __HIP_DEVICE_COMPILE__
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
     constexpr int OT = 2 * RW / SW;                    // output row tiles per workgroup (half as many gate/up pairs)
@@ -368,67 +389,91 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     const int grp = wave8 >> 2, wave = wave8 & 3, wy = wave >> 1, wx = wave & 1;
     const int li = lane & 15, lg = lane >> 4;
 
+    // What the first loads need of the arguments, requested together: taken as they come up they are a chain of round trips to memory.  Clocks from
+    // a workgroup's start to its first load / to its first MFMA, 7B shape, 512 columns, gate/up: 4300 / 13300 with divisions and arguments as they
+    // came up, 3350 / 11500 with the divisors' reciprocals from the host and each load sent as soon as its address is known, 1700 / 9300 with this.
+    const bf16_t *const arg_hi = a.x_hi, *const arg_lo = a.x_lo;
+    const void *const arg_w0 = a.w[0], *const arg_w1 = MODE == MODE_RESID ? nullptr : a.w[1], *const arg_w2 = MODE == MODE_RESID || MODE == MODE_SWIGLU ? nullptr : a.w[2];
+    const int K = a.K, x_stride = a.x_stride, total_rows = a.total_rows, rows0 = a.rows[0], rows1 = a.rows[1];
+    asm volatile("" :: "s"(arg_hi), "s"(arg_lo), "s"(arg_w0), "s"(arg_w1), "s"(arg_w2), "s"(K), "s"(x_stride), "s"(total_rows), "s"(rows0), "s"(rows1),
+                 "s"(order.n_rb), "s"(order.n_cb), "s"(order.n_whole), "s"(order.group_tiles.m));
+
     // ---- launch order -> tile, K part; tile -> (row block, column block) ----
+    const int n_whole = order.n_whole;
     int tile_id = blockIdx.x, slice = 0, parts = 1;
     if (tile_id >= n_whole) {                          // part by part: neighbours in the order share the part's columns of K
-        const int rest = n_rb * n_cb - n_whole;
-        slice = (tile_id - n_whole) / rest;
-        tile_id -= slice * rest;
-        parts = ks;
+        slice = order.rest.of(tile_id - n_whole);
+        tile_id -= slice * order.rest.d;
+        parts = order.ks.d;
     }
     int rb, cb;
     {
-        constexpr int GR = 4, GC = 8;
-        const int own = n_rb / 8, even = own * 8 * n_cb;       // row blocks per XCD; what is left of them comes last, in plain order
+        const int own = order.n_rb / 8, even = own * 8 * order.n_cb;   // row blocks per XCD; what is left of them comes last, in plain order
         if (tile_id < even) {
             const int xcd = tile_id & 7, idx = tile_id >> 3;
-            const int group = idx / (GR * n_cb), rem = idx - group * GR * n_cb;
-            const int in_group = min(GR, own - GR * group);
-            const int chunk = rem / (in_group * GC), r2 = rem - chunk * in_group * GC;
-            rb = (GR * group + r2 % in_group) * 8 + xcd;
-            cb = chunk * GC + r2 / in_group;
+            const int group = order.group_tiles.of(idx), rem = idx - group * order.group_tiles.d;
+            int chunk, row;
+            if (kGroupR * group + kGroupR <= own) {
+                chunk = rem / (kGroupR * kGroupC);
+                cb = rem % (kGroupR * kGroupC) / kGroupR;
+                row = rem % kGroupR;
+            } else {
+                chunk = order.last_chunk.of(rem);
+                const int r2 = rem - chunk * order.last_chunk.d;
+                cb = order.last_group.of(r2);
+                row = r2 - cb * order.last_group.d;
+            }
+            rb = (kGroupR * group + row) * 8 + xcd;
+            cb += chunk * kGroupC;
         } else {
-            const int left = n_rb - own * 8;
-            rb = own * 8 + (tile_id - even) % left;
-            cb = (tile_id - even) / left;
+            cb = order.left.of(tile_id - even);
+            rb = own * 8 + (tile_id - even) - cb * order.left.d;
         }
     }
-    const int K = a.K, tiles = a.total_rows / 16;      // output row tiles of the whole matrix
+    const int tiles = total_rows / 16;                 // output row tiles of the whole matrix
     // whole stages go to the parts in pairs; the last part takes what is over: an odd stage, and the half stage of K % 64 == 32
-    const int pairs = K / (2 * kBK), pair0 = (int)((long long)pairs * slice / parts);
-    const int s0 = 2 * pair0, n_stages = 2 * ((int)((long long)pairs * (slice + 1) / parts) - pair0);
+    const int pairs = K / (2 * kBK), pair0 = parts == 1 ? 0 : order.ks.of(pairs * slice);
+    const int s0 = 2 * pair0, n_stages = 2 * ((parts == 1 ? pairs : order.ks.of(pairs * (slice + 1))) - pair0);
     const int s_end = (K + kBK - 1) / kBK, n_single = slice == parts - 1 ? s_end - 2 * pairs : 0;      // 0, 1 or 2
     // (the launcher sees to at least two whole stages per part)
 
     // ---- this wave's eight-row blocks of a stage (wave8, wave8 + 8, ...): the first 32 are weight rows, then hi, then lo ----
     // Slab tile st = 8 wy + t is wave row wy's tile t.  Plain modes: output tile OT rb + st.  SwiGLU: tiles t < 4 are gate rows,
     // the others the up rows of the same outputs OT rb + 4 wy + t % 4.  Tiles past the matrix re-read the last one (result dropped).
-    __amdgpu_buffer_rsrc_t src[kLoads];
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-        const int blk = wave8 + kWaves * j;
-        const bf16_t* p;
-        if (blk < kTileM / 8) {
-            const int st = blk >> 1, t = st % RW;
-            int otile = MODE == MODE_SWIGLU ? rb * OT + (st / RW) * (RW / 2) + t % (RW / 2) : rb * OT + st;
-            otile = otile < tiles ? otile : tiles - 1;
-            int m = MODE == MODE_SWIGLU ? t / (RW / 2) : 0, local = otile * 16;
-            if (MODE != MODE_SWIGLU && local >= a.rows[0]) { local -= a.rows[0]; m = 1; if (local >= a.rows[1]) { local -= a.rows[1]; m = 2; } }
-            p = static_cast<const bf16_t*>(a.w[m]) + (size_t)(local + 8 * (blk & 1)) * K;
-        } else {
-            const int b = 8 * (blk - kTileM / 8), plane = b / kTileN;
-            p = (plane ? a.x_lo : a.x_hi) + (size_t)(cb * kTileN + b % kTileN) * a.x_stride;
-        }
-        const int row_elems = blk < kTileM / 8 ? K : a.x_stride;
-        src[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 2 * (7 * row_elems + K), 0x00027000);   // eight rows
-    }
+    // Each block's first load goes out before the next block's address is worked out: the code up to here comes from memory too, a line at a time.
     // lane l of a load: row l / 8 of the block, LDS position l % 8, i.e. segment (l % 8) ^ ((slab row / 2) % 8) of that row
     const int prow = lane >> 3, pseg = (lane & 7) ^ ((lane >> 4) | (4 * (wave8 & 1)));
-    const int voff_w = 2 * (prow * K + pseg * 8), voff_x = 2 * (prow * a.x_stride + pseg * 8);
+    const int voff_w = 2 * (prow * K + pseg * 8), voff_x = 2 * (prow * x_stride + pseg * 8), voff_x64 = voff_x + 2 * 64 * x_stride;
+    __amdgpu_buffer_rsrc_t src[kLoadsW + 2];           // a block of eight weight rows each; the wave's columns c and c + 64 of a plane each
+    static_assert(kLoadsX == 4, "two loads of eight columns per plane");
     auto load1 = [&](int j, int t, int lds) {         // t: stage of the whole K; lds: where its slab (weights j < kLoadsW, or activations) lies
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(src[j], (__attribute__((address_space(3))) void*)((lds_char*)prompt_lds + lds + (wave8 + kWaves * (j < kLoadsW ? j : j - kLoadsW)) * 1024),
-                                                 16, j < kLoadsW ? voff_w : voff_x, t * kPitch, 0, 0);
+        const int jx = j - kLoadsW;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src[j < kLoadsW ? j : kLoadsW + jx / 2], (__attribute__((address_space(3))) void*)((lds_char*)prompt_lds + lds + (wave8 + kWaves * (j < kLoadsW ? j : jx)) * 1024),
+                                                 16, j < kLoadsW ? voff_w : jx % 2 ? voff_x64 : voff_x, t * kPitch, 0, 0);
     };
+    int w0 = 0, w1 = kABytes, w2 = 2 * kABytes;        // the weight slabs of this stage and the next two
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+        if (j < kLoadsW) {
+            const int blk = wave8 + kWaves * j, st = blk >> 1, t = st % RW;
+            int otile = MODE == MODE_SWIGLU ? rb * OT + (st / RW) * (RW / 2) + t % (RW / 2) : rb * OT + st;
+            otile = otile < tiles ? otile : tiles - 1;
+            int local = otile * 16;
+            const void* w = MODE == MODE_SWIGLU && t >= RW / 2 ? arg_w1 : arg_w0;
+            if (MODE != MODE_SWIGLU && MODE != MODE_RESID && local >= rows0) {
+                local -= rows0;
+                w = arg_w1;
+                if (local >= rows1) { local -= rows1; w = arg_w2; }
+            }
+            const bf16_t* p = static_cast<const bf16_t*>(w) + (size_t)(local + 8 * (blk & 1)) * K;
+            src[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 2 * 8 * K, 0x00027000);
+        } else if ((j - kLoadsW) % 2 == 0) {
+            const bf16_t* p = (j == kLoadsW ? arg_hi : arg_lo) + (size_t)(cb * kTileN + 8 * wave8) * x_stride;
+            src[kLoadsW + (j - kLoadsW) / 2] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 2 * (71 * x_stride + K), 0x00027000);
+        }
+        load1(j, s0, j < kLoadsW ? w0 : kLdsX);
+        fixed_here();
+    }
     auto load_w = [&](int t, int lds) {
 #pragma unroll
         for (int j = 0; j < kLoadsW; ++j) load1(j, t, lds);
@@ -450,7 +495,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
         for (int tt = 0; tt < 2 * CW; ++tt) acc[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
     u32x4 A0[RW], A1[RW];                             // weight fragments of this stage and the next
     PromptB f0, f1, f2;                                // activation fragments of three column tiles
-    int w0 = 0, w1 = kABytes, w2 = 2 * kABytes;        // the weight slabs of this stage and the next two
     // Stage t, activations in buffer BUF, on the weight fragments A; X holds column tile 0 when it starts (requested, like A, by the stage
     // before) and column tile 3 in the end, Y the next stage's column tile 0.  MORE: a stage follows; loads: so do two; loads_w: three.
     // A wave's LDS reads return in order, so "at most n outstanding" names the oldest ones that have arrived.
@@ -508,8 +552,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, in
     constexpr std::integral_constant<int, 1> b1{};
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
-    load_w(s0, w0); load_x(s0, 0);
-    fixed_here();
     // 16 threads take one column's partial sums of squares (thread tid: columns tid / 16 + 32 u), requested between the first stage's loads and
     // the second's: they arrive with the first stage
     const bool norm = MODE != MODE_RESID && a.ssq_in;
@@ -759,14 +801,14 @@ int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, PromptSplit sp, hipStre
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_prompt_kernel<MODE>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return (int)attr;
     const int grid = sp.n_whole + (n_rb * n_cb - sp.n_whole) * sp.ks;
-    hipLaunchKernelGGL(gemm_prompt_kernel<MODE>, dim3(grid), dim3(kThreads), lds, s, a, n_rb, n_cb, sp.n_whole, sp.ks);
+    hipLaunchKernelGGL(gemm_prompt_kernel<MODE>, dim3(grid), dim3(kThreads), lds, s, a, TileOrder(n_rb, n_cb, sp.n_whole, sp.ks));
     return (int)hipGetLastError();
 }
 
 }  // namespace
 
 // Requirements: those of launch_gemm_mfma (bf16 weights, K % 32 == 0, row counts multiples of 16), K >= 128, 1 <= ncols <=
-// kPassCols (x_hi / x_lo hold ncols rounded up to 128 rows); with ssq_out at most kSsqStride row blocks.  MODE_QKV_ROPE: head_dim
+// kPassCols (x_hi / x_lo hold ncols rounded up to 128 rows); one matrix in MODE_RESID; with ssq_out at most kSsqStride row blocks.  MODE_QKV_ROPE: head_dim
 // 128, ssq_in, col_at and rope_cs set, only q is written to out.
 // Up to 128 columns the panel kernel is the other choice.  It slows down past 64 (its LDS pipe, or two launches of 64), the LDS-tiled
 // kernel takes one column block whatever its width and wants row blocks.  Measured at 65 / 77 / 128 columns (us between events, panel -> LDS-tiled): 48 or
