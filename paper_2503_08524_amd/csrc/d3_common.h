@@ -127,6 +127,8 @@ struct GemvArgs {
     // group (zero between launches)
     float* part;
     int* part_tickets;
+    // vector-ALU GEMV, set by its launcher: units per wave, and how many waves have one more
+    int wave_units, wave_units_over;
 };
 
 // Launch-shape overrides for measurements, read from the environment ONCE by d3_create (0 / default = the library's

@@ -142,8 +142,8 @@ __device__ __forceinline__ void store_qkv(const GemvArgs& a, const f32x4 (&acc)[
     if (head >= a.H + 2 * a.H_kv) return;
     const bool is_q = head < a.H, is_v = head >= a.H + a.H_kv;
     const int kvh = is_v ? head - a.H - a.H_kv : head - a.H;
-    void *kc = a.k_cache, *vc = a.v_cache;
-    asm volatile("" : "+s"(kc), "+s"(vc));             // two values: the compiler would choose between their places, in a copy on the stack
+    void *const kc = a.k_cache, *const vc = a.v_cache;
+    asm volatile("" :: "s"(kc), "s"(vc));              // two values: the compiler would choose between their places, in a copy on the stack
     int2 at[CW];                                       // (sequence, cache row) of this lane's columns
     float4 c0[CW][RW / 2], c1[CW][RW / 2];             // (cos, sin) of dims j, j + 1 and j + 2, j + 3
 #pragma unroll

@@ -22,11 +22,12 @@ namespace {
 
 template <typename W, int NC, int MODE, bool NORM>
 __global__ __launch_bounds__(kGemvThreads) void gemv_alu_kernel(GemvArgs a) {
+    gemv_take_args(a);
     extern __shared__ float4 xs[];                     // [NC][f4_per_col]
     __shared__ float red[NC][kGemvWaves];
     __shared__ GemvEpBuf<NC> ep[kGemvWaves];
     constexpr int R = kGemvStageR / NC;
-    const int tid = threadIdx.x, wave = tid >> 6;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // the units' addresses are the wave's: scalar
     // Units go round-robin over the waves of the whole grid, so that at any moment the chip streams one contiguous
     // band of the matrix (spread over every memory channel); numbering the waves workgroup-fastest hands the units
     // that do not divide evenly to different workgroups, one each.
@@ -43,7 +44,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_alu_kernel(GemvArgs a) {
 }
 
 template <typename W, int NC>
-int launch_nc(const GemvArgs& a, int mode, bool norm, int n_wg, hipStream_t s) {
+int launch_nc(GemvArgs a, int mode, bool norm, int n_wg, hipStream_t s) {
     const size_t lds = (size_t)NC * gemv_f4_per_col<W>(a.K) * sizeof(float4);
     const int n_units = gemv_n_units(a, mode);
     // n_wg workgroups, a multiple of the CU count (a compute unit is the unit of bandwidth: the same number of
@@ -51,6 +52,9 @@ int launch_nc(const GemvArgs& a, int mode, bool norm, int n_wg, hipStream_t s) {
     int grid = (n_units + kGemvWaves - 1) / kGemvWaves;
     if (grid > n_wg) grid = n_wg;
     if ((long long)grid * kGemvWaves * kGemvEpCap < n_units) return (int)hipErrorInvalidValue;   // a wave parks at most kGemvEpCap (= 64 lanes) units
+    const int n_waves = grid * kGemvWaves;
+    a.wave_units = n_units / n_waves;
+    a.wave_units_over = n_units % n_waves;
 #define D3_LAUNCH(MODE, NORM) hipLaunchKernelGGL((gemv_alu_kernel<W, NC, MODE, NORM>), dim3(grid), dim3(kGemvThreads), lds, s, a)
     if (mode == MODE_STORE) { if (norm) D3_LAUNCH(MODE_STORE, true); else D3_LAUNCH(MODE_STORE, false); }
     else if (mode == MODE_RESID) { D3_LAUNCH(MODE_RESID, false); }
@@ -79,7 +83,7 @@ size_t gemv_alu_max_cols(int K, int weight_dtype) {
 }
 
 // Requirements (checked by the caller): K % 8 == 0, total_rows even, 1 <= ncols <= gemv_alu_max_cols,
-// MODE_RESID without norm, MODE_SWIGLU / MODE_QKV_ROPE with norm, x/out/weights 16-byte aligned.
+// MODE_RESID without norm and of one matrix, MODE_SWIGLU / MODE_QKV_ROPE with norm, x/out/weights 16-byte aligned.
 int launch_gemv_alu(const GemvArgs& a, int weight_dtype, int mode, bool norm, int n_wg, hipStream_t s) {
     return weight_dtype == 0 ? launch_w<float>(a, mode, norm, n_wg, s) : launch_w<bf16_t>(a, mode, norm, n_wg, s);
 }
