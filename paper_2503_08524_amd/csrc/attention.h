@@ -25,24 +25,13 @@ template <> struct KvVec<f16_t> {
     static __device__ __forceinline__ void store(f16_t* p, float v) { *p = (f16_t)fminf(fmaxf(v, -65504.f), 65504.f); }
 };
 
-// Sum over each aligned group of LPR lanes, every lane of a group ending with the same bits.  Sixteen lanes
-// are one DPP row: four rotate-and-add steps on the vector ALU instead of four trips through the LDS crossbar
-// (after the step by 8 the values have period 8, after the step by 4 period 4, ..., so all lanes agree exactly).
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
+// Sum over each aligned group of LPR lanes, every lane of a group ending with the same bits.
 template <int LPR>
 __device__ __forceinline__ float group_sum(float v) {
-    if (LPR == 16) {
-        v += dpp_move<0x128>(v);           // row_ror:8
-        v += dpp_move<0x124>(v);           // row_ror:4
-        v += dpp_move<0x122>(v);           // row_ror:2
-        v += dpp_move<0x121>(v);           // row_ror:1
-    } else {
+    if (LPR == 32) v = reduce_row_pairs(v, AddOp());
+    if (LPR >= 16) return reduce_row(v, AddOp());
 #pragma unroll
-        for (int o = LPR / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    }
+    for (int o = LPR / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
 
@@ -333,8 +322,7 @@ __device__ __forceinline__ void attn_split(const AttnArgs& a, int split, int h0,
                     if (j < j1) { sv[u] = s; cmax = fmaxf(cmax, s); }
                 }
             }
-#pragma unroll
-            for (int o = LPR; o < 64; o <<= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, o, 64));   // equal within a row group already
+            cmax = reduce_across<LPR>(cmax, MaxOp());  // equal within a row group already
             const float m_new = fmaxf(m[g], cmax);          // a wave with no valid row in this chunk keeps -inf
             if (m_new > -INFINITY) {
                 const float keep = exp2f(m[g] - m_new);       // exp2(-inf) = 0 the first time
@@ -368,10 +356,7 @@ __device__ __forceinline__ void attn_split(const AttnArgs& a, int split, int h0,
 #pragma unroll
     for (int g = 0; g < G; ++g) {
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-#pragma unroll
-            for (int o = LPR; o < 64; o <<= 1) acc[g][e] += __shfl_xor(acc[g][e], o, 64);
-        }
+        for (int e = 0; e < EPL; ++e) acc[g][e] = reduce_across<LPR>(acc[g][e], AddOp());
         const float lw = wave_sum(l[g]);
         if (rg == 0) {
 #pragma unroll
@@ -653,8 +638,7 @@ __device__ __forceinline__ void attn_split_mfma(const AttnArgs& a, int split, in
                 if (r0 + 16 * t + 4 * g + e >= j1) S[t][e] = -INFINITY;
                 mx = fmaxf(mx, S[t][e]);
             }
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));        // finite: row r0 is valid
+        mx = reduce_across<16>(mx, MaxOp());           // finite: row r0 is valid
         const float m_new = fmaxf(m, mx);
         const float keep = exp2f(m - m_new);           // exp2(-inf) = 0 the first time
         attn_half8 phi, plo;
@@ -697,8 +681,7 @@ __device__ __forceinline__ void attn_split_mfma(const AttnArgs& a, int split, in
     }
 
     // ---- waves -> LDS (the staging tiles give way to the merge area), then the common second half ----
-    lsum += __shfl_xor(lsum, 16, 64);
-    lsum += __shfl_xor(lsum, 32, 64);
+    lsum = reduce_across<16>(lsum, AddOp());
     __syncthreads();
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt)
@@ -795,8 +778,7 @@ __device__ __forceinline__ void attn_qtile_mfma(const AttnArgs& a, int split, in
                 if (row >= j1 || row >= ctx_i) S[t][e] = -INFINITY;  // past the split, or after this entry's own position
                 mx = fmaxf(mx, S[t][e]);
             }
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = reduce_across<16>(mx, MaxOp());
         const float m_new = fmaxf(m, mx);
         const bool any = m_new > -INFINITY;                           // an entry may have no row yet (its context ends earlier)
         const float keep = any ? exp2f(m - m_new) : 1.f;
@@ -832,8 +814,7 @@ __device__ __forceinline__ void attn_qtile_mfma(const AttnArgs& a, int split, in
         __builtin_amdgcn_wave_barrier();
     }
 
-    lsum += __shfl_xor(lsum, 16, 64);
-    lsum += __shfl_xor(lsum, 32, 64);
+    lsum = reduce_across<16>(lsum, AddOp());
     __syncthreads();
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt)

@@ -212,7 +212,7 @@ __global__ __launch_bounds__(512, 2) void attn_prompt_kernel(AttnArgs a, SeqRuns
             for (int t = 0; t < SUB; ++t)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[t][i]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            mx = reduce_halves(mx, MaxOp());
             if (__any(mx > m + kPaSlack)) {            // rare after the first tiles
                 const float m_new = fmaxf(m, mx), keep = __builtin_amdgcn_exp2f(m - m_new);
                 lsum *= keep;
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(512, 2) void attn_prompt_kernel(AttnArgs a, SeqRuns
     }
 
     // ---- group 1 hands its state over (an entry that saw none of its rows: maximum at the floor, zero sums), group 0 merges ----
-    lsum += __shfl_xor(lsum, 32, 64);
+    lsum = reduce_halves(lsum, AddOp());
     attn_f32x4* xa = reinterpret_cast<attn_f32x4*>(lds) + tid;   // [16][256]
     float2* xm = reinterpret_cast<float2*>(lds + 64 * 1024) + tid;
     if (grp == 1) {

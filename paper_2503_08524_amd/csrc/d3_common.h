@@ -74,16 +74,36 @@ __device__ __forceinline__ void st_agent(float* p, float v) { __hip_atomic_store
 __device__ __forceinline__ float ld_agent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+// Reductions over lanes on the vector ALU: halves of a wave and pairs of its rows of 16 lanes by lane swaps, a row by rotations.  Every lane gets the
+// result, and lanes are paired as in a butterfly of shuffles by the same distances, but a shuffle is a round trip to the LDS and
+// the six of a wave's sum wait for each other.
+struct AddOp { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct MaxOp { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+template <int N> __device__ __forceinline__ float row_rotated(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+template <typename F> __device__ __forceinline__ float reduce_halves(float v, F op) {         // lanes l and l ^ 32
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
+template <typename F> __device__ __forceinline__ float reduce_row_pairs(float v, F op) {      // lanes l and l ^ 16
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+template <typename F> __device__ __forceinline__ float reduce_row(float v, F op) {            // the 16 lanes of a row (after a step by n the values have period n)
+    v = op(v, row_rotated<8>(v));
+    v = op(v, row_rotated<4>(v));
+    v = op(v, row_rotated<2>(v));
+    return op(v, row_rotated<1>(v));
+}
+// lanes that agree modulo FROM = 8, 16 or 32
+template <int FROM, typename F> __device__ __forceinline__ float reduce_across(float v, F op) {
+    static_assert(FROM == 8 || FROM == 16 || FROM == 32, "");
+    if (FROM == 8) v = op(v, row_rotated<8>(v));
+    if (FROM <= 16) v = reduce_row_pairs(v, op);
+    return reduce_halves(v, op);
+}
+__device__ __forceinline__ float wave_sum(float v) { return reduce_row(reduce_row_pairs(reduce_halves(v, AddOp()), AddOp()), AddOp()); }
 
 // ---------------- projections ----------------
 enum GemvMode { MODE_STORE = 0, MODE_RESID = 1, MODE_SWIGLU = 2, MODE_QKV_ROPE = 3 };

@@ -180,8 +180,7 @@ __global__ __launch_bounds__(512) void gemm_mfma_kernel(GemvArgs a) {   // <= 8 
 #pragma unroll
                 for (int j = 0; j < 8; ++j) ss += t[j];
             }
-#pragma unroll
-            for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
+            ss = reduce_row(ss, AddOp());
             if ((tid & 15) == 0) inv_rms[col] = 1.0f / sqrtf(ss / (float)K + a.eps);
         }
     };

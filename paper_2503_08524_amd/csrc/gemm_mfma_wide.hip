@@ -200,8 +200,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
 #pragma unroll
                 for (int j = 0; j < 8; ++j) ss += tv[j];
             }
-#pragma unroll
-            for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
+            ss = reduce_row(ss, AddOp());
             if ((tid & 15) == 0) inv_rms[col] = 1.0f / sqrtf(ss / (float)K + a.eps);
         }
     };
@@ -333,8 +332,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
     if (MODE == MODE_RESID && a.ssq_out) {             // rows of a column: the 4 lane groups by butterfly, then the waves in order
 #pragma unroll
         for (int tt = 0; tt < CT; ++tt) {
-            sq[tt] += __shfl_xor(sq[tt], 16, 64);
-            sq[tt] += __shfl_xor(sq[tt], 32, 64);
+            sq[tt] = reduce_across<16>(sq[tt], AddOp());
             if (g4 == 0) ssq_w[wave][tt * 16 + ci] = sq[tt];
         }
         __syncthreads();

@@ -586,8 +586,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
                 const float* p = a.ssq_in + (size_t)min(cb * kTileN + (tid >> 4) + kThreads / 16 * u, a.ncols - 1) * kSsqStride;
                 for (int i0 = 32 + (tid & 15); i0 < a.ssq_parts; i0 += 16) ss += p[i0];
             }
-#pragma unroll
-            for (int o = 8; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
+            ss = reduce_row(ss, AddOp());
             if ((tid & 15) == u) inv = 1.0f / sqrtf(ss / (float)K + a.eps);
         }
     }
