@@ -35,6 +35,16 @@ __device__ __forceinline__ float group_sum(float v) {
     return v;
 }
 
+// What the first loads need of the arguments, requested together: read as they come up, each is a round trip to memory that the next one waits behind.
+__device__ __forceinline__ void attn_take_args(const AttnArgs& a) {
+    asm volatile("" :: "s"(a.q), "s"(a.rope_cs), "s"(a.row0), "s"(a.q_stride), "s"(a.k_cache), "s"(a.v_cache), "s"(a.cm.base), "s"(a.cm.pos_begin),
+                       "s"(a.cm.seq0), "s"(a.H), "s"(a.H_kv), "s"(a.max_seq), "s"(a.split_len), "s"(a.by_b.d), "s"(a.by_b.m), "s"(a.by_group.m), "s"(a.by_split.m));
+}
+// position of column c of the pass, counted from the start of the pass, and its sequence (ColMap's, without its division)
+__device__ __forceinline__ int attn_step_of(const AttnArgs& a, int c) { return a.by_b.of(a.cm.base + c); }
+__device__ __forceinline__ int attn_seq(const AttnArgs& a, int c) { return a.cm.seq0 + a.cm.base + c - attn_step_of(a, c) * a.by_b.d; }
+__device__ __forceinline__ int attn_pos(const AttnArgs& a, int c) { return a.cm.pos_begin + attn_step_of(a, c); }
+
 template <int HD, int NW, int G>
 struct AttnShared {
     float m[G][NW], l[G][NW];              // per wave: running max and sum of each head's scores
@@ -181,16 +191,17 @@ __device__ __forceinline__ void attn_split(const AttnArgs& a, int split, int h0,
     constexpr int ITMAX = 8;               // loads of K (and of V) in flight per lane
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int seq = a.cm.seq(c);
+    attn_take_args(a);
+    const int seq = attn_seq(a, c);
     const int row0 = a.row0 ? a.row0[seq] : 0;         // left-padded batch: this sequence's rows begin here; rows are counted from it
-    const int ctx = a.cm.pos(c) + 1 - row0;
+    const int ctx = attn_pos(a, c) + 1 - row0;
     const int j0 = split * a.split_len;
     const int jend = min(j0 + a.split_len, ctx);
     if (j0 >= jend) return;                // nothing of this column's context falls in this split
     const bool has_new = ROPE && jend == ctx;          // ROPE: the newest position comes from the projection buffer ...
     const int j1 = has_new ? ctx - 1 : jend;           // ... and the cache rows of this split end before it
-    const int n_live = (ctx + a.split_len - 1) / a.split_len;   // splits of this column that hold rows
-    const int kvh = h0 / (a.H / a.H_kv);
+    const int n_live = a.by_split.of(ctx + a.split_len - 1);   // splits of this column that hold rows
+    const int kvh = a.by_group.of(h0);
     const size_t head_off = (((size_t)seq * a.H_kv + kvh) * a.max_seq + row0) * HD;
     const T* Kb = static_cast<const T*>(a.k_cache) + head_off;
     const T* Vb = static_cast<const T*>(a.v_cache) + head_off;
@@ -499,15 +510,16 @@ __device__ __forceinline__ void attn_split_mfma(const AttnArgs& a, int split, in
     constexpr int PL = AttnStage<T>::PL;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, g = lane >> 4;
-    const int seq = a.cm.seq(c);
+    attn_take_args(a);
+    const int seq = attn_seq(a, c);
     const int row0 = a.row0 ? a.row0[seq] : 0;         // left-padded batch: rows are counted from the sequence's first row
-    const int ctx = a.cm.pos(c) + 1 - row0;
+    const int ctx = attn_pos(a, c) + 1 - row0;
     const int j0 = split * a.split_len;
     const int j1 = min(j0 + a.split_len, ctx);
     if (j0 >= j1) return;
     const bool has_new = ROPE && j1 == ctx;            // the newest row is patched into the staged tiles, not read from the cache
-    const int n_live = (ctx + a.split_len - 1) / a.split_len;
-    const int kvh = h0 / (a.H / a.H_kv);
+    const int n_live = a.by_split.of(ctx + a.split_len - 1);
+    const int kvh = a.by_group.of(h0);
     const size_t head_off = (((size_t)seq * a.H_kv + kvh) * a.max_seq + row0) * HD;
     const T* Kb = static_cast<const T*>(a.k_cache) + head_off;
     const T* Vb = static_cast<const T*>(a.v_cache) + head_off;
@@ -706,21 +718,22 @@ __device__ __forceinline__ void attn_qtile_mfma(const AttnArgs& a, int split, in
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, g = lane >> 4;
     const int c_last = min(c0 + 16 / GH, a.ncols) - 1;               // last column of the tile that exists
-    const int seq = a.cm.seq(c0);
+    attn_take_args(a);
+    const int seq = attn_seq(a, c0);
     const int row0 = a.row0 ? a.row0[seq] : 0;         // left-padded batch: rows are counted from the sequence's first row
-    const int ctx_max = a.cm.pos(c_last) + 1 - row0;
+    const int ctx_max = attn_pos(a, c_last) + 1 - row0;
     const int j0 = split * a.split_len;
     const int j1 = min(j0 + a.split_len, ctx_max);
     if (j0 >= j1) return;
-    const int n_live = (ctx_max + a.split_len - 1) / a.split_len;
-    const int kvh = h0 / (a.H / a.H_kv);
+    const int n_live = a.by_split.of(ctx_max + a.split_len - 1);
+    const int kvh = a.by_group.of(h0);
     const size_t head_off = (((size_t)seq * a.H_kv + kvh) * a.max_seq + row0) * HD;
     const T* Kb = static_cast<const T*>(a.k_cache) + head_off;
     const T* Vb = static_cast<const T*>(a.v_cache) + head_off;
     const float scale = 1.4426950408889634f / sqrtf((float)HD);
     const int ci = c0 + i / GH;                                      // this lane's entry: column, head, end of context
     const bool live = ci < a.ncols;
-    const int ctx_i = live ? a.cm.pos(ci) + 1 - row0 : 0;
+    const int ctx_i = live ? attn_pos(a, ci) + 1 - row0 : 0;
 
     attn_half8 qhi[4], qlo[4];
     {

@@ -106,7 +106,9 @@ int launch_t(const AttnArgs& a, int kv_dtype, bool use_mfma, hipStream_t s) {
 // With rope_cs set, q and the newest K/V row of each column are still unrotated in the projection buffer and
 // the kernel rotates and appends them itself; the columns of such a pass must belong to different sequences.
 // use_mfma = false keeps grouped-query and query-tile attention on the vector ALUs (for comparisons).
-int launch_attention(const AttnArgs& a, int kv_dtype, bool use_mfma, hipStream_t s) {
+int launch_attention(const AttnArgs& args, int kv_dtype, bool use_mfma, hipStream_t s) {
+    AttnArgs a = args;
+    a.by_b = Divisor(a.cm.B); a.by_group = Divisor(a.H / a.H_kv); a.by_split = Divisor(a.split_len);
     return a.rope_cs ? launch_t<true>(a, kv_dtype, use_mfma, s) : launch_t<false>(a, kv_dtype, use_mfma, s);
 }
 

@@ -23,6 +23,19 @@ typedef _Float16 f16_t;            // IEEE half (KV cache only)
 // bytes per KV-cache element for a d3_dtype value (0 f32, 2 f16)
 inline int kv_elem_bytes(int kv_dtype) { return kv_dtype == 0 ? 4 : 2; }
 
+// Division by a number that the host knows: a multiplication and a correction instead of the 25 dependent instructions of a division.  With
+// m = floor(2^32 / d) (one less for d = 1) the product's upper word is the quotient or one less, for every x in [0, 2^31).
+struct Divisor {
+    int d = 1;
+    uint32_t m = 0xffffffffu;
+    Divisor() = default;
+    explicit Divisor(int v) : d(v), m(v > 1 ? (uint32_t)((1ull << 32) / v) : 0xffffffffu) {}
+    __host__ __device__ __forceinline__ int of(int x) const {
+        const int q = (int)(((unsigned long long)(uint32_t)x * m) >> 32);
+        return x - q * d >= d ? q + 1 : q;
+    }
+};
+
 // Which (sequence, position, token) a column of the current pass stands for.
 // Column c has global index g = base + c; sequence g % B, row pos_begin + g / B.
 // Decode: base 0, P 1 (column b = sequence b).  Prompt pass: position-major
@@ -230,6 +243,8 @@ struct AttnArgs {
     float* out;            // [ncols][H*hd]
     bf16_t* out_hi;        // optional split copy
     bf16_t* out_lo;
+    // set by launch_attention: what the kernel divides by: columns per position, query heads per KV head, split length
+    Divisor by_b, by_group, by_split;
 };
 int launch_attention(const AttnArgs& a, int kv_dtype, bool use_mfma, hipStream_t s);
 

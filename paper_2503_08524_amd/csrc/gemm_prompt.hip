@@ -355,15 +355,6 @@ __device__ __forceinline__ void mma_hl(f32x4 (&acc)[RW][2 * CW], int tt, const u
     }
 }
 
-// Division by a number that the host knows: one multiplication instead of the 25 dependent instructions of a division.  m = ceil(2^32 / d);
-// exact while x * d < 2^32.
-struct Divisor {
-    int d = 1;
-    uint32_t m = 0;
-    Divisor() = default;
-    explicit Divisor(int v) : d(v), m(v > 1 ? (uint32_t)(((1ull << 32) + v - 1) / v) : 0) {}
-    __device__ __forceinline__ int of(int x) const { return d == 1 ? x : (int)__umulhi((uint32_t)x, m); }
-};
 // Launch order of the tiles.  Tiles [0, n_whole) have a workgroup each, the others ks of them, one per part of K.  n_rb row blocks: each
 // XCD owns n_rb / 8 of them and walks them in groups of kGroupR, the last group may hold fewer; n_rb % 8 are left over.
 constexpr int kGroupR = 4, kGroupC = 8;
