@@ -164,6 +164,24 @@ struct GemvArgs {
     int wave_units, wave_units_over;
 };
 
+// What the first loads of a matrix-core projection need of the arguments, requested together: read as they come up, each is a round trip to memory
+// that the next one waits behind.
+__device__ __forceinline__ void gemm_take_args(const GemvArgs& a) {
+    asm volatile("" :: "s"(a.x_hi), "s"(a.x_lo), "s"(a.x_stride), "s"(a.w[0]), "s"(a.w[1]), "s"(a.w[2]), "s"(a.rows[0]), "s"(a.rows[1]),
+                       "s"(a.K), "s"(a.total_rows), "s"(a.ncols), "s"(a.ssq_in), "s"(a.ssq_parts));
+}
+// The matrix that output row `row` of a row-stacked projection belongs to, and the row's number in it (a choice among three scalars: by index, the
+// argument is read a second time, from an address that depends on the first).
+__device__ __forceinline__ const bf16_t* gemm_row(const GemvArgs& a, int row) {
+    const void* w = a.w[0];
+    if (row >= a.rows[0]) {
+        row -= a.rows[0];
+        w = a.w[1];
+        if (row >= a.rows[1]) { row -= a.rows[1]; w = a.w[2]; }
+    }
+    return static_cast<const bf16_t*>(w) + (size_t)row * a.K;
+}
+
 // Launch-shape overrides for measurements, read from the environment ONCE by d3_create (0 / default = the library's
 // own choice).  D3_MFMA_RT, D3_MFMA_WAVES: row tiles per workgroup and waves of the narrow matrix-core projection;
 // D3_MFMA_WIDE=0: no panel kernel (passes are limited to kMaxCols columns); D3_WIDE_RT, D3_WIDE_KS: row tiles per wave
