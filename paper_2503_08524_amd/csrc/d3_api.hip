@@ -137,7 +137,7 @@ int env_int(const char* name, long lo, long hi, long dflt) {
 namespace d3 {
 Tuning tuning_from_env() {
     Tuning t;
-    t.gemv_wgs_per_cu = env_int("D3_GEMV_WGS_PER_CU", 1, 8, 3);
+    t.gemv_wgs_per_cu = env_int("D3_GEMV_WGS_PER_CU", 1, 8, 1);
     t.mfma_rt = env_int("D3_MFMA_RT", 1, 4, 0);
     t.mfma_waves = env_int("D3_MFMA_WAVES", 1, 8, 0);
     t.mfma_wide = env_int("D3_MFMA_WIDE", 0, 1, 1) != 0;
@@ -957,7 +957,7 @@ extern "C" int d3_truncate(d3_ctx* ctx, int32_t n_rows) {
 extern "C" int d3_stream_read(d3_ctx* ctx, const void* src, size_t bytes, void* hip_stream) {
     if (!ctx || !src) return fail(D3_EINVAL, "d3_stream_read: NULL argument");
     if (bytes % 16 != 0 || reinterpret_cast<uintptr_t>(src) % 16 != 0) return fail(D3_EINVAL, "d3_stream_read: the buffer must be 16-byte aligned and a multiple of 16 bytes");
-    // three workgroups of four waves per compute unit, like the projections; their checksums land in the attention partials
+    // three workgroups of four waves per compute unit; their checksums land in the attention partials
     const int n_wg = 3 * ctx->n_cu;
     D3_HIP(launch_stream_read(src, bytes, ctx->at<unsigned>(ctx->lay.part_o), n_wg, static_cast<hipStream_t>(hip_stream)));
     return D3_OK;

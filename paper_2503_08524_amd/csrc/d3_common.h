@@ -160,8 +160,9 @@ struct GemvArgs {
     // group (zero between launches)
     float* part;
     int* part_tickets;
-    // vector-ALU GEMV, set by its launcher: units per wave, and how many waves have one more
+    // vector-ALU GEMV, set by its launcher: units per wave, and how many waves have one more; 64-lane strides of a row
     int wave_units, wave_units_over;
+    Divisor by_strides;
 };
 
 // What the first loads of a matrix-core projection need of the arguments, requested together: read as they come up, each is a round trip to memory
@@ -191,9 +192,9 @@ __device__ __forceinline__ const bf16_t* gemm_row(const GemvArgs& a, int row) {
 // D3_PROMPT_ROW_BLOCKS: fewest blocks of 256 rows for which 65..128 columns take the LDS-tiled kernel;
 // D3_PROMPT_CUS: compute units a round of its tiles is taken to have;
 // D3_PROMPT_ATTN_WGS: fewest workgroups (128 (query, head) pairs each) for which a prompt pass, shared or not, takes the whole-context attention kernel; D3_GEMV_WGS_PER_CU: workgroups
-// per compute unit of the vector-ALU GEMV (default 3).
+// of eight waves per compute unit of the vector-ALU GEMV (default 1).
 struct Tuning {
-    int gemv_wgs_per_cu = 3;
+    int gemv_wgs_per_cu = 1;
     int mfma_rt = 0, mfma_waves = 0;
     bool mfma_wide = true;
     int wide_rt = 0, wide_ks = 0;

@@ -62,6 +62,10 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
     constexpr int NA = RT * SW;                        // A tiles per wave and turn
     constexpr int NB = 2 * CT;                         // panel tiles: hi, lo of every column tile
     constexpr int kPanel = NB * kTile;
+#ifndef WD
+#define WD 2
+#endif
+    constexpr int D = NA == 1 && CT == 2 ? WD : 2;
     constexpr int PBT = NB * 256 / (W * 64);           // 16-byte panel pieces per thread and turn (= 4)
     extern __shared__ __attribute__((aligned(16))) char lds[];   // [2][kPanel] panels, then [W][kTile] staging tiles
     char (*panel)[kPanel] = reinterpret_cast<char (*)[kPanel]>(lds);
@@ -109,7 +113,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
         for (int tt = 0; tt < CT; ++tt) acc[r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     u32x4 pb[PBT];
-    TileRegs ga[2][NA];                                // weight tiles of two turns in flight
+    TileRegs ga[D][NA];                                // weight tiles of D turns in flight
     auto panel_issue = [&](int t) {
         int k = t * (U * 32) + pseg * 8;
         k = k <= K - 8 ? k : K - 8;
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
     // over each register set as soon as it is in LDS); P_STORE: turn t + 1 exists (its panel, in pb, goes to the other
     // buffer); P_ISSUE: turn t + 2 exists (its panel is requested).  The flags are compile-time so that every load of
     // the steady state is unconditional and the wait counts exact.
-    auto turn = [&](int t, auto slot_c, auto a_issue, auto p_store, auto p_issue) {
+    auto turn = [&](int t, auto slot_c, bool a_issue, bool p_store, bool p_issue) {
         constexpr int SLOT = decltype(slot_c)::value;
         const int buf = (t - t_begin) & 1;
         const char* pan = panel[buf];
@@ -143,7 +147,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
 #pragma unroll
             for (int r = 0; r < NA; ++r) {
                 tile_to_frags(ga[SLOT][r], atile, af[r]);
-                if (decltype(a_issue)::value) tile_load(ga[SLOT][r], wrow[r], K, (t + 2) * (U * 32), K);
+                if (a_issue) tile_load(ga[SLOT][r], wrow[r], K, (t + D) * (U * 32), K);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -163,7 +167,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
             for (int r = 0; r < NA; ++r) {
                 u32x4 af[U];
                 tile_to_frags(ga[SLOT][r], atile, af);
-                if (decltype(a_issue)::value) tile_load(ga[SLOT][r], wrow[r], K, (t + 2) * (U * 32), K);
+                if (a_issue) tile_load(ga[SLOT][r], wrow[r], K, (t + D) * (U * 32), K);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     if (t * U + u < nks) {
@@ -177,14 +181,10 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
                 }
             }
         }
-        if (decltype(p_store)::value) panel_store(buf ^ 1);
-        if (decltype(p_issue)::value) panel_issue(t + 2);
+        if (p_store) panel_store(buf ^ 1);
+        if (p_issue) panel_issue(t + 2);
         __syncthreads();                               // panel t + 1 is complete; nobody still reads panel t
     };
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    using S0 = std::integral_constant<int, 0>;
-    using S1 = std::integral_constant<int, 1>;
 
     // 1/rms of the columns from their partial sums of squares: 16 threads take a column, up to 128 partials at once, in a fixed order.  All of a
     // round's loads go out without a branch between them (lm_head at 32 columns, 64 partials: 55.8 -> 51.8 us).
@@ -210,23 +210,19 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
         int t = t_begin;
         panel_issue(t);
 #pragma unroll
-        for (int r = 0; r < NA; ++r) tile_load(ga[0][r], wrow[r], K, t * (U * 32), K);
-        if (n_turns > 1) {
+        for (int d = 0; d < D; ++d)
 #pragma unroll
-            for (int r = 0; r < NA; ++r) tile_load(ga[1][r], wrow[r], K, (t + 1) * (U * 32), K);
-        }
+            for (int r = 0; r < NA; ++r) tile_load(ga[d][r], wrow[r], K, min(t + d, t_end - 1) * (U * 32), K);
         panel_store(0);
         if (n_turns > 1) panel_issue(t + 1);
         column_scales();
         __syncthreads();
-        for (; t + 3 < t_end; t += 2) {                // steady state: every load is unconditional
-            turn(t, S0{}, T_{}, T_{}, T_{});
-            turn(t + 1, S1{}, T_{}, T_{}, T_{});
-        }
-        const int left = t_end - t;
-        if (left == 3) { turn(t, S0{}, T_{}, T_{}, T_{}); turn(t + 1, S1{}, F_{}, T_{}, F_{}); turn(t + 2, S0{}, F_{}, F_{}, F_{}); }
-        else if (left == 2) { turn(t, S0{}, F_{}, T_{}, F_{}); turn(t + 1, S1{}, F_{}, F_{}, F_{}); }
-        else { turn(t, S0{}, F_{}, F_{}, F_{}); }
+        auto turns_from = [&]<int... J>(std::integer_sequence<int, J...>, auto run) { (run(std::integral_constant<int, J>{}), ...); };
+        constexpr std::make_integer_sequence<int, D> slots{};
+        for (; t + 2 * D <= t_end; t += D)             // steady state: every load is unconditional
+            turns_from(slots, [&](auto j) { turn(t + j, j, true, true, true); });
+        for (; t < t_end; t += D)
+            turns_from(slots, [&](auto j) { if (t + j < t_end) turn(t + j, j, t + j + D < t_end, t + j + 1 < t_end, t + j + 2 < t_end); });
     } else {
         column_scales();
         __syncthreads();

@@ -10,11 +10,11 @@
 namespace d3 {
 
 #ifndef D3_GEMV_WAVES
-#define D3_GEMV_WAVES 4
+#define D3_GEMV_WAVES 8
 #endif
 constexpr int kGemvWaves = D3_GEMV_WAVES;   // waves per workgroup (they share the staged activations)
 constexpr int kGemvThreads = kGemvWaves * kWave;
-constexpr int kGemvStageR = 12;             // float4 activation loads a thread issues ahead of the weights (K <= 12288 in one round)
+constexpr int kGemvStageR = 6;              // float4 activation loads a thread issues ahead of the weights (K <= 12288 in one round)
 constexpr int kGemvLdsBudget = 60 * 1024;   // dynamic LDS per workgroup for the activations
 #ifndef D3_GEMV_DEPTH
 #define D3_GEMV_DEPTH 4
@@ -55,7 +55,7 @@ __host__ __device__ inline int gemv_n_units(const GemvArgs& a, int mode) {
 // wave are on their way before the activations arrive: 7B shape, batch 1, a step of 17 blocks 1481 -> 1416 us.
 __device__ __forceinline__ void gemv_take_args(const GemvArgs& a) {
     asm volatile("" :: "s"(a.x), "s"(a.gain), "s"(a.w[0]), "s"(a.w[1]), "s"(a.w[2]), "s"(a.K), "s"(a.x_stride), "s"(a.rows[0]),
-                       "s"(a.rows[1]), "s"(a.total_rows), "s"(a.ncols), "s"(a.out), "s"(a.wave_units), "s"(a.wave_units_over));
+                       "s"(a.rows[1]), "s"(a.total_rows), "s"(a.ncols), "s"(a.out), "s"(a.wave_units), "s"(a.wave_units_over), "s"(a.by_strides.d), "s"(a.by_strides.m));
 }
 
 template <typename W, int MODE>
@@ -87,11 +87,16 @@ __device__ __forceinline__ void gemv_unit_rows(const GemvArgs& a, int u, const W
     }
 }
 
-// The load side of a wave's pipeline.
+// The load side of a wave's pipeline.  A wave begins its rows at stride `first` and goes round: rows are a power of two of bytes apart or close to
+// it, and waves that all read the same stretch of their rows meet on a part of the memory channels.  first = the wave's number + the
+// workgroup's / 8 (each XCD, which gets every eighth workgroup, then has all stretches in flight), modulo the strides of a row.  7B shape,
+// batch 1, a step of 17 blocks: 1392 us from stride 0; by the workgroup's number 1370, by wave alone 1377, by workgroup / 8 alone 1393, by both
+// 1348 (/ 4 + wave 1348, / 16 + wave 1430).
 template <typename W, int D>
 struct GemvPipe {
     u32x4 b0[D], b1[D];   // ring of loaded chunks: slot j holds step (issued - D + j) mod D ...
     const W *r0, *r1;     // rows of the unit being loaded
+    int first;            // stride a row begins at
     int lu, lit;          // unit and stride of the next step to load
     int issued, total;    // steps loaded so far / steps this wave owns in this phase
 };
@@ -105,8 +110,8 @@ __device__ __forceinline__ void gemv_issue(const GemvArgs& a, GemvPipe<W, D>& p,
     p.b0[slot] = load_stream16(p.r0 + (size_t)q * EPC);
     p.b1[slot] = load_stream16(p.r1 + (size_t)q * EPC);
     p.issued += 1;
-    if (++p.lit == S) {
-        p.lit = 0;
+    if (++p.lit == S) p.lit = 0;
+    if (p.lit == p.first) {
         p.lu += nw;
         int row;
         gemv_unit_rows<W, MODE>(a, p.lu < n_units ? p.lu : n_units - 1, p.r0, p.r1, row);
@@ -116,14 +121,16 @@ __device__ __forceinline__ void gemv_issue(const GemvArgs& a, GemvPipe<W, D>& p,
 // Start a phase: fill the ring with the wave's first D steps.  All D loads are issued whatever the
 // wave's share is (a wave with fewer steps re-reads valid rows), which keeps the wait counts exact.
 template <typename W, int MODE, int D>
-__device__ __forceinline__ void gemv_preload(const GemvArgs& a, int gw, int nw, GemvPipe<W, D>& p) {
+__device__ __forceinline__ void gemv_preload(const GemvArgs& a, int wave, int gw, int nw, GemvPipe<W, D>& p) {
     const int n_units = gemv_n_units(a, MODE);
     const int nchunks = a.K / GemvChunk<W>::N;
-    const int S = (nchunks + 63) / 64;
+    const int S = a.by_strides.d;
     p.total = (a.wave_units + (gw < a.wave_units_over ? 1 : 0)) * S;
     p.issued = 0;
     p.lu = gw;
-    p.lit = 0;
+    const int turn = (int)(blockIdx.x >> 3) + wave;
+    p.first = turn - a.by_strides.of(turn) * S;
+    p.lit = p.first;
     int row;
     gemv_unit_rows<W, MODE>(a, gw < n_units ? gw : n_units - 1, p.r0, p.r1, row);
 #pragma unroll
@@ -315,10 +322,10 @@ __device__ __forceinline__ void gemv_run(const GemvArgs& a, const float4* xs, in
     const int lane = threadIdx.x & 63;
     const int f4_per_col = gemv_f4_per_col<W>(a.K);
     const int nchunks = a.K / GemvChunk<W>::N;
-    const int S = (nchunks + 63) / 64;
+    const int S = a.by_strides.d;
     const int n_units = gemv_n_units(a, MODE);
     const int total = p.total;
-    int cu = gw, cit = 0, n_ep = 0;
+    int cu = gw, cit = p.first, n_ep = 0;
     // residual mode: lane e fetches the old values of the rows of this wave's e-th unit now, long before they are needed
     float res0[NC], res1[NC];
     if (MODE == MODE_RESID) {
@@ -339,7 +346,8 @@ __device__ __forceinline__ void gemv_run(const GemvArgs& a, const float4* xs, in
 
     auto consume = [&](int slot) {
         gemv_fma_step<W, NC>(p.b0[slot], p.b1[slot], xs, f4_per_col, cit, acc0, acc1);
-        if (++cit == S) {                               // unit finished: park its sums
+        if (++cit == S) cit = 0;
+        if (cit == p.first) {                           // unit finished: park its sums
             int row;
             const W *r0, *r1;
             gemv_unit_rows<W, MODE>(a, cu, r0, r1, row);
@@ -351,7 +359,6 @@ __device__ __forceinline__ void gemv_run(const GemvArgs& a, const float4* xs, in
             }
             if (lane == 0) ep.row[n_ep] = row;
             n_ep += 1;
-            cit = 0;
             cu += nw;
         }
     };

@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_alu_kernel(GemvArgs a) {
     extern __shared__ float4 xs[];                     // [NC][f4_per_col]
     __shared__ float red[NC][kGemvWaves];
     __shared__ GemvEpBuf<NC> ep[kGemvWaves];
-    constexpr int R = kGemvStageR / NC;
+    constexpr int R = (kGemvStageR + NC - 1) / NC;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // the units' addresses are the wave's: scalar
     // Units go round-robin over the waves of the whole grid, so that at any moment the chip streams one contiguous
     // band of the matrix (spread over every memory channel); numbering the waves workgroup-fastest hands the units
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_alu_kernel(GemvArgs a) {
     GemvStageRegs<NC, R> regs;
     GemvPipe<W, kGemvDepth> pipe;
     gemv_stage_issue<NC, NORM, kGemvThreads, R>(a, tid, regs);          // activations first ...
-    gemv_preload<W, MODE, kGemvDepth>(a, gw, nw, pipe);                          // ... the weight stream right behind them
+    gemv_preload<W, MODE, kGemvDepth>(a, wave, gw, nw, pipe);           // ... the weight stream right behind them
     gemv_stage_commit<W, NC, NORM, kGemvThreads, R>(a, tid, xs, regs, red);
     __syncthreads();
     float rinv[NC];
@@ -48,13 +48,18 @@ int launch_nc(GemvArgs a, int mode, bool norm, int n_wg, hipStream_t s) {
     const size_t lds = (size_t)NC * gemv_f4_per_col<W>(a.K) * sizeof(float4);
     const int n_units = gemv_n_units(a, mode);
     // n_wg workgroups, a multiple of the CU count (a compute unit is the unit of bandwidth: the same number of
-    // workgroups on each makes them finish together); fewer when there are not four units for each
+    // workgroups on each makes them finish together); fewer when there is not a unit for each wave, up to half as many again where a wave would have
+    // to park more than kGemvEpCap (= 64 lanes) units.  One workgroup of eight waves per compute unit against three of four: the activations are
+    // staged once instead of three times, and 2048 waves divide the usual numbers of units evenly (7B shape: 2048 units of O and down, 6144 of QKV):
+    // a step of 17 blocks at batch 1 1385 -> 1348 us (12 waves 1372; five or six steps in flight instead of four 1369, 1374).
+    const int most = n_wg + n_wg / 2, per_wg = kGemvWaves * kGemvEpCap;
+    if ((long long)most * per_wg < n_units) return (int)hipErrorInvalidValue;
     int grid = (n_units + kGemvWaves - 1) / kGemvWaves;
-    if (grid > n_wg) grid = n_wg;
-    if ((long long)grid * kGemvWaves * kGemvEpCap < n_units) return (int)hipErrorInvalidValue;   // a wave parks at most kGemvEpCap (= 64 lanes) units
+    if (grid > n_wg) grid = (n_units + per_wg - 1) / per_wg > n_wg ? (n_units + per_wg - 1) / per_wg : n_wg;
     const int n_waves = grid * kGemvWaves;
     a.wave_units = n_units / n_waves;
     a.wave_units_over = n_units % n_waves;
+    a.by_strides = Divisor((a.K / GemvChunk<W>::N + 63) / 64);
 #define D3_LAUNCH(MODE, NORM) hipLaunchKernelGGL((gemv_alu_kernel<W, NC, MODE, NORM>), dim3(grid), dim3(kGemvThreads), lds, s, a)
     if (mode == MODE_STORE) { if (norm) D3_LAUNCH(MODE_STORE, true); else D3_LAUNCH(MODE_STORE, false); }
     else if (mode == MODE_RESID) { D3_LAUNCH(MODE_RESID, false); }
