@@ -183,6 +183,12 @@ __device__ __forceinline__ const bf16_t* gemm_row(const GemvArgs& a, int row) {
     return static_cast<const bf16_t*>(w) + (size_t)row * a.K;
 }
 
+// Whether the workgroups of a batched projection begin their rows at different places.  Rows a multiple of 8 KB apart start on the same few memory
+// channels, and workgroups that walk them in step meet there; measured, from the first k / from different ones, narrow kernel: rows of 16 KB (70B
+// shape, 8 columns, kernel trace) gate/up 153.9 / 141.6 us (6.6 TB/s), QKV 32.2 / 30.9, lm_head 89.5 / 79.3; of 56 KB (down) 77 / 76.  Not where
+// rows are 8 KB or no multiple of it: 7B and 13B shapes, 2 blocks and the head, 2 columns 231 / 233 and 310 / 312, 12 columns 261 / 265 and 350 / 351.
+inline bool gemm_rounds(int K) { return K % 4096 == 0 && K >= 8192; }
+
 // Launch-shape overrides for measurements, read from the environment ONCE by d3_create (0 / default = the library's
 // own choice).  D3_MFMA_RT, D3_MFMA_WAVES: row tiles per workgroup and waves of the narrow matrix-core projection;
 // D3_MFMA_WIDE=0: no panel kernel (passes are limited to kMaxCols columns); D3_WIDE_RT, D3_WIDE_KS: row tiles per wave

@@ -80,8 +80,10 @@ __device__ __forceinline__ void tile_to_frags(const TileRegs& r, char* tile, u32
     __builtin_amdgcn_wave_barrier();
 }
 
-template <int NT, int MODE, int RT, bool PACK>
-__global__ __launch_bounds__(512) void gemm_mfma_kernel(GemvArgs a) {   // <= 8 waves
+// ROUND: a wave's turns begin at turn (workgroup / 8) modulo their number and go round (gemm_rounds says where).  The eight workgroups of one start go
+// to the eight XCDs.  Up to eight columns four waves per SIMD have to fit where they did before: 128 registers for a tile pair.
+template <int NT, int MODE, int RT, bool PACK, bool ROUND>
+__global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2 : 1) <= 2 ? 4 : 1) void gemm_mfma_kernel(GemvArgs a) {   // <= 8 waves
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;  // weight matrices per output tile
     constexpr int NA = RT * SW;                        // A tiles per wave
     constexpr int NB = PACK ? 1 : 2 * NT;              // B tiles per wave and turn (hi and lo of each column tile, or one packed tile)
@@ -187,11 +189,23 @@ __global__ __launch_bounds__(512) void gemm_mfma_kernel(GemvArgs a) {   // <= 8 
 
     int ks0 = wave * U;
     if (ks0 < nks) {
-        issue(ks0);
-        column_scales();
-        while (ks0 + stride < nks) {                   // steady state: every register set is re-issued unconditionally
-            turn(ks0, true, ks0 + stride);
-            ks0 += stride;
+        if constexpr (ROUND) {
+            int left = (nks - ks0 - 1) / stride;       // turns after the first
+            ks0 += (int)((unsigned)(blockIdx.x >> 3) % (unsigned)(left + 1)) * stride;
+            issue(ks0);
+            column_scales();
+            for (; left > 0; --left) {
+                const int ks1 = ks0 + stride < nks ? ks0 + stride : wave * U;
+                turn(ks0, true, ks1);
+                ks0 = ks1;
+            }
+        } else {
+            issue(ks0);
+            column_scales();
+            while (ks0 + stride < nks) {               // steady state: every register set is re-issued unconditionally
+                turn(ks0, true, ks0 + stride);
+                ks0 += stride;
+            }
         }
         turn(ks0, false, 0);
     } else {
@@ -254,7 +268,9 @@ __global__ __launch_bounds__(512) void gemm_mfma_kernel(GemvArgs a) {   // <= 8 
 
 template <int NT, int MODE, bool PACK>
 int launch_rt(const GemvArgs& a, int rt, int tiles, int waves, size_t lds, hipStream_t s) {
-#define D3_LAUNCH(RT) hipLaunchKernelGGL((gemm_mfma_kernel<NT, MODE, RT, PACK>), dim3(tiles / RT), dim3(64 * waves), lds, s, a)
+    const bool round = NT == 1 && gemm_rounds(a.K);
+#define D3_LAUNCH(RT) do { if (round) hipLaunchKernelGGL((gemm_mfma_kernel<NT, MODE, RT, PACK, NT == 1>), dim3(tiles / RT), dim3(64 * waves), lds, s, a); \
+                           else hipLaunchKernelGGL((gemm_mfma_kernel<NT, MODE, RT, PACK, false>), dim3(tiles / RT), dim3(64 * waves), lds, s, a); } while (0)
     if (rt == 4) { if (MODE == MODE_SWIGLU) return (int)hipErrorInvalidValue; D3_LAUNCH((MODE == MODE_SWIGLU ? 2 : 4)); }
     else if (rt == 2) D3_LAUNCH(2);
     else D3_LAUNCH(1);

@@ -56,16 +56,13 @@ __device__ __forceinline__ void tile_to_frags(const TileRegs& r, char* tile, u32
 // A gate/up pair of tiles per wave wants 204 registers (two waves per SIMD); its launch has 2.7 workgroups per CU, so at that
 // size the last quarter of them starts only when the first ones have finished (entry times up to 24 us into a 42 us
 // launch).  Held to three waves per SIMD (168 registers, 33 spilled) every workgroup starts at once: 42 -> 38 us.
-template <int MODE, int RT, int CT, int W>
+template <int MODE, int RT, int CT, int W, bool ROUND>
 __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) void gemm_wide_kernel(GemvArgs a) {
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
     constexpr int NA = RT * SW;                        // A tiles per wave and turn
     constexpr int NB = 2 * CT;                         // panel tiles: hi, lo of every column tile
     constexpr int kPanel = NB * kTile;
-#ifndef WD
-#define WD 2
-#endif
-    constexpr int D = NA == 1 && CT == 2 ? WD : 2;
+    constexpr int D = 2;                               // turns whose weights are in flight (3 and 4: 7B shape, batch 32, a step of 4 blocks 1126 -> 1136, 1143 us)
     constexpr int PBT = NB * 256 / (W * 64);           // 16-byte panel pieces per thread and turn (= 4)
     extern __shared__ __attribute__((aligned(16))) char lds[];   // [2][kPanel] panels, then [W][kTile] staging tiles
     char (*panel)[kPanel] = reinterpret_cast<char (*)[kPanel]>(lds);
@@ -79,6 +76,9 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
     const int KS = gridDim.y;
     const int t_begin = (int)((long long)turns * blockIdx.y / KS), t_end = (int)((long long)turns * (blockIdx.y + 1) / KS);
     const int n_turns = t_end - t_begin;
+    // turn t of the slice's order is turn kt(t) of K: with ROUND, workgroup / 8 modulo the turns further on, and round
+    const int first = ROUND && n_turns > 0 ? (int)((unsigned)(blockIdx.x >> 3) % (unsigned)n_turns) : 0;
+    auto kt = [&](int t) { return !ROUND ? t : t + first < t_end ? t + first : t + first - n_turns; };
     const int tiles = a.total_rows / 16;
     const int tile0 = (blockIdx.x * W + wave) * RT;
     char* atile = stage[wave];
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
     u32x4 pb[PBT];
     TileRegs ga[D][NA];                                // weight tiles of D turns in flight
     auto panel_issue = [&](int t) {
-        int k = t * (U * 32) + pseg * 8;
+        int k = kt(t) * (U * 32) + pseg * 8;
         k = k <= K - 8 ? k : K - 8;
 #pragma unroll
         for (int i = 0; i < PBT; ++i) {
@@ -147,11 +147,11 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
 #pragma unroll
             for (int r = 0; r < NA; ++r) {
                 tile_to_frags(ga[SLOT][r], atile, af[r]);
-                if (a_issue) tile_load(ga[SLOT][r], wrow[r], K, (t + D) * (U * 32), K);
+                if (a_issue) tile_load(ga[SLOT][r], wrow[r], K, kt(t + D) * (U * 32), K);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (t * U + u < nks) {
+                if (kt(t) * U + u < nks) {
 #pragma unroll
                     for (int tt = 0; tt < CT; ++tt) {
                         const bf16x8 bh = b_frag(2 * tt, u), bl = b_frag(2 * tt + 1, u);
@@ -167,10 +167,10 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
             for (int r = 0; r < NA; ++r) {
                 u32x4 af[U];
                 tile_to_frags(ga[SLOT][r], atile, af);
-                if (a_issue) tile_load(ga[SLOT][r], wrow[r], K, (t + D) * (U * 32), K);
+                if (a_issue) tile_load(ga[SLOT][r], wrow[r], K, kt(t + D) * (U * 32), K);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (t * U + u < nks) {
+                    if (kt(t) * U + u < nks) {
                         const bf16x8 wa = __builtin_bit_cast(bf16x8, af[u]);
 #pragma unroll
                         for (int tt = 0; tt < CT; ++tt) {
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
 #pragma unroll
         for (int d = 0; d < D; ++d)
 #pragma unroll
-            for (int r = 0; r < NA; ++r) tile_load(ga[d][r], wrow[r], K, min(t + d, t_end - 1) * (U * 32), K);
+            for (int r = 0; r < NA; ++r) tile_load(ga[d][r], wrow[r], K, kt(min(t + d, t_end - 1)) * (U * 32), K);
         panel_store(0);
         if (n_turns > 1) panel_issue(t + 1);
         column_scales();
@@ -342,16 +342,26 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
     }
 }
 
-template <int MODE, int RT, int CT, int W>
-int launch_one(const GemvArgs& a, int groups, int ks, hipStream_t s) {
+template <int MODE, int RT, int CT, int W, bool ROUND>
+int launch_kernel(const GemvArgs& a, int groups, int ks, hipStream_t s) {
     constexpr size_t lds = (size_t)(2 * 2 * CT + W) * kTile;
-    auto* k = gemm_wide_kernel<MODE, RT, CT, W>;
+    auto* k = gemm_wide_kernel<MODE, RT, CT, W, ROUND>;
     if (lds > 48 * 1024) {
         static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (once != hipSuccess) return (int)once;
     }
     hipLaunchKernelGGL(k, dim3(groups, ks), dim3(W * 64), lds, s, a);
     return (int)hipGetLastError();
+}
+
+// Slices that begin at different turns (see gemm_rounds): here also rows of 8 KB, where a slice is long enough for the starts to spread (lm_head of the
+// 7B shape at 32 columns, 32 turns, 52.8 -> 47.7 us; QKV and gate/up, 8 turns a slice, do not gain, and at 128 columns O and down lose).
+template <int MODE, int RT, int CT, int W>
+int launch_one(const GemvArgs& a, int groups, int ks, hipStream_t s) {
+    if constexpr (CT <= 4) {
+        if (a.K % 4096 == 0 && a.K / 128 >= 10 * ks) return launch_kernel<MODE, RT, CT, W, true>(a, groups, ks, s);
+    }
+    return launch_kernel<MODE, RT, CT, W, false>(a, groups, ks, s);
 }
 
 template <int MODE>
