@@ -306,6 +306,35 @@ def test_prompt_tiles_whole_and_in_parts_in_one_launch(monkeypatch, cus, F, P):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("F,P,parts", [(512, 130, 18), (2560, 70, 72)])
+def test_prompt_kernel_adds_up_many_partial_sums_of_squares(F, P, parts):
+    # a column's sum of squares in more partials than one read of 16 threads takes: 18 row blocks of the LDS-tiled kernel's own O and down
+    # projections, and the panel kernel's 72 row groups read by the LDS-tiled gate/up (20 row blocks, 70 columns)
+    s = ModelShape("many-parts", L=2, d=4608, H=2, H_kv=1, hd=128, F=F, V=512, dtype="bf16")
+    assert parts == (4608 // 256 if P > 128 else 4608 // 64)
+    gpu, gens = _run(s, 1, P, 2, 1.0, 1, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
+@pytest.mark.parametrize("d,F,B,P", [(8192, 256, 3, 2), (8192, 256, 12, 1), (12288, 256, 20, 1), (256, 12288, 2, 20), (256, 12288, 1, 40)])
+def test_rows_a_multiple_of_8_kb_apart(d, F, B, P):
+    # batched projections whose workgroups begin their rows at different places: QKV, gate/up and lm_head over K = 8192 with 3 (packed) and 12
+    # columns and over K = 12288 with 20 (panel kernel, 8 slices of 12 turns), the down projection over K = 12288 with 2, 20 shared and 40 columns.
+    # Only fp32 sums and the 16 bits of an activation's two bf16 halves are left with an fp32 cache.
+    s = ModelShape("far-rows", L=1, d=d, H=2, H_kv=1, hd=128, F=F, V=512, dtype="bf16")
+    gpu, gens = _run(s, B, P, 2, 1.0, 0, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
+@pytest.mark.parametrize("d,F,V,B", [(64, 64, 270016, 1), (64, 4160, 512, 2), (1408, 64, 512, 3)])
+def test_vector_alu_gemv_strides_and_units(d, F, V, B):
+    # rows of one 64-lane stride, of 16 and a quarter and of five and a half, begun at every stride of a row; one more than a wave's fill of units per wave,
+    # which takes more workgroups than the launch would have (135008 pairs of rows against 2048 waves of 64)
+    s = ModelShape("gemv", L=2, d=d, H=1, H_kv=1, hd=64, F=F, V=V, dtype="f32")
+    gpu, gens = _run(s, B, 3, 3, 1.0, 1, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 3, logit_atol=1e-4, hidden_tol=1e-5)
+
+
 @pytest.mark.parametrize("B", [1, 2])
 @pytest.mark.parametrize("H,H_kv,kv,P", [(2, 2, "f16", 130), (2, 2, "f16", 257), (3, 3, "f32", 65), (4, 2, "f16", 193), (4, 2, "f32", 129),
                                          (8, 2, "f16", 161), (8, 1, "f16", 150), (8, 1, "f32", 97), (8, 8, "f16", 64)])
