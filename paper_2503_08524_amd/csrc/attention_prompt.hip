@@ -85,6 +85,9 @@ __global__ __launch_bounds__(512, 2) void attn_prompt_kernel(AttnArgs a, SeqRuns
     const int tid = threadIdx.x & 255, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3, grp = wave8 >> 2;
     const int e = lane & 31, h = lane >> 5;
 
+    // what the first loads need of the arguments, requested together: read as they come up, each is a round trip that the next one waits behind
+    asm volatile("" :: "s"(a.q), "s"(a.row0), "s"(a.q_stride), "s"(a.k_cache), "s"(a.v_cache), "s"(a.H_kv), "s"(a.max_seq), "s"(runs.n), "s"(runs.col[0]), "s"(runs.col[1]),
+                       "s"(runs.seq[0]), "s"(runs.pos[0]), "s"(n_tiles));
     // ---- launch order -> (KV head, tile of queries): a run's tiles with the longest contexts first, all heads' of them, the last run's
     // ahead of the first's (whatever their contexts); a head's tiles stay on one XCD when the heads divide over them (its L2 then serves the rows to all of them) ----
     int kvh, tile;
