@@ -306,6 +306,17 @@ def test_prompt_tiles_whole_and_in_parts_in_one_launch(monkeypatch, cus, F, P):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("cus,d,F,P", [(4, 2048, 384, 300), (7, 2048, 512, 400), (5, 4096, 640, 300), (4, 2080, 384, 300)])
+def test_storing_projections_whole_and_in_parts_in_one_launch(monkeypatch, cus, d, F, P):
+    # QKV (two row blocks) and gate/up (3 to 5) x 3 or 4 column blocks in rounds of 4, 5 or 7 tiles: whole tiles, which store everything, and in the
+    # same launch tiles in parts, which store a share each: QKV 1 or 2 tiles in 2, 4 and 5 parts, gate/up in 3 and 4 (and whole tiles alone); 32 stages,
+    # 64, and 32.5 with the half stage in the last part
+    monkeypatch.setenv("D3_PROMPT_CUS", str(cus))
+    s = ModelShape("mixed-store", L=2, d=d, H=2, H_kv=1, hd=128, F=F, V=512, dtype="bf16")
+    gpu, gens = _run(s, 1, P, 2, 1.0, 1, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
 @pytest.mark.parametrize("F,P,parts", [(512, 130, 18), (2560, 70, 72)])
 def test_prompt_kernel_adds_up_many_partial_sums_of_squares(F, P, parts):
     # a column's sum of squares in more partials than one read of 16 threads takes: 18 row blocks of the LDS-tiled kernel's own O and down
