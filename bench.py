@@ -121,7 +121,7 @@ def run_decode(dec, torch, first_tok, P, G, alpha, start, requests, fill="copy",
 def yardsticks(dec, torch, dev):
     """A plain 1 GiB device-to-device copy (read + written bytes per second; it also scales the FETCH_SIZE / WRITE_SIZE
     counters when this command runs under rocprofv3 --pmc) and a read-only stream over 2 GiB with the projections' own
-    load instructions and launch shape: what the memory system gives a kernel that only reads."""
+    load instructions: what the memory system gives a kernel that only reads."""
     cal_src = torch.empty(1 << 30, dtype=torch.uint8, device=dev)
     cal_dst = torch.empty(1 << 30, dtype=torch.uint8, device=dev)
     cal_dst.copy_(cal_src)
@@ -412,7 +412,7 @@ def main() -> int:
         "by_alpha": m["by_alpha"],
         "stream_copy": {"GBps": copy_gbps, "what": "1 GiB device-to-device copy, read + written bytes per second (5 repeats)"},
         "stream_read": {"GBps": m["stream_read_GBps"],
-                        "what": "read-only stream with the projections' load instructions and launch shape (d3_stream_read), "
+                        "what": "read-only stream with the projections' load instructions (d3_stream_read), "
                                 "bytes read per second by buffer size"},
         "roofline": roofline,
         "kernels": m["kernels"],

@@ -235,8 +235,8 @@ int d3_profile_select(d3_ctx *ctx, int32_t kernel_class);
 int d3_profile_read(d3_ctx *ctx, double *total_ms, int64_t *launches);
 
 /* Measurement aid: one launch that reads `bytes` of device memory (16-byte aligned, a multiple of 16) exactly once
- * and writes nothing but a checksum, with the same load instructions and launch shape as the weight-streaming
- * projections (Section 4.2 measures wall-clock time; this is the read-only yardstick the achieved HBM rates are held
+ * and writes nothing but a checksum, with the load instructions of the weight-streaming projections, three workgroups
+ * of four waves per compute unit (Section 4.2 measures wall-clock time; this is the read-only yardstick the achieved HBM rates are held
  * against).  Asynchronous on the given stream; the checksum lands in the context's workspace. */
 int d3_stream_read(d3_ctx *ctx, const void *src, size_t bytes, void *hip_stream);
 

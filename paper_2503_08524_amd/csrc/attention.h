@@ -169,7 +169,7 @@ __device__ __forceinline__ void attn_merge_publish(const AttnArgs& a, int split,
 // kernel is not instantiated for, handled one query head at a time).  Every cache row of the split is
 // loaded ONCE into registers, 16 bytes per lane, and used for all G heads; K and V loads go out
 // together, in chunks of up to ITMAX * RPB rows.  Each wave keeps an online softmax per head (running
-// max, sum, unnormalised output; reductions by wave shuffles), the waves are merged through LDS, and the
+// max, sum, unnormalised output; reductions by lane swaps and row rotations), the waves are merged through LDS, and the
 // split that arrives last (arrival counter per (column, KV head)) merges all splits.
 //
 // FUSED: the call runs inside a kernel that also produced q and the newest K/V row in this launch:
@@ -388,7 +388,7 @@ __device__ __forceinline__ void attn_split(const AttnArgs& a, int split, int h0,
 //   scores^T [row][head] = K [row][hd] . q^T [hd][head]: A = a 16-row K tile (coalesced load, re-shaped through
 //     LDS into fragments), B = q (scaled, split hi + lo in fp16): the result leaves lane (i, g) with head i,
 //     rows 4g..4g+3 of the tile; two tiles give each lane 8 of the 32 rows of its head;
-//   online softmax per head in that layout (max / sum across the 4 lanes of a head by shuffles);
+//   online softmax per head in that layout (max / sum across the 4 lanes of a head by lane swaps);
 //   out [head][col] += P [head][row] . V [row][col]: A = P (hi + lo in fp16), whose 8 rows per lane are exactly an A
 //     fragment under the row numbering k = 8g + j <-> row 4g + j (j < 4), 16 + 4g + j - 4 (j >= 4);
 //     B = V read from its LDS tile in the same numbering (eight 2-byte reads per fragment: V's contraction

@@ -4,7 +4,7 @@
 // split that finishes last merges them (an arrival counter per (column, head)).  K and V rows
 // are streamed straight from HBM,
 // 16 bytes per lane, several rows per wave per load, once for all query heads of a KV head;
-// every wave keeps an online softmax per head in registers; reductions are wave shuffles plus
+// every wave keeps an online softmax per head in registers; reductions are lane swaps and row rotations plus
 // one LDS hop across the four waves.
 #include <cstdlib>
 #include <type_traits>

@@ -53,9 +53,9 @@ __device__ __forceinline__ void tile_to_frags(const TileRegs& r, char* tile, u32
 // grid: (row groups of W * RT tiles, K slices).  CT column tiles (2: up to 32 columns, 4 waves per workgroup; 4: up to
 // 64 columns, 8 waves per workgroup, so that the bigger panel is shared by more row tiles; 8: up to 128 columns, 4 waves
 // with up to 512 registers each, the two panels fill the LDS).
-// A gate/up pair of tiles per wave wants 204 registers (two waves per SIMD); its launch has 2.7 workgroups per CU, so at that
+// A gate/up pair of tiles per wave took 204 registers (two waves per SIMD) unbounded; its launch has 2.7 workgroups per CU, so at that
 // size the last quarter of them starts only when the first ones have finished (entry times up to 24 us into a 42 us
-// launch).  Held to three waves per SIMD (168 registers, 33 spilled) every workgroup starts at once: 42 -> 38 us.
+// launch).  Held to three waves per SIMD (168 registers; 156 are used) every workgroup starts at once: 42 -> 38 us.
 template <int MODE, int RT, int CT, int W, bool ROUND>
 __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) void gemm_wide_kernel(GemvArgs a) {
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
