@@ -15,6 +15,7 @@
 // Operand layouts and the RMSNorm folding are those of gemm_mfma.hip.
 #include <cstdlib>
 #include <type_traits>
+#include <utility>
 
 #include "d3_common.h"
 
@@ -30,6 +31,10 @@ constexpr int kPitch = 272;          // LDS pitch of a staged 16 x 256 B tile (+
 constexpr int kTile = 16 * kPitch;
 
 struct TileRegs { u32x4 q[4]; };
+
+// run(0), run(1), ... with constants: register arrays indexed by them stay in registers
+template <int... J, typename F>
+__device__ __forceinline__ void each_slot(std::integer_sequence<int, J...>, F run) { (run(std::integral_constant<int, J>{}), ...); }
 
 __device__ __forceinline__ void tile_load(TileRegs& r, const bf16_t* row0, size_t row_stride, int k0, int K) {
     const int lane = threadIdx.x & 63;
@@ -217,12 +222,11 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
         if (n_turns > 1) panel_issue(t + 1);
         column_scales();
         __syncthreads();
-        auto turns_from = [&]<int... J>(std::integer_sequence<int, J...>, auto run) { (run(std::integral_constant<int, J>{}), ...); };
         constexpr std::make_integer_sequence<int, D> slots{};
         for (; t + 2 * D <= t_end; t += D)             // steady state: every load is unconditional
-            turns_from(slots, [&](auto j) { turn(t + j, j, true, true, true); });
+            each_slot(slots, [&](auto j) { turn(t + j, j, true, true, true); });
         for (; t < t_end; t += D)
-            turns_from(slots, [&](auto j) { if (t + j < t_end) turn(t + j, j, t + j + D < t_end, t + j + 1 < t_end, t + j + 2 < t_end); });
+            each_slot(slots, [&](auto j) { if (t + j < t_end) turn(t + j, j, t + j + D < t_end, t + j + 1 < t_end, t + j + 2 < t_end); });
     } else {
         column_scales();
         __syncthreads();

@@ -186,42 +186,57 @@ __global__ __launch_bounds__(64) void rope_append_kernel(RopeArgs a) {
 }
 
 // ---------------- greedy argmax, lowest index on ties ----------------
+// A chain of round trips bounds it: the loads of up to 32768 logits go out in one round without a branch per thread (a round ends where the row does),
+// and lanes are compared by swaps and rotations instead of LDS shuffles, the sixteen waves' winners by a row of lanes instead of one thread.
+// 1024 / 32000 logits 3.5 / 6.8 -> 2.1 / 4.8 us, 32 rows of 32000 7.5 -> 5.5 (kernel trace).
+struct Best { float v; int i; };
+__device__ __forceinline__ Best better(const Best& a, const Best& b) { return b.v > a.v || (b.v == a.v && b.i < a.i) ? b : a; }
+template <int N> __device__ __forceinline__ Best best_rotated(const Best& b) {
+    return Best{row_rotated<N>(b.v), __builtin_amdgcn_update_dpp(0, b.i, 0x120 + N, 0xf, 0xf, false)};
+}
+__device__ __forceinline__ Best best_of_row(Best b) {          // of the 16 lanes of a row
+    b = better(b, best_rotated<8>(b));
+    b = better(b, best_rotated<4>(b));
+    b = better(b, best_rotated<2>(b));
+    return better(b, best_rotated<1>(b));
+}
+__device__ __forceinline__ Best best_of_wave(Best b) {
+    auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(b.v), __float_as_uint(b.v), false, false);
+    auto i = __builtin_amdgcn_permlane32_swap((unsigned)b.i, (unsigned)b.i, false, false);
+    b = better(Best{__uint_as_float(v[0]), (int)i[0]}, Best{__uint_as_float(v[1]), (int)i[1]});
+    v = __builtin_amdgcn_permlane16_swap(__float_as_uint(b.v), __float_as_uint(b.v), false, false);
+    i = __builtin_amdgcn_permlane16_swap((unsigned)b.i, (unsigned)b.i, false, false);
+    return best_of_row(better(Best{__uint_as_float(v[0]), (int)i[0]}, Best{__uint_as_float(v[1]), (int)i[1]}));
+}
 __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ logits, int vocab, int32_t* __restrict__ out) {
+    constexpr int R = 16;                              // pairs of logits in flight per thread
     __shared__ float bv[16];
     __shared__ int bi[16];
     const int c = blockIdx.x, tid = threadIdx.x;
     const float* lg = logits + (size_t)c * vocab;
-    float best = -INFINITY;
-    int idx = 0x7fffffff;
-    auto take = [&](float v, int j) { if (v > best || (v == best && j < idx)) { best = v; idx = j; } };
-    // vocab % 2 == 0: pairs, eight pair-loads in flight per thread
-    const int n2 = vocab / 2;
-    for (int base = 0; base < n2; base += 1024 * 8) {
-        float2 v[8];
+    Best best{-INFINITY, 0x7fffffff};
+    const int n2 = vocab / 2;                          // vocab % 2 == 0
+    for (int base = 0; base < n2; base += 1024 * R) {
+        float2 v[R];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int p = base + r * 1024 + tid;
-            v[r] = p < n2 ? *reinterpret_cast<const float2*>(lg + 2 * p) : make_float2(-INFINITY, -INFINITY);
+        for (int r = 0; r < R; ++r) {
+            if (base + r * 1024 >= n2) break;
+            v[r] = *reinterpret_cast<const float2*>(lg + 2 * min(base + r * 1024 + tid, n2 - 1));
         }
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int p = base + r * 1024 + tid;
-            if (p < n2) { take(v[r].x, 2 * p); take(v[r].y, 2 * p + 1); }
+        for (int r = 0; r < R; ++r) {
+            if (base + r * 1024 >= n2) break;
+            const int p = min(base + r * 1024 + tid, n2 - 1);          // threads past the end look at the last pair once more
+            best = better(better(best, Best{v[r].x, 2 * p}), Best{v[r].y, 2 * p + 1});
         }
     }
     // NaN logits never win (comparisons false); an all-NaN row yields index clamp below
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const float ov = __shfl_xor(best, o, 64);
-        const int oi = __shfl_xor(idx, o, 64);
-        if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
-    }
-    if ((tid & 63) == 0) { bv[tid >> 6] = best; bi[tid >> 6] = idx; }
+    best = best_of_wave(best);
+    if ((tid & 63) == 0) { bv[tid >> 6] = best.v; bi[tid >> 6] = best.i; }
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < 16; ++w)
-            if (bv[w] > best || (bv[w] == best && bi[w] < idx)) { best = bv[w]; idx = bi[w]; }
-        out[c] = idx >= vocab ? 0 : idx;
+    if (tid < 16) {
+        best = best_of_row(Best{bv[tid], bi[tid]});
+        if (tid == 0) out[c] = best.i >= vocab ? 0 : best.i;
     }
 }
 

@@ -600,3 +600,38 @@ def test_full_size_batched_configurations_sampled_against_oracle(name, B, P):
     assert s >= 1 and torch.equal(dec.k_cache[s, B - 1, :, pos], dec.k_cache[s - 1, B - 1, :, pos])
     assert torch.equal(dec.v_cache[s + n - 1, 0, :, pos], dec.v_cache[s - 1, 0, :, pos])
     dec.close()
+
+
+@pytest.mark.parametrize("V,B", [(64, 2), (1024, 1), (2050, 3), (32768, 2), (32770, 1), (65602, 2)])
+@pytest.mark.parametrize("kind", ["drawn", "every logit twice", "some not numbers", "all equal", "no numbers", "the last one"])
+def test_greedy_token_is_the_first_of_the_largest_logits(V, B, kind):
+    # rows of less than a wave's pairs, of one and of several rounds of 32768 logits and one pair more; exact, against the returned logits
+    import torch
+    from paper_2503_08524_amd import binding
+    s = ModelShape("argmax", L=1, d=64, H=1, H_kv=1, hd=64, F=64, V=V, dtype="f32")
+    w = binding.weights_to_device(s, d3_inputs.make_weights(s, 3), "cuda:0")
+    head = w["lm_head"]
+    if kind == "every logit twice":
+        head[V // 2:] = head[:V // 2].clone()
+    elif kind == "some not numbers":
+        head[::3] = float("nan")
+    elif kind == "all equal":
+        head.zero_()
+    elif kind == "no numbers":
+        head.fill_(float("nan"))
+    dec = binding.Decoder(s, w, B, 8, kv_dtype="f32")
+    tok, lg = torch.empty(B, dtype=torch.int32, device="cuda:0"), torch.empty(B, V, device="cuda:0")
+    prompt = torch.from_numpy(d3_inputs.make_prompt(B, 3, V, seed=5)).to("cuda:0")
+    dec.prefill(prompt, next_tok=tok, logits=lg)
+    if kind == "the last one":                         # ... of the first sequence: a row of the head along its final hidden state
+        dec.close()
+        head[V - 1] = 50.0 * head[int(tok[0])]
+        dec = binding.Decoder(s, w, B, 8, kv_dtype="f32")
+        dec.prefill(prompt, next_tok=tok, logits=lg)
+    torch.cuda.synchronize()
+    x = lg.cpu().numpy()
+    want = [0 if np.isnan(r).all() else int(np.nanargmax(r)) for r in x]
+    assert tok.cpu().tolist() == want
+    if kind == "the last one":
+        assert want[0] == V - 1
+    dec.close()
