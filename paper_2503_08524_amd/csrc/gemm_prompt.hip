@@ -183,7 +183,8 @@ __device__ __forceinline__ void store_qkv(const GemvArgs& a, const f32x4 (&acc)[
             const float cs[4] = {c0.x, c0.z, c1.x, c1.z}, sn[4] = {c0.y, c0.w, c1.y, c1.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float y0 = lo[e] * cs[e] - hi[e] * sn[e], y1 = lo[e] * sn[e] + hi[e] * cs[e];
+                // the two roundings of each are stated: left to the compiler, which product joins the addition unrounded changed with the code around it
+                const float y0 = fmaf(lo[e], cs[e], -(hi[e] * sn[e])), y1 = fmaf(lo[e], sn[e], hi[e] * cs[e]);
                 lo[e] = y0; hi[e] = y1;
             }
         }

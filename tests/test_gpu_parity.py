@@ -317,6 +317,31 @@ def test_storing_projections_whole_and_in_parts_in_one_launch(monkeypatch, cus, 
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("ks", [1, 2])
+def test_prompt_projection_rotates_with_two_stated_roundings(monkeypatch, ks):
+    # 200 times the same token: every position has the same unrotated key, which position 0 (cos 1, sin 0) shows, so the rotated ones follow
+    # bit by bit from fma(lo, cos, -(hi sin)), fma(lo, sin, hi cos) over the table's floats.  The products are exact in float64; rounding their sum
+    # to float64 first, or a cosine that two libraries round to neighbouring floats, is left to one element in a thousand.
+    import torch
+    from paper_2503_08524_amd import binding
+    monkeypatch.setenv("D3_PROMPT_KS", str(ks))
+    P, hd = 200, 128
+    s = ModelShape("rotate", L=1, d=256, H=2, H_kv=1, hd=hd, F=256, V=512, dtype="bf16")
+    dec = binding.Decoder(s, binding.weights_to_device(s, d3_inputs.make_weights(s, 3), "cuda:0"), 1, P + 1, kv_dtype="f32")
+    print(f"case rotate ks={ks}", flush=True)
+    dec.prefill(torch.full((1, P), 7, dtype=torch.int32, device="cuda:0"))
+    torch.cuda.synchronize()
+    k = dec.k_cache[0, 0, 0, :P].cpu().numpy()
+    dec.close()
+    lo, hi = k[0, :hd // 2], k[0, hd // 2:]
+    angle = np.arange(P)[:, None] * s.rope_base ** (-2.0 * np.arange(hd // 2) / hd)
+    cs, sn = np.cos(angle).astype(np.float32), np.sin(angle).astype(np.float32)
+    exact = lambda a, b: a.astype(np.float64) * b.astype(np.float64)
+    y0 = (exact(lo, cs) - (hi * sn).astype(np.float64)).astype(np.float32)
+    y1 = (exact(lo, sn) + (hi * cs).astype(np.float64)).astype(np.float32)
+    assert np.mean(np.concatenate([y0, y1], 1) != k) <= 1e-3
+
+
 @pytest.mark.parametrize("F,P,parts", [(512, 130, 18), (2560, 70, 72)])
 def test_prompt_kernel_adds_up_many_partial_sums_of_squares(F, P, parts):
     # a column's sum of squares in more partials than one read of 16 threads takes: 18 row blocks of the LDS-tiled kernel's own O and down
