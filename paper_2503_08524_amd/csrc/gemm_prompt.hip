@@ -660,7 +660,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
         return;
     }
     // ---- K parts of the other projections: as in add_residual_parts, with the units of the tile dealt out to the parts in runs.  (With the part that
-    // arrives last adding up and finishing the whole tile: 7B shape, 512 columns, kernel trace, gate/up 157.8 -> 155.2 us, 88 of 344 tiles in two parts each.) ----
+    // arrives last adding up and finishing the whole tile: 7B shape, 512 columns, kernel trace, gate/up 157.8 -> 155.2 us, 88 of 344 tiles in two parts each.)
+    // The part that comes last finds most runs waiting for it, so it takes all of them together: each part's sums are a round trip, and run by
+    // run they were one more for every run (QKV at 77 columns, 7B and 70B shapes: 54.2 and 72.1 us run by run, 49.1 and 61.4
+    // together, 50.5 and 64.0 where the last part finishes the whole tile). ----
     int* tickets = a.part_tickets + part_id * parts;
     constexpr unsigned all_units = (1u << CW * kUnits) - 1;        // bit tt kUnits + r
     auto run = [&](int j) { return parts == 1 ? all_units : (1u << order.ks.of(CW * kUnits * (j + 1))) - (1u << order.ks.of(CW * kUnits * j)); };
@@ -688,46 +691,50 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
             __syncthreads();
         }
     }
-    QkvColumns q_cols;
-    if constexpr (MODE == MODE_QKV_ROPE) q_cols.load(a, cb, grp, wx);
-    for (int j = 0; j < parts; ++j) {                  // a whole tile is one run
-        if (parts > 1) {
+    unsigned mine = all_units;                         // a whole tile is one run
+    if (parts > 1) {
+        mine = 0;
+        for (int j = 0; j < parts; ++j) {
             if (!last_at[j]) continue;
+            mine |= run(j);
             if (tid == 0) __hip_atomic_store(&tickets[j], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // all have been here: leave it clean
         }
-        const unsigned run_j = run(j);
+        mine = __builtin_amdgcn_readfirstlane(mine);
+        if (mine == 0) return;
+    }
+    QkvColumns q_cols;
+    if constexpr (MODE == MODE_QKV_ROPE) q_cols.load(a, cb, grp, wx);
 #pragma unroll
-        for (int tt = 0; tt < CW; ++tt) {
-            const unsigned units = run_j >> (tt * kUnits) & ((1u << kUnits) - 1);
-            if (units == 0) continue;
-            f32x4 sum[RW];
-            if (parts == 1) {
+    for (int tt = 0; tt < CW; ++tt) {
+        const unsigned units = mine >> (tt * kUnits) & ((1u << kUnits) - 1);
+        if (units == 0) continue;
+        f32x4 sum[RW];
+        if (parts == 1) {
 #pragma unroll
-                for (int r = 0; r < RW; ++r) sum[r] = fin[r][tt];
-            } else {
+            for (int r = 0; r < RW; ++r) sum[r] = fin[r][tt];
+        } else {
 #pragma unroll
-                for (int r = 0; r < RW; ++r) sum[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-                for (int part = 0; part < parts; ++part) {             // in the order of the parts, whoever adds them up
-                    if (part == slice) {                               // (its own it still has in registers)
+            for (int r = 0; r < RW; ++r) sum[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int part = 0; part < parts; ++part) {                 // in the order of the parts, whoever adds them up
+                if (part == slice) {                                   // (its own it still has in registers)
 #pragma unroll
-                        for (int r = 0; r < RW; ++r) sum[r] += fin[r][tt];
-                        continue;
-                    }
-                    u32x4 v[RW];
-#pragma unroll
-                    for (int r = 0; r < RW; ++r) {
-                        v[r] = u32x4{0, 0, 0, 0};
-                        if (units >> (r % kUnits) & 1) v[r] = __builtin_amdgcn_raw_buffer_load_b128(pr.buf, 16 * tid, part * kPartBytes + (r * CW + tt) * 16 * kThreads, kAgent);
-                    }
-#pragma unroll
-                    for (int r = 0; r < RW; ++r) sum[r] += __builtin_bit_cast(f32x4, v[r]);
+                    for (int r = 0; r < RW; ++r) sum[r] += fin[r][tt];
+                    continue;
                 }
+                u32x4 v[RW];
+#pragma unroll
+                for (int r = 0; r < RW; ++r) {
+                    v[r] = u32x4{0, 0, 0, 0};
+                    if (units >> (r % kUnits) & 1) v[r] = __builtin_amdgcn_raw_buffer_load_b128(pr.buf, 16 * tid, part * kPartBytes + (r * CW + tt) * 16 * kThreads, kAgent);
+                }
+#pragma unroll
+                for (int r = 0; r < RW; ++r) sum[r] += __builtin_bit_cast(f32x4, v[r]);
             }
-            if constexpr (MODE == MODE_QKV_ROPE) {
-                if (a.kv_dtype == 0) store_qkv<float>(a, sum, q_cols, tt, units, rb, cb, grp, wy, wx, inv_rms);
-                else store_qkv<f16_t>(a, sum, q_cols, tt, units, rb, cb, grp, wy, wx, inv_rms);
-            } else store_tiles<MODE>(a, sum, tt, units, rb, cb, tiles, grp, wy, wx, inv_rms);
         }
+        if constexpr (MODE == MODE_QKV_ROPE) {
+            if (a.kv_dtype == 0) store_qkv<float>(a, sum, q_cols, tt, units, rb, cb, grp, wy, wx, inv_rms);
+            else store_qkv<f16_t>(a, sum, q_cols, tt, units, rb, cb, grp, wy, wx, inv_rms);
+        } else store_tiles<MODE>(a, sum, tt, units, rb, cb, tiles, grp, wy, wx, inv_rms);
     }
 #endif
 }

@@ -317,6 +317,17 @@ def test_storing_projections_whole_and_in_parts_in_one_launch(monkeypatch, cus, 
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("ks", [3, 5, 6, 7])
+def test_parts_that_finish_several_runs_together(monkeypatch, ks):
+    # QKV (four row blocks) and gate/up (five) of one column block, every tile in 3 to 7 parts with 8 units between them: runs of one to three units,
+    # on both sides of the two column tiles, of which the part that comes last takes all that wait for it; 16 stages
+    monkeypatch.setenv("D3_PROMPT_KS", str(ks))
+    monkeypatch.setenv("D3_PROMPT_ROW_BLOCKS", "1")
+    s = ModelShape("runs", L=2, d=1024, H=4, H_kv=2, hd=128, F=640, V=512, dtype="bf16")
+    gpu, gens = _run(s, 1, 100, 2, 1.0, 1, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
 @pytest.mark.parametrize("ks", [1, 2])
 def test_prompt_projection_rotates_with_two_stated_roundings(monkeypatch, ks):
     # 200 times the same token: every position has the same unrotated key, which position 0 (cos 1, sin 0) shows, so the rotated ones follow
