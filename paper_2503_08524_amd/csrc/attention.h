@@ -333,7 +333,15 @@ __device__ __forceinline__ void attn_split(const AttnArgs& a, int split, int h0,
                     if (j < j1) { sv[u] = s; cmax = fmaxf(cmax, s); }
                 }
             }
-            cmax = reduce_across<LPR>(cmax, MaxOp());  // equal within a row group already
+            // Equal within a row group already.  Eight lanes to a row (head_dim 64, fp16 rows): the vector ALU has most to do here and its three
+            // steps per chunk and head are better left to the LDS (4 blocks of 8 KV heads of 4, 6000 rows, batch 8 / 32: the step took 1.2 / 5 %
+            // longer with lane swaps than with shuffles ahead of the other steps' swaps, and takes 2.5 / 3 % less with shuffles here alone).
+            if (LPR == 8) {
+#pragma unroll
+                for (int o = LPR; o < 64; o <<= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, o, 64));
+            } else {
+                cmax = reduce_across<LPR>(cmax, MaxOp());
+            }
             const float m_new = fmaxf(m[g], cmax);          // a wave with no valid row in this chunk keeps -inf
             if (m_new > -INFINITY) {
                 const float keep = exp2f(m[g] - m_new);       // exp2(-inf) = 0 the first time

@@ -259,6 +259,9 @@ extern "C" int d3_create(d3_ctx** out, const d3_model_desc* desc, const d3_weigh
     // one workgroup per CU (70B shape, batch 8: 24.41 against 24.55 ms a step), the others with two (13B, batch 4: 5.71 against 5.78)
     c->attn_wgs_per_cu = (desc->head_dim == 128 && desc->n_kv_heads > 0 &&
                           (desc->n_heads / desc->n_kv_heads == 4 || desc->n_heads / desc->n_kv_heads == 8)) ? 1 : 2;
+    // pairs of heads over fp32 rows of 128: a compute unit holds four workgroups, and with two the last splits over 512 workgroups (576 at batch 12 and 24)
+    // hold the step up: 4 blocks of 8 KV heads, 7000 rows, batch 6 / 12 / 24 / 32, two 401 / 656 / 1179 / 1279 us a step, three 359 / 590 / 1042 / 1308
+    if (desc->head_dim == 128 && desc->n_heads == 2 * desc->n_kv_heads && desc->kv_dtype == D3_F32) c->attn_wgs_per_cu = 3;
     c->prefill_by_seq = env_int("D3_PREFILL_BY_SEQ", 0, 1, 1) != 0;
     c->attn_wgs_per_cu = env_int("D3_ATTN_WGS_PER_CU", 1, 16, c->attn_wgs_per_cu);
     c->mfma_ok = mfma_fits(*desc);

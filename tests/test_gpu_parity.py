@@ -459,6 +459,15 @@ def test_batch1_decode_grouped_query_head_dim_128(kv):
     _run(SMALL_GQA, 1, 70, 12, 0.85, 1, forced_seed=14, kv_dtype=kv)
 
 
+@pytest.mark.parametrize("B,hd,H,H_kv,kv", [(1, 128, 4, 2, "f32"), (3, 128, 4, 2, "f32"), (2, 64, 8, 2, "f16"), (2, 64, 8, 1, "f16"), (3, 64, 4, 4, "f16")])
+def test_vector_alu_attention_over_several_splits(B, hd, H, H_kv, kv):
+    # pairs of heads over fp32 rows of 128 (three workgroups per compute unit), and rows of eight lanes, whose maxima go through the LDS: 4 splits
+    s = ModelShape("splits", L=2, d=256, H=H, H_kv=H_kv, hd=hd, F=256, V=512, dtype="bf16")
+    gpu, gens = _run(s, B, 400, 3, 1.0, 1, forced_seed=19, kv_dtype=kv)
+    if kv == "f32":
+        helpers.compare(gpu, gens, 3, logit_atol=2e-4, hidden_tol=1e-4)
+
+
 def test_batch1_zero_blocks_and_free_running_tokens():
     gpu, gens = _run(SMALL_GQA, 1, 9, 6, 0.5, 1)      # keep = 3, 1, 0, 0, ...: steps with no block at all
     assert gens[0].keep[2] == 0
