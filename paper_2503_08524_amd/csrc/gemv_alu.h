@@ -87,11 +87,16 @@ __device__ __forceinline__ void gemv_unit_rows(const GemvArgs& a, int u, const W
     }
 }
 
-// The load side of a wave's pipeline.  A wave begins its rows at stride `first` and goes round: rows are a power of two of bytes apart or close to
-// it, and waves that all read the same stretch of their rows meet on a part of the memory channels.  first = the wave's number + the
-// workgroup's / 8 (each XCD, which gets every eighth workgroup, then has all stretches in flight), modulo the strides of a row.  7B shape,
-// batch 1, a step of 17 blocks: 1392 us from stride 0; by the workgroup's number 1370, by wave alone 1377, by workgroup / 8 alone 1393, by both
-// 1348 (/ 4 + wave 1348, / 16 + wave 1430).
+// The load side of a wave's pipeline.  A wave begins its rows at stride `first` and goes round: rows are often a power of two of bytes apart, and
+// waves that all read the same stretch of their rows meet on a part of the memory channels.  Measured at batch 1, a step with three workgroups of
+// four waves per compute unit that all begin at stride 0 / the present shape from stride 0 / from workgroup / 8 + wave / from this one, us:
+//   7B widths, rows of 8 KB, 17 blocks                  1473 / 1391 / 1349 / 1350
+//   rows of 16 KB, bf16, 8192 wide, 3 blocks             490 /  466 /  538 /  449   (QKV 33.1 / 32.2 / 38.0 / 29.7, O 27.2 / 25.5 / 32.6 / 24.9)
+//   rows of 16 KB, fp32, 4096 wide, 4 blocks             661 /  633 /  690 /  612
+//   rows of 32 KB, fp32, 8192 wide, 2 blocks             761 /  743 /  755 /  751
+// A start that follows a bit of the row's address undoes the spread that the address alone would have: workgroup / 8 does so where two rows are 32 KB
+// and eight such pairs 256 KB, / 4 at 64 KB a pair, / 16 at 16 KB.  Odd multiples of a quarter of the workgroup's number and of the wave's do not,
+// at rows of 2 to 56 KB.
 template <typename W, int D>
 struct GemvPipe {
     u32x4 b0[D], b1[D];   // ring of loaded chunks: slot j holds step (issued - D + j) mod D ...
@@ -128,7 +133,7 @@ __device__ __forceinline__ void gemv_preload(const GemvArgs& a, int wave, int gw
     p.total = (a.wave_units + (gw < a.wave_units_over ? 1 : 0)) * S;
     p.issued = 0;
     p.lu = gw;
-    const int turn = (int)(blockIdx.x >> 3) + wave;
+    const int turn = 5 * (int)(blockIdx.x >> 2) + 3 * wave;
     p.first = turn - a.by_strides.of(turn) * S;
     p.lit = p.first;
     int row;

@@ -373,6 +373,41 @@ def test_rows_a_multiple_of_8_kb_apart(d, F, B, P):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("dtype,H", [("bf16", 64), ("f32", 32)])
+def test_rows_of_16_kb_stream_as_fast_as_others(dtype, H):
+    # the O projection at batch 1, square: rows of 16 KB (a power of two) against rows one head longer, four blocks of each.  The rate of either differs by a
+    # few per cent from run to run; waves that meet on a part of the memory channels cost a fifth of it.  Best of eight readings of each.
+    import torch
+    from paper_2503_08524_amd import binding
+
+    def rate(heads):
+        s = ModelShape("rows", L=4, d=heads * 128, H=heads, H_kv=heads, hd=128, F=64, V=64, dtype=dtype)
+        wt = torch.bfloat16 if dtype == "bf16" else torch.float32
+        new = lambda r, c: torch.empty(r, c, device="cuda:0").normal_(0, 0.02).to(wt)
+        gain = torch.ones(s.d, device="cuda:0")
+        kv = s.H_kv * s.hd
+        w = {"tok_emb": new(s.V, s.d), "lm_head": new(s.V, s.d), "final_norm": gain, "layers": [
+            {"attn_norm": gain, "wq": new(s.d, s.d), "wk": new(kv, s.d), "wv": new(kv, s.d), "wo": new(s.d, s.d), "mlp_norm": gain,
+             "w_gate": new(s.F, s.d), "w_up": new(s.F, s.d), "w_down": new(s.d, s.F)} for _ in range(s.L)]}
+        dec = binding.Decoder(s, w, 1, 64, kv_dtype="f32")
+        tok = dec.prefill(torch.ones(1, 4, dtype=torch.int32, device="cuda:0"))
+        out, best = torch.empty_like(tok), 0.0
+        dec.set_plan_table([s.L, s.L], [0, 0])
+        dec.profile_select(binding.D3_K_OPROJ)
+        for _ in range(9):
+            for _ in range(10):
+                dec.truncate(4)
+                dec.decode_step(tok, 1, out)
+            ms, n = dec.profile_read()
+            best = max(best, s.d * s.d * w["lm_head"].element_size() * n / ms / 1e9)
+        dec.close()
+        return best
+
+    plain, odd = rate(H), rate(H + 1)
+    print(f"case rows {dtype}: 16 KB {plain:.2f} TB/s, longer {odd:.2f} TB/s", flush=True)
+    assert plain > 0.9 * odd
+
+
 @pytest.mark.parametrize("d,F,V,B", [(64, 64, 270016, 1), (64, 4160, 512, 2), (1408, 64, 512, 3)])
 def test_vector_alu_gemv_strides_and_units(d, F, V, B):
     # rows of one 64-lane stride, of 16 and a quarter and of five and a half, begun at every stride of a row; one more than a wave's fill of units per wave,
