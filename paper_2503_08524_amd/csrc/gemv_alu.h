@@ -193,7 +193,7 @@ __device__ __forceinline__ void gemv_stage_commit(const GemvArgs& a, int tid, fl
         if (i4 < f4_per_col) {
             const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-            for (int n = 0; n < NC; ++n) put(i4, n, n < a.ncols && i4 < f4_used ? regs.v[n][r] : zero, regs.g[r]);
+            for (int n = 0; n < NC; ++n) put(i4, n, n < a.ncols && i4 < f4_used ? regs.v[n][r] : zero, NORM && i4 < f4_used ? regs.g[r] : zero);   // (a gain may be infinite)
         }
     }
     for (int i4 = tid + R * THREADS; i4 < f4_per_col; i4 += THREADS) {      // wide inputs: the rest, one at a time

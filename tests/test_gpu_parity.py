@@ -373,6 +373,24 @@ def test_rows_a_multiple_of_8_kb_apart(d, F, B, P):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("d,B", [(1408, 1), (1408, 3), (64, 1), (4160, 1)])
+def test_infinite_gain_stays_out_of_the_padding(d, B):
+    # an infinite gain of the last element makes every logit infinite, with the sign of that element times its weight, and none of them no number:
+    # what fills the last stride of a row is zero, whatever the gains (fp32: rows of 5.5, 0.25 and 16.25 strides)
+    import torch
+    from paper_2503_08524_amd import binding
+    s = ModelShape("inf-gain", L=1, d=d, H=1, H_kv=1, hd=64, F=64, V=512, dtype="f32")
+    w = binding.weights_to_device(s, d3_inputs.make_weights(s, 3), "cuda:0")
+    w["final_norm"][d - 1] = float("inf")
+    dec = binding.Decoder(s, w, B, 8, kv_dtype="f32")
+    lg, hid = torch.empty(B, s.V, device="cuda:0"), torch.empty(2, B, d, device="cuda:0")
+    print(f"case inf-gain d={d} B={B}", flush=True)
+    dec.prefill(torch.from_numpy(d3_inputs.make_prompt(B, 1, s.V, seed=5)).to("cuda:0"), logits=lg, hidden_dump=hid)
+    want = torch.sign(hid[1, :, d - 1:] * w["lm_head"][:, d - 1]) * float("inf")
+    assert torch.equal(lg, want)
+    dec.close()
+
+
 @pytest.mark.parametrize("dtype,H", [("bf16", 64), ("f32", 32)])
 def test_rows_of_16_kb_stream_as_fast_as_others(dtype, H):
     # the O projection at batch 1, square: rows of 16 KB (a power of two) against rows one head longer, four blocks of each.  The rate of either differs by a
