@@ -14,7 +14,7 @@ namespace d3 {
 #endif
 constexpr int kGemvWaves = D3_GEMV_WAVES;   // waves per workgroup (they share the staged activations)
 constexpr int kGemvThreads = kGemvWaves * kWave;
-constexpr int kGemvStageR = 6;              // float4 activation loads a thread issues ahead of the weights (K <= 12288 in one round)
+constexpr int kGemvStageR = 6;              // float4 activation loads a thread issues ahead of the weights, of all columns (K <= 12288 of one column, 6144 of two, 4096 of four in one round)
 constexpr int kGemvLdsBudget = 60 * 1024;   // dynamic LDS per workgroup for the activations
 #ifndef D3_GEMV_DEPTH
 #define D3_GEMV_DEPTH 4

@@ -43,6 +43,18 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_alu_kernel(GemvArgs a) {
     gemv_run<W, NC, MODE, kGemvDepth>(a, xs, gw, nw, pipe, ep[wave], rinv);
 }
 
+// A workgroup's LDS is up to 60 KB of activations and, for four columns, 18 KB of finished units: past 64 KB together.
+template <typename W, int NC, int MODE, bool NORM>
+int launch_kernel(const GemvArgs& a, int grid, size_t lds, hipStream_t s) {
+    auto* k = gemv_alu_kernel<W, NC, MODE, NORM>;
+    if (lds + sizeof(GemvEpBuf<NC>) * kGemvWaves > 48 * 1024) {
+        static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kGemvLdsBudget);
+        if (once != hipSuccess) return (int)once;
+    }
+    hipLaunchKernelGGL(k, dim3(grid), dim3(kGemvThreads), lds, s, a);
+    return (int)hipGetLastError();
+}
+
 template <typename W, int NC>
 int launch_nc(GemvArgs a, int mode, bool norm, int n_wg, hipStream_t s) {
     const size_t lds = (size_t)NC * gemv_f4_per_col<W>(a.K) * sizeof(float4);
@@ -52,7 +64,7 @@ int launch_nc(GemvArgs a, int mode, bool norm, int n_wg, hipStream_t s) {
     // to park more than kGemvEpCap (= 64 lanes) units.  One workgroup of eight waves per compute unit against three of four: the activations are
     // staged once instead of three times, and 2048 waves divide the usual numbers of units evenly (7B shape: 2048 units of O and down, 6144 of QKV):
     // a step of 17 blocks at batch 1 1385 -> 1348 us (12 waves 1372; five or six steps in flight instead of four 1369, 1374).
-    const int most = n_wg + n_wg / 2, per_wg = kGemvWaves * kGemvEpCap;
+    const int most = n_wg + (n_wg + 1) / 2, per_wg = kGemvWaves * kGemvEpCap;
     if ((long long)most * per_wg < n_units) return (int)hipErrorInvalidValue;
     int grid = (n_units + kGemvWaves - 1) / kGemvWaves;
     if (grid > n_wg) grid = (n_units + per_wg - 1) / per_wg > n_wg ? (n_units + per_wg - 1) / per_wg : n_wg;
@@ -60,13 +72,10 @@ int launch_nc(GemvArgs a, int mode, bool norm, int n_wg, hipStream_t s) {
     a.wave_units = n_units / n_waves;
     a.wave_units_over = n_units % n_waves;
     a.by_strides = Divisor((a.K / GemvChunk<W>::N + 63) / 64);
-#define D3_LAUNCH(MODE, NORM) hipLaunchKernelGGL((gemv_alu_kernel<W, NC, MODE, NORM>), dim3(grid), dim3(kGemvThreads), lds, s, a)
-    if (mode == MODE_STORE) { if (norm) D3_LAUNCH(MODE_STORE, true); else D3_LAUNCH(MODE_STORE, false); }
-    else if (mode == MODE_RESID) { D3_LAUNCH(MODE_RESID, false); }
-    else if (mode == MODE_SWIGLU) { D3_LAUNCH(MODE_SWIGLU, true); }
-    else { D3_LAUNCH(MODE_QKV_ROPE, true); }
-#undef D3_LAUNCH
-    return (int)hipGetLastError();
+    if (mode == MODE_STORE) return norm ? launch_kernel<W, NC, MODE_STORE, true>(a, grid, lds, s) : launch_kernel<W, NC, MODE_STORE, false>(a, grid, lds, s);
+    if (mode == MODE_RESID) return launch_kernel<W, NC, MODE_RESID, false>(a, grid, lds, s);
+    if (mode == MODE_SWIGLU) return launch_kernel<W, NC, MODE_SWIGLU, true>(a, grid, lds, s);
+    return launch_kernel<W, NC, MODE_QKV_ROPE, true>(a, grid, lds, s);
 }
 
 template <typename W>

@@ -373,6 +373,15 @@ def test_rows_a_multiple_of_8_kb_apart(d, F, B, P):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+@pytest.mark.parametrize("dtype,d,F,B", [("f32", 64, 15360, 1), ("bf16", 64, 15360, 1), ("f32", 3840, 64, 4), ("f32", 3072, 64, 3), ("f32", 64, 7680, 2), ("f32", 2816, 3840, 4)])
+def test_vector_alu_gemv_with_most_lds(dtype, d, F, B):
+    # as many columns as an input's LDS budget of 60 KB takes, beside which every column count keeps its finished units: 66, 70 and 78 KB a workgroup, and
+    # the first width at which four columns pass 64 KB
+    s = ModelShape("gemv-lds", L=1, d=d, H=1, H_kv=1, hd=64, F=F, V=256, dtype=dtype)
+    gpu, gens = _run(s, B, 3, 3, 1.0, 0, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 3, logit_atol=1e-4, hidden_tol=1e-5)
+
+
 @pytest.mark.parametrize("d,B", [(1408, 1), (1408, 3), (64, 1), (4160, 1)])
 def test_infinite_gain_stays_out_of_the_padding(d, B):
     # an infinite gain of the last element makes every logit infinite, with the sign of that element times its weight, and none of them no number:
