@@ -26,9 +26,10 @@
 //    into the buffers just freed and with the reads of the next stage's first fragments, and slot 0
 //    consumes the weight fragments as they arrive.  Reads and loads issued ahead of the MFMAs instead cost 15-20 %.
 // The bound is the matrix cores at the clock that their power leaves them: on operands drawn from a normal distribution they
-// alone sustain 1.9-2.0 PFLOP/s (the clock drops with the toggling of the operands), the loop without its global loads 1.5-1.65, and
-// the launches at 2048 columns 1.2 (O) to 1.4 (down) as issued, QKV and gate/up 1.33.  7B shape, 2048 columns, the kernel with stages of 32 k (128 x 64 per wave with two workgroups per
-// compute unit, or eight waves of 64 x 64) -> this one: QKV 350 -> 308 us (rotation and cache append now included), gate/up
+// alone sustain 2.2 PFLOP/s in this kernel's order (both planes of an accumulator back to back; 2.0 with the planes apart; the clock drops with the toggling of the
+// operands), and the launches at 2048 columns, 7B shape, 1.2 (O) to 1.4 (QKV 293 us, gate/up 536, down 262) as issued.  Launches of
+// the kernel with stages of 32 k (128 x 64 per wave with two workgroups per
+// compute unit, or eight waves of 64 x 64) -> the first one with stages of 64 k: QKV 350 -> 308 us (rotation and cache append now included), gate/up
 // 657 -> 555, O 165 -> 115, down 362 -> 263.
 //
 // The LDS reads are inline assembly: the compiler orders every LDS read it knows of behind ALL outstanding direct-to-LDS
@@ -785,11 +786,12 @@ __global__ __launch_bounds__(512, 2) void mfma_yardstick_kernel(float* __restric
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
 #pragma unroll
-            for (int r = 0; r < RWY; ++r) acc[r][tt] = mfma(cur.a[r], cur.bh[tt], acc[r][tt]);
-#pragma unroll
-            for (int r = 0; r < RWY; ++r) acc[r][tt] = mfma(cur.a[r], cur.bl[tt], acc[r][tt]);
+            for (int r = 0; r < RWY; ++r) {            // both planes of an accumulator back to back, as the kernel above does (mma_hl)
+                acc[r][tt] = mfma(cur.a[r], cur.bh[tt], acc[r][tt]);
+                acc[r][tt] = mfma(cur.a[r], cur.bl[tt], acc[r][tt]);
+                fixed_here();
+            }
         }
-        __builtin_amdgcn_sched_barrier(0);
     };
     for (int t = 0; t < stages; t += 2) { half(f0, f1); half(f1, f0); }
     lds_reads_left<0>();

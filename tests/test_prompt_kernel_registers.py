@@ -108,8 +108,10 @@ def test_the_check_itself(text, n_faults):
     assert len(faults(listing(text))[0]) == n_faults
 
 
-def test_fragments_in_flight_are_left_alone(tmp_path):
-    out = str(tmp_path / "gemm_prompt.s")
+@pytest.fixture(scope="module")
+def compiled(tmp_path_factory):
+    """(lines of the compiled file, {kernel: its lines})."""
+    out = str(tmp_path_factory.mktemp("prompt") / "gemm_prompt.s")
     src = os.path.join(d3_build.CSRC, "gemm_prompt.hip")
     r = subprocess.run([d3_build.HIPCC] + d3_build.FLAGS + ["-x", "hip", "--cuda-device-only", "-S", src, "-o", out], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
@@ -118,6 +120,22 @@ def test_fragments_in_flight_are_left_alone(tmp_path):
     kernels = {name: lines[i + 1:end] for (i, name), end in zip(starts, [i for i, _ in starts[1:]] + [len(lines)])}
     kernels = {n: [ln for ln in body] for n, body in kernels.items() if "gemm_prompt_kernel" in n or "mfma_yardstick_kernel" in n}
     assert len(kernels) == 7
+    return lines, kernels
+
+
+def test_yardstick_issues_the_planes_of_an_accumulator_back_to_back(compiled):
+    # the order that the prompt kernel uses and that draws least power: a bound for it has to be measured in that order
+    for name, body in compiled[1].items():
+        if "mfma_yardstick" not in name:
+            continue
+        issued = [re.search(r"v_mfma\S+ (\S+), \S+, \S+, (\S+)", raw) for _, raw in body]
+        issued = [m.groups() for m in issued if m]
+        assert len(issued) == 64, name
+        assert all(hi[0] == lo[1] for hi, lo in zip(issued[::2], issued[1::2])), name
+
+
+def test_fragments_in_flight_are_left_alone(compiled):
+    lines, kernels = compiled
     for name, body in kernels.items():
         end = next(i for i, (_, raw) in enumerate(body) if raw.strip().startswith(".section"))
         found, n_reads = faults(body[:end])
