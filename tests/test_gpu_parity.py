@@ -353,13 +353,27 @@ def test_prompt_projection_rotates_with_two_stated_roundings(monkeypatch, ks):
     assert np.mean(np.concatenate([y0, y1], 1) != k) <= 1e-3
 
 
-@pytest.mark.parametrize("F,P,parts", [(512, 130, 18), (2560, 70, 72)])
-def test_prompt_kernel_adds_up_many_partial_sums_of_squares(F, P, parts):
-    # a column's sum of squares in more partials than one read of 16 threads takes: 18 row blocks of the LDS-tiled kernel's own O and down
-    # projections, and the panel kernel's 72 row groups read by the LDS-tiled gate/up (20 row blocks, 70 columns)
+@pytest.mark.parametrize("F,P,split_mb", [(512, 130, 300), (2560, 70, 300), (2560, 70, 1)])
+def test_prompt_kernel_adds_up_many_partial_sums_of_squares(monkeypatch, F, P, split_mb):
+    # a column's sum of squares in more partials than one read of 16 threads takes: 130 columns, which all projections take to the LDS-tiled kernel: the
+    # 18 row blocks of its own O and down.  70 columns, where 18 row blocks stay with the panel kernel and the 20 of gate/up do not, by the line pinned
+    # here: the 72 row groups of one launch (four waves of one row tile), or the 36 of two launches of 64 columns (eight waves, one row tile pinned).
+    monkeypatch.setenv("D3_PROMPT_ROW_BLOCKS", "20")
+    monkeypatch.setenv("D3_WIDE_SPLIT_MB", str(split_mb))
+    monkeypatch.setenv("D3_WIDE_RT", "1")
     s = ModelShape("many-parts", L=2, d=4608, H=2, H_kv=1, hd=128, F=F, V=512, dtype="bf16")
-    assert parts == (4608 // 256 if P > 128 else 4608 // 64)
     gpu, gens = _run(s, 1, P, 2, 1.0, 1, forced_seed=19, kv_dtype="f32")
+    helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+
+
+@pytest.mark.parametrize("rt", [1, 2, 4])
+@pytest.mark.parametrize("d,F,B,P", [(8192, 256, 3, 2), (8192, 256, 12, 1), (256, 12288, 2, 5)])
+def test_rows_begun_at_different_places_by_every_number_of_row_tiles(monkeypatch, d, F, B, P, rt):
+    # QKV, gate/up and lm_head over K = 8192 with 3 (packed) and 12 columns, down over K = 12288 with 2 and 5 of a prompt, with 1, 2 and 4 row
+    # tiles a wave (gate/up: 1 and 2 pairs), the largest that is at most the one pinned
+    monkeypatch.setenv("D3_MFMA_RT", str(rt))
+    s = ModelShape("far-rows", L=1, d=d, H=2, H_kv=1, hd=128, F=F, V=512, dtype="bf16")
+    gpu, gens = _run(s, B, P, 2, 1.0, 0, forced_seed=19, kv_dtype="f32")
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
