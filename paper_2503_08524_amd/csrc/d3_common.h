@@ -184,9 +184,14 @@ __device__ __forceinline__ const bf16_t* gemm_row(const GemvArgs& a, int row) {
 }
 
 // Whether the workgroups of a batched projection begin their rows at different places.  Rows a multiple of 8 KB apart start on the same few memory
-// channels, and workgroups that walk them in step meet there; measured, from the first k / from different ones, narrow kernel: rows of 16 KB (70B
-// shape, 8 columns, kernel trace) gate/up 153.9 / 141.6 us (6.6 TB/s), QKV 32.2 / 30.9, lm_head 89.5 / 79.3; of 56 KB (down) 77 / 76.  Not where
-// rows are 8 KB or no multiple of it: 7B and 13B shapes, 2 blocks and the head, 2 columns 231 / 233 and 310 / 312, 12 columns 261 / 265 and 350 / 351.
+// channels, and workgroups that walk them in step meet there; measured, from the first k / from different ones, narrow kernel, 2 columns (8 and 16 alike):
+//   rows of 16 KB  70B shape, gate/up 156.4 / 141.6 us (8 columns 6.6 TB/s), QKV 35.7 / 33.0, lm_head 90.1 / 81.4; QKV of 64 KV heads 81.0 / 70.8
+//           24 KB  QKV 60.4 / 59.4, O 57.2 / 55.8, gate/up 121.9 / 119.8 (12288 wide); down 38.0 / 35.7
+//           32 KB  gate/up 276 / 209, O 97.6 / 84.7, QKV 137.4 / 127.0 (16384 wide); down 81.0 / 66.2
+//           40 KB  QKV 173.5 / 171.6, O 167.6 / 165.3 (20480 wide); down 107.2 / 104.2
+//      48, 56 KB  down 41.1 / 39.7, 77.0 / 75.2
+// Not where rows are 8 KB or no multiple of it: 7B and 13B shapes, 2 blocks and the head, 2 columns 231 / 233 and 310 / 312, 12 columns 261 / 265 and
+// 350 / 351.
 inline bool gemm_rounds(int K) { return K % 4096 == 0 && K >= 8192; }
 
 // Launch-shape overrides for measurements, read from the environment ONCE by d3_create (0 / default = the library's

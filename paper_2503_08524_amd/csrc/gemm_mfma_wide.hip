@@ -359,7 +359,9 @@ int launch_kernel(const GemvArgs& a, int groups, int ks, hipStream_t s) {
 }
 
 // Slices that begin at different turns (see gemm_rounds): here also rows of 8 KB, where a slice is long enough for the starts to spread (lm_head of the
-// 7B shape at 32 columns, 32 turns, 52.8 -> 47.7 us; QKV and gate/up, 8 turns a slice, do not gain, and at 128 columns O and down lose).
+// 7B shape at 32 columns, 32 turns, 52.8 -> 47.7 us; QKV and gate/up, 8 turns a slice, do not gain, and at 128 columns O and down lose).  What a launch
+// takes without it, against with it: 20 and 32 columns, 70B shape gate/up 1.07, lm_head 1.10 to 1.13, rows of 24 KB 1.03 to 1.16, of 32 KB
+// 1.08 to 1.29; 33 to 64 columns, 7B shape gate/up 1.05, rows of 16 and 24 KB 1.00 to 1.07, of 32 KB O 1.08 to 1.09, but QKV (two row tiles a wave) 0.93 to 0.95.
 template <int MODE, int RT, int CT, int W>
 int launch_one(const GemvArgs& a, int groups, int ks, hipStream_t s) {
     if constexpr (CT <= 4) {
