@@ -82,11 +82,7 @@ __device__ __forceinline__ void attn_merge_publish(const AttnArgs& a, int split,
             const float r = o / L;
             const size_t oi = (size_t)ce * a.H * HD + (size_t)he * HD + t;
             if (FUSED) st_agent(&a.out[oi], r); else a.out[oi] = r;
-            if (a.out_hi) {
-                const uint32_t hb = f32_to_bf16(r);
-                a.out_hi[oi] = (bf16_t)hb;
-                a.out_lo[oi] = (bf16_t)f32_to_bf16(r - bf16_to_f32(hb));
-            }
+            if (a.out_split) store_split1(a.out_split + ce * split_pitch(a.H * HD), he * HD + t, r);
             continue;
         }
         const size_t pidx = ((size_t)ce * a.H + he) * a.n_splits + split;
@@ -156,11 +152,7 @@ __device__ __forceinline__ void attn_merge_publish(const AttnArgs& a, int split,
         const float r = o[i] / L[i];
         const size_t oi = (size_t)ce * a.H * HD + (size_t)(h0 + ge % GH) * HD + idx % HD;
         if (FUSED) st_agent(&a.out[oi], r); else a.out[oi] = r;
-        if (a.out_hi) {
-            const uint32_t hb = f32_to_bf16(r);
-            a.out_hi[oi] = (bf16_t)hb;
-            a.out_lo[oi] = (bf16_t)f32_to_bf16(r - bf16_to_f32(hb));
-        }
+        if (a.out_split) store_split1(a.out_split + ce * split_pitch(a.H * HD), (h0 + ge % GH) * HD + idx % HD, r);
     }
 }
 

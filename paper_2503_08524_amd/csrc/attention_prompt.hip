@@ -301,15 +301,7 @@ __global__ __launch_bounds__(512, 2) void attn_prompt_kernel(AttnArgs a, SeqRuns
         if (c >= c_end) continue;
         const float4 u = o[en * 32 + ((2 * part) ^ en)], w = o[en * 32 + ((2 * part + 1) ^ en)];
         const float f[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
-        uint32_t hb[8], lb[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            hb[i] = f32_to_bf16(f[i]);
-            lb[i] = f32_to_bf16(f[i] - bf16_to_f32(hb[i]));
-        }
-        const size_t oi = (size_t)c * a.H * HD + (size_t)(h0 + (32 * wave + en) % GH) * HD + 8 * part;
-        *reinterpret_cast<uint4*>(a.out_hi + oi) = make_uint4(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16), hb[4] | (hb[5] << 16), hb[6] | (hb[7] << 16));
-        *reinterpret_cast<uint4*>(a.out_lo + oi) = make_uint4(lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16), lb[4] | (lb[5] << 16), lb[6] | (lb[7] << 16));
+        store_split8(a.out_split + c * split_pitch(a.H * HD), (size_t)(h0 + (32 * wave + en) % GH) * HD + 8 * part, f);
     }
 }
 
@@ -338,9 +330,9 @@ int launch_t(const AttnArgs& a, const SeqRuns& runs, hipStream_t s) {
 }  // namespace
 
 // Requirements (checked by the caller): hd 128, group size 1, 2, 4 or 8, q rotated and the runs' K/V rows in the cache; every run
-// holds at least one column; out_hi / out_lo set (a.out is not written).
+// holds at least one column; out_split set (a.out is not written).
 int launch_attention_prompt(const AttnArgs& a, const SeqRuns& runs, int kv_dtype, hipStream_t s) {
-    if (a.hd != 128 || runs.n < 1 || runs.n > kMaxCols || !a.out_hi || !a.out_lo) return (int)hipErrorInvalidValue;
+    if (a.hd != 128 || runs.n < 1 || runs.n > kMaxCols || !a.out_split) return (int)hipErrorInvalidValue;
     if (kv_dtype == 0) return launch_t<float>(a, runs, s);
     if (kv_dtype == 2) return launch_t<f16_t>(a, runs, s);
     return (int)hipErrorInvalidValue;

@@ -23,7 +23,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {          // byte offsets into the workspace
-    size_t x, qkv, attn_o, act, part_o, part_ml, tickets, logits, s_hi, s_lo, f_hi, f_lo, inv_freq, rope_cs, n_hi, n_lo, ssq, h_skip, gemm_part, gemm_tickets, row0, col_at, h_last, total;
+    size_t x, qkv, attn_o, act, part_o, part_ml, tickets, logits, s_split, f_split, inv_freq, rope_cs, n_split, ssq, h_skip, gemm_part, gemm_part_bytes, gemm_tickets, row0, col_at, h_last, total;
 };
 
 // The vector-ALU GEMV stages one column of its input in LDS.
@@ -72,7 +72,9 @@ size_t gemm_part_bytes(const d3_model_desc& d, size_t C, bool prompt_passes) {
     if (!prompt_passes) return kGemmPartBytes;
     const size_t qkv = (size_t)(d.n_heads + 2 * d.n_kv_heads) * d.head_dim, residual = d.d_model, pairs = d.d_ffn;
     const size_t row_blocks = std::max(std::max((qkv + 255) / 256, (residual + 255) / 256), (pairs + 127) / 128);
-    return std::min(std::max(row_blocks * ((C + 127) / 128) * kPromptMaxParts * kPromptPartTile, kGemmPartBytes), kPromptPartBytes);
+    const size_t parts = std::min(std::max(row_blocks * ((C + 127) / 128) * kPromptMaxParts * kPromptPartTile, kGemmPartBytes), kPromptPartBytes);
+    const int longest = std::max(std::max(d.d_model, d.d_ffn), d.n_heads * d.head_dim);
+    return C > 128 && longest >= kPromptCutK ? kPromptPartBytes256 : parts;
 }
 
 // C columns of fp32 activations, CS columns of bf16 hi/lo splits (the matrix-core projections read whole column tiles:
@@ -94,17 +96,15 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
     l.part_ml = take(PC * d.n_heads * kMaxSplits * 2 * 4);
     l.tickets = take(C * d.n_heads * 4);
     l.logits = take(PC * (size_t)d.vocab * 4);                        // one row per sequence
-    l.s_hi = take(CS * s_dim * 2);
-    l.s_lo = take(CS * s_dim * 2);
-    l.f_hi = take(CS * (size_t)d.d_ffn * 2);
-    l.f_lo = take(CS * (size_t)d.d_ffn * 2);
+    l.s_split = take(CS * split_pitch(s_dim) * 2);
+    l.f_split = take(CS * split_pitch(d.d_ffn) * 2);
     l.inv_freq = take((size_t)d.head_dim / 2 * 8);
     l.rope_cs = take(C * (size_t)d.head_dim / 2 * 8);
-    l.n_hi = take(CS * d.d_model * 2);
-    l.n_lo = take(CS * d.d_model * 2);
+    l.n_split = take(CS * split_pitch(d.d_model) * 2);
     l.ssq = take(C * kSsqStride * 4);
     l.h_skip = take(PC * d.d_model * 4);                              // decode passes only
-    l.gemm_part = take(with_gemm_part ? gemm_part_bytes(d, C, prompt_passes) : 0);
+    l.gemm_part_bytes = with_gemm_part ? gemm_part_bytes(d, C, prompt_passes) : 0;
+    l.gemm_part = take(l.gemm_part_bytes);
     l.gemm_tickets = take((size_t)kGemmPartTickets * 4);
     l.row0 = take(kMaxCols * 4);
     const bool runs = prompt_passes && shares_passes(d);
@@ -121,7 +121,7 @@ int pass_cols(const d3_model_desc& d) {
     return (int)(need < kPassCols ? need : kPassCols);
 }
 // The caller's workspace serves prompt chunks of up to pass_cols() columns.
-Layout make_layout(const d3_model_desc& d) { return make_layout(d, pass_cols(d), pass_cols(d), true, true); }
+Layout make_layout(const d3_model_desc& d) { return make_layout(d, pass_cols(d), (size_t)(pass_cols(d) + 255) / 256 * 256, true, true); }
 
 }  // namespace
 
@@ -150,6 +150,7 @@ Tuning tuning_from_env() {
     t.prefill_cols = pc % 64 == 0 ? pc : 0;
     t.prompt_ks = env_int("D3_PROMPT_KS", 1, kPromptMaxParts, 0);
     t.prompt_row_blocks = env_int("D3_PROMPT_ROW_BLOCKS", 1, 1 << 20, t.prompt_row_blocks);
+    t.prompt_tile = env_int("D3_PROMPT_TILE", 128, 256, 0);
     t.prompt_cus = env_int("D3_PROMPT_CUS", 1, 4096, 0);
     t.prompt_attn_wgs = env_int("D3_PROMPT_ATTN_WGS", 1, 1 << 20, 0);
     return t;
@@ -453,8 +454,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     float* qkv = c->at<float>(c->lay.qkv);
     float* attn_o = c->at<float>(c->lay.attn_o);
     float* act = c->at<float>(c->lay.act);
-    bf16_t *s_hi = c->at<bf16_t>(c->lay.s_hi), *s_lo = c->at<bf16_t>(c->lay.s_lo);
-    bf16_t *f_hi = c->at<bf16_t>(c->lay.f_hi), *f_lo = c->at<bf16_t>(c->lay.f_lo);
+    bf16_t *s_split = c->at<bf16_t>(c->lay.s_split), *f_split = c->at<bf16_t>(c->lay.f_split);
     const bool mfma = c->mfma_ok && !fp32_projections && (ncols >= 2 || shared || !c->alu_ok);
     // a decode pass (every column a different sequence) leaves the rotary embedding and the cache append to the
     // attention kernel (batch 1, 7B shape: the projection's rotate-and-scatter epilogue cost it 1.5 us, the attention
@@ -464,7 +464,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
 
     float2* rope_cs = c->at<float2>(c->lay.rope_cs);
     const int* row0 = c->ragged ? c->at<int>(c->lay.row0) : nullptr;
-    bf16_t *n_hi = c->at<bf16_t>(c->lay.n_hi), *n_lo = c->at<bf16_t>(c->lay.n_lo);   // split of residual * next norm's gain
+    bf16_t* n_split = c->at<bf16_t>(c->lay.n_split);   // split of residual * next norm's gain
     float* ssq = c->at<float>(c->lay.ssq);
     int ssq_parts = 1;
     // Matrix-core path: RMSNorm lives inside the projections.  Whoever writes the residual (the embedding first) also writes the split of
@@ -473,7 +473,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     auto gain_after = [&](int e) -> const float* {
         return static_cast<const float*>(e + 1 < n_ids ? c->layers[ids[e + 1]].attn_norm : c->final_norm);
     };
-    const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_hi, n_lo, ssq};
+    const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_split, ssq};
 
     // a prompt chunk of one sequence (consecutive positions) or of several: tiles of queries share the cache rows they read
     const int grp = d.n_heads / d.n_kv_heads;
@@ -511,7 +511,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         if (!saved && l >= save_before) D3_HIP(save_skip());
         // --- attention half: x += Wo . attention(RoPE(Wq a), cache) with a = RMSNorm(x) ---
         GemvArgs g{};
-        g.part = c->at<float>(c->lay.gemm_part); g.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
         g.K = dm; g.eps = d.rms_eps;
         g.w[0] = w.wq; g.w[1] = w.wk; g.w[2] = w.wv;
         g.rows[0] = qdim; g.rows[1] = kvdim; g.rows[2] = kvdim; g.total_rows = qkv_dim;
@@ -519,7 +519,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         void* k_layer = c->k_cache + (size_t)l * c->kv_layer_bytes();
         void* v_layer = c->v_cache + (size_t)l * c->kv_layer_bytes();
         if (mfma) {
-            g.x_hi = n_hi; g.x_lo = n_lo; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = ssq_parts;
+            g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = ssq_parts;
             const bool rope_in_qkv = qtile && gemm_prompt_takes(g, MODE_QKV_ROPE, c->tn);
             {
                 Timed t(c, D3_K_QKV, s);
@@ -548,7 +548,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         at.ncols = ncols; at.H = d.n_heads; at.H_kv = d.n_kv_heads; at.hd = hd; at.max_seq = d.max_seq;
         at.split_len = split_len; at.n_splits = n_splits;
         at.part_o = c->at<float>(c->lay.part_o); at.part_ml = c->at<float>(c->lay.part_ml); at.tickets = c->at<int>(c->lay.tickets);
-        at.out = attn_o; at.out_hi = mfma ? s_hi : nullptr; at.out_lo = mfma ? s_lo : nullptr;
+        at.out = attn_o; at.out_split = mfma ? s_split : nullptr;
         at.rope_cs = rope_in_attn ? rope_cs : nullptr;
         at.qtile = qtile ? 1 : 0;
         at.row0 = row0;
@@ -559,7 +559,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
                 own.ncols = runs.col[r + 1] - col;
                 own.cm = ColMap{0, 1, own.ncols, runs.pos[r], runs.seq[r]};
                 own.q += (size_t)col * qkv_dim;
-                own.out += (size_t)col * qdim; own.out_hi += (size_t)col * qdim; own.out_lo += (size_t)col * qdim;
+                own.out += (size_t)col * qdim; own.out_split += col * split_pitch(qdim);
                 pick_splits(c, own.ncols, runs.pos[r] + own.ncols, c->attn_wgs_per_cu * c->n_cu, &own.split_len, &own.n_splits, true);
                 Timed t(c, D3_K_ATTN, s);
                 D3_HIP(launch_attention(own, d.kv_dtype, true, s));
@@ -571,13 +571,13 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         }
 
         GemvArgs o{};
-        o.part = c->at<float>(c->lay.gemm_part); o.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        o.part = c->at<float>(c->lay.gemm_part); o.part_bytes = c->lay.gemm_part_bytes; o.part_tickets = c->at<int>(c->lay.gemm_tickets);
         o.K = qdim; o.w[0] = w.wo; o.rows[0] = dm; o.total_rows = dm; o.out = x; o.out_stride = dm; o.ncols = ncols;
         {
             Timed t(c, D3_K_OPROJ, s);
             if (mfma) {
-                o.x_hi = s_hi; o.x_lo = s_lo; o.x_stride = qdim;
-                o.out_hi = n_hi; o.out_lo = n_lo; o.gain_next = static_cast<const float*>(w.mlp_norm); o.ssq_out = ssq;
+                o.x_split = s_split; o.x_stride = qdim;
+                o.out_split = n_split; o.gain_next = static_cast<const float*>(w.mlp_norm); o.ssq_out = ssq;
                 D3_HIP(launch_gemm_mfma(o, MODE_RESID, c->n_cu, c->tn, s, &ssq_parts));
             }
             else { o.x = attn_o; o.x_stride = qdim; D3_HIP(alu(o, 0, ncols, MODE_RESID, false)); }
@@ -585,18 +585,18 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
 
         // --- SwiGLU half: x += Wd (silu(Wg m) * (Wu m)) with m = RMSNorm(x) ---
         GemvArgs u{};
-        u.part = c->at<float>(c->lay.gemm_part); u.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        u.part = c->at<float>(c->lay.gemm_part); u.part_bytes = c->lay.gemm_part_bytes; u.part_tickets = c->at<int>(c->lay.gemm_tickets);
         u.K = dm; u.eps = d.rms_eps; u.w[0] = w.w_gate; u.w[1] = w.w_up; u.rows[0] = F; u.rows[1] = F; u.total_rows = F;
         u.out_stride = F; u.ncols = ncols;
         GemvArgs dn{};
-        dn.part = c->at<float>(c->lay.gemm_part); dn.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        dn.part = c->at<float>(c->lay.gemm_part); dn.part_bytes = c->lay.gemm_part_bytes; dn.part_tickets = c->at<int>(c->lay.gemm_tickets);
         dn.K = F; dn.w[0] = w.w_down; dn.rows[0] = dm; dn.total_rows = dm; dn.out = x; dn.out_stride = dm; dn.ncols = ncols;
         if (mfma) {
-            u.x_hi = n_hi; u.x_lo = n_lo; u.x_stride = dm; u.ssq_in = ssq; u.ssq_parts = ssq_parts;
-            u.out = nullptr; u.out_hi = f_hi; u.out_lo = f_lo;
+            u.x_split = n_split; u.x_stride = dm; u.ssq_in = ssq; u.ssq_parts = ssq_parts;
+            u.out = nullptr; u.out_split = f_split;
             { Timed t(c, D3_K_GATE_UP, s); D3_HIP(launch_gemm_mfma(u, MODE_SWIGLU, c->n_cu, c->tn, s)); }
-            dn.x_hi = f_hi; dn.x_lo = f_lo; dn.x_stride = F;
-            dn.out_hi = n_hi; dn.out_lo = n_lo; dn.gain_next = gain_after(e); dn.ssq_out = ssq;
+            dn.x_split = f_split; dn.x_stride = F;
+            dn.out_split = n_split; dn.gain_next = gain_after(e); dn.ssq_out = ssq;
             { Timed t(c, D3_K_EMPTY, s); }
             { Timed t(c, D3_K_DOWN, s); D3_HIP(launch_gemm_mfma(dn, MODE_RESID, c->n_cu, c->tn, s, &ssq_parts)); }
         } else {
@@ -612,11 +612,11 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     if (!saved) D3_HIP(save_skip());
     if (head) {
         GemvArgs g{};
-        g.part = c->at<float>(c->lay.gemm_part); g.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
         g.K = dm; g.eps = d.rms_eps; g.w[0] = c->lm_head; g.rows[0] = d.vocab; g.total_rows = d.vocab;
         g.out = head->logits; g.out_stride = d.vocab; g.ncols = head->n_cols;
         if (mfma) {
-            g.x_hi = n_hi + (size_t)head->first_col * dm; g.x_lo = n_lo + (size_t)head->first_col * dm; g.x_stride = dm;
+            g.x_split = n_split + head->first_col * split_pitch(dm); g.x_stride = dm;
             g.ssq_in = ssq + (size_t)head->first_col * kSsqStride; g.ssq_parts = ssq_parts;
             Timed t(c, D3_K_LM_HEAD, s);
             D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s));
@@ -683,14 +683,14 @@ int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin
         const HeadOut head{0, B, logits, next_tok};
         return forward(c, tokens, last, B, all.data(), d.n_layers, hidden_dump, 0, B, &head, s, -1, B, 0, nullptr, nullptr, true);
     }
-    bf16_t *n_hi = c->at<bf16_t>(c->lay.n_hi), *n_lo = c->at<bf16_t>(c->lay.n_lo);
+    bf16_t* n_split = c->at<bf16_t>(c->lay.n_split);
     float* ssq = c->at<float>(c->lay.ssq);
-    D3_HIP(launch_gain_split(h_last, dm, static_cast<const float*>(c->final_norm), dm, B, n_hi, n_lo, ssq, s));
+    D3_HIP(launch_gain_split(h_last, dm, static_cast<const float*>(c->final_norm), dm, B, n_split, ssq, s));
     GemvArgs g{};
-    g.part = c->at<float>(c->lay.gemm_part); g.part_tickets = c->at<int>(c->lay.gemm_tickets);
+    g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
     g.K = dm; g.eps = d.rms_eps; g.w[0] = c->lm_head; g.rows[0] = d.vocab; g.total_rows = d.vocab;
     g.out = logits; g.out_stride = d.vocab; g.ncols = B;
-    g.x_hi = n_hi; g.x_lo = n_lo; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1;
+    g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1;
     { Timed t(c, D3_K_LM_HEAD, s); D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s)); }
     D3_HIP(launch_argmax(logits, d.vocab, B, next_tok, s));
     for (int a = 0; a < B && n_alone > 0; ++a) {       // unequal prompts: these sequences' rows of the head are written again
@@ -886,14 +886,14 @@ int fill_recompute(d3_ctx* c, int pos_begin, int pos_end, hipStream_t s) {
         void* k_layer = c->k_cache + (size_t)l * c->kv_layer_bytes();
         void* v_layer = c->v_cache + (size_t)l * c->kv_layer_bytes();
         GemvArgs g{};
-        g.part = c->at<float>(c->lay.gemm_part); g.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
         g.K = dm; g.eps = d.rms_eps; g.w[0] = w.wk; g.w[1] = w.wv; g.rows[0] = kvdim; g.rows[1] = kvdim; g.total_rows = 2 * kvdim;
         g.out = kv; g.out_stride = 2 * kvdim; g.ncols = B;
         if (mfma) {
-            bf16_t *n_hi = c->at<bf16_t>(c->lay.n_hi), *n_lo = c->at<bf16_t>(c->lay.n_lo);
+            bf16_t* n_split = c->at<bf16_t>(c->lay.n_split);
             float* ssq = c->at<float>(c->lay.ssq);
-            D3_HIP(launch_gain_split(h, dm, static_cast<const float*>(w.attn_norm), dm, B, n_hi, n_lo, ssq, s));
-            g.x_hi = n_hi; g.x_lo = n_lo; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1;
+            D3_HIP(launch_gain_split(h, dm, static_cast<const float*>(w.attn_norm), dm, B, n_split, ssq, s));
+            g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1;
             D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s));
             RopeArgs r{};
             r.qkv = kv; r.k_cache = k_layer; r.v_cache = v_layer; r.rope_cs = rope_cs;

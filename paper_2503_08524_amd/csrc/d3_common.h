@@ -8,12 +8,17 @@ namespace d3 {
 
 constexpr int kWave = 64;          // CDNA wavefront
 constexpr int kMaxCols = 32;       // largest batch; columns of a decode pass
-constexpr int kPassCols = 2048;    // most columns of a prompt pass on the matrix-core path (a context holds min(this, n rounded up to 128), n = the cache rows of one sequence, or of all where they share passes)
+// Most columns of a prompt pass on the matrix-core path (a context holds min(this, n rounded up to 128), n = the cache rows of one sequence, or of all where they share
+// passes).  The 7B widths' O and down projections are 128 of the large tiles at 2048 columns, a full round of compute units at 4096: 32 x 2048 tokens, 2 blocks, 79.0 ms in
+// passes of 2048, 74.7 of 4096, 74.9 of 8192.
+constexpr int kPassCols = 4096;
 constexpr int kMaxSplits = 32;     // context splits of one attention head
 constexpr size_t kGemmPartBytes = 16u << 20;   // partial accumulators of a K-sliced wide MFMA projection
 constexpr size_t kPromptPartTile = 128u << 10;  // ... of one K part of a tile (256 rows x 128 columns) of a prompt pass's projection
 constexpr int kPromptMaxParts = 8;             // most K parts of such a tile
 constexpr size_t kPromptPartBytes = 64u << 20; // most of them that a launch may publish (512 parts)
+constexpr size_t kPromptPartBytes256 = 128u << 20;   // the same of a launch of the larger tiles (256 columns), which cuts contractions of kPromptCutK and more
+constexpr int kPromptCutK = 24 * 64;
 constexpr int kGemmPartTickets = 2048;         // row groups such a projection may have
 constexpr int kSsqStride = 512;    // partial sums of squares kept per column (one per workgroup of the producing projection)
 
@@ -73,10 +78,56 @@ __device__ __forceinline__ u32x4 load_stream16(const void* p) {
 __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 __device__ __forceinline__ float bf16_lo(uint32_t pair) { return __uint_as_float(pair << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
-// round to nearest even (finite inputs)
-__device__ __forceinline__ uint32_t f32_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+// Two values rounded to nearest even: one instruction for both (with integer additions, five for each).
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
+// Activations of the matrix-core projections are split x = hi + lo into two bf16 halves, 32 hi halves and then their 32 lo halves: one 128-byte line
+// holds everything of 32 k, which is what a k-step of the MFMAs reads.  A row of K values is split_pitch(K) halves; value k's hi half is number split_at(k)
+// (k, k + 1, ... of one run of 32 are adjacent), its lo half kSplitLo further on.
+constexpr int kSplitLo = 32;
+__host__ __device__ __forceinline__ size_t split_pitch(size_t K) { return 2 * K; }         // (a line more, so that columns start on different channels: no difference)
+__host__ __device__ __forceinline__ size_t split_at(size_t k) { return 2 * k - (k & 31); }
+// Which of the 32 16-byte pieces of 128 split values (four lines) a lane of a half wave takes: hi or lo, and which eight values of the 128.  Sixteen lanes hold a
+// quarter of the banks' rows each, whether hi and lo rows are staged a multiple of 256 bytes apart or half of that more.
+struct SplitPiece {
+    int lo, seg;
+    __device__ __forceinline__ explicit SplitPiece(int lane) : lo(lane >> 3 & 1), seg(8 * ((lane >> 3 ^ lane >> 4) & 1) + (lane & 7)) {}
+    __device__ __forceinline__ int index() const { return 8 * (seg >> 2) + 4 * lo + (seg & 3); }
+};
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
+    hi = bf16_pair(a, b);
+    lo = bf16_pair(a - bf16_lo(hi), b - bf16_hi(hi));
+}
+// four adjacent values, k % 4 == 0; row: their row of the split
+__device__ __forceinline__ void store_split4(bf16_t* row, size_t k, const float (&v)[4]) {
+    uint2 h, l;
+    split_pair(v[0], v[1], h.x, l.x);
+    split_pair(v[2], v[3], h.y, l.y);
+    bf16_t* p = row + split_at(k);
+    *reinterpret_cast<uint2*>(p) = h;
+    *reinterpret_cast<uint2*>(p + kSplitLo) = l;
+}
+// eight, k % 8 == 0
+__device__ __forceinline__ void store_split8(bf16_t* row, size_t k, const float (&v)[8]) {
+    uint4 h, l;
+    split_pair(v[0], v[1], h.x, l.x);
+    split_pair(v[2], v[3], h.y, l.y);
+    split_pair(v[4], v[5], h.z, l.z);
+    split_pair(v[6], v[7], h.w, l.w);
+    bf16_t* p = row + split_at(k);
+    *reinterpret_cast<uint4*>(p) = h;
+    *reinterpret_cast<uint4*>(p + kSplitLo) = l;
+}
+__device__ __forceinline__ void store_split1(bf16_t* row, size_t k, float v) {
+    uint32_t h, l;
+    split_pair(v, 0.f, h, l);
+    bf16_t* p = row + split_at(k);
+    p[0] = (bf16_t)h;
+    p[kSplitLo] = (bf16_t)l;
 }
 
 // Data handed from one workgroup to another inside a kernel is written and read with agent-scope
@@ -122,10 +173,10 @@ __device__ __forceinline__ float wave_sum(float v) { return reduce_row(reduce_ro
 enum GemvMode { MODE_STORE = 0, MODE_RESID = 1, MODE_SWIGLU = 2, MODE_QKV_ROPE = 3 };
 
 struct GemvArgs {
-    // activations: fp32 [ncols][x_stride] (ALU path) or bf16 hi/lo halves [.][x_stride] (MFMA path)
+    // activations: fp32 [ncols][x_stride] (ALU path) or their split into bf16 halves [.][split_pitch(K)] (MFMA path)
     const float* x;
-    const bf16_t* x_hi;
-    const bf16_t* x_lo;
+    const bf16_t* x_split;
+    size_t part_bytes;   // what part holds
     int x_stride;
     const float* gain;   // RMSNorm gain [K] when the norm is fused (ALU path), else nullptr
     float eps;
@@ -135,8 +186,8 @@ struct GemvArgs {
     int rows[3];
     int total_rows;      // output rows
     float* out;          // fp32 [ncols][out_stride]
-    bf16_t* out_hi;      // optional split copy of the output for an MFMA consumer
-    bf16_t* out_lo;
+    bf16_t* out_split;   // optional split copy [ncols][split_pitch(out_stride)] of the output for an MFMA consumer
+    const float* gain_next;   // [total_rows], see ssq_out
     int out_stride;
     int ncols;
     // MODE_QKV_ROPE only: rotate q and k, append k and v to this block's cache
@@ -148,14 +199,13 @@ struct GemvArgs {
     const int2* col_at;      // prompt pass on the matrix cores, instead of cm: (sequence, cache row) of every column
     int H, H_kv, hd, max_seq, kv_dtype;
     // MFMA path, RMSNorm folded into the projections around it.  A projection whose input is a normalised
-    // residual (STORE, SWIGLU) gets x * gain pre-split in x_hi/x_lo and scales its sums by
+    // residual (STORE, SWIGLU) gets x * gain pre-split in x_split and scales its sums by
     // 1/sqrt(sum(ssq_in[col][0..ssq_parts)) / K + eps); a residual projection (RESID) with ssq_out set also
-    // writes the split of (new x) * gain_next to out_hi/out_lo and its workgroup's sum of squares of the new x
+    // writes the split of (new x) * gain_next to out_split and its workgroup's sum of squares of the new x
     // to ssq_out[col][workgroup].
     const float* ssq_in;     // [ncols][kSsqStride]
     int ssq_parts;
     float* ssq_out;          // [ncols][kSsqStride]
-    const float* gain_next;  // [total_rows]
     // wide MFMA kernel (17..32 columns), K cut into slices: partial accumulators and one arrival counter per row
     // group (zero between launches)
     float* part;
@@ -168,7 +218,7 @@ struct GemvArgs {
 // What the first loads of a matrix-core projection need of the arguments, requested together: read as they come up, each is a round trip to memory
 // that the next one waits behind.
 __device__ __forceinline__ void gemm_take_args(const GemvArgs& a) {
-    asm volatile("" :: "s"(a.x_hi), "s"(a.x_lo), "s"(a.x_stride), "s"(a.w[0]), "s"(a.w[1]), "s"(a.w[2]), "s"(a.rows[0]), "s"(a.rows[1]),
+    asm volatile("" :: "s"(a.x_split), "s"(a.w[0]), "s"(a.w[1]), "s"(a.w[2]), "s"(a.rows[0]), "s"(a.rows[1]),
                        "s"(a.K), "s"(a.total_rows), "s"(a.ncols), "s"(a.ssq_in), "s"(a.ssq_parts));
 }
 // The matrix that output row `row` of a row-stacked projection belongs to, and the row's number in it (a choice among three scalars: by index, the
@@ -199,7 +249,8 @@ inline bool gemm_rounds(int K) { return K % 4096 == 0 && K >= 8192; }
 // D3_MFMA_WIDE=0: no panel kernel (passes are limited to kMaxCols columns); D3_WIDE_RT, D3_WIDE_KS: row tiles per wave
 // and K slices of the panel kernel; D3_WIDE_SPLIT_MB: matrix size above which a pass of more than 64 columns runs as
 // two 64-column launches; D3_ATTN_MFMA=0: grouped-query and query-tile attention on the vector ALUs;
-// D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most 2048); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8; a contraction without two stages for every part stays whole);
+// D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most kPassCols); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8; a contraction without two stages for every part stays whole);
+// D3_PROMPT_TILE: 128 or 256, columns of a tile of the prompt pass's projections (default: the launcher's estimate; D3_PROMPT_KS and D3_PROMPT_CUS mean tiles of 128 unless it says 256);
 // D3_PROMPT_ROW_BLOCKS: fewest blocks of 256 rows for which 65..128 columns take the LDS-tiled kernel;
 // D3_PROMPT_CUS: compute units a round of its tiles is taken to have;
 // D3_PROMPT_ATTN_WGS: fewest workgroups (128 (query, head) pairs each) for which a prompt pass, shared or not, takes the whole-context attention kernel; D3_GEMV_WGS_PER_CU: workgroups
@@ -213,7 +264,7 @@ struct Tuning {
     bool attn_mfma = true;
     int attn_min_split = 128;
     int prefill_cols = 0;
-    int prompt_ks = 0, prompt_cus = 0, prompt_row_blocks = 20;
+    int prompt_ks = 0, prompt_cus = 0, prompt_row_blocks = 20, prompt_tile = 0;
     int prompt_attn_wgs = 0;
 };
 Tuning tuning_from_env();
@@ -224,18 +275,21 @@ int launch_gemv_alu(const GemvArgs& a, int weight_dtype, int mode, bool norm, in
 int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups = nullptr);
 int launch_gemm_mfma_wide(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // 17..128 columns
 bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn);   // launch_gemm_mfma sends the launch to launch_gemm_prompt
+// gemm_prompt_256.hip, which launch_gemm_prompt chooses by this estimate (in its own unit; infinite: not for that kernel)
+double gemm_prompt_256_cost(const GemvArgs& a, int mode, int n_cu);
+int launch_gemm_prompt_256(const GemvArgs& a, int mode, int n_cu, hipStream_t s, int* n_groups);
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // up to kPassCols columns: LDS-tiled, compute-bound
 size_t gemv_alu_max_cols(int K, int weight_dtype);   // columns one ALU launch can take (LDS bound)
 
-// hi + lo = x * gain (bf16 halves), ssq[col * kSsqStride] = sum(x^2)
+// split = x * gain (bf16 halves), ssq[col * kSsqStride] = sum(x^2)
 int launch_gain_split(const float* x, int x_stride, const float* gain, int K, int ncols,
-                      bf16_t* hi, bf16_t* lo, float* ssq, hipStream_t s);
+                      bf16_t* split, float* ssq, hipStream_t s);
 
 // ---------------- the rest of a block ----------------
 // x[c][:] = E[token(c)][:], and the pass's rotary table rope_cs[c][j] = (cos, sin)((pos(c) - row0[seq(c)]) * inv_freq[j])
 // (row0 optional: the first cache row of each sequence of a left-padded batch)
 // What a pass on the matrix-core path starts from, beside x (gain NULL: not wanted; bf16 tables only): launch_gain_split's outputs.
-struct EmbedSplit { const float* gain; bf16_t *hi, *lo; float* ssq; };
+struct EmbedSplit { const float* gain; bf16_t* split; float* ssq; };
 // The columns of `runs`: tokens [B][P] of the cache rows from pos_begin on; also col_at[c] = (sequence, cache row) of every column.
 int launch_embed_runs(const void* tok_emb, const int32_t* tokens, const SeqRuns& runs, int P, int pos_begin, int ncols, int d, int vocab,
                       float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, int2* col_at, const EmbedSplit& split, hipStream_t s);   // bf16 table
@@ -271,8 +325,7 @@ struct AttnArgs {
     float* part_ml;        // [ncols][H][n_splits][2]  (max, sum)
     int* tickets;          // [ncols][H] arrival counters, zero between launches
     float* out;            // [ncols][H*hd]
-    bf16_t* out_hi;        // optional split copy
-    bf16_t* out_lo;
+    bf16_t* out_split;     // optional split copy [ncols][split_pitch(H*hd)]
     // set by launch_attention: what the kernel divides by: columns per position, query heads per KV head, split length
     Divisor by_b, by_group, by_split;
 };

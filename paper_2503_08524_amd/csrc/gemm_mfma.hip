@@ -46,38 +46,49 @@ __device__ __forceinline__ void tile_load(TileRegs& r, const bf16_t* row0_k0, si
 #pragma unroll
     for (int q = 0; q < 4; ++q) r.q[q] = load_stream16(row0_k0 + (size_t)(4 * q + (lane >> 4)) * row_stride + (k - k0));
 }
-__device__ __forceinline__ void tile_load_cached(TileRegs& r, const bf16_t* row0_k0, size_t row_stride, int k0, int K) {
+// ... of one half of split activations (row0: the tile's first row, from the half's first value on)
+__device__ __forceinline__ void tile_load_cached(TileRegs& r, const bf16_t* row0, int k0, int K) {
     const int lane = threadIdx.x & 63;
-    int k = k0 + (lane & 15) * 8;
-    k = k <= K - 8 ? k : K - 8;
+    const int at = min(2 * k0 + (int)split_at((lane & 15) * 8), (int)split_at(K - 8));         // k0 is a multiple of 32
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const uint4 v = *reinterpret_cast<const uint4*>(row0_k0 + (size_t)(4 * q + (lane >> 4)) * row_stride + (k - k0));
+        const uint4 v = *reinterpret_cast<const uint4*>(row0 + (4 * q + (lane >> 4)) * split_pitch(K) + at);
         r.q[q] = u32x4{v.x, v.y, v.z, v.w};
     }
 }
-// the packed B tile of up to 8 columns: tile rows 0..7 are the hi halves of columns 0..7, rows 8..15 their lo halves
-__device__ __forceinline__ void tile_load_packed(TileRegs& r, const bf16_t* hi_k0, const bf16_t* lo_k0, size_t row_stride, int k0, int K) {
+// The packed B tile of up to 8 columns: tile rows 0..7 are the hi halves of columns 0..7, rows 8..15 their lo halves.  32 lanes read a column's 512 bytes (whole
+// lines; 64 bytes of every line twice cost a step at the 70B widths 0.5 %), in the order of SplitPiece.
+__device__ __forceinline__ void tile_load_packed(TileRegs& r, const bf16_t* split, int k0, int K) {
     const int lane = threadIdx.x & 63;
-    int k = k0 + (lane & 15) * 8;
-    k = k <= K - 8 ? k : K - 8;
+    const int at = min(2 * k0 + 8 * SplitPiece(lane).index(), 2 * K - 8);      // a ragged last turn re-reads valid bytes
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const bf16_t* base = q < 2 ? hi_k0 : lo_k0;
-        const uint4 v = *reinterpret_cast<const uint4*>(base + (size_t)(4 * (q & 1) + (lane >> 4)) * row_stride + (k - k0));
+        const uint4 v = *reinterpret_cast<const uint4*>(split + (2 * q + (lane >> 5)) * split_pitch(K) + at);
         r.q[q] = u32x4{v.x, v.y, v.z, v.w};
     }
+}
+__device__ __forceinline__ void frags_of(const char* tile, u32x4 (&frag)[U]) {
+    const int lane = threadIdx.x & 63;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        frag[u] = *reinterpret_cast<const u32x4*>(tile + (lane & 15) * kTileRowBytes + u * 64 + (lane >> 4) * 16);
+    __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void packed_to_frags(const TileRegs& r, char* tile, u32x4 (&frag)[U]) {
+    const int lane = threadIdx.x & 63;
+    const SplitPiece p(lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<u32x4*>(tile + (2 * q + (lane >> 5) + 8 * p.lo) * kTileRowBytes + p.seg * 16) = r.q[q];
+    frags_of(tile, frag);
 }
 __device__ __forceinline__ void tile_to_frags(const TileRegs& r, char* tile, u32x4 (&frag)[U]) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         *reinterpret_cast<u32x4*>(tile + (4 * q + (lane >> 4)) * kTileRowBytes + (lane & 15) * 16) = r.q[q];
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-        frag[u] = *reinterpret_cast<const u32x4*>(tile + (lane & 15) * kTileRowBytes + u * 64 + (lane >> 4) * 16);
-    __builtin_amdgcn_wave_barrier();
+    frags_of(tile, frag);
 }
 
 // ROUND: a wave's turns begin at turn (workgroup / 8) modulo their number and go round (gemm_rounds says where).  The eight workgroups of one start go
@@ -120,12 +131,12 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
     auto issue = [&](int ks0) {
         const int k0 = ks0 * 32;
         if constexpr (PACK) {
-            tile_load_packed(gb[0], a.x_hi + k0, a.x_lo + k0, a.x_stride, k0, K);
+            tile_load_packed(gb[0], a.x_split, k0, K);
         } else {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                tile_load_cached(gb[2 * t], a.x_hi + (size_t)(t * 16) * a.x_stride + k0, a.x_stride, k0, K);
-                tile_load_cached(gb[2 * t + 1], a.x_lo + (size_t)(t * 16) * a.x_stride + k0, a.x_stride, k0, K);
+                tile_load_cached(gb[2 * t], a.x_split + t * 16 * split_pitch(K), k0, K);
+                tile_load_cached(gb[2 * t + 1], a.x_split + t * 16 * split_pitch(K) + kSplitLo, k0, K);
             }
         }
 #pragma unroll
@@ -136,15 +147,15 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
         u32x4 bf[NB][U];
         const int k1 = ks_next * 32;
         if constexpr (PACK) {
-            tile_to_frags(gb[0], tile, bf[0]);
-            if (next) tile_load_packed(gb[0], a.x_hi + k1, a.x_lo + k1, a.x_stride, k1, K);
+            packed_to_frags(gb[0], tile, bf[0]);
+            if (next) tile_load_packed(gb[0], a.x_split, k1, K);
         } else {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 tile_to_frags(gb[2 * t], tile, bf[2 * t]);
-                if (next) tile_load_cached(gb[2 * t], a.x_hi + (size_t)(t * 16) * a.x_stride + k1, a.x_stride, k1, K);
+                if (next) tile_load_cached(gb[2 * t], a.x_split + t * 16 * split_pitch(K), k1, K);
                 tile_to_frags(gb[2 * t + 1], tile, bf[2 * t + 1]);
-                if (next) tile_load_cached(gb[2 * t + 1], a.x_lo + (size_t)(t * 16) * a.x_stride + k1, a.x_stride, k1, K);
+                if (next) tile_load_cached(gb[2 * t + 1], a.x_split + t * 16 * split_pitch(K) + kSplitLo, k1, K);
             }
         }
 #pragma unroll
@@ -249,11 +260,7 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
             sq[col][r * 16 + 4 * (l >> 4) + e] = v * v;
             split = v * a.gain_next[row];
         }
-        if (a.out_hi) {
-            const uint32_t hb = f32_to_bf16(split);
-            a.out_hi[oi] = (bf16_t)hb;
-            a.out_lo[oi] = (bf16_t)f32_to_bf16(split - bf16_to_f32(hb));
-        }
+        if (a.out_split) store_split1(a.out_split + col * split_pitch(a.out_stride), row, split);
     }
     if (MODE == MODE_RESID && a.ssq_out) {
         __syncthreads();
@@ -288,7 +295,7 @@ int launch_mode(const GemvArgs& a, int mode, int rt, int tiles, int waves, size_
 }  // namespace
 
 // Requirements (checked by the caller): bf16 weights; K % 32 == 0; total_rows and every rows[m]
-// multiples of 16; 1 <= ncols <= 32; x_hi/x_lo hold 32 rows of x_stride elements (rows beyond
+// multiples of 16; 1 <= ncols <= 32; x_split holds 32 rows (rows beyond
 // ncols may hold anything finite or not: their columns are never written); with ssq_out, total_rows / 16 <=
 // kSsqStride (every workgroup owns a slot).
 int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {

@@ -100,15 +100,16 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
         }
     }
 
-    // this thread's pieces of the panel: start of the activation row, k offset inside a turn, LDS offset
+    // this thread's pieces of the panel: start of the column, LDS offset; 32 threads read a column's 512 bytes of a turn (64 bytes of every line twice: 1 %)
     const bf16_t* psrc[PBT];
     int pdst[PBT];
-    const int pseg = tid & 15;
+    const SplitPiece piece(tid);
+    const int pat = 8 * piece.index();
 #pragma unroll
     for (int i = 0; i < PBT; ++i) {
-        const int cidx = tid + i * (W * 64), tb = cidx >> 8, r = (cidx >> 4) & 15;
-        psrc[i] = ((tb & 1) ? a.x_lo : a.x_hi) + (size_t)((tb >> 1) * 16 + r) * a.x_stride;
-        pdst[i] = tb * kTile + r * kPitch + pseg * 16;
+        const int col = (tid + i * (W * 64)) >> 5;
+        psrc[i] = a.x_split + col * split_pitch(K);
+        pdst[i] = (2 * (col >> 4) + piece.lo) * kTile + (col & 15) * kPitch + piece.seg * 16;
     }
 
     f32x4 acc[NA][CT];
@@ -120,11 +121,10 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
     u32x4 pb[PBT];
     TileRegs ga[D][NA];                                // weight tiles of D turns in flight
     auto panel_issue = [&](int t) {
-        int k = kt(t) * (U * 32) + pseg * 8;
-        k = k <= K - 8 ? k : K - 8;
+        const int at = min(2 * kt(t) * (U * 32) + pat, 2 * K - 8);
 #pragma unroll
         for (int i = 0; i < PBT; ++i) {
-            const uint4 v = *reinterpret_cast<const uint4*>(psrc[i] + k);
+            const uint4 v = *reinterpret_cast<const uint4*>(psrc[i] + at);
             pb[i] = u32x4{v.x, v.y, v.z, v.w};
         }
     };
@@ -318,16 +318,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
                 split[0] = v[0] * gn.x; split[1] = v[1] * gn.y; split[2] = v[2] * gn.z; split[3] = v[3] * gn.w;
             }
             if (a.out) *reinterpret_cast<float4*>(a.out + oi) = make_float4(v[0], v[1], v[2], v[3]);
-            if (a.out_hi) {
-                uint32_t hb[4], lb[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    hb[e] = f32_to_bf16(split[e]);
-                    lb[e] = f32_to_bf16(split[e] - bf16_to_f32(hb[e]));
-                }
-                *reinterpret_cast<uint2*>(a.out_hi + oi) = make_uint2(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16));
-                *reinterpret_cast<uint2*>(a.out_lo + oi) = make_uint2(lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16));
-            }
+            if (a.out_split) store_split4(a.out_split + col * split_pitch(a.out_stride), row, split);
         }
     }
     if (MODE == MODE_RESID && a.ssq_out) {             // rows of a column: the 4 lane groups by butterfly, then the waves in order
@@ -389,7 +380,7 @@ int launch_rt(const GemvArgs& a, int ct, int rt, int groups, int ks, hipStream_t
 
 }  // namespace
 
-// Requirements: those of launch_gemm_mfma, 17 <= ncols <= kPassCols (x_hi / x_lo hold kPassCols rows); a.part holds kGemmPartBytes and a.part_tickets
+// Requirements: those of launch_gemm_mfma, 17 <= ncols <= kPassCols (x_split holds kPassCols rows); a.part holds kGemmPartBytes and a.part_tickets
 // kGemmPartTickets zeroed counters (the kernel leaves them zero).
 namespace {
 
@@ -399,9 +390,9 @@ int launch_config(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipSt
 GemvArgs columns_of(const GemvArgs& a, int first, int n) {
     GemvArgs g = a;
     g.ncols = n;
-    g.x_hi += (size_t)first * a.x_stride; g.x_lo += (size_t)first * a.x_stride;
+    g.x_split += first * split_pitch(a.K);
     if (g.out) g.out += (size_t)first * a.out_stride;
-    if (g.out_hi) { g.out_hi += (size_t)first * a.out_stride; g.out_lo += (size_t)first * a.out_stride; }
+    if (g.out_split) g.out_split += first * split_pitch(a.out_stride);
     if (g.ssq_in) g.ssq_in += (size_t)first * kSsqStride;
     if (g.ssq_out) g.ssq_out += (size_t)first * kSsqStride;
     return g;

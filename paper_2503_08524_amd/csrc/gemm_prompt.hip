@@ -1,10 +1,10 @@
-// Tiled GEMM on the matrix cores for the prompt pass, up to 2048 activation columns per launch:
+// Tiled GEMM on the matrix cores for the prompt pass, up to kPassCols activation columns per launch:
 // out[col][row] = sum_k W[row][k] * x[col][k], bf16 weights, activations x = hi + lo (two bf16 halves).
 //
 // With hundreds of columns the contraction is compute-bound (the prompt pass is the one part of the path that is), so
 // the design is the opposite of the skinny kernels': operands are staged in LDS and re-used from there.  A workgroup of
 // eight waves owns a tile of 256 weight rows x 128 columns and walks K in stages of 64: the stage's weight slab (256 rows x
-// 128 bytes) and activation slab (128 columns, hi plane and lo plane) go from global memory straight into LDS
+// 128 bytes) and activation slab (128 columns, a plane of 32 k, hi and lo halves, per k-step) go from global memory straight into LDS
 // (buffer_load_dwordx4 ... lds: 16 bytes per lane, lane l of the wave lands at base + 16 l, one instruction fills eight
 // 128-byte slab rows).  LDS holds three weight slabs and two activation slabs, 160 KB; one workgroup per compute unit.
 //
@@ -52,147 +52,24 @@
 // wave, so a wave finishes silu(gate) * up from its own accumulators.  Operand layouts, RMSNorm folding (1/rms from the
 // producer's partial sums of squares, x * gain and the sum of squares of the new residual handed to the consumer) and
 // epilogues are those of the skinny matrix-core kernels.
-#include <type_traits>
-#include <utility>
+#include <cmath>
 
-#include "d3_common.h"
+#include "gemm_prompt.h"
 
 namespace d3 {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) char lds_char;
-
-constexpr int kBK = 64;                        // k per stage: one MFMA k-step per wave group
-constexpr int kPitch = 2 * kBK;                // bytes per staged row: eight 16-byte segments = one cache line
 constexpr int kTileM = 256, kTileN = 128;      // weight rows and columns of a workgroup tile
-constexpr int kThreads = 512, kWaves = 8;
 constexpr int kABytes = kTileM * kPitch;       // weight slab of a stage
-constexpr int kPlane = kTileN * kPitch;        // one plane of its activation slab (hi, then lo)
+constexpr int kPlane = kTileN * kPitch;        // one plane of its activation slab: 32 k, hi and lo halves
 constexpr int kXBytes = 2 * kPlane;
 constexpr int kLdsX = 3 * kABytes;             // LDS: three weight slabs, two activation slabs
 constexpr int kPromptLds = kLdsX + 2 * kXBytes;        // 160 KB, all there is
 [[maybe_unused]] constexpr int kLoadsW = kABytes / 1024 / kWaves, kLoadsX = kXBytes / 1024 / kWaves, kLoads = kLoadsW + kLoadsX;   // direct loads per wave and stage
-constexpr int RW = 8;                          // 16-row tiles per wave
 constexpr int CW = 2;                          // column tiles a wave finishes (it multiplies 2 CW)
 [[maybe_unused]] constexpr int kSsqCols = kTileN * 16 / kThreads;   // columns a group of 16 threads takes the sums of squares of
 constexpr int kAccWords = RW * CW * 4;         // accumulator words per lane of a finished (half) wave tile
-
-// Instructions stay on their side of this point: what interleaves the MFMAs with loads and reads as written.
-__device__ __forceinline__ void fixed_here() { __builtin_amdgcn_sched_barrier(0); }
-
-__device__ __forceinline__ void store_split(const GemvArgs& a, size_t oi, const float (&v)[4]) {
-    uint32_t hb[4], lb[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        hb[e] = f32_to_bf16(v[e]);
-        lb[e] = f32_to_bf16(v[e] - bf16_to_f32(hb[e]));
-    }
-    *reinterpret_cast<uint2*>(a.out_hi + oi) = make_uint2(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16));
-    *reinterpret_cast<uint2*>(a.out_lo + oi) = make_uint2(lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16));
-}
-// the cache's element type from four fp32 values
-__device__ __forceinline__ void store_row4(float* p, const float (&v)[4]) { *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]); }
-__device__ __forceinline__ void store_row4(f16_t* p, const float (&v)[4]) {
-    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-    half4 h;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) h[e] = (f16_t)fminf(fmaxf(v[e], -65504.f), 65504.f);
-    *reinterpret_cast<half4*>(p) = h;
-}
-
-// ---- epilogues of the projections that only store, from the summed accumulators: lane (i, g) holds column i of a column tile, rows 4g..4g+3 of each
-// row tile.  Wave (wy, wx) of group grp finishes slab rows 128 wy .. + 128 of the columns 64 wx + 32 grp .. + 32.  Row tiles r and r + 4 of a
-// column tile (a gate tile and its up tile, the two dims of a rotation) are a unit: a call stores those of column tile tt whose bit r is set. ----
-constexpr int kUnits = RW / 2;                         // per column tile
-template <int MODE>
-__device__ __forceinline__ void store_tiles(const GemvArgs& a, const f32x4 (&acc)[RW], int tt, unsigned units, int rb, int cb, int tiles, int grp, int wy, int wx,
-                                            const float* inv_rms) {
-    constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
-    constexpr int OT = 2 * RW / SW;                    // output row tiles per workgroup
-    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-    const int cl = wx * 64 + grp * 32 + tt * 16 + li, col = cb * kTileN + cl;
-    const float sc = a.ssq_in ? inv_rms[cl] : 1.0f;
-#pragma unroll
-    for (int r = 0; r < RW / SW; ++r) {
-        if (!(units >> (r % kUnits) & 1)) continue;
-        const int otile = rb * OT + wy * (RW / SW) + r, row = otile * 16 + 4 * lg;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            v[e] = acc[r][e] * sc;
-            if (MODE == MODE_SWIGLU) v[e] = v[e] / (1.0f + expf(-v[e])) * (acc[r + RW / 2][e] * sc);
-        }
-        if (otile < tiles && col < a.ncols) {
-            const size_t oi = (size_t)col * a.out_stride + row;
-            if (a.out) *reinterpret_cast<float4*>(a.out + oi) = make_float4(v[0], v[1], v[2], v[3]);
-            if (a.out_hi) store_split(a, oi, v);
-        }
-    }
-}
-
-// ---- QKV of a prompt pass at head_dim 128: a wave's 128 rows are one head, and row tiles r and r + 4 hold the dims j and j + 64 that one
-// rotation pairs, so q and k are rotated and k and v appended to the cache straight from the accumulators (as a launch of its own
-// over fp32 q, k, v that took 24 us of a 2048-column block at the 7B shape). ----
-struct QkvColumns {
-    int2 at[CW];                                       // (sequence, cache row) of this lane's columns
-    float4 c0[CW][RW / 2], c1[CW][RW / 2];             // (cos, sin) of dims j, j + 1 and j + 2, j + 3
-    __device__ __forceinline__ void load(const GemvArgs& a, int cb, int grp, int wx) {         // all requested before the first store, which they might alias
-        const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-#pragma unroll
-        for (int tt = 0; tt < CW; ++tt) {
-            const int col_raw = cb * kTileN + wx * 64 + grp * 32 + tt * 16 + li, col = col_raw < a.ncols ? col_raw : a.ncols - 1;
-            at[tt] = a.col_at[col];
-#pragma unroll
-            for (int r = 0; r < RW / 2; ++r) {
-                const float2* cs = a.rope_cs + (size_t)col * 64 + 16 * r + 4 * lg;
-                c0[tt][r] = *reinterpret_cast<const float4*>(cs);
-                c1[tt][r] = *reinterpret_cast<const float4*>(cs + 2);
-            }
-        }
-        fixed_here();
-    }
-};
-template <typename T>
-__device__ __forceinline__ void store_qkv(const GemvArgs& a, const f32x4 (&acc)[RW], const QkvColumns& q_cols, int tt, unsigned units, int rb, int cb, int grp, int wy, int wx,
-                                          const float* inv_rms) {
-    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-    const int head = 2 * rb + wy;
-    if (head >= a.H + 2 * a.H_kv) return;
-    const bool is_q = head < a.H, is_v = head >= a.H + a.H_kv;
-    const int kvh = is_v ? head - a.H - a.H_kv : head - a.H;
-    void *const kc = a.k_cache, *const vc = a.v_cache;
-    asm volatile("" :: "s"(kc), "s"(vc));              // two values: the compiler would choose between their places, in a copy on the stack
-    const int cl = wx * 64 + grp * 32 + tt * 16 + li, col = cb * kTileN + cl;
-    if (col >= a.ncols) return;
-    const float sc = inv_rms[cl];
-    const int2 at = q_cols.at[tt];
-    float* q = a.out + (size_t)col * a.out_stride + head * 128;
-    T* row = nullptr;
-    if (!is_q) row = static_cast<T*>(is_v ? vc : kc) + (((size_t)at.x * a.H_kv + kvh) * a.max_seq + at.y) * 128;
-#pragma unroll
-    for (int r = 0; r < RW / 2; ++r) {
-        if (!(units >> r & 1)) continue;
-        const int j = 16 * r + 4 * lg;
-        float lo[4], hi[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { lo[e] = acc[r][e] * sc; hi[e] = acc[r + RW / 2][e] * sc; }
-        if (!is_v) {
-            const float4 c0 = q_cols.c0[tt][r], c1 = q_cols.c1[tt][r];
-            const float cs[4] = {c0.x, c0.z, c1.x, c1.z}, sn[4] = {c0.y, c0.w, c1.y, c1.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                // the two roundings of each are stated: left to the compiler, which product joins the addition unrounded changed with the code around it
-                const float y0 = fmaf(lo[e], cs[e], -(hi[e] * sn[e])), y1 = fmaf(lo[e], sn[e], hi[e] * cs[e]);
-                lo[e] = y0; hi[e] = y1;
-            }
-        }
-        if (is_q) { store_row4(q + j, lo); store_row4(q + j + 64, hi); }
-        else { store_row4(row + j, lo); store_row4(row + j + 64, hi); }
-    }
-}
 
 // ---- residual projections.  The finished sums go through LDS, [128 columns][256 rows] of fp32, so that a wave then takes whole columns and
 // its loads and stores are 512 bytes to 1 KB in a row.  From the accumulators' own layout an instruction touches 16 columns' rows of 32
@@ -207,8 +84,6 @@ __device__ __forceinline__ f32x4* staged(char* lds, int c, int u) { return reint
 static_assert(kPartBytes == (int)kPromptPartTile && kAccWords * kThreads * 4 == kPartBytes, "the workspace is laid out for these");
 #ifdef __HIP_DEVICE_COMPILE__
 struct PartRef { __amdgpu_buffer_rsrc_t buf; int parts, slice; };      // a tile's parts [part][128 columns][256 rows], and which one this is
-// 16 bytes per lane and access, at agent scope (past the XCD's own L2, like st_agent / ld_agent)
-constexpr int kAgent = 16;
 template <int N>
 __device__ __forceinline__ void add_residual(const GemvArgs& a, char* lds, int rb, int cb, int lo, int hi, const PartRef& pr, int wave8, int lane) {
     const int row_raw = rb * kTileM + 4 * lane;
@@ -248,9 +123,9 @@ __device__ __forceinline__ void add_residual(const GemvArgs& a, char* lds, int r
         if (live) {
             const size_t oi = (size_t)(cb * kTileN + column(i)) * a.out_stride + row;
             store_row4(a.out + oi, v);
-            if (a.out_hi) {                            // a normalised projection reads it next: hand it x * gain (and sum(x^2) below)
+            if (a.out_split) {                         // a normalised projection reads it next: hand it x * gain (and sum(x^2) below)
                 const float w[4] = {v[0] * gain.x, v[1] * gain.y, v[2] * gain.z, v[3] * gain.w};
-                store_split(a, oi, w);
+                store_split4(a.out_split + (cb * kTileN + column(i)) * split_pitch(a.out_stride), row, w);
             }
         }
     }
@@ -313,54 +188,6 @@ __device__ __forceinline__ void add_residual_parts(const GemvArgs& a, char* lds,
 }
 #endif
 
-extern __shared__ __attribute__((aligned(16))) char prompt_lds[];
-
-template <int OFF>
-__device__ __forceinline__ u32x4 lds_read_frag(uint32_t addr) {
-    u32x4 v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
-    return v;
-}
-// Fragments are kept as four words and become bf16 vectors at the MFMA: a vector of bf16 that lives across the loop's back
-// edge is taken apart and put together again there, while it may still be in flight.
-__device__ __forceinline__ f32x4 mfma(const u32x4& fa, const u32x4& fb, const f32x4& c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa), __builtin_bit_cast(bf16x8, fb), c, 0, 0, 0);
-}
-template <int N> __device__ __forceinline__ void vm_loads_left() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
-template <int N> __device__ __forceinline__ void lds_reads_left() { asm volatile("s_waitcnt lgkmcnt(%0)" :: "n"(N) : "memory"); }
-// Nothing that uses the fragment moves above this statement, and volatile statements keep their order: after a wait it
-// keeps the MFMAs behind the wait.
-__device__ __forceinline__ void pin_frag(u32x4& v) { asm volatile("" : "+v"(v)); }
-// all LDS reads have arrived, these among them
-__device__ __forceinline__ void all_arrived(u32x4 (&f)[RW]) {
-    lds_reads_left<0>();
-#pragma unroll
-    for (int r = 0; r < RW; ++r) pin_frag(f[r]);
-}
-struct PromptB { u32x4 h, l; };                       // one column tile's activation fragments: hi and lo plane
-__device__ __forceinline__ void all_arrived(PromptB& f) { lds_reads_left<0>(); pin_frag(f.h); pin_frag(f.l); }
-template <int... R>
-__device__ __forceinline__ void read_a_frags(u32x4 (&f)[RW], uint32_t A, std::integer_sequence<int, R...>) {
-    ((f[R] = lds_read_frag<R * 16 * kPitch>(A)), ...);
-}
-// column tile tt of a stage whose activation fragments start at B
-template <int TT>
-__device__ __forceinline__ void read_b_frags(PromptB& f, uint32_t B) {
-    f.h = lds_read_frag<TT * 16 * kPitch>(B);
-    f.l = lds_read_frag<kPlane + TT * 16 * kPitch>(B);
-}
-// 2 N MFMAs: row tiles R0 .. R0 + N - 1 of one column tile, both planes.  The two products of an accumulator stand one after the other: that
-// toggles less than eight row tiles of the hi plane and then eight of the lo plane, and the clock is what the power leaves (the MFMAs
-// alone on random operands 2.03 -> 2.20 PFLOP/s at 2.05 -> 2.22 GHz; 13B shape, 4 x 1024 columns, 4 blocks 16.26 -> 16.05 ms).
-template <int R0, int N>
-__device__ __forceinline__ void mma_hl(f32x4 (&acc)[RW][2 * CW], int tt, const u32x4 (&fa)[RW], const PromptB& fb) {
-#pragma unroll
-    for (int r = R0; r < R0 + N; ++r) {
-        acc[r][tt] = mfma(fa[r], fb.h, acc[r][tt]);
-        acc[r][tt] = mfma(fa[r], fb.l, acc[r][tt]);
-    }
-}
-
 // Launch order of the tiles.  Tiles [0, n_whole) have a workgroup each, the others ks of them, one per part of K.  n_rb row blocks: each
 // XCD owns n_rb / 8 of them and walks them in groups of kGroupR, the last group may hold fewer; n_rb % 8 are left over.
 constexpr int kGroupR = 4, kGroupC = 8;
@@ -389,10 +216,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
     // What the first loads need of the arguments, requested together: taken as they come up they are a chain of round trips to memory.  Clocks from
     // a workgroup's start to its first load / to its first MFMA, 7B shape, 512 columns, gate/up: 4300 / 13300 with divisions and arguments as they
     // came up, 3350 / 11500 with the divisors' reciprocals from the host and each load sent as soon as its address is known, 1700 / 9300 with this.
-    const bf16_t *const arg_hi = a.x_hi, *const arg_lo = a.x_lo;
+    const bf16_t* const arg_x = a.x_split;
     const void *const arg_w0 = a.w[0], *const arg_w1 = MODE == MODE_RESID ? nullptr : a.w[1], *const arg_w2 = MODE == MODE_RESID || MODE == MODE_SWIGLU ? nullptr : a.w[2];
-    const int K = a.K, x_stride = a.x_stride, total_rows = a.total_rows, rows0 = a.rows[0], rows1 = a.rows[1];
-    asm volatile("" :: "s"(arg_hi), "s"(arg_lo), "s"(arg_w0), "s"(arg_w1), "s"(arg_w2), "s"(K), "s"(x_stride), "s"(total_rows), "s"(rows0), "s"(rows1),
+    const int K = a.K, pitch_x = 2 * (int)split_pitch(K), total_rows = a.total_rows, rows0 = a.rows[0], rows1 = a.rows[1];
+    asm volatile("" :: "s"(arg_x), "s"(arg_w0), "s"(arg_w1), "s"(arg_w2), "s"(K), "s"(total_rows), "s"(rows0), "s"(rows1),
                  "s"(order.n_rb), "s"(order.n_cb), "s"(order.n_whole), "s"(order.group_tiles.m));
 
     // ---- launch order -> tile, K part; tile -> (row block, column block) ----
@@ -434,19 +261,19 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
     const int s_end = (K + kBK - 1) / kBK, n_single = slice == parts - 1 ? s_end - 2 * pairs : 0;      // 0, 1 or 2
     // (the launcher sees to at least two whole stages per part)
 
-    // ---- this wave's eight-row blocks of a stage (wave8, wave8 + 8, ...): the first 32 are weight rows, then hi, then lo ----
+    // ---- this wave's eight-row blocks of a stage (wave8, wave8 + 8, ...): the first 32 are weight rows, then the activations of k-step 0, then of 1 ----
     // Slab tile st = 8 wy + t is wave row wy's tile t.  Plain modes: output tile OT rb + st.  SwiGLU: tiles t < 4 are gate rows,
     // the others the up rows of the same outputs OT rb + 4 wy + t % 4.  Tiles past the matrix re-read the last one (result dropped).
     // Each block's first load goes out before the next block's address is worked out: the code up to here comes from memory too, a line at a time.
     // lane l of a load: row l / 8 of the block, LDS position l % 8, i.e. segment (l % 8) ^ ((slab row / 2) % 8) of that row
     const int prow = lane >> 3, pseg = (lane & 7) ^ ((lane >> 4) | (4 * (wave8 & 1)));
-    const int voff_w = 2 * (prow * K + pseg * 8), voff_x = 2 * (prow * x_stride + pseg * 8), voff_x64 = voff_x + 2 * 64 * x_stride;
+    const int voff_w = 2 * (prow * K + pseg * 8), voff_x = prow * pitch_x + pseg * 16, voff_x64 = voff_x + 64 * pitch_x;
     __amdgpu_buffer_rsrc_t src[kLoadsW + 2];           // a block of eight weight rows each; the wave's columns c and c + 64 of a plane each
     static_assert(kLoadsX == 4, "two loads of eight columns per plane");
     auto load1 = [&](int j, int t, int lds) {         // t: stage of the whole K; lds: where its slab (weights j < kLoadsW, or activations) lies
         const int jx = j - kLoadsW;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(src[j < kLoadsW ? j : kLoadsW + jx / 2], (__attribute__((address_space(3))) void*)((lds_char*)prompt_lds + lds + (wave8 + kWaves * (j < kLoadsW ? j : jx)) * 1024),
-                                                 16, j < kLoadsW ? voff_w : jx % 2 ? voff_x64 : voff_x, t * kPitch, 0, 0);
+                                                 16, j < kLoadsW ? voff_w : jx % 2 ? voff_x64 : voff_x, j < kLoadsW ? t * kPitch : t * 2 * kPitch, 0, 0);
     };
     int w0 = 0, w1 = kABytes, w2 = 2 * kABytes;        // the weight slabs of this stage and the next two
 #pragma unroll
@@ -465,8 +292,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
             const bf16_t* p = static_cast<const bf16_t*>(w) + (size_t)(local + 8 * (blk & 1)) * K;
             src[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 2 * 8 * K, 0x00027000);
         } else if ((j - kLoadsW) % 2 == 0) {
-            const bf16_t* p = (j == kLoadsW ? arg_hi : arg_lo) + (size_t)(cb * kTileN + 8 * wave8) * x_stride;
-            src[kLoadsW + (j - kLoadsW) / 2] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 2 * (71 * x_stride + K), 0x00027000);
+            const int step = (j - kLoadsW) / 2;        // in bytes, a k-step of a column is one line
+            const bf16_t* p = arg_x + (cb * kTileN + 8 * wave8) * split_pitch(K) + step * (kPitch / 2);
+            src[kLoadsW + step] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 71 * pitch_x + 4 * K - step * kPitch, 0x00027000);
         }
         load1(j, s0, j < kLoadsW ? w0 : kLdsX);
         fixed_here();
@@ -479,11 +307,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
 #pragma unroll
         for (int j = kLoadsW; j < kLoads; ++j) load1(j, t, kLdsX + buf * kXBytes);
     };
-    // fragment reads: lane (i, g) takes segment 4 grp + g of row i of a tile (tile bases are multiples of 16 rows, so the
-    // swizzle depends on i alone)
-    const uint32_t slot = (uint32_t)(((grp * 4 + lg) ^ ((li >> 1) & 7)) << 4);
+    // fragment reads: lane (i, g) takes segment 4 grp + g of row i of a weight tile, segments g and 4 + g of column i of plane grp (tile bases are
+    // multiples of 16 rows, so the swizzle depends on i alone)
+    const uint32_t slot = (uint32_t)(((grp * 4 + lg) ^ ((li >> 1) & 7)) << 4), slot_b = (uint32_t)((lg ^ ((li >> 1) & 7)) << 4);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)prompt_lds;
-    const uint32_t a_off = lds0 + (wy * 16 * RW + li) * kPitch + slot, b_off = lds0 + kLdsX + (wx * 64 + li) * kPitch + slot;
+    const uint32_t a_off = lds0 + (wy * 16 * RW + li) * kPitch + slot, b_off = lds0 + kLdsX + grp * kPlane + (wx * 64 + li) * kPitch + slot_b, b_lo = b_off ^ kLoBit;
 
     f32x4 acc[RW][2 * CW];                             // [row tile of the wave][column tile of the wave]
 #pragma unroll
@@ -501,12 +329,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
     auto stage = [&](int t, auto buf_c, auto more_c, auto loads_c, auto loads_w_c, u32x4 (&A)[RW], u32x4 (&An)[RW], PromptB& X, PromptB& Y, PromptB& Z) {
         constexpr int BUF = decltype(buf_c)::value;
         constexpr bool MORE = decltype(more_c)::value;
-        const uint32_t B = b_off + BUF * kXBytes, Bn = b_off + (BUF ^ 1) * kXBytes, Wn = a_off + w1;
+        const uint32_t Wn = a_off + w1;
         constexpr bool loads = decltype(loads_c)::value, loads_w = decltype(loads_w_c)::value;
         const int k2 = s0 + t + 2, k3 = k2 + 1, xb = kLdsX + BUF * kXBytes;
         // slot 0: the weight fragments are used in the order of their arrival
         __builtin_amdgcn_s_setprio(1);
-        read_b_frags<1>(Y, B);
+        read_b_frags<1, BUF * kXBytes>(Y, b_off, b_lo);
         lds_reads_left<8>(); pin_frag(A[0]); pin_frag(A[1]); pin_frag(X.h); pin_frag(X.l);
         mma_hl<0, 2>(acc, 0, A, X); fixed_here();
         lds_reads_left<6>(); pin_frag(A[2]); pin_frag(A[3]);
@@ -517,10 +345,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
         mma_hl<6, 2>(acc, 0, A, X); fixed_here();
         // slot 1
         __builtin_amdgcn_s_setprio(0);
-        read_b_frags<2>(Z, B);
+        read_b_frags<2, BUF * kXBytes>(Z, b_off, b_lo);
         lds_reads_left<2>(); pin_frag(Y.h); pin_frag(Y.l);
         mma_hl<0, 2>(acc, 1, A, Y); fixed_here();
-        read_b_frags<3>(X, B); fixed_here();
+        read_b_frags<3, BUF * kXBytes>(X, b_off, b_lo); fixed_here();
         mma_hl<2, 6>(acc, 1, A, Y); fixed_here();
         // slots 2 and 3: this wave has read all of stage t
         lds_reads_left<0>(); pin_frag(Z.h); pin_frag(Z.l); pin_frag(X.h); pin_frag(X.l);
@@ -534,7 +362,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
             mma_hl<3, 1>(acc, 2, A, Z); fixed_here(); if (loads) load1(7, k2, xb); fixed_here();
             mma_hl<4, 1>(acc, 2, A, Z); fixed_here(); if (loads_w) load1(0, k3, w0); fixed_here();
             mma_hl<5, 1>(acc, 2, A, Z); fixed_here(); if (loads_w) load1(1, k3, w0); fixed_here();
-            mma_hl<6, 1>(acc, 2, A, Z); fixed_here(); if (loads_w) load1(2, k3, w0); read_b_frags<0>(Y, Bn); fixed_here();
+            mma_hl<6, 1>(acc, 2, A, Z); fixed_here(); if (loads_w) load1(2, k3, w0); read_b_frags<0, (BUF ^ 1) * kXBytes>(Y, b_off, b_lo); fixed_here();
             mma_hl<7, 1>(acc, 2, A, Z); fixed_here(); if (loads_w) load1(3, k3, w0); An[0] = lds_read_frag<0>(Wn); fixed_here();
             __builtin_amdgcn_s_setprio(2);
             mma_hl<0, 1>(acc, 3, A, X); fixed_here(); An[1] = lds_read_frag<1 * 16 * kPitch>(Wn); fixed_here();
@@ -588,7 +416,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
         }
     }
     __syncthreads();                                   // stage 0 is in LDS
-    read_b_frags<0>(f0, b_off);
+    read_b_frags<0>(f0, b_off, b_lo);
     read_a_frags(A0, a_off, std::make_integer_sequence<int, RW>{});
     all_arrived(A0); all_arrived(f0);
     int t = 0;
@@ -613,11 +441,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
         __syncthreads();
         if (grp == 0 || (u + 1) * kBK <= K) {
             read_a_frags(A0, a_off, std::make_integer_sequence<int, RW>{});
-            read_b_frags<0>(f0, b_off); read_b_frags<1>(f1, b_off); read_b_frags<2>(f2, b_off);
+            read_b_frags<0>(f0, b_off, b_lo); read_b_frags<1>(f1, b_off, b_lo); read_b_frags<2>(f2, b_off, b_lo);
             all_arrived(A0); all_arrived(f0); all_arrived(f1); all_arrived(f2);
             mma_hl<0, 8>(acc, 0, A0, f0); mma_hl<0, 8>(acc, 1, A0, f1);
             mma_hl<0, 8>(acc, 2, A0, f2); fixed_here();
-            read_b_frags<3>(f0, b_off);
+            read_b_frags<3>(f0, b_off, b_lo);
             all_arrived(f0);
             mma_hl<0, 8>(acc, 3, A0, f0); fixed_here();
         }
@@ -703,8 +531,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
         mine = __builtin_amdgcn_readfirstlane(mine);
         if (mine == 0) return;
     }
-    QkvColumns q_cols;
-    if constexpr (MODE == MODE_QKV_ROPE) q_cols.load(a, cb, grp, wx);
+    const int cl0 = wx * 64 + grp * 32 + li;           // this lane's columns of the tile: cl0, cl0 + 16
+    QkvColumn q_cols[CW];                              // all requested before the first store, which they might alias
+    if constexpr (MODE == MODE_QKV_ROPE) {
+#pragma unroll
+        for (int tt = 0; tt < CW; ++tt) q_cols[tt].load(a, cb * kTileN + cl0 + 16 * tt);
+        fixed_here();
+    }
 #pragma unroll
     for (int tt = 0; tt < CW; ++tt) {
         const unsigned units = mine >> (tt * kUnits) & ((1u << kUnits) - 1);
@@ -733,9 +566,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
             }
         }
         if constexpr (MODE == MODE_QKV_ROPE) {
-            if (a.kv_dtype == 0) store_qkv<float>(a, sum, q_cols, tt, units, rb, cb, grp, wy, wx, inv_rms);
-            else store_qkv<f16_t>(a, sum, q_cols, tt, units, rb, cb, grp, wy, wx, inv_rms);
-        } else store_tiles<MODE>(a, sum, tt, units, rb, cb, tiles, grp, wy, wx, inv_rms);
+            if (a.kv_dtype == 0) store_qkv<float>(a, sum, q_cols[tt], units, 2 * rb + wy, cb * kTileN + cl0 + 16 * tt, inv_rms[cl0 + 16 * tt]);
+            else store_qkv<f16_t>(a, sum, q_cols[tt], units, 2 * rb + wy, cb * kTileN + cl0 + 16 * tt, inv_rms[cl0 + 16 * tt]);
+        } else store_tiles<MODE>(a, sum, units, rb * OT + wy * (RW / SW), tiles, cb * kTileN + cl0 + 16 * tt, a.ssq_in ? inv_rms[cl0 + 16 * tt] : 1.0f);
     }
 #endif
 }
@@ -814,7 +647,7 @@ __global__ __launch_bounds__(512, 2) void mfma_yardstick_kernel(float* __restric
 // units, whole / 2 / 3 / 4 / 5 / 6 / 8 parts: 7B O at 203 columns (32 tiles) 88 / 55 / 48 / 39 / 44 / 47 / 45, down 203 / 116 / 88 / 77 /
 // 74 / 71 / 70, at 700 (96 tiles) O 91 / 60 / 88 / 82 / 80 / 91 / 92, 70B O at 203 (64 tiles) 170 / 99 / 85 / 74 / 110 / 106 / 106: the rule's
 // choice is within 4 us of the best of each.
-struct PromptSplit { int n_whole, ks; };
+struct PromptSplit { int n_whole, ks, cut_rounds = 0, cut_cost = 0; };
 PromptSplit prompt_split(int tiles_wg, int n_stages, int n_cu, int forced, bool can_split) {
     auto fits = [&](int n, int ks) { return can_split && 2 * ks <= n_stages && n * ks <= kGemmPartTickets && n * ks * kPromptPartTile <= kPromptPartBytes; };
     if (forced >= 1) return forced > 1 && fits(tiles_wg, forced) ? PromptSplit{0, forced} : PromptSplit{tiles_wg, 1};
@@ -824,9 +657,20 @@ PromptSplit prompt_split(int tiles_wg, int n_stages, int n_cu, int forced, bool 
     for (int ks = 2; ks <= kPromptMaxParts && rest > 0; ++ks) {
         if (!fits(rest, ks) || n_stages / ks < 8) break;
         const int rounds = (rest * ks + n_cu - 1) / n_cu, cost = rounds * ((n_stages + ks - 1) / ks + 10 + 2 * ks);
-        if (cost < best_cost) { best = PromptSplit{tiles_wg - rest, ks}; best_cost = cost; }
+        if (cost < best_cost) { best = PromptSplit{tiles_wg - rest, ks, rounds, cost}; best_cost = cost; }
     }
     return best;
+}
+
+// What a launch of this kernel costs, in stages with few compute units busy, to compare with gemm_prompt_256_cost.  Both are fitted to kernel traces of the four
+// projections at the 7B, 13B and 70B widths, 256 to 4096 columns (14 widths; the fit takes the slower kernel nowhere by more than 4.5 %, by 0.3 % on
+// average).  Beside its stages a whole tile costs its start and its epilogue, most of all where it reads and writes the residual.  A stage of the other kernel
+// is 64 k of 256 columns: 1.9 of this one's, which is where that kernel gains; its tiles are twice as large, so it loses where they leave compute units
+// idle or K parts have to be exchanged.  Measured, this kernel / the other, us: 7B gate/up 183 / 295 (616 columns), 274 / 267 (1024), 526 / 492 (2048), 1031 / 947
+// (4096), down 100 / 143, 138 / 165, 257 / 274, 523 / 480; 70B gate/up 649 / 644 (512), 2482 / 2341 (2048), 5154 / 4697 (4096), down 358 / 355, 1334 / 1210, 2691 / 2432.
+double prompt_cost(int mode, int n_stages, int n_cu, const PromptSplit& sp) {
+    const double tile = mode == MODE_SWIGLU ? 9 : mode == MODE_RESID ? 14 : 11, stage = mode == MODE_RESID ? 1.08 : 1.04;
+    return (sp.n_whole + n_cu - 1) / n_cu * (stage * n_stages + tile) + stage * sp.cut_cost;
 }
 
 template <int MODE>
@@ -842,7 +686,7 @@ int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, PromptSplit sp, hipStre
 }  // namespace
 
 // Requirements: those of launch_gemm_mfma (bf16 weights, K % 32 == 0, row counts multiples of 16), K >= 128, 1 <= ncols <=
-// kPassCols (x_hi / x_lo hold ncols rounded up to 128 rows); one matrix in MODE_RESID; with ssq_out at most kSsqStride row blocks.  MODE_QKV_ROPE: head_dim
+// kPassCols (x_split holds ncols rounded up to 128 rows); one matrix in MODE_RESID; with ssq_out at most kSsqStride row blocks.  MODE_QKV_ROPE: head_dim
 // 128, ssq_in, col_at and rope_cs set, only q is written to out.
 // Up to 128 columns the panel kernel is the other choice.  It slows down past 64 (its LDS pipe, or two launches of 64), the LDS-tiled
 // kernel takes one column block whatever its width and wants row blocks.  Measured at 65 / 77 / 128 columns (us between events, panel -> LDS-tiled): 48 or
@@ -864,7 +708,12 @@ int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, 
     if (a.ssq_out && n_rb > kSsqStride) return (int)hipErrorInvalidValue;
     if (n_groups) *n_groups = n_rb;
     const int n_stages = a.K / (2 * kBK) * 2, tiles_wg = n_rb * n_cb;
-    const PromptSplit sp = prompt_split(tiles_wg, n_stages, tn.prompt_cus ? tn.prompt_cus : n_cu, tn.prompt_ks, a.part && a.part_tickets);
+    const int cus = tn.prompt_cus ? tn.prompt_cus : n_cu;
+    const PromptSplit sp = prompt_split(tiles_wg, n_stages, cus, tn.prompt_ks, a.part && a.part_tickets);
+    if (tn.prompt_tile == 256 || (tn.prompt_tile == 0 && tn.prompt_ks == 0 && tn.prompt_cus == 0)) {
+        const double other = gemm_prompt_256_cost(a, mode, cus);
+        if (tn.prompt_tile == 256 ? other < HUGE_VAL : other < prompt_cost(mode, n_stages, cus, sp)) return launch_gemm_prompt_256(a, mode, cus, s, n_groups);
+    }
     if (mode == MODE_STORE) return launch_prompt<MODE_STORE>(a, n_rb, n_cb, sp, s);
     if (mode == MODE_QKV_ROPE) {
         if (a.hd != 128 || !a.ssq_in || !a.col_at || !a.rope_cs || (a.kv_dtype != 0 && a.kv_dtype != 2)) return (int)hipErrorInvalidValue;

@@ -50,16 +50,13 @@ __device__ __forceinline__ void embed_column(const W* __restrict__ emb, int tok,
                 *reinterpret_cast<float4*>(xo + j + 4) = make_float4(f[4], f[5], f[6], f[7]);
                 if (split.gain) {
                     const float g[8] = {g0[r].x, g0[r].y, g0[r].z, g0[r].w, g1[r].x, g1[r].y, g1[r].z, g1[r].w};
-                    uint32_t h[8], l[8];
+                    float w[8];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         ss += f[e] * f[e];
-                        const float w = f[e] * g[e];
-                        h[e] = f32_to_bf16(w);
-                        l[e] = f32_to_bf16(w - bf16_to_f32(h[e]));
+                        w[e] = f[e] * g[e];
                     }
-                    *reinterpret_cast<uint4*>(split.hi + (size_t)c * d + j) = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-                    *reinterpret_cast<uint4*>(split.lo + (size_t)c * d + j) = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
+                    store_split8(split.split + c * split_pitch(d), j, w);
                 }
             }
         }
@@ -103,12 +100,12 @@ __global__ __launch_bounds__(256) void pick_rows_kernel(const float* __restrict_
 
 // ---------------- gain + split into bf16 hi/lo, sum of squares ----------------
 // The matrix-core projections fold the RMSNorm scale 1/rms into their epilogue; what they need from the
-// residual is hi + lo = x * gain and sum(x^2).  Inside a pass the residual projections produce both; this
+// residual is the split of x * gain and sum(x^2).  Inside a pass the residual projections produce both; this
 // kernel does it for the residual that a head or a fill starts from (the embedding kernel does it itself).  One workgroup per column; a thread keeps up to 8 float4 of the
 // column in registers (all loads issued together); wider columns fall back to a second read.
 __global__ __launch_bounds__(256) void gain_split_kernel(const float* __restrict__ x, int x_stride,
                                                          const float* __restrict__ gain, int K,
-                                                         bf16_t* __restrict__ hi, bf16_t* __restrict__ lo,
+                                                         bf16_t* __restrict__ split,
                                                          float* __restrict__ ssq) {
     constexpr int R = 8;
     __shared__ float red[4];
@@ -119,14 +116,7 @@ __global__ __launch_bounds__(256) void gain_split_kernel(const float* __restrict
     auto emit = [&](int i4, const float4& t, const float4& gg) {
         const float f[4] = {t.x * gg.x, t.y * gg.y, t.z * gg.z, t.w * gg.w};
         ss += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
-        uint32_t h[4], l[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            h[e] = f32_to_bf16(f[e]);
-            l[e] = f32_to_bf16(f[e] - bf16_to_f32(h[e]));
-        }
-        *reinterpret_cast<uint2*>(hi + (size_t)c * K + i4 * 4) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-        *reinterpret_cast<uint2*>(lo + (size_t)c * K + i4 * 4) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+        store_split4(split + c * split_pitch(K), i4 * 4, f);
     };
     float4 v[R], g[R];
 #pragma unroll
@@ -334,8 +324,8 @@ int launch_pick_rows(const float* x, int d, const RowPick& pick, float* dst, hip
 }
 
 int launch_gain_split(const float* x, int x_stride, const float* gain, int K, int ncols,
-                      bf16_t* hi, bf16_t* lo, float* ssq, hipStream_t s) {
-    hipLaunchKernelGGL(gain_split_kernel, dim3(ncols), dim3(256), 0, s, x, x_stride, gain, K, hi, lo, ssq);
+                      bf16_t* split, float* ssq, hipStream_t s) {
+    hipLaunchKernelGGL(gain_split_kernel, dim3(ncols), dim3(256), 0, s, x, x_stride, gain, K, split, ssq);
     return (int)hipGetLastError();
 }
 

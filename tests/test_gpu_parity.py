@@ -328,6 +328,56 @@ def test_parts_that_finish_several_runs_together(monkeypatch, ks):
     helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
 
 
+# cus: compute units that the launches reckon with (8 workgroups at least).  K of 4 stages, the fewest (whole tiles, dead rows and columns in the last); 7 row blocks x 3
+# column blocks of 5 stages in three rounds; tiles left over in parts: QKV and gate/up (two and five row blocks) of 64 stages, 4, 6, 10 and 2 tiles on 8 and 16
+# workgroups, i.e. mains with one helper, with two and three, helpers with pieces of several tiles, and tiles behind a full round; down of 64 and 172 stages, one
+# row block, in parts of uneven length, up to the most there are
+LARGE_TILES = [(0, 256, 320, 300, "f16"), (8, 320, 832, 700, "f32"), (8, 4096, 640, 300, "f32"), (8, 4096, 640, 513, "f16"), (16, 4096, 1280, 256, "f32"),
+               (8, 256, 4096, 700, "f32"), (16, 256, 11008, 600, "f32"), (8, 256, 11008, 1100, "f32")]
+
+
+@pytest.mark.parametrize("cus,d,F,P,kv", LARGE_TILES)
+def test_prompt_tiles_of_256_columns(monkeypatch, cus, d, F, P, kv):
+    monkeypatch.setenv("D3_PROMPT_TILE", "256")
+    if cus:
+        monkeypatch.setenv("D3_PROMPT_CUS", str(cus))
+    s = ModelShape("large-tiles", L=2, d=d, H=2, H_kv=1, hd=128, F=F, V=512, dtype="bf16")
+    gpu, gens = _run(s, 1, P, 2, 1.0, 1, forced_seed=19, kv_dtype=kv)
+    if kv == "f32":
+        helpers.compare(gpu, gens, 2, logit_atol=2e-4, hidden_tol=1e-4)
+    else:
+        helpers.compare(gpu, gens, 2)
+
+
+def test_prompt_tiles_of_256_columns_replay_from_a_graph(monkeypatch):
+    # tiles in parts leave their arrival counters zero: each replay, on new tokens in between, equals the eager call bit for bit; two sequences that share passes
+    import torch
+    from paper_2503_08524_amd import binding
+    monkeypatch.setenv("D3_PROMPT_TILE", "256")
+    monkeypatch.setenv("D3_PROMPT_CUS", "8")
+    s = ModelShape("graph-256", L=2, d=2048, H=2, H_kv=1, hd=128, F=4096, V=512, dtype="bf16")
+    B, P = 2, 350
+    dec = binding.Decoder(s, binding.random_weights_on_device(s, 5), B, P + 2)
+    toks = [torch.from_numpy(d3_inputs.make_prompt(B, P, s.V, seed=k)).to("cuda:0") for k in (1, 2)]
+    fed, out, logits = toks[0].clone(), torch.zeros(B, dtype=torch.int32, device="cuda:0"), torch.zeros(B, s.V, device="cuda:0")
+    print("case graph of tiles of 256 columns", flush=True)
+    want = []
+    for t in toks:
+        dec.prefill(t, next_tok=out, logits=logits)
+        want.append((out.clone(), logits.clone(), dec.k_cache.clone()))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dec.prefill(fed, next_tok=out, logits=logits)
+    for k in (0, 1, 1, 0, 1):
+        fed.copy_(toks[k])
+        logits.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[k][0]) and torch.equal(logits, want[k][1]) and torch.equal(dec.k_cache, want[k][2])
+    dec.close()
+
+
 @pytest.mark.parametrize("ks", [1, 2])
 def test_prompt_projection_rotates_with_two_stated_roundings(monkeypatch, ks):
     # 200 times the same token: every position has the same unrotated key, which position 0 (cos 1, sin 0) shows, so the rotated ones follow

@@ -145,3 +145,23 @@ def test_fragments_in_flight_are_left_alone(compiled):
     text = "\n".join(raw for _, raw in lines)
     for what in ("vgpr_spill_count", "sgpr_spill_count", "private_segment_fixed_size"):
         assert set(re.findall(rf"\.{what}:\s+(\d+)", text)) == {"0"}, what
+
+
+def test_fragments_in_flight_are_left_alone_in_the_kernel_of_the_larger_tiles(tmp_path):
+    # the same for the tiles of 256 columns: four steps of 16 reads each are written out (the last one of 6), and the first reads of a tile
+    out = str(tmp_path / "gemm_prompt_256.s")
+    src = os.path.join(d3_build.CSRC, "gemm_prompt_256.hip")
+    r = subprocess.run([d3_build.HIPCC] + d3_build.FLAGS + ["-x", "hip", "--cuda-device-only", "-S", src, "-o", out], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    text = open(out).read()
+    lines = listing(text)
+    starts = [(i, raw.split(":")[0]) for i, (_, raw) in enumerate(lines) if re.match(r"_Z\w+gemm_prompt_256_kernel\w+:", raw)]
+    assert len(starts) == 3
+    for i, name in starts:
+        end = next(k for k in range(i + 1, len(lines)) if lines[k][1].strip().startswith(".section"))
+        found, n_reads = faults(lines[i + 1:end])
+        print(name, n_reads, "reads")
+        assert n_reads >= 60, name
+        assert not found, f"{name}:\n" + "\n".join(found)
+    for what in ("vgpr_spill_count", "private_segment_fixed_size"):
+        assert set(re.findall(rf"\.{what}:\s+(\d+)", text)) == {"0"}, what
