@@ -114,9 +114,10 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
     return l;
 }
 // Columns of a prompt chunk: a whole sequence if it fits kPassCols (one pass over the weights per sequence, and enough
-// column blocks for the 4096-row projections to fill the chip), or several sequences that share it; never more than the cache can hold.
+// column blocks for the 4096-row projections to fill the chip), or several sequences that share it (on the matrix cores, where their attention takes runs; on the
+// vector ALUs always); never more than the cache can hold.
 int pass_cols(const d3_model_desc& d) {
-    const long long rows = (long long)d.max_seq * (shares_passes(d) ? d.max_batch : 1);
+    const long long rows = (long long)d.max_seq * (shares_passes(d) || !mfma_fits(d) ? d.max_batch : 1);
     const long long need = (rows + 127) / 128 * 128;
     return (int)(need < kPassCols ? need : kPassCols);
 }
@@ -422,20 +423,13 @@ bool whole_context_attention(const d3_ctx* c, const SeqRuns& runs, bool shared) 
     return std::max(2.85 * longest, 3.3 * steps / c->n_cu) <= tiles_us;
 }
 
-// ALU path: a projection takes as many columns per launch as its input fits in LDS
+// ALU path: the columns [first, first + count) of a pass
 int alu_projection(d3_ctx* c, GemvArgs g, int first, int count, int mode, bool norm, hipStream_t s) {
-    const int per = (int)gemv_alu_max_cols(g.K, c->desc.weight_dtype);
-    for (int c0 = 0; c0 < count; c0 += per) {
-        GemvArgs h = g;
-        h.x = g.x + (size_t)(first + c0) * g.x_stride;
-        h.out = g.out + (size_t)(first + c0) * g.out_stride;
-        h.ncols = count - c0 < per ? count - c0 : per;
-        h.col0 = first + c0;
-        int rc = launch_gemv_alu(h, c->desc.weight_dtype, mode, norm, c->n_cu * c->tn.gemv_wgs_per_cu, s);
-        if (rc != 0) return rc;
-
-    }
-    return 0;
+    g.x += (size_t)first * g.x_stride;
+    g.out += (size_t)first * g.out_stride;
+    g.ncols = count;
+    g.col0 = first;
+    return launch_gemv_alu(g, c->desc.weight_dtype, mode, norm, c->n_cu * c->tn.gemv_wgs_per_cu, s);
 }
 
 // One pass of `ncols` columns through the listed blocks.  hidden_dump (or NULL): dev
@@ -736,13 +730,13 @@ int prefill_impl(d3_ctx* ctx, const int32_t* tokens, int32_t B, int32_t P, int32
     std::vector<int32_t> all(d.n_layers);
     for (int l = 0; l < d.n_layers; ++l) all[l] = l;
     float* lg = logits ? logits : ctx->at<float>(ctx->lay.logits);
-    if (ctx->prefill_by_seq || (ctx->ragged && pos_begin == 0)) {
+    const int fit = pass_cols(d);
+    const int wide_cols = ctx->tn.prefill_cols && ctx->tn.prefill_cols < fit ? ctx->tn.prefill_cols : fit;
+    if ((ctx->prefill_by_seq && ctx->mfma_ok) || (ctx->ragged && pos_begin == 0)) {
         // consecutive positions of a sequence per pass: the attention of such a chunk reads every cache row once per tile of
         // queries instead of once per query.  The matrix-core path takes pass_cols() columns (the weights are streamed once per
         // pass), of several sequences if its attention kernel can; else one sequence at a time
-        const int fit = pass_cols(d);
-        const int wide_cols = ctx->tn.prefill_cols && ctx->tn.prefill_cols < fit ? ctx->tn.prefill_cols : fit;
-        const int chunk_cols = ctx->mfma_ok && ctx->tn.mfma_wide ? wide_cols : kMaxCols;
+        const int chunk_cols = ctx->mfma_ok && !ctx->tn.mfma_wide ? kMaxCols : wide_cols;
         if (B > 1 && ctx->prefill_by_seq && shares_passes(d) && ctx->tn.mfma_wide && ctx->tn.attn_mfma) {
             const int rc = prefill_shared(ctx, tokens, B, P, pos_begin, chunk_cols, all, next_tok, lg, hidden_dump, s);
             if (rc != D3_OK) return rc;
@@ -759,7 +753,9 @@ int prefill_impl(d3_ctx* ctx, const int32_t* tokens, int32_t B, int32_t P, int32
             }
         }
     } else {
-        const int chunk = (kMaxCols / B) * B;
+        // On the vector ALUs alone a pass gains nothing from the columns of one sequence, so all sequences share passes, as wide as the workspace: each
+        // launch is a few us whatever its columns (tiny fp32 model, 8 prompts of 64 tokens, a pass for each sequence's 32 -> one for all 512: 2221 -> 517 us).
+        const int chunk = ((ctx->mfma_ok ? kMaxCols : wide_cols) / B) * B;
         const int total = B * P;
         // position-major columns in chunks that are multiples of B: the last B columns of the last
         // chunk are the last prompt position of every sequence

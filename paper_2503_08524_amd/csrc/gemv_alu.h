@@ -106,14 +106,15 @@ struct GemvPipe {
     int issued, total;    // steps loaded so far / steps this wave owns in this phase
 };
 
-template <typename W, int MODE, int D>
+// MANY: other workgroups read the same rows, for other columns, at about the same time: ordinary loads, which leave them in the L2.
+template <typename W, int MODE, int D, bool MANY>
 __device__ __forceinline__ void gemv_issue(const GemvArgs& a, GemvPipe<W, D>& p, int slot, int nw, int n_units, int nchunks, int S) {
     constexpr int EPC = GemvChunk<W>::N;
     const int lane = threadIdx.x & 63;
     int q = lane + 64 * p.lit;
     q = q < nchunks ? q : nchunks - 1;                 // ragged last stride: reload a valid chunk (its activations are zero)
-    p.b0[slot] = load_stream16(p.r0 + (size_t)q * EPC);
-    p.b1[slot] = load_stream16(p.r1 + (size_t)q * EPC);
+    p.b0[slot] = MANY ? *reinterpret_cast<const u32x4*>(p.r0 + (size_t)q * EPC) : load_stream16(p.r0 + (size_t)q * EPC);
+    p.b1[slot] = MANY ? *reinterpret_cast<const u32x4*>(p.r1 + (size_t)q * EPC) : load_stream16(p.r1 + (size_t)q * EPC);
     p.issued += 1;
     if (++p.lit == S) p.lit = 0;
     if (p.lit == p.first) {
@@ -125,21 +126,21 @@ __device__ __forceinline__ void gemv_issue(const GemvArgs& a, GemvPipe<W, D>& p,
 
 // Start a phase: fill the ring with the wave's first D steps.  All D loads are issued whatever the
 // wave's share is (a wave with fewer steps re-reads valid rows), which keeps the wait counts exact.
-template <typename W, int MODE, int D>
-__device__ __forceinline__ void gemv_preload(const GemvArgs& a, int wave, int gw, int nw, GemvPipe<W, D>& p) {
+template <typename W, int MODE, int D, bool MANY>
+__device__ __forceinline__ void gemv_preload(const GemvArgs& a, int wg, int wave, int gw, int nw, GemvPipe<W, D>& p) {
     const int n_units = gemv_n_units(a, MODE);
     const int nchunks = a.K / GemvChunk<W>::N;
     const int S = a.by_strides.d;
     p.total = (a.wave_units + (gw < a.wave_units_over ? 1 : 0)) * S;
     p.issued = 0;
     p.lu = gw;
-    const int turn = 5 * (int)(blockIdx.x >> 2) + 3 * wave;
+    const int turn = 5 * (wg >> 2) + 3 * wave;
     p.first = turn - a.by_strides.of(turn) * S;
     p.lit = p.first;
     int row;
     gemv_unit_rows<W, MODE>(a, gw < n_units ? gw : n_units - 1, p.r0, p.r1, row);
 #pragma unroll
-    for (int j = 0; j < D; ++j) gemv_issue<W, MODE, D>(a, p, j, nw, n_units, nchunks, S);
+    for (int j = 0; j < D; ++j) gemv_issue<W, MODE, D, MANY>(a, p, j, nw, n_units, nchunks, S);
 }
 
 // Activations -> LDS (fp32), in two halves so that a kernel can put its weight preload in between:
@@ -321,7 +322,7 @@ __device__ __forceinline__ void gemv_flush(const GemvArgs& a, const GemvEpBuf<NC
 }
 
 // Main loop of a phase: consume the wave's steps, keeping the ring full.  `ep` is this wave's buffer.
-template <typename W, int NC, int MODE, int D>
+template <typename W, int NC, int MODE, int D, bool MANY>
 __device__ __forceinline__ void gemv_run(const GemvArgs& a, const float4* xs, int gw, int nw, GemvPipe<W, D>& p, GemvEpBuf<NC>& ep,
                                          const float (&scale)[NC]) {
     const int lane = threadIdx.x & 63;
@@ -373,7 +374,7 @@ __device__ __forceinline__ void gemv_run(const GemvArgs& a, const float4* xs, in
 #pragma unroll
         for (int j = 0; j < D; ++j) {
             consume(j);
-            gemv_issue<W, MODE, D>(a, p, j, nw, n_units, nchunks, S);
+            gemv_issue<W, MODE, D, MANY>(a, p, j, nw, n_units, nchunks, S);
         }
         t += D;
     }
@@ -382,7 +383,7 @@ __device__ __forceinline__ void gemv_run(const GemvArgs& a, const float4* xs, in
         for (int j = 0; j < D; ++j) {
             if (t + j < total) {
                 consume(j);
-                if (p.issued < total) gemv_issue<W, MODE, D>(a, p, j, nw, n_units, nchunks, S);
+                if (p.issued < total) gemv_issue<W, MODE, D, MANY>(a, p, j, nw, n_units, nchunks, S);
             }
         }
     }

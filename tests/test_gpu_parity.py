@@ -107,6 +107,47 @@ def test_tiny_fp32_batches_use_the_alu_path(B):
     _run(d3_inputs.TINY, B, 9, 8, 0.9, 1, kv_dtype="f32", forced_seed=6)
 
 
+# Groups of columns in one launch of the vector-ALU projections: 4, 2 and 1 columns a workgroup (rows of up to 15 KB, 30 KB and 60 KB of fp32 activations), batches that fill their
+# last group and that do not, group by group in decode and in prompt passes of several sequences (of 15 to 340 columns, of more than one chunk, beside a ragged batch, which stays
+# one sequence a pass), fp32 and bf16 rows (bf16: widths that the matrix cores do not take), a cache of 16 bits
+@pytest.mark.parametrize("B,P,d,F,dtype,kv,lengths", [
+    (5, 3, 256, 688, "f32", "f32", None), (8, 40, 256, 688, "f32", "f32", None), (9, 33, 256, 688, "f32", "f16", None), (32, 5, 256, 688, "f32", "f32", None), (3, 97, 256, 688, "f32", "f32", None),
+    (5, 7, 256, 6000, "f32", "f32", None), (3, 20, 256, 12000, "f32", "f32", None), (7, 50, 264, 696, "bf16", "f32", None), (3, 70, 256, 688, "f32", "f32", (70, 1, 41))])
+def test_groups_of_columns_on_the_vector_alus(B, P, d, F, dtype, kv, lengths):
+    s = ModelShape("groups", L=2, d=d, H=4, H_kv=2, hd=64, F=F, V=1000, dtype=dtype)
+    kw = {} if lengths is None else {"lengths": np.array(lengths, np.int32)}
+    gpu, gens = _run(s, B, P, 3, 0.8, 1, kv_dtype=kv, forced_seed=6, **kw)
+    if kv == "f32":
+        helpers.compare(gpu, gens, 3, logit_atol=1e-4, hidden_tol=1e-5)
+
+
+def test_batch_on_the_vector_alus_equals_its_sequences_one_at_a_time():
+    # the sums of a column do not depend on the group it is in: logits and cache rows of a batch, prompt and decode step, bit for bit those of each sequence alone
+    # (16 rows: attention cuts neither context)
+    import torch
+    from paper_2503_08524_amd import binding
+    s = d3_inputs.TINY
+    w, B, P = binding.weights_to_device(s, d3_inputs.make_weights(s, 3), "cuda:0"), 7, 16
+    toks = torch.from_numpy(d3_inputs.make_prompt(B, P, s.V, seed=4)).to("cuda:0")
+    print("case batch against its sequences", flush=True)
+
+    def run(t):
+        n = t.shape[0]
+        dec = binding.Decoder(s, w, n, P + 2, kv_dtype="f32")
+        out, lg = torch.zeros(n, dtype=torch.int32, device="cuda:0"), torch.zeros(2, n, s.V, device="cuda:0")
+        dec.prefill(t, next_tok=out, logits=lg[0])
+        dec.set_plan_table([s.L, s.L], [0, 0])
+        dec.decode_step(t[:, 0].contiguous(), 1, out, logits=lg[1])
+        torch.cuda.synchronize()
+        got = lg.clone(), dec.k_cache.clone(), dec.v_cache.clone()
+        dec.close()
+        return got
+    lg, k, v = run(toks)
+    for b in range(B):
+        one = run(toks[b:b + 1].contiguous())
+        assert torch.equal(one[0][:, 0], lg[:, b]) and torch.equal(one[1][:, 0, :, :P + 1], k[:, b, :, :P + 1]) and torch.equal(one[2][:, 0, :, :P + 1], v[:, b, :, :P + 1])
+
+
 @pytest.mark.parametrize("B,P", [(1, 16), (2, 7), (5, 13), (16, 3), (17, 4), (32, 2)])
 def test_small_bf16_matrix_core_path(B, P):
     # B = 1 decodes on the vector ALUs and prefills on the matrix cores; B >= 2 uses the matrix cores throughout
