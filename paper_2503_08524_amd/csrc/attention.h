@@ -82,7 +82,7 @@ __device__ __forceinline__ void attn_merge_publish(const AttnArgs& a, int split,
             const float r = o / L;
             const size_t oi = (size_t)ce * a.H * HD + (size_t)he * HD + t;
             if (FUSED) st_agent(&a.out[oi], r); else a.out[oi] = r;
-            if (a.out_split) store_split1(a.out_split + ce * split_pitch(a.H * HD), he * HD + t, r);
+            if (a.out_split) store_split1(a.out_split + ce * split_pitch(a.H * HD), he * HD + t, r, a.split_lo);
             continue;
         }
         const size_t pidx = ((size_t)ce * a.H + he) * a.n_splits + split;
@@ -152,7 +152,7 @@ __device__ __forceinline__ void attn_merge_publish(const AttnArgs& a, int split,
         const float r = o[i] / L[i];
         const size_t oi = (size_t)ce * a.H * HD + (size_t)(h0 + ge % GH) * HD + idx % HD;
         if (FUSED) st_agent(&a.out[oi], r); else a.out[oi] = r;
-        if (a.out_split) store_split1(a.out_split + ce * split_pitch(a.H * HD), (h0 + ge % GH) * HD + idx % HD, r);
+        if (a.out_split) store_split1(a.out_split + ce * split_pitch(a.H * HD), (h0 + ge % GH) * HD + idx % HD, r, a.split_lo);
     }
 }
 

@@ -467,7 +467,8 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     auto gain_after = [&](int e) -> const float* {
         return static_cast<const float*>(e + 1 < n_ids ? c->layers[ids[e + 1]].attn_norm : c->final_norm);
     };
-    const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_split, ssq};
+    const bool planar = mfma && split_planar(ncols);   // ... in this form from the embedding to the head
+    const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_split, ssq, split_lo(planar, dm)};
 
     // a prompt chunk of one sequence (consecutive positions) or of several: tiles of queries share the cache rows they read
     const int grp = d.n_heads / d.n_kv_heads;
@@ -513,7 +514,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         void* k_layer = c->k_cache + (size_t)l * c->kv_layer_bytes();
         void* v_layer = c->v_cache + (size_t)l * c->kv_layer_bytes();
         if (mfma) {
-            g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = ssq_parts;
+            g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = ssq_parts; g.planar = planar;
             const bool rope_in_qkv = qtile && gemm_prompt_takes(g, MODE_QKV_ROPE, c->tn);
             {
                 Timed t(c, D3_K_QKV, s);
@@ -542,7 +543,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         at.ncols = ncols; at.H = d.n_heads; at.H_kv = d.n_kv_heads; at.hd = hd; at.max_seq = d.max_seq;
         at.split_len = split_len; at.n_splits = n_splits;
         at.part_o = c->at<float>(c->lay.part_o); at.part_ml = c->at<float>(c->lay.part_ml); at.tickets = c->at<int>(c->lay.tickets);
-        at.out = attn_o; at.out_split = mfma ? s_split : nullptr;
+        at.out = attn_o; at.out_split = mfma ? s_split : nullptr; at.split_lo = split_lo(planar, qdim);
         at.rope_cs = rope_in_attn ? rope_cs : nullptr;
         at.qtile = qtile ? 1 : 0;
         at.row0 = row0;
@@ -570,7 +571,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         {
             Timed t(c, D3_K_OPROJ, s);
             if (mfma) {
-                o.x_split = s_split; o.x_stride = qdim;
+                o.x_split = s_split; o.x_stride = qdim; o.planar = planar;
                 o.out_split = n_split; o.gain_next = static_cast<const float*>(w.mlp_norm); o.ssq_out = ssq;
                 D3_HIP(launch_gemm_mfma(o, MODE_RESID, c->n_cu, c->tn, s, &ssq_parts));
             }
@@ -586,10 +587,10 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         dn.part = c->at<float>(c->lay.gemm_part); dn.part_bytes = c->lay.gemm_part_bytes; dn.part_tickets = c->at<int>(c->lay.gemm_tickets);
         dn.K = F; dn.w[0] = w.w_down; dn.rows[0] = dm; dn.total_rows = dm; dn.out = x; dn.out_stride = dm; dn.ncols = ncols;
         if (mfma) {
-            u.x_split = n_split; u.x_stride = dm; u.ssq_in = ssq; u.ssq_parts = ssq_parts;
+            u.x_split = n_split; u.x_stride = dm; u.ssq_in = ssq; u.ssq_parts = ssq_parts; u.planar = planar;
             u.out = nullptr; u.out_split = f_split;
             { Timed t(c, D3_K_GATE_UP, s); D3_HIP(launch_gemm_mfma(u, MODE_SWIGLU, c->n_cu, c->tn, s)); }
-            dn.x_split = f_split; dn.x_stride = F;
+            dn.x_split = f_split; dn.x_stride = F; dn.planar = planar;
             dn.out_split = n_split; dn.gain_next = gain_after(e); dn.ssq_out = ssq;
             { Timed t(c, D3_K_EMPTY, s); }
             { Timed t(c, D3_K_DOWN, s); D3_HIP(launch_gemm_mfma(dn, MODE_RESID, c->n_cu, c->tn, s, &ssq_parts)); }
@@ -611,7 +612,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         g.out = head->logits; g.out_stride = d.vocab; g.ncols = head->n_cols;
         if (mfma) {
             g.x_split = n_split + head->first_col * split_pitch(dm); g.x_stride = dm;
-            g.ssq_in = ssq + (size_t)head->first_col * kSsqStride; g.ssq_parts = ssq_parts;
+            g.ssq_in = ssq + (size_t)head->first_col * kSsqStride; g.ssq_parts = ssq_parts; g.planar = planar;
             Timed t(c, D3_K_LM_HEAD, s);
             D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s));
         } else {
@@ -679,12 +680,12 @@ int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin
     }
     bf16_t* n_split = c->at<bf16_t>(c->lay.n_split);
     float* ssq = c->at<float>(c->lay.ssq);
-    D3_HIP(launch_gain_split(h_last, dm, static_cast<const float*>(c->final_norm), dm, B, n_split, ssq, s));
+    D3_HIP(launch_gain_split(h_last, dm, static_cast<const float*>(c->final_norm), dm, B, n_split, ssq, split_planar(B), s));
     GemvArgs g{};
     g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
     g.K = dm; g.eps = d.rms_eps; g.w[0] = c->lm_head; g.rows[0] = d.vocab; g.total_rows = d.vocab;
     g.out = logits; g.out_stride = d.vocab; g.ncols = B;
-    g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1;
+    g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1; g.planar = split_planar(B);
     { Timed t(c, D3_K_LM_HEAD, s); D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s)); }
     D3_HIP(launch_argmax(logits, d.vocab, B, next_tok, s));
     for (int a = 0; a < B && n_alone > 0; ++a) {       // unequal prompts: these sequences' rows of the head are written again
@@ -888,8 +889,8 @@ int fill_recompute(d3_ctx* c, int pos_begin, int pos_end, hipStream_t s) {
         if (mfma) {
             bf16_t* n_split = c->at<bf16_t>(c->lay.n_split);
             float* ssq = c->at<float>(c->lay.ssq);
-            D3_HIP(launch_gain_split(h, dm, static_cast<const float*>(w.attn_norm), dm, B, n_split, ssq, s));
-            g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1;
+            D3_HIP(launch_gain_split(h, dm, static_cast<const float*>(w.attn_norm), dm, B, n_split, ssq, split_planar(B), s));
+            g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1; g.planar = split_planar(B);
             D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s));
             RopeArgs r{};
             r.qkv = kv; r.k_cache = k_layer; r.v_cache = v_layer; r.rope_cs = rope_cs;

@@ -87,10 +87,16 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
 
 // Activations of the matrix-core projections are split x = hi + lo into two bf16 halves, 32 hi halves and then their 32 lo halves: one 128-byte line
 // holds everything of 32 k, which is what a k-step of the MFMAs reads.  A row of K values is split_pitch(K) halves; value k's hi half is number split_at(k)
-// (k, k + 1, ... of one run of 32 are adjacent), its lo half kSplitLo further on.
+// (k, k + 1, ... of one run of 32 are adjacent), its lo half kSplitLo further on.  In the planar form, which passes of 9 to 16 columns use (split_planar),
+// a row is its K hi halves and then its K lo halves: `lo` below is the distance of a value's two halves, kSplitLo or (planar) K.
 constexpr int kSplitLo = 32;
 __host__ __device__ __forceinline__ size_t split_pitch(size_t K) { return 2 * K; }         // (a line more, so that columns start on different channels: no difference)
-__host__ __device__ __forceinline__ size_t split_at(size_t k) { return 2 * k - (k & 31); }
+__host__ __device__ __forceinline__ size_t split_at(size_t k, int lo = kSplitLo) { return lo == kSplitLo ? 2 * k - (k & 31) : k; }      // the forms of 32 values are the same
+// The narrow projection reads 9 to 16 columns as a tile of hi and a tile of lo halves, 256 bytes of a row at a time; where these are four pieces of 64 bytes it waits longer
+// (sums of the four projections of a block, hi and lo in one line -> planar: 7B shape, 14 columns 98.5 -> 96.5 us; 13B, 12 columns 136.4 -> 134.2; 70B, 16 columns 304.7 -> 302.9,
+// and that with whole lines in the hi and lo tiles of eight columns each; halves of lines, as the planar form's kernel reads them, gave a decode step at the 7B widths 8 % back).
+inline bool split_planar(int ncols) { return ncols > 8 && ncols <= 16; }
+__host__ __device__ __forceinline__ int split_lo(bool planar, int K) { return planar ? K : kSplitLo; }
 // Which of the 32 16-byte pieces of 128 split values (four lines) a lane of a half wave takes: hi or lo, and which eight values of the 128.  Sixteen lanes hold a
 // quarter of the banks' rows each, whether hi and lo rows are staged a multiple of 256 bytes apart or half of that more.
 struct SplitPiece {
@@ -103,31 +109,31 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint3
     lo = bf16_pair(a - bf16_lo(hi), b - bf16_hi(hi));
 }
 // four adjacent values, k % 4 == 0; row: their row of the split
-__device__ __forceinline__ void store_split4(bf16_t* row, size_t k, const float (&v)[4]) {
+__device__ __forceinline__ void store_split4(bf16_t* row, size_t k, const float (&v)[4], int lo = kSplitLo) {
     uint2 h, l;
     split_pair(v[0], v[1], h.x, l.x);
     split_pair(v[2], v[3], h.y, l.y);
-    bf16_t* p = row + split_at(k);
+    bf16_t* p = row + split_at(k, lo);
     *reinterpret_cast<uint2*>(p) = h;
-    *reinterpret_cast<uint2*>(p + kSplitLo) = l;
+    *reinterpret_cast<uint2*>(p + lo) = l;
 }
 // eight, k % 8 == 0
-__device__ __forceinline__ void store_split8(bf16_t* row, size_t k, const float (&v)[8]) {
+__device__ __forceinline__ void store_split8(bf16_t* row, size_t k, const float (&v)[8], int lo = kSplitLo) {
     uint4 h, l;
     split_pair(v[0], v[1], h.x, l.x);
     split_pair(v[2], v[3], h.y, l.y);
     split_pair(v[4], v[5], h.z, l.z);
     split_pair(v[6], v[7], h.w, l.w);
-    bf16_t* p = row + split_at(k);
+    bf16_t* p = row + split_at(k, lo);
     *reinterpret_cast<uint4*>(p) = h;
-    *reinterpret_cast<uint4*>(p + kSplitLo) = l;
+    *reinterpret_cast<uint4*>(p + lo) = l;
 }
-__device__ __forceinline__ void store_split1(bf16_t* row, size_t k, float v) {
+__device__ __forceinline__ void store_split1(bf16_t* row, size_t k, float v, int lo = kSplitLo) {
     uint32_t h, l;
     split_pair(v, 0.f, h, l);
-    bf16_t* p = row + split_at(k);
+    bf16_t* p = row + split_at(k, lo);
     p[0] = (bf16_t)h;
-    p[kSplitLo] = (bf16_t)l;
+    p[lo] = (bf16_t)l;
 }
 
 // Data handed from one workgroup to another inside a kernel is written and read with agent-scope
@@ -205,6 +211,7 @@ struct GemvArgs {
     // to ssq_out[col][workgroup].
     const float* ssq_in;     // [ncols][kSsqStride]
     int ssq_parts;
+    int planar;              // x_split and out_split are in the planar form (projections of up to 16 columns)
     float* ssq_out;          // [ncols][kSsqStride]
     // wide MFMA kernel (17..32 columns), K cut into slices: partial accumulators and one arrival counter per row
     // group (zero between launches)
@@ -219,7 +226,7 @@ struct GemvArgs {
 // that the next one waits behind.
 __device__ __forceinline__ void gemm_take_args(const GemvArgs& a) {
     asm volatile("" :: "s"(a.x_split), "s"(a.w[0]), "s"(a.w[1]), "s"(a.w[2]), "s"(a.rows[0]), "s"(a.rows[1]),
-                       "s"(a.K), "s"(a.total_rows), "s"(a.ncols), "s"(a.ssq_in), "s"(a.ssq_parts));
+                       "s"(a.K), "s"(a.total_rows), "s"(a.ncols), "s"(a.ssq_in), "s"(a.ssq_parts), "s"(a.planar));
 }
 // The matrix that output row `row` of a row-stacked projection belongs to, and the row's number in it (a choice among three scalars: by index, the
 // argument is read a second time, from an address that depends on the first).
@@ -283,13 +290,13 @@ size_t gemv_alu_max_cols(int K, int weight_dtype);   // columns one ALU launch c
 
 // split = x * gain (bf16 halves), ssq[col * kSsqStride] = sum(x^2)
 int launch_gain_split(const float* x, int x_stride, const float* gain, int K, int ncols,
-                      bf16_t* split, float* ssq, hipStream_t s);
+                      bf16_t* split, float* ssq, bool planar, hipStream_t s);
 
 // ---------------- the rest of a block ----------------
 // x[c][:] = E[token(c)][:], and the pass's rotary table rope_cs[c][j] = (cos, sin)((pos(c) - row0[seq(c)]) * inv_freq[j])
 // (row0 optional: the first cache row of each sequence of a left-padded batch)
 // What a pass on the matrix-core path starts from, beside x (gain NULL: not wanted; bf16 tables only): launch_gain_split's outputs.
-struct EmbedSplit { const float* gain; bf16_t* split; float* ssq; };
+struct EmbedSplit { const float* gain; bf16_t* split; float* ssq; int lo; };
 // The columns of `runs`: tokens [B][P] of the cache rows from pos_begin on; also col_at[c] = (sequence, cache row) of every column.
 int launch_embed_runs(const void* tok_emb, const int32_t* tokens, const SeqRuns& runs, int P, int pos_begin, int ncols, int d, int vocab,
                       float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, int2* col_at, const EmbedSplit& split, hipStream_t s);   // bf16 table
@@ -325,7 +332,8 @@ struct AttnArgs {
     float* part_ml;        // [ncols][H][n_splits][2]  (max, sum)
     int* tickets;          // [ncols][H] arrival counters, zero between launches
     float* out;            // [ncols][H*hd]
-    bf16_t* out_split;     // optional split copy [ncols][split_pitch(H*hd)]
+    bf16_t* out_split;     // optional split copy [ncols][split_pitch(H*hd)] ...
+    int split_lo;          // ... and the distance of a value's halves in it
     // set by launch_attention: what the kernel divides by: columns per position, query heads per KV head, split length
     Divisor by_b, by_group, by_split;
 };

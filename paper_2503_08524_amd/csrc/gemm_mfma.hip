@@ -46,10 +46,10 @@ __device__ __forceinline__ void tile_load(TileRegs& r, const bf16_t* row0_k0, si
 #pragma unroll
     for (int q = 0; q < 4; ++q) r.q[q] = load_stream16(row0_k0 + (size_t)(4 * q + (lane >> 4)) * row_stride + (k - k0));
 }
-// ... of one half of split activations (row0: the tile's first row, from the half's first value on)
-__device__ __forceinline__ void tile_load_cached(TileRegs& r, const bf16_t* row0, int k0, int K) {
+// ... of one half of split activations (row0: the tile's first row, from the half's first value on; lo: see split_at)
+__device__ __forceinline__ void tile_load_cached(TileRegs& r, const bf16_t* row0, int k0, int K, int lo) {
     const int lane = threadIdx.x & 63;
-    const int at = min(2 * k0 + (int)split_at((lane & 15) * 8), (int)split_at(K - 8));         // k0 is a multiple of 32
+    const int k = min(k0 + (lane & 15) * 8, K - 8), at = (int)split_at(k, lo);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const uint4 v = *reinterpret_cast<const uint4*>(row0 + (4 * q + (lane >> 4)) * split_pitch(K) + at);
@@ -57,10 +57,10 @@ __device__ __forceinline__ void tile_load_cached(TileRegs& r, const bf16_t* row0
     }
 }
 // The packed B tile of up to 8 columns: tile rows 0..7 are the hi halves of columns 0..7, rows 8..15 their lo halves.  32 lanes read a column's 512 bytes (whole
-// lines; 64 bytes of every line twice cost a step at the 70B widths 0.5 %), in the order of SplitPiece.
+// lines; 64 bytes of every line twice cost a step at the 70B widths 0.5 %).  Staged, 16 lanes hold all banks once: the lo rows lie half of the banks further on.
 __device__ __forceinline__ void tile_load_packed(TileRegs& r, const bf16_t* split, int k0, int K) {
     const int lane = threadIdx.x & 63;
-    const int at = min(2 * k0 + 8 * SplitPiece(lane).index(), 2 * K - 8);      // a ragged last turn re-reads valid bytes
+    const int at = min(2 * k0 + 8 * (lane & 31), 2 * K - 8);      // a ragged last turn re-reads valid bytes
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const uint4 v = *reinterpret_cast<const uint4*>(split + (2 * q + (lane >> 5)) * split_pitch(K) + at);
@@ -77,10 +77,10 @@ __device__ __forceinline__ void frags_of(const char* tile, u32x4 (&frag)[U]) {
 }
 __device__ __forceinline__ void packed_to_frags(const TileRegs& r, char* tile, u32x4 (&frag)[U]) {
     const int lane = threadIdx.x & 63;
-    const SplitPiece p(lane);
+    const int lo = lane >> 2 & 1, seg = 4 * (lane >> 3 & 3) + (lane & 3);
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<u32x4*>(tile + (2 * q + (lane >> 5) + 8 * p.lo) * kTileRowBytes + p.seg * 16) = r.q[q];
+        *reinterpret_cast<u32x4*>(tile + (2 * q + (lane >> 5) + 8 * lo) * kTileRowBytes + seg * 16) = r.q[q];
     frags_of(tile, frag);
 }
 __device__ __forceinline__ void tile_to_frags(const TileRegs& r, char* tile, u32x4 (&frag)[U]) {
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
     __shared__ float inv_rms[kMaxCols];                // RMSNorm scale of each column (input side)
     __shared__ float sq[MODE == MODE_RESID ? kMaxCols : 1][16 * RT];   // squares of the new residual (output side)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
-    const int K = a.K, row0 = blockIdx.x * (16 * RT);
+    const int K = a.K, lo = split_lo(a.planar, K), out_lo = split_lo(a.planar, a.out_stride), row0 = blockIdx.x * (16 * RT);
     char* tile = reinterpret_cast<char*>(red) + (size_t)wave * kTileBytes;
 
     const bf16_t* wrow[NA];                            // row 0 of each A tile
@@ -135,8 +135,8 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
         } else {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                tile_load_cached(gb[2 * t], a.x_split + t * 16 * split_pitch(K), k0, K);
-                tile_load_cached(gb[2 * t + 1], a.x_split + t * 16 * split_pitch(K) + kSplitLo, k0, K);
+                tile_load_cached(gb[2 * t], a.x_split + t * 16 * split_pitch(K), k0, K, lo);
+                tile_load_cached(gb[2 * t + 1], a.x_split + t * 16 * split_pitch(K) + lo, k0, K, lo);
             }
         }
 #pragma unroll
@@ -153,9 +153,9 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 tile_to_frags(gb[2 * t], tile, bf[2 * t]);
-                if (next) tile_load_cached(gb[2 * t], a.x_split + t * 16 * split_pitch(K), k1, K);
+                if (next) tile_load_cached(gb[2 * t], a.x_split + t * 16 * split_pitch(K), k1, K, lo);
                 tile_to_frags(gb[2 * t + 1], tile, bf[2 * t + 1]);
-                if (next) tile_load_cached(gb[2 * t + 1], a.x_split + t * 16 * split_pitch(K) + kSplitLo, k1, K);
+                if (next) tile_load_cached(gb[2 * t + 1], a.x_split + t * 16 * split_pitch(K) + lo, k1, K, lo);
             }
         }
 #pragma unroll
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
             sq[col][r * 16 + 4 * (l >> 4) + e] = v * v;
             split = v * a.gain_next[row];
         }
-        if (a.out_split) store_split1(a.out_split + col * split_pitch(a.out_stride), row, split);
+        if (a.out_split) store_split1(a.out_split + col * split_pitch(a.out_stride), row, split, out_lo);
     }
     if (MODE == MODE_RESID && a.ssq_out) {
         __syncthreads();
@@ -301,13 +301,14 @@ int launch_mode(const GemvArgs& a, int mode, int rt, int tiles, int waves, size_
 int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {
     const int tiles = a.total_rows / 16;
     const int nt = a.ncols > 16 ? 2 : 1;
+    if (a.planar && a.ncols > 16) return (int)hipErrorInvalidValue;       // the narrow kernel's
     if (gemm_prompt_takes(a, mode, tn)) return launch_gemm_prompt(a, mode, n_cu, tn, s, n_groups);
     if (mode == MODE_QKV_ROPE) return (int)hipErrorInvalidValue;
     if (nt == 2 && a.part && tn.mfma_wide) return launch_gemm_mfma_wide(a, mode, n_cu, tn, s, n_groups);
     if (a.ncols > kMaxCols) return (int)hipErrorInvalidValue;
     const int sw = mode == MODE_SWIGLU ? 2 : 1;
     const int turns = (a.K / 32 + U - 1) / U;                  // 128-k turns along K
-    const bool pack = a.ncols <= 8;
+    const bool pack = a.ncols <= 8 && !a.planar;       // (the head of few columns of a planar pass)
     const int nb = pack ? 1 : 2 * nt;
     // Most tiles per workgroup (activation reuse) that still puts a workgroup on at least 0.6 of the compute units
     // (measured: fewer starve the memory system, more only add activation traffic) and >= 4 waves per CU on the

@@ -210,6 +210,20 @@ def test_recompute_fill_matches_oracle_and_continuation_reads_it(B, start, kv):
     print(f"  worst recomputed row err {worst:.3e}; continuation logit abs err {wl:.3e}, hidden {wh:.3e}", flush=True)
 
 
+@pytest.mark.parametrize("B", [9, 16])
+def test_recompute_fill_of_nine_to_sixteen_columns(B):
+    # the kept residual, split in the planar form that the projections of so many columns read
+    from paper_2503_08524_amd import binding
+    shape, P, G, alpha, start = SHAPE, 6, 9, 0.8, 2
+    w = d3_inputs.make_weights(shape, 2)
+    prompts, forced = d3_inputs.make_prompt(B, P, shape.V, seed=1), d3_inputs.make_prompt(B, G - 1, shape.V, seed=4)
+    print(f"case recompute fill B={B}", flush=True)
+    gpu = helpers.gpu_generate(shape, w, prompts, G, alpha, start, forced=forced, kv_dtype="f32", fill_each_step=True, fill_mode=binding.D3_FILL_RECOMPUTE)
+    _, gens = helpers.oracle_generate(shape, w, prompts, G, alpha, start, forced=forced, max_seq=P + G)
+    helpers.compare(gpu, gens, G)
+    _check_recomputed_rows(gpu["decoder"], gens, shape, P, G, 5e-5)
+
+
 @pytest.mark.parametrize("mode", ["copy", "recompute"])
 def test_schedule_whose_depth_rises_again_reads_the_filled_rows(mode):
     """The case the paper's first challenge describes (Section 1): a token runs blocks that an earlier token skipped, so

@@ -154,6 +154,16 @@ def test_small_bf16_matrix_core_path(B, P):
     _run(SMALL_BF16, B, P, 8, 0.9, 2, forced_seed=7)
 
 
+# planar split: decode and prompt passes of 9 to 16 columns, heads of as many and of fewer columns behind them, heads of 9 to 16 columns behind a wider pass (hi and lo
+# in one line), contractions whose last turn is ragged, grouped queries
+@pytest.mark.parametrize("B,P,d,F,H_kv,kv", [(9, 1, 96, 160, 2, "f32"), (16, 1, 256, 416, 1, "f16"), (1, 13, 96, 160, 1, "f32"), (3, 4, 160, 96, 2, "f32"), (8, 2, 256, 224, 2, "f32"),
+                                             (12, 3, 160, 288, 1, "f32"), (16, 9, 256, 512, 2, "f32"), (1, 75, 96, 160, 2, "f32"), (11, 5, 32, 32, 1, "f16")])
+def test_nine_to_sixteen_columns(B, P, d, F, H_kv, kv):
+    s = ModelShape("planar", L=3, d=d, H=2, H_kv=H_kv, hd=64, F=F, V=512, dtype="bf16")
+    gpu, gens = _run(s, B, P, 4, 0.97, 2, forced_seed=19, kv_dtype=kv)
+    helpers.compare(gpu, gens, 4, **({} if kv == "f16" else {"logit_atol": 2e-4, "hidden_tol": 1e-4}))
+
+
 @pytest.mark.parametrize("shape,B,P", [(SMALL_BF16, 2, 24), (SMALL_BF16, 2, 97), (SMALL_BF16, 1, 81), (SMALL_GQA, 1, 80),
                                        (SMALL_GQA, 2, 72), (SMALL_GQA, 1, 128), (SMALL_BF16, 2, 50), (SMALL_GQA, 1, 168),
                                        (SMALL_GQA, 1, 136), (SMALL_BF16, 1, 144), (SMALL_GQA, 2, 145), (SMALL_GQA, 1, 72), (SMALL_GQA, 1, 145),
