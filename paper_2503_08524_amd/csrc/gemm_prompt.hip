@@ -706,6 +706,7 @@ int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, 
     const int ot = mode == MODE_SWIGLU ? 8 : 16;       // output row tiles per workgroup: 256 slab rows
     const int n_rb = (tiles + ot - 1) / ot;
     if (a.ssq_out && n_rb > kSsqStride) return (int)hipErrorInvalidValue;
+    if (mode == MODE_QKV_ROPE && (a.hd != 128 || !a.ssq_in || !a.col_at || !a.rope_cs || (a.kv_dtype != 0 && a.kv_dtype != 2))) return (int)hipErrorInvalidValue;
     if (n_groups) *n_groups = n_rb;
     const int n_stages = a.K / (2 * kBK) * 2, tiles_wg = n_rb * n_cb;
     const int cus = tn.prompt_cus ? tn.prompt_cus : n_cu;
@@ -715,10 +716,7 @@ int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, 
         if (tn.prompt_tile == 256 ? other < HUGE_VAL : other < prompt_cost(mode, n_stages, cus, sp)) return launch_gemm_prompt_256(a, mode, cus, s, n_groups);
     }
     if (mode == MODE_STORE) return launch_prompt<MODE_STORE>(a, n_rb, n_cb, sp, s);
-    if (mode == MODE_QKV_ROPE) {
-        if (a.hd != 128 || !a.ssq_in || !a.col_at || !a.rope_cs || (a.kv_dtype != 0 && a.kv_dtype != 2)) return (int)hipErrorInvalidValue;
-        return launch_prompt<MODE_QKV_ROPE>(a, n_rb, n_cb, sp, s);
-    }
+    if (mode == MODE_QKV_ROPE) return launch_prompt<MODE_QKV_ROPE>(a, n_rb, n_cb, sp, s);
     if (mode == MODE_SWIGLU) return launch_prompt<MODE_SWIGLU>(a, n_rb, n_cb, sp, s);
     return launch_prompt<MODE_RESID>(a, n_rb, n_cb, sp, s);
 }
