@@ -23,7 +23,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {          // byte offsets into the workspace
-    size_t x, qkv, attn_o, act, part_o, part_ml, tickets, logits, s_split, f_split, inv_freq, rope_cs, n_split, ssq, h_skip, gemm_part, gemm_part_bytes, gemm_tickets, row0, col_at, h_last, total;
+    size_t x, qkv, attn_o, act, part_o, part_ml, tickets, logits, s_split, f_split, split_cols, inv_freq, rope_cs, n_split, ssq, h_skip, gemm_part, gemm_part_bytes, gemm_tickets, row0, col_at, h_last, total;
 };
 
 // The vector-ALU GEMV stages one column of its input in LDS.
@@ -96,11 +96,12 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
     l.part_ml = take(PC * d.n_heads * kMaxSplits * 2 * 4);
     l.tickets = take(C * d.n_heads * 4);
     l.logits = take(PC * (size_t)d.vocab * 4);                        // one row per sequence
-    l.s_split = take(CS * split_pitch(s_dim) * 2);
-    l.f_split = take(CS * split_pitch(d.d_ffn) * 2);
+    l.split_cols = CS;
+    l.s_split = take(CS * s_dim * 4);
+    l.f_split = take(CS * (size_t)d.d_ffn * 4);
     l.inv_freq = take((size_t)d.head_dim / 2 * 8);
     l.rope_cs = take(C * (size_t)d.head_dim / 2 * 8);
-    l.n_split = take(CS * split_pitch(d.d_model) * 2);
+    l.n_split = take(CS * (size_t)d.d_model * 4);
     l.ssq = take(C * kSsqStride * 4);
     l.h_skip = take(PC * d.d_model * 4);                              // decode passes only
     l.gemm_part_bytes = with_gemm_part ? gemm_part_bytes(d, C, prompt_passes) : 0;
@@ -467,8 +468,6 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     auto gain_after = [&](int e) -> const float* {
         return static_cast<const float*>(e + 1 < n_ids ? c->layers[ids[e + 1]].attn_norm : c->final_norm);
     };
-    const bool planar = mfma && split_planar(ncols);   // ... in this form from the embedding to the head
-    const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_split, ssq, split_lo(planar, dm)};
 
     // a prompt chunk of one sequence (consecutive positions) or of several: tiles of queries share the cache rows they read
     const int grp = d.n_heads / d.n_kv_heads;
@@ -477,6 +476,11 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     SeqRuns one{};
     one.n = 1; one.seq[0] = cm.seq(0); one.col[1] = ncols; one.pos[0] = cm.pos(0);
     const SeqRuns& runs = shared ? *shared : one;
+    // the form of the pass's split activations
+    const PromptDims dims{dm, qdim, qkv_dim, F, qtile};
+    const bool lines = ncols <= 8 || (mfma && prompt_pass_in_lines(dims, ncols, c->lay.gemm_part_bytes, c->n_cu, c->tn));
+    auto form = [&](int K) { return lines ? split_lines(K) : split_planes(K, c->lay.split_cols); };
+    const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_split, ssq, form(dm)};
     int2* col_at = qtile ? c->at<int2>(c->lay.col_at) : nullptr;
     if (qtile) D3_HIP(launch_embed_runs(c->tok_emb, tokens, runs, cm.P, cm.pos_begin, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, col_at, split, s));
     else D3_HIP(launch_embed(c->tok_emb, d.weight_dtype, tokens, cm, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, split, s));
@@ -514,7 +518,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         void* k_layer = c->k_cache + (size_t)l * c->kv_layer_bytes();
         void* v_layer = c->v_cache + (size_t)l * c->kv_layer_bytes();
         if (mfma) {
-            g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = ssq_parts; g.planar = planar;
+            g.x_split = n_split; g.x_form = form(dm); g.ssq_in = ssq; g.ssq_parts = ssq_parts;
             const bool rope_in_qkv = qtile && gemm_prompt_takes(g, MODE_QKV_ROPE, c->tn);
             {
                 Timed t(c, D3_K_QKV, s);
@@ -543,7 +547,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         at.ncols = ncols; at.H = d.n_heads; at.H_kv = d.n_kv_heads; at.hd = hd; at.max_seq = d.max_seq;
         at.split_len = split_len; at.n_splits = n_splits;
         at.part_o = c->at<float>(c->lay.part_o); at.part_ml = c->at<float>(c->lay.part_ml); at.tickets = c->at<int>(c->lay.tickets);
-        at.out = attn_o; at.out_split = mfma ? s_split : nullptr; at.split_lo = split_lo(planar, qdim);
+        at.out = attn_o; at.out_split = mfma ? s_split : nullptr; at.out_form = form(qdim);
         at.rope_cs = rope_in_attn ? rope_cs : nullptr;
         at.qtile = qtile ? 1 : 0;
         at.row0 = row0;
@@ -554,7 +558,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
                 own.ncols = runs.col[r + 1] - col;
                 own.cm = ColMap{0, 1, own.ncols, runs.pos[r], runs.seq[r]};
                 own.q += (size_t)col * qkv_dim;
-                own.out += (size_t)col * qdim; own.out_split += col * split_pitch(qdim);
+                own.out += (size_t)col * qdim; own.out_split += (size_t)col * at.out_form.pitch;
                 pick_splits(c, own.ncols, runs.pos[r] + own.ncols, c->attn_wgs_per_cu * c->n_cu, &own.split_len, &own.n_splits, true);
                 Timed t(c, D3_K_ATTN, s);
                 D3_HIP(launch_attention(own, d.kv_dtype, true, s));
@@ -571,8 +575,8 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         {
             Timed t(c, D3_K_OPROJ, s);
             if (mfma) {
-                o.x_split = s_split; o.x_stride = qdim; o.planar = planar;
-                o.out_split = n_split; o.gain_next = static_cast<const float*>(w.mlp_norm); o.ssq_out = ssq;
+                o.x_split = s_split; o.x_form = form(qdim);
+                o.out_split = n_split; o.out_form = form(dm); o.gain_next = static_cast<const float*>(w.mlp_norm); o.ssq_out = ssq;
                 D3_HIP(launch_gemm_mfma(o, MODE_RESID, c->n_cu, c->tn, s, &ssq_parts));
             }
             else { o.x = attn_o; o.x_stride = qdim; D3_HIP(alu(o, 0, ncols, MODE_RESID, false)); }
@@ -587,11 +591,11 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         dn.part = c->at<float>(c->lay.gemm_part); dn.part_bytes = c->lay.gemm_part_bytes; dn.part_tickets = c->at<int>(c->lay.gemm_tickets);
         dn.K = F; dn.w[0] = w.w_down; dn.rows[0] = dm; dn.total_rows = dm; dn.out = x; dn.out_stride = dm; dn.ncols = ncols;
         if (mfma) {
-            u.x_split = n_split; u.x_stride = dm; u.ssq_in = ssq; u.ssq_parts = ssq_parts; u.planar = planar;
-            u.out = nullptr; u.out_split = f_split;
+            u.x_split = n_split; u.x_form = form(dm); u.ssq_in = ssq; u.ssq_parts = ssq_parts;
+            u.out = nullptr; u.out_split = f_split; u.out_form = form(F);
             { Timed t(c, D3_K_GATE_UP, s); D3_HIP(launch_gemm_mfma(u, MODE_SWIGLU, c->n_cu, c->tn, s)); }
-            dn.x_split = f_split; dn.x_stride = F; dn.planar = planar;
-            dn.out_split = n_split; dn.gain_next = gain_after(e); dn.ssq_out = ssq;
+            dn.x_split = f_split; dn.x_form = form(F);
+            dn.out_split = n_split; dn.out_form = form(dm); dn.gain_next = gain_after(e); dn.ssq_out = ssq;
             { Timed t(c, D3_K_EMPTY, s); }
             { Timed t(c, D3_K_DOWN, s); D3_HIP(launch_gemm_mfma(dn, MODE_RESID, c->n_cu, c->tn, s, &ssq_parts)); }
         } else {
@@ -611,8 +615,8 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         g.K = dm; g.eps = d.rms_eps; g.w[0] = c->lm_head; g.rows[0] = d.vocab; g.total_rows = d.vocab;
         g.out = head->logits; g.out_stride = d.vocab; g.ncols = head->n_cols;
         if (mfma) {
-            g.x_split = n_split + head->first_col * split_pitch(dm); g.x_stride = dm;
-            g.ssq_in = ssq + (size_t)head->first_col * kSsqStride; g.ssq_parts = ssq_parts; g.planar = planar;
+            g.x_form = form(dm); g.x_split = n_split + (size_t)head->first_col * g.x_form.pitch;
+            g.ssq_in = ssq + (size_t)head->first_col * kSsqStride; g.ssq_parts = ssq_parts;
             Timed t(c, D3_K_LM_HEAD, s);
             D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s));
         } else {
@@ -680,12 +684,13 @@ int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin
     }
     bf16_t* n_split = c->at<bf16_t>(c->lay.n_split);
     float* ssq = c->at<float>(c->lay.ssq);
-    D3_HIP(launch_gain_split(h_last, dm, static_cast<const float*>(c->final_norm), dm, B, n_split, ssq, split_planar(B), s));
     GemvArgs g{};
+    g.x_form = B <= 8 ? split_lines(dm) : split_planes(dm, c->lay.split_cols);
+    D3_HIP(launch_gain_split(h_last, dm, static_cast<const float*>(c->final_norm), dm, B, n_split, ssq, g.x_form, s));
     g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
     g.K = dm; g.eps = d.rms_eps; g.w[0] = c->lm_head; g.rows[0] = d.vocab; g.total_rows = d.vocab;
     g.out = logits; g.out_stride = d.vocab; g.ncols = B;
-    g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1; g.planar = split_planar(B);
+    g.x_split = n_split; g.ssq_in = ssq; g.ssq_parts = 1;
     { Timed t(c, D3_K_LM_HEAD, s); D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s)); }
     D3_HIP(launch_argmax(logits, d.vocab, B, next_tok, s));
     for (int a = 0; a < B && n_alone > 0; ++a) {       // unequal prompts: these sequences' rows of the head are written again
@@ -889,8 +894,9 @@ int fill_recompute(d3_ctx* c, int pos_begin, int pos_end, hipStream_t s) {
         if (mfma) {
             bf16_t* n_split = c->at<bf16_t>(c->lay.n_split);
             float* ssq = c->at<float>(c->lay.ssq);
-            D3_HIP(launch_gain_split(h, dm, static_cast<const float*>(w.attn_norm), dm, B, n_split, ssq, split_planar(B), s));
-            g.x_split = n_split; g.x_stride = dm; g.ssq_in = ssq; g.ssq_parts = 1; g.planar = split_planar(B);
+            g.x_form = B <= 8 ? split_lines(dm) : split_planes(dm, c->lay.split_cols);
+            D3_HIP(launch_gain_split(h, dm, static_cast<const float*>(w.attn_norm), dm, B, n_split, ssq, g.x_form, s));
+            g.x_split = n_split; g.ssq_in = ssq; g.ssq_parts = 1;
             D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s));
             RopeArgs r{};
             r.qkv = kv; r.k_cache = k_layer; r.v_cache = v_layer; r.rope_cs = rope_cs;

@@ -85,40 +85,40 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
 }
 
-// Activations of the matrix-core projections are split x = hi + lo into two bf16 halves, 32 hi halves and then their 32 lo halves: one 128-byte line
-// holds everything of 32 k, which is what a k-step of the MFMAs reads.  A row of K values is split_pitch(K) halves; value k's hi half is number split_at(k)
-// (k, k + 1, ... of one run of 32 are adjacent), its lo half kSplitLo further on.  In the planar form, which passes of 9 to 16 columns use (split_planar),
-// a row is its K hi halves and then its K lo halves: `lo` below is the distance of a value's two halves, kSplitLo or (planar) K.
+// Activations of the matrix-core projections are split x = hi + lo into two bf16 halves, in one of two forms, which a pass keeps from the embedding to the head:
+//  * planes: the hi halves of a column are a row of K, and the lo halves one of another array.  What moves 16 columns or more reads 256 bytes of a row at a time.
+//  * lines: 32 hi halves and then their 32 lo halves, so that one 128-byte line holds everything of 32 k, which is what a k-step of the MFMAs reads; a row is 2 K halves.  For
+//    up to 8 columns, which are one MFMA operand together (64 bytes of every line twice cost a step at the 70B widths 0.5 %), and for passes that take tiles of 256 columns, whose
+//    slab of activations is 32 k.  Elsewhere it loses: columns are twice as far apart, and those a large power of two apart meet on memory channels, and 16 columns' rows are read
+//    by shorter pieces.  Lines / planes, us: a block's four projections at 14 columns of the 7B shape 98.5 / 96.5; prompts: 2048 wide, head_dim 64, 256 columns 554 / 541 (its down
+//    projection 52 / 41), 70B widths, 128 columns, 1179 / 1154, 13B widths, 129 columns, 708 / 693, 7B shape, 128 columns, 492 / 488; decode steps of 17 to 32 columns equal to 0.5 %.
+//    Rows of lines padded by 128 to 1152 bytes mend the first and the third and cost the second 2 to 7 %.
+// pitch: halves from column to column; lo: halves from a value's hi half to its lo half.
+struct SplitForm { int pitch; size_t lo; };
 constexpr int kSplitLo = 32;
-__host__ __device__ __forceinline__ size_t split_pitch(size_t K) { return 2 * K; }         // (a line more, so that columns start on different channels: no difference)
-__host__ __device__ __forceinline__ size_t split_at(size_t k, int lo = kSplitLo) { return lo == kSplitLo ? 2 * k - (k & 31) : k; }      // the forms of 32 values are the same
-// The narrow projection reads 9 to 16 columns as a tile of hi and a tile of lo halves, 256 bytes of a row at a time; where these are four pieces of 64 bytes it waits longer
-// (sums of the four projections of a block, hi and lo in one line -> planar: 7B shape, 14 columns 98.5 -> 96.5 us; 13B, 12 columns 136.4 -> 134.2; 70B, 16 columns 304.7 -> 302.9,
-// and that with whole lines in the hi and lo tiles of eight columns each; halves of lines, as the planar form's kernel reads them, gave a decode step at the 7B widths 8 % back).
-inline bool split_planar(int ncols) { return ncols > 8 && ncols <= 16; }
-__host__ __device__ __forceinline__ int split_lo(bool planar, int K) { return planar ? K : kSplitLo; }
-// Which of the 32 16-byte pieces of 128 split values (four lines) a lane of a half wave takes: hi or lo, and which eight values of the 128.  Sixteen lanes hold a
-// quarter of the banks' rows each, whether hi and lo rows are staged a multiple of 256 bytes apart or half of that more.
-struct SplitPiece {
-    int lo, seg;
-    __device__ __forceinline__ explicit SplitPiece(int lane) : lo(lane >> 3 & 1), seg(8 * ((lane >> 3 ^ lane >> 4) & 1) + (lane & 7)) {}
-    __device__ __forceinline__ int index() const { return 8 * (seg >> 2) + 4 * lo + (seg & 3); }
-};
+inline SplitForm split_lines(int K) { return SplitForm{2 * K, kSplitLo}; }
+inline SplitForm split_planes(int K, size_t columns) { return SplitForm{K, columns * K}; }     // columns: of the whole plane, 32 or more
+__host__ __device__ __forceinline__ bool split_in_lines(const SplitForm& f, int K) { return f.pitch == 2 * K; }
+// where in its row value k's hi half is (k, k + 1, ... of one run of 32 are adjacent); a kernel that knows the form says so
+enum { SPLIT_ANY, SPLIT_LINES, SPLIT_PLANES };
+template <int FORM = SPLIT_ANY>
+__device__ __forceinline__ size_t split_at(size_t k, size_t lo) { return FORM == SPLIT_LINES || (FORM == SPLIT_ANY && lo == kSplitLo) ? 2 * k - (k & 31) : k; }
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
     hi = bf16_pair(a, b);
     lo = bf16_pair(a - bf16_lo(hi), b - bf16_hi(hi));
 }
 // four adjacent values, k % 4 == 0; row: their row of the split
-__device__ __forceinline__ void store_split4(bf16_t* row, size_t k, const float (&v)[4], int lo = kSplitLo) {
+template <int FORM = SPLIT_ANY>
+__device__ __forceinline__ void store_split4(bf16_t* row, size_t k, const float (&v)[4], size_t lo) {
     uint2 h, l;
     split_pair(v[0], v[1], h.x, l.x);
     split_pair(v[2], v[3], h.y, l.y);
-    bf16_t* p = row + split_at(k, lo);
+    bf16_t* p = row + split_at<FORM>(k, lo);
     *reinterpret_cast<uint2*>(p) = h;
     *reinterpret_cast<uint2*>(p + lo) = l;
 }
 // eight, k % 8 == 0
-__device__ __forceinline__ void store_split8(bf16_t* row, size_t k, const float (&v)[8], int lo = kSplitLo) {
+__device__ __forceinline__ void store_split8(bf16_t* row, size_t k, const float (&v)[8], size_t lo) {
     uint4 h, l;
     split_pair(v[0], v[1], h.x, l.x);
     split_pair(v[2], v[3], h.y, l.y);
@@ -128,10 +128,11 @@ __device__ __forceinline__ void store_split8(bf16_t* row, size_t k, const float 
     *reinterpret_cast<uint4*>(p) = h;
     *reinterpret_cast<uint4*>(p + lo) = l;
 }
-__device__ __forceinline__ void store_split1(bf16_t* row, size_t k, float v, int lo = kSplitLo) {
+template <int FORM = SPLIT_ANY>
+__device__ __forceinline__ void store_split1(bf16_t* row, size_t k, float v, size_t lo) {
     uint32_t h, l;
     split_pair(v, 0.f, h, l);
-    bf16_t* p = row + split_at(k, lo);
+    bf16_t* p = row + split_at<FORM>(k, lo);
     p[0] = (bf16_t)h;
     p[lo] = (bf16_t)l;
 }
@@ -179,9 +180,10 @@ __device__ __forceinline__ float wave_sum(float v) { return reduce_row(reduce_ro
 enum GemvMode { MODE_STORE = 0, MODE_RESID = 1, MODE_SWIGLU = 2, MODE_QKV_ROPE = 3 };
 
 struct GemvArgs {
-    // activations: fp32 [ncols][x_stride] (ALU path) or their split into bf16 halves [.][split_pitch(K)] (MFMA path)
+    // activations: fp32 [ncols][x_stride] (ALU path) or their split into bf16 halves in x_form (MFMA path)
     const float* x;
     const bf16_t* x_split;
+    SplitForm x_form;
     size_t part_bytes;   // what part holds
     int x_stride;
     const float* gain;   // RMSNorm gain [K] when the norm is fused (ALU path), else nullptr
@@ -192,7 +194,8 @@ struct GemvArgs {
     int rows[3];
     int total_rows;      // output rows
     float* out;          // fp32 [ncols][out_stride]
-    bf16_t* out_split;   // optional split copy [ncols][split_pitch(out_stride)] of the output for an MFMA consumer
+    bf16_t* out_split;   // optional split copy of the output for an MFMA consumer
+    SplitForm out_form;
     const float* gain_next;   // [total_rows], see ssq_out
     int out_stride;
     int ncols;
@@ -211,7 +214,6 @@ struct GemvArgs {
     // to ssq_out[col][workgroup].
     const float* ssq_in;     // [ncols][kSsqStride]
     int ssq_parts;
-    int planar;              // x_split and out_split are in the planar form (projections of up to 16 columns)
     float* ssq_out;          // [ncols][kSsqStride]
     // wide MFMA kernel (17..32 columns), K cut into slices: partial accumulators and one arrival counter per row
     // group (zero between launches)
@@ -225,8 +227,8 @@ struct GemvArgs {
 // What the first loads of a matrix-core projection need of the arguments, requested together: read as they come up, each is a round trip to memory
 // that the next one waits behind.
 __device__ __forceinline__ void gemm_take_args(const GemvArgs& a) {
-    asm volatile("" :: "s"(a.x_split), "s"(a.w[0]), "s"(a.w[1]), "s"(a.w[2]), "s"(a.rows[0]), "s"(a.rows[1]),
-                       "s"(a.K), "s"(a.total_rows), "s"(a.ncols), "s"(a.ssq_in), "s"(a.ssq_parts), "s"(a.planar));
+    asm volatile("" :: "s"(a.x_split), "s"(a.x_form.lo), "s"(a.w[0]), "s"(a.w[1]), "s"(a.w[2]), "s"(a.rows[0]), "s"(a.rows[1]),
+                       "s"(a.K), "s"(a.total_rows), "s"(a.ncols), "s"(a.ssq_in), "s"(a.ssq_parts));
 }
 // The matrix that output row `row` of a row-stacked projection belongs to, and the row's number in it (a choice among three scalars: by index, the
 // argument is read a second time, from an address that depends on the first).
@@ -282,21 +284,24 @@ int launch_gemv_alu(const GemvArgs& a, int weight_dtype, int mode, bool norm, in
 int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups = nullptr);
 int launch_gemm_mfma_wide(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // 17..128 columns
 bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn);   // launch_gemm_mfma sends the launch to launch_gemm_prompt
-// gemm_prompt_256.hip, which launch_gemm_prompt chooses by this estimate (in its own unit; infinite: not for that kernel)
-double gemm_prompt_256_cost(const GemvArgs& a, int mode, int n_cu);
+// gemm_prompt_256.hip, which launch_gemm_prompt chooses by this estimate (in its own unit; infinite: not for that kernel); part_bytes: 0 without part buffer
+double gemm_prompt_256_cost(int mode, int total_rows, int K, int ncols, size_t part_bytes, int n_cu);
 int launch_gemm_prompt_256(const GemvArgs& a, int mode, int n_cu, hipStream_t s, int* n_groups);
+// Whether a prompt pass keeps its split activations in lines, because its projections then take less (launch_gemm_prompt).
+struct PromptDims { int d_model, q_dim, qkv_rows, d_ffn; bool rope_in_qkv; };
+bool prompt_pass_in_lines(const PromptDims& d, int ncols, size_t part_bytes, int n_cu, const Tuning& tn);
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups);   // up to kPassCols columns: LDS-tiled, compute-bound
 size_t gemv_alu_max_cols(int K, int weight_dtype);   // columns one ALU launch can take (LDS bound)
 
 // split = x * gain (bf16 halves), ssq[col * kSsqStride] = sum(x^2)
 int launch_gain_split(const float* x, int x_stride, const float* gain, int K, int ncols,
-                      bf16_t* split, float* ssq, bool planar, hipStream_t s);
+                      bf16_t* split, float* ssq, SplitForm form, hipStream_t s);
 
 // ---------------- the rest of a block ----------------
 // x[c][:] = E[token(c)][:], and the pass's rotary table rope_cs[c][j] = (cos, sin)((pos(c) - row0[seq(c)]) * inv_freq[j])
 // (row0 optional: the first cache row of each sequence of a left-padded batch)
 // What a pass on the matrix-core path starts from, beside x (gain NULL: not wanted; bf16 tables only): launch_gain_split's outputs.
-struct EmbedSplit { const float* gain; bf16_t* split; float* ssq; int lo; };
+struct EmbedSplit { const float* gain; bf16_t* split; float* ssq; SplitForm form; };
 // The columns of `runs`: tokens [B][P] of the cache rows from pos_begin on; also col_at[c] = (sequence, cache row) of every column.
 int launch_embed_runs(const void* tok_emb, const int32_t* tokens, const SeqRuns& runs, int P, int pos_begin, int ncols, int d, int vocab,
                       float* x, const double* inv_freq, int half_hd, float2* rope_cs, const int* row0, int2* col_at, const EmbedSplit& split, hipStream_t s);   // bf16 table
@@ -332,8 +337,8 @@ struct AttnArgs {
     float* part_ml;        // [ncols][H][n_splits][2]  (max, sum)
     int* tickets;          // [ncols][H] arrival counters, zero between launches
     float* out;            // [ncols][H*hd]
-    bf16_t* out_split;     // optional split copy [ncols][split_pitch(H*hd)] ...
-    int split_lo;          // ... and the distance of a value's halves in it
+    bf16_t* out_split;     // optional split copy
+    SplitForm out_form;
     // set by launch_attention: what the kernel divides by: columns per position, query heads per KV head, split length
     Divisor by_b, by_group, by_split;
 };

@@ -46,13 +46,13 @@ __device__ __forceinline__ void tile_load(TileRegs& r, const bf16_t* row0_k0, si
 #pragma unroll
     for (int q = 0; q < 4; ++q) r.q[q] = load_stream16(row0_k0 + (size_t)(4 * q + (lane >> 4)) * row_stride + (k - k0));
 }
-// ... of one half of split activations (row0: the tile's first row, from the half's first value on; lo: see split_at)
-__device__ __forceinline__ void tile_load_cached(TileRegs& r, const bf16_t* row0, int k0, int K, int lo) {
+// ... of one plane of split activations (row0: the tile's first row in it)
+__device__ __forceinline__ void tile_load_cached(TileRegs& r, const bf16_t* row0, int k0, int K) {
     const int lane = threadIdx.x & 63;
-    const int k = min(k0 + (lane & 15) * 8, K - 8), at = (int)split_at(k, lo);
+    const int k = min(k0 + (lane & 15) * 8, K - 8);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const uint4 v = *reinterpret_cast<const uint4*>(row0 + (4 * q + (lane >> 4)) * split_pitch(K) + at);
+        const uint4 v = *reinterpret_cast<const uint4*>(row0 + (size_t)(4 * q + (lane >> 4)) * K + k);
         r.q[q] = u32x4{v.x, v.y, v.z, v.w};
     }
 }
@@ -63,7 +63,7 @@ __device__ __forceinline__ void tile_load_packed(TileRegs& r, const bf16_t* spli
     const int at = min(2 * k0 + 8 * (lane & 31), 2 * K - 8);      // a ragged last turn re-reads valid bytes
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const uint4 v = *reinterpret_cast<const uint4*>(split + (2 * q + (lane >> 5)) * split_pitch(K) + at);
+        const uint4 v = *reinterpret_cast<const uint4*>(split + (size_t)(2 * q + (lane >> 5)) * 2 * K + at);
         r.q[q] = u32x4{v.x, v.y, v.z, v.w};
     }
 }
@@ -91,9 +91,22 @@ __device__ __forceinline__ void tile_to_frags(const TileRegs& r, char* tile, u32
     frags_of(tile, frag);
 }
 
+// ... and from planes: 16 lanes read 256 bytes of a column's row in one of them
+__device__ __forceinline__ void tile_load_packed(TileRegs& r, const bf16_t* hi, const bf16_t* lo, int k0, int K) {
+    const int lane = threadIdx.x & 63;
+    const int k = min(k0 + (lane & 15) * 8, K - 8);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint4 v = *reinterpret_cast<const uint4*>((q < 2 ? hi : lo) + (size_t)(4 * (q & 1) + (lane >> 4)) * K + k);
+        r.q[q] = u32x4{v.x, v.y, v.z, v.w};
+    }
+}
+
+// PACK: up to 8 columns in one B tile, of split activations in lines, or (the head of few columns behind a wider pass) in planes.
+enum { PACK_NONE = 0, PACK_LINES = 1, PACK_PLANES = 2 };
 // ROUND: a wave's turns begin at turn (workgroup / 8) modulo their number and go round (gemm_rounds says where).  The eight workgroups of one start go
 // to the eight XCDs.  Up to eight columns four waves per SIMD have to fit where they did before: 128 registers for a tile pair.
-template <int NT, int MODE, int RT, bool PACK, bool ROUND>
+template <int NT, int MODE, int RT, int PACK, bool ROUND>
 __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2 : 1) <= 2 ? 4 : 1) void gemm_mfma_kernel(GemvArgs a) {   // <= 8 waves
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;  // weight matrices per output tile
     constexpr int NA = RT * SW;                        // A tiles per wave
@@ -103,7 +116,7 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
     __shared__ float inv_rms[kMaxCols];                // RMSNorm scale of each column (input side)
     __shared__ float sq[MODE == MODE_RESID ? kMaxCols : 1][16 * RT];   // squares of the new residual (output side)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
-    const int K = a.K, lo = split_lo(a.planar, K), out_lo = split_lo(a.planar, a.out_stride), row0 = blockIdx.x * (16 * RT);
+    const int K = a.K, row0 = blockIdx.x * (16 * RT);
     char* tile = reinterpret_cast<char*>(red) + (size_t)wave * kTileBytes;
 
     const bf16_t* wrow[NA];                            // row 0 of each A tile
@@ -130,13 +143,15 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
     TileRegs ga[NA], gb[NB];                           // the loads of one turn, in flight while the previous turn computes
     auto issue = [&](int ks0) {
         const int k0 = ks0 * 32;
-        if constexpr (PACK) {
+        if constexpr (PACK == PACK_LINES) {
             tile_load_packed(gb[0], a.x_split, k0, K);
+        } else if constexpr (PACK == PACK_PLANES) {
+            tile_load_packed(gb[0], a.x_split, a.x_split + a.x_form.lo, k0, K);
         } else {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                tile_load_cached(gb[2 * t], a.x_split + t * 16 * split_pitch(K), k0, K, lo);
-                tile_load_cached(gb[2 * t + 1], a.x_split + t * 16 * split_pitch(K) + lo, k0, K, lo);
+                tile_load_cached(gb[2 * t], a.x_split + (size_t)(t * 16) * K, k0, K);
+                tile_load_cached(gb[2 * t + 1], a.x_split + a.x_form.lo + (size_t)(t * 16) * K, k0, K);
             }
         }
 #pragma unroll
@@ -146,16 +161,19 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
     auto turn = [&](int ks0, bool next, int ks_next) {
         u32x4 bf[NB][U];
         const int k1 = ks_next * 32;
-        if constexpr (PACK) {
+        if constexpr (PACK == PACK_LINES) {
             packed_to_frags(gb[0], tile, bf[0]);
             if (next) tile_load_packed(gb[0], a.x_split, k1, K);
+        } else if constexpr (PACK == PACK_PLANES) {
+            tile_to_frags(gb[0], tile, bf[0]);
+            if (next) tile_load_packed(gb[0], a.x_split, a.x_split + a.x_form.lo, k1, K);
         } else {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 tile_to_frags(gb[2 * t], tile, bf[2 * t]);
-                if (next) tile_load_cached(gb[2 * t], a.x_split + t * 16 * split_pitch(K), k1, K, lo);
+                if (next) tile_load_cached(gb[2 * t], a.x_split + (size_t)(t * 16) * K, k1, K);
                 tile_to_frags(gb[2 * t + 1], tile, bf[2 * t + 1]);
-                if (next) tile_load_cached(gb[2 * t + 1], a.x_split + t * 16 * split_pitch(K) + lo, k1, K, lo);
+                if (next) tile_load_cached(gb[2 * t + 1], a.x_split + a.x_form.lo + (size_t)(t * 16) * K, k1, K);
             }
         }
 #pragma unroll
@@ -167,7 +185,7 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
             for (int u = 0; u < U; ++u) {
                 if (ks0 + u < nks) {
                     const bf16x8 wa = __builtin_bit_cast(bf16x8, af[u]);
-                    if constexpr (PACK)
+                    if constexpr (PACK != PACK_NONE)
                         acc[r][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, __builtin_bit_cast(bf16x8, bf[0][u]), acc[r][0], 0, 0, 0);
 #pragma unroll
                     for (int t = 0; t < (PACK ? 0 : NT); ++t) {
@@ -260,7 +278,10 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
             sq[col][r * 16 + 4 * (l >> 4) + e] = v * v;
             split = v * a.gain_next[row];
         }
-        if (a.out_split) store_split1(a.out_split + col * split_pitch(a.out_stride), row, split, out_lo);
+        if (a.out_split) {
+            if constexpr (PACK == PACK_LINES) store_split1<SPLIT_LINES>(a.out_split + (size_t)col * 2 * a.out_stride, row, split, kSplitLo);
+            else store_split1<SPLIT_PLANES>(a.out_split + (size_t)col * a.out_stride, row, split, a.out_form.lo);
+        }
     }
     if (MODE == MODE_RESID && a.ssq_out) {
         __syncthreads();
@@ -273,7 +294,7 @@ __global__ __launch_bounds__(512, ROUND && PACK && RT * (MODE == MODE_SWIGLU ? 2
     }
 }
 
-template <int NT, int MODE, bool PACK>
+template <int NT, int MODE, int PACK>
 int launch_rt(const GemvArgs& a, int rt, int tiles, int waves, size_t lds, hipStream_t s) {
     const bool round = NT == 1 && gemm_rounds(a.K);
 #define D3_LAUNCH(RT) do { if (round) hipLaunchKernelGGL((gemm_mfma_kernel<NT, MODE, RT, PACK, NT == 1>), dim3(tiles / RT), dim3(64 * waves), lds, s, a); \
@@ -285,30 +306,32 @@ int launch_rt(const GemvArgs& a, int rt, int tiles, int waves, size_t lds, hipSt
     return (int)hipGetLastError();
 }
 
-template <int NT, bool PACK>
+template <int NT, int PACK>
 int launch_mode(const GemvArgs& a, int mode, int rt, int tiles, int waves, size_t lds, hipStream_t s) {
     if (mode == MODE_STORE) return launch_rt<NT, MODE_STORE, PACK>(a, rt, tiles, waves, lds, s);
-    if (mode == MODE_RESID) return launch_rt<NT, MODE_RESID, PACK>(a, rt, tiles, waves, lds, s);
-    return launch_rt<NT, MODE_SWIGLU, PACK>(a, rt, tiles, waves, lds, s);
+    if constexpr (PACK == PACK_PLANES) return (int)hipErrorInvalidValue;
+    else if (mode == MODE_RESID) return launch_rt<NT, MODE_RESID, PACK>(a, rt, tiles, waves, lds, s);
+    else return launch_rt<NT, MODE_SWIGLU, PACK>(a, rt, tiles, waves, lds, s);
 }
 
 }  // namespace
 
 // Requirements (checked by the caller): bf16 weights; K % 32 == 0; total_rows and every rows[m]
-// multiples of 16; 1 <= ncols <= 32; x_split holds 32 rows (rows beyond
+// multiples of 16; 1 <= ncols <= 32; x_split in lines for up to 8 columns, or in planes, of 32 columns (those beyond
 // ncols may hold anything finite or not: their columns are never written); with ssq_out, total_rows / 16 <=
 // kSsqStride (every workgroup owns a slot).
 int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {
     const int tiles = a.total_rows / 16;
     const int nt = a.ncols > 16 ? 2 : 1;
-    if (a.planar && a.ncols > 16) return (int)hipErrorInvalidValue;       // the narrow kernel's
     if (gemm_prompt_takes(a, mode, tn)) return launch_gemm_prompt(a, mode, n_cu, tn, s, n_groups);
     if (mode == MODE_QKV_ROPE) return (int)hipErrorInvalidValue;
+    const bool lines = split_in_lines(a.x_form, a.K);
+    if (lines ? a.ncols > 8 : a.x_form.pitch != a.K) return (int)hipErrorInvalidValue;      // lines: the packed kernel alone
     if (nt == 2 && a.part && tn.mfma_wide) return launch_gemm_mfma_wide(a, mode, n_cu, tn, s, n_groups);
     if (a.ncols > kMaxCols) return (int)hipErrorInvalidValue;
     const int sw = mode == MODE_SWIGLU ? 2 : 1;
     const int turns = (a.K / 32 + U - 1) / U;                  // 128-k turns along K
-    const bool pack = a.ncols <= 8 && !a.planar;       // (the head of few columns of a planar pass)
+    const bool pack = lines || (a.ncols <= 8 && mode == MODE_STORE);
     const int nb = pack ? 1 : 2 * nt;
     // Most tiles per workgroup (activation reuse) that still puts a workgroup on at least 0.6 of the compute units
     // (measured: fewer starve the memory system, more only add activation traffic) and >= 4 waves per CU on the
@@ -342,9 +365,10 @@ int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hi
     if (a.ssq_out && tiles / best_rt > kSsqStride) return (int)hipErrorInvalidValue;
     size_t lds = (size_t)best_waves * best_rt * sw * nt * 4 * 64 * sizeof(float);   // cross-wave sum ...
     if (lds < (size_t)best_waves * kTileBytes) lds = (size_t)best_waves * kTileBytes;    // ... or one staging tile per wave
-    if (nt == 2) return launch_mode<2, false>(a, mode, best_rt, tiles, best_waves, lds, s);
-    if (pack) return launch_mode<1, true>(a, mode, best_rt, tiles, best_waves, lds, s);
-    return launch_mode<1, false>(a, mode, best_rt, tiles, best_waves, lds, s);
+    if (nt == 2) return launch_mode<2, PACK_NONE>(a, mode, best_rt, tiles, best_waves, lds, s);
+    if (lines) return launch_mode<1, PACK_LINES>(a, mode, best_rt, tiles, best_waves, lds, s);
+    if (pack) return launch_mode<1, PACK_PLANES>(a, mode, best_rt, tiles, best_waves, lds, s);
+    return launch_mode<1, PACK_NONE>(a, mode, best_rt, tiles, best_waves, lds, s);
 }
 
 }  // namespace d3

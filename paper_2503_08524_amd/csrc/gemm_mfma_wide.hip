@@ -100,16 +100,15 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
         }
     }
 
-    // this thread's pieces of the panel: start of the column, LDS offset; 32 threads read a column's 512 bytes of a turn (64 bytes of every line twice: 1 %)
+    // this thread's pieces of the panel: start of the column's plane, k offset inside a turn, LDS offset
     const bf16_t* psrc[PBT];
     int pdst[PBT];
-    const SplitPiece piece(tid);
-    const int pat = 8 * piece.index();
+    const int pseg = tid & 15;
 #pragma unroll
     for (int i = 0; i < PBT; ++i) {
-        const int col = (tid + i * (W * 64)) >> 5;
-        psrc[i] = a.x_split + col * split_pitch(K);
-        pdst[i] = (2 * (col >> 4) + piece.lo) * kTile + (col & 15) * kPitch + piece.seg * 16;
+        const int cidx = tid + i * (W * 64), tb = cidx >> 8, r = (cidx >> 4) & 15;
+        psrc[i] = a.x_split + ((tb & 1) ? a.x_form.lo : 0) + (size_t)((tb >> 1) * 16 + r) * K;
+        pdst[i] = tb * kTile + r * kPitch + pseg * 16;
     }
 
     f32x4 acc[NA][CT];
@@ -121,10 +120,10 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
     u32x4 pb[PBT];
     TileRegs ga[D][NA];                                // weight tiles of D turns in flight
     auto panel_issue = [&](int t) {
-        const int at = min(2 * kt(t) * (U * 32) + pat, 2 * K - 8);
+        const int k = min(kt(t) * (U * 32) + pseg * 8, K - 8);
 #pragma unroll
         for (int i = 0; i < PBT; ++i) {
-            const uint4 v = *reinterpret_cast<const uint4*>(psrc[i] + at);
+            const uint4 v = *reinterpret_cast<const uint4*>(psrc[i] + k);
             pb[i] = u32x4{v.x, v.y, v.z, v.w};
         }
     };
@@ -318,7 +317,7 @@ __global__ __launch_bounds__(W * 64, (MODE == MODE_SWIGLU && CT == 2) ? 3 : 1) v
                 split[0] = v[0] * gn.x; split[1] = v[1] * gn.y; split[2] = v[2] * gn.z; split[3] = v[3] * gn.w;
             }
             if (a.out) *reinterpret_cast<float4*>(a.out + oi) = make_float4(v[0], v[1], v[2], v[3]);
-            if (a.out_split) store_split4(a.out_split + col * split_pitch(a.out_stride), row, split);
+            if (a.out_split) store_split4<SPLIT_PLANES>(a.out_split + (size_t)col * a.out_stride, row, split, a.out_form.lo);
         }
     }
     if (MODE == MODE_RESID && a.ssq_out) {             // rows of a column: the 4 lane groups by butterfly, then the waves in order
@@ -380,7 +379,7 @@ int launch_rt(const GemvArgs& a, int ct, int rt, int groups, int ks, hipStream_t
 
 }  // namespace
 
-// Requirements: those of launch_gemm_mfma, 17 <= ncols <= kPassCols (x_split holds kPassCols rows); a.part holds kGemmPartBytes and a.part_tickets
+// Requirements: those of launch_gemm_mfma, 17 <= ncols <= kPassCols (x_split in planes, of ncols columns rounded up to the launch's 32, 64 or 128); a.part holds kGemmPartBytes and a.part_tickets
 // kGemmPartTickets zeroed counters (the kernel leaves them zero).
 namespace {
 
@@ -390,9 +389,9 @@ int launch_config(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipSt
 GemvArgs columns_of(const GemvArgs& a, int first, int n) {
     GemvArgs g = a;
     g.ncols = n;
-    g.x_split += first * split_pitch(a.K);
+    g.x_split += (size_t)first * a.x_form.pitch;
     if (g.out) g.out += (size_t)first * a.out_stride;
-    if (g.out_split) g.out_split += first * split_pitch(a.out_stride);
+    if (g.out_split) g.out_split += (size_t)first * a.out_form.pitch;
     if (g.ssq_in) g.ssq_in += (size_t)first * kSsqStride;
     if (g.ssq_out) g.ssq_out += (size_t)first * kSsqStride;
     return g;

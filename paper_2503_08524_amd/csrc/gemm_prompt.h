@@ -51,7 +51,7 @@ template <int... R>
 __device__ __forceinline__ void read_a_frags(u32x4 (&f)[RW], uint32_t A, std::integer_sequence<int, R...>) {
     ((f[R] = lds_read_frag<R * 16 * kPitch>(A)), ...);
 }
-// Column tile TT of a k-step whose activation fragments start OFF bytes behind h (hi halves) and l (lo halves: the segments of the lo halves are four from
+// Column tile TT of a k-step whose activation fragments start OFF bytes behind h (hi halves) and l (lo halves; where a line holds both, their segments are four from
 // those of the hi halves, and the swizzle leaves that a single bit of the address).
 constexpr uint32_t kLoBit = 4 * 16;
 template <int TT, int OFF = 0>
@@ -100,7 +100,7 @@ __device__ __forceinline__ void store_tiles(const GemvArgs& a, const f32x4 (&acc
         }
         if (otile < tiles && col < a.ncols) {
             if (a.out) *reinterpret_cast<float4*>(a.out + (size_t)col * a.out_stride + row) = make_float4(v[0], v[1], v[2], v[3]);
-            if (a.out_split) store_split4(a.out_split + col * split_pitch(a.out_stride), row, v);
+            if (a.out_split) store_split4(a.out_split + (size_t)col * a.out_form.pitch, row, v, a.out_form.lo);
         }
     }
 }

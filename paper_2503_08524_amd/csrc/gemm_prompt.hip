@@ -4,7 +4,7 @@
 // With hundreds of columns the contraction is compute-bound (the prompt pass is the one part of the path that is), so
 // the design is the opposite of the skinny kernels': operands are staged in LDS and re-used from there.  A workgroup of
 // eight waves owns a tile of 256 weight rows x 128 columns and walks K in stages of 64: the stage's weight slab (256 rows x
-// 128 bytes) and activation slab (128 columns, a plane of 32 k, hi and lo halves, per k-step) go from global memory straight into LDS
+// 128 bytes) and activation slab (128 columns, hi plane and lo plane, or a plane of 32 k, hi and lo halves, per k-step: see SplitForm) go from global memory straight into LDS
 // (buffer_load_dwordx4 ... lds: 16 bytes per lane, lane l of the wave lands at base + 16 l, one instruction fills eight
 // 128-byte slab rows).  LDS holds three weight slabs and two activation slabs, 160 KB; one workgroup per compute unit.
 //
@@ -52,6 +52,7 @@
 // wave, so a wave finishes silu(gate) * up from its own accumulators.  Operand layouts, RMSNorm folding (1/rms from the
 // producer's partial sums of squares, x * gain and the sum of squares of the new residual handed to the consumer) and
 // epilogues are those of the skinny matrix-core kernels.
+#include <algorithm>
 #include <cmath>
 
 #include "gemm_prompt.h"
@@ -62,7 +63,7 @@ namespace {
 
 constexpr int kTileM = 256, kTileN = 128;      // weight rows and columns of a workgroup tile
 constexpr int kABytes = kTileM * kPitch;       // weight slab of a stage
-constexpr int kPlane = kTileN * kPitch;        // one plane of its activation slab: 32 k, hi and lo halves
+constexpr int kPlane = kTileN * kPitch;        // one plane of its activation slab: 64 hi or lo halves, or 32 k of both
 constexpr int kXBytes = 2 * kPlane;
 constexpr int kLdsX = 3 * kABytes;             // LDS: three weight slabs, two activation slabs
 constexpr int kPromptLds = kLdsX + 2 * kXBytes;        // 160 KB, all there is
@@ -125,7 +126,7 @@ __device__ __forceinline__ void add_residual(const GemvArgs& a, char* lds, int r
             store_row4(a.out + oi, v);
             if (a.out_split) {                         // a normalised projection reads it next: hand it x * gain (and sum(x^2) below)
                 const float w[4] = {v[0] * gain.x, v[1] * gain.y, v[2] * gain.z, v[3] * gain.w};
-                store_split4(a.out_split + (cb * kTileN + column(i)) * split_pitch(a.out_stride), row, w);
+                store_split4(a.out_split + (size_t)(cb * kTileN + column(i)) * a.out_form.pitch, row, w, a.out_form.lo);
             }
         }
     }
@@ -217,9 +218,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
     // a workgroup's start to its first load / to its first MFMA, 7B shape, 512 columns, gate/up: 4300 / 13300 with divisions and arguments as they
     // came up, 3350 / 11500 with the divisors' reciprocals from the host and each load sent as soon as its address is known, 1700 / 9300 with this.
     const bf16_t* const arg_x = a.x_split;
+    const size_t arg_lo = a.x_form.lo;
     const void *const arg_w0 = a.w[0], *const arg_w1 = MODE == MODE_RESID ? nullptr : a.w[1], *const arg_w2 = MODE == MODE_RESID || MODE == MODE_SWIGLU ? nullptr : a.w[2];
-    const int K = a.K, pitch_x = 2 * (int)split_pitch(K), total_rows = a.total_rows, rows0 = a.rows[0], rows1 = a.rows[1];
-    asm volatile("" :: "s"(arg_x), "s"(arg_w0), "s"(arg_w1), "s"(arg_w2), "s"(K), "s"(total_rows), "s"(rows0), "s"(rows1),
+    const int K = a.K, total_rows = a.total_rows, rows0 = a.rows[0], rows1 = a.rows[1];
+    asm volatile("" :: "s"(arg_x), "s"(arg_lo), "s"(arg_w0), "s"(arg_w1), "s"(arg_w2), "s"(K), "s"(total_rows), "s"(rows0), "s"(rows1),
                  "s"(order.n_rb), "s"(order.n_cb), "s"(order.n_whole), "s"(order.group_tiles.m));
 
     // ---- launch order -> tile, K part; tile -> (row block, column block) ----
@@ -261,19 +263,20 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
     const int s_end = (K + kBK - 1) / kBK, n_single = slice == parts - 1 ? s_end - 2 * pairs : 0;      // 0, 1 or 2
     // (the launcher sees to at least two whole stages per part)
 
-    // ---- this wave's eight-row blocks of a stage (wave8, wave8 + 8, ...): the first 32 are weight rows, then the activations of k-step 0, then of 1 ----
+    // ---- this wave's eight-row blocks of a stage (wave8, wave8 + 8, ...): the first 32 are weight rows, then the activations' first plane, then the second ----
     // Slab tile st = 8 wy + t is wave row wy's tile t.  Plain modes: output tile OT rb + st.  SwiGLU: tiles t < 4 are gate rows,
     // the others the up rows of the same outputs OT rb + 4 wy + t % 4.  Tiles past the matrix re-read the last one (result dropped).
     // Each block's first load goes out before the next block's address is worked out: the code up to here comes from memory too, a line at a time.
     // lane l of a load: row l / 8 of the block, LDS position l % 8, i.e. segment (l % 8) ^ ((slab row / 2) % 8) of that row
     const int prow = lane >> 3, pseg = (lane & 7) ^ ((lane >> 4) | (4 * (wave8 & 1)));
-    const int voff_w = 2 * (prow * K + pseg * 8), voff_x = prow * pitch_x + pseg * 16, voff_x64 = voff_x + 64 * pitch_x;
+    const bool lines = arg_lo == kSplitLo;             // see SplitForm
+    const int pitch_x = lines ? 4 * K : 2 * K, step_x = lines ? 2 * kPitch : kPitch, voff_w = 2 * (prow * K + pseg * 8), voff_x = prow * pitch_x + pseg * 16, voff_x64 = voff_x + 64 * pitch_x;
     __amdgpu_buffer_rsrc_t src[kLoadsW + 2];           // a block of eight weight rows each; the wave's columns c and c + 64 of a plane each
     static_assert(kLoadsX == 4, "two loads of eight columns per plane");
     auto load1 = [&](int j, int t, int lds) {         // t: stage of the whole K; lds: where its slab (weights j < kLoadsW, or activations) lies
         const int jx = j - kLoadsW;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(src[j < kLoadsW ? j : kLoadsW + jx / 2], (__attribute__((address_space(3))) void*)((lds_char*)prompt_lds + lds + (wave8 + kWaves * (j < kLoadsW ? j : jx)) * 1024),
-                                                 16, j < kLoadsW ? voff_w : jx % 2 ? voff_x64 : voff_x, j < kLoadsW ? t * kPitch : t * 2 * kPitch, 0, 0);
+                                                 16, j < kLoadsW ? voff_w : jx % 2 ? voff_x64 : voff_x, j < kLoadsW ? t * kPitch : t * step_x, 0, 0);
     };
     int w0 = 0, w1 = kABytes, w2 = 2 * kABytes;        // the weight slabs of this stage and the next two
 #pragma unroll
@@ -292,9 +295,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
             const bf16_t* p = static_cast<const bf16_t*>(w) + (size_t)(local + 8 * (blk & 1)) * K;
             src[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 2 * 8 * K, 0x00027000);
         } else if ((j - kLoadsW) % 2 == 0) {
-            const int step = (j - kLoadsW) / 2;        // in bytes, a k-step of a column is one line
-            const bf16_t* p = arg_x + (cb * kTileN + 8 * wave8) * split_pitch(K) + step * (kPitch / 2);
-            src[kLoadsW + step] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 71 * pitch_x + 4 * K - step * kPitch, 0x00027000);
+            const int half = (j - kLoadsW) / 2;
+            const bf16_t* p = arg_x + (size_t)(cb * kTileN + 8 * wave8) * (pitch_x / 2) + (half ? lines ? kPitch / 2 : arg_lo : 0);
+            src[kLoadsW + half] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, 72 * pitch_x - (lines ? half * kPitch : 0), 0x00027000);
         }
         load1(j, s0, j < kLoadsW ? w0 : kLdsX);
         fixed_here();
@@ -307,11 +310,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_kernel(GemvArgs a, Ti
 #pragma unroll
         for (int j = kLoadsW; j < kLoads; ++j) load1(j, t, kLdsX + buf * kXBytes);
     };
-    // fragment reads: lane (i, g) takes segment 4 grp + g of row i of a weight tile, segments g and 4 + g of column i of plane grp (tile bases are
-    // multiples of 16 rows, so the swizzle depends on i alone)
+    // fragment reads: lane (i, g) takes segment 4 grp + g of row i of a weight tile and of column i of both planes, or segments g and 4 + g of column i of plane grp
+    // (tile bases are multiples of 16 rows, so the swizzle depends on i alone)
     const uint32_t slot = (uint32_t)(((grp * 4 + lg) ^ ((li >> 1) & 7)) << 4), slot_b = (uint32_t)((lg ^ ((li >> 1) & 7)) << 4);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)prompt_lds;
-    const uint32_t a_off = lds0 + (wy * 16 * RW + li) * kPitch + slot, b_off = lds0 + kLdsX + grp * kPlane + (wx * 64 + li) * kPitch + slot_b, b_lo = b_off ^ kLoBit;
+    const uint32_t a_off = lds0 + (wy * 16 * RW + li) * kPitch + slot, b_off = lds0 + kLdsX + (wx * 64 + li) * kPitch + (lines ? grp * kPlane + slot_b : slot),
+                   b_lo = lines ? b_off ^ kLoBit : b_off + kPlane;
 
     f32x4 acc[RW][2 * CW];                             // [row tile of the wave][column tile of the wave]
 #pragma unroll
@@ -673,6 +677,16 @@ double prompt_cost(int mode, int n_stages, int n_cu, const PromptSplit& sp) {
     return (sp.n_whole + n_cu - 1) / n_cu * (stage * n_stages + tile) + stage * sp.cut_cost;
 }
 
+// Both kernels' costs of a launch; the measurements' overrides make one of them infinite.
+struct PromptCosts { double small, large; };
+PromptCosts prompt_costs(int mode, int total_rows, int K, int ncols, size_t part_bytes, int n_cu, const Tuning& tn) {
+    const int tiles = total_rows / 16, ot = mode == MODE_SWIGLU ? 8 : 16, n_rb = (tiles + ot - 1) / ot, n_cb = (ncols + kTileN - 1) / kTileN, n_stages = K / (2 * kBK) * 2;
+    PromptCosts c{prompt_cost(mode, n_stages, n_cu, prompt_split(n_rb * n_cb, n_stages, n_cu, tn.prompt_ks, part_bytes > 0)), HUGE_VAL};
+    if (tn.prompt_tile == 256 || (tn.prompt_tile == 0 && tn.prompt_ks == 0 && tn.prompt_cus == 0)) c.large = gemm_prompt_256_cost(mode, total_rows, K, ncols, part_bytes, n_cu);
+    if (tn.prompt_tile == 256 && c.large < HUGE_VAL) c.small = HUGE_VAL;
+    return c;
+}
+
 template <int MODE>
 int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, PromptSplit sp, hipStream_t s) {
     constexpr int lds = kPromptLds;
@@ -686,7 +700,7 @@ int launch_prompt(const GemvArgs& a, int n_rb, int n_cb, PromptSplit sp, hipStre
 }  // namespace
 
 // Requirements: those of launch_gemm_mfma (bf16 weights, K % 32 == 0, row counts multiples of 16), K >= 128, 1 <= ncols <=
-// kPassCols (x_split holds ncols rounded up to 128 rows); one matrix in MODE_RESID; with ssq_out at most kSsqStride row blocks.  MODE_QKV_ROPE: head_dim
+// kPassCols (x_split holds ncols columns rounded up to 128, in either form); one matrix in MODE_RESID; with ssq_out at most kSsqStride row blocks.  MODE_QKV_ROPE: head_dim
 // 128, ssq_in, col_at and rope_cs set, only q is written to out.
 // Up to 128 columns the panel kernel is the other choice.  It slows down past 64 (its LDS pipe, or two launches of 64), the LDS-tiled
 // kernel takes one column block whatever its width and wants row blocks.  Measured at 65 / 77 / 128 columns (us between events, panel -> LDS-tiled): 48 or
@@ -699,6 +713,19 @@ bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn) {
     return a.K >= 2 * kBK && a.part && tn.mfma_wide && (a.ncols > 128 || (a.ncols > 64 && row_blocks >= tn.prompt_row_blocks));
 }
 
+bool prompt_pass_in_lines(const PromptDims& d, int ncols, size_t part_bytes, int n_cu, const Tuning& tn) {
+    if (!tn.mfma_wide || ncols <= 128 || std::min(std::min(d.d_model, d.q_dim), d.d_ffn) < 2 * kBK) return false;      // all of its projections have to read this form
+    const struct { int mode, rows, K; } launches[] = {{d.rope_in_qkv ? MODE_QKV_ROPE : MODE_STORE, d.qkv_rows, d.d_model}, {MODE_RESID, d.d_model, d.q_dim},
+                                                      {MODE_SWIGLU, d.d_ffn, d.d_model}, {MODE_RESID, d.d_model, d.d_ffn}};
+    double small = 0, best = 0;
+    for (const auto& l : launches) {
+        const PromptCosts c = prompt_costs(l.mode, l.rows, l.K, ncols, part_bytes, tn.prompt_cus ? tn.prompt_cus : n_cu, tn);
+        small += c.small;
+        best += std::min(c.small, c.large);
+    }
+    return best < 0.99 * small;
+}
+
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {
     const int tiles = a.total_rows / 16;
     const int n_cb = (a.ncols + kTileN - 1) / kTileN;
@@ -706,15 +733,16 @@ int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, 
     const int ot = mode == MODE_SWIGLU ? 8 : 16;       // output row tiles per workgroup: 256 slab rows
     const int n_rb = (tiles + ot - 1) / ot;
     if (a.ssq_out && n_rb > kSsqStride) return (int)hipErrorInvalidValue;
-    if (mode == MODE_QKV_ROPE && (a.hd != 128 || !a.ssq_in || !a.col_at || !a.rope_cs || (a.kv_dtype != 0 && a.kv_dtype != 2))) return (int)hipErrorInvalidValue;
     if (n_groups) *n_groups = n_rb;
     const int n_stages = a.K / (2 * kBK) * 2, tiles_wg = n_rb * n_cb;
     const int cus = tn.prompt_cus ? tn.prompt_cus : n_cu;
-    const PromptSplit sp = prompt_split(tiles_wg, n_stages, cus, tn.prompt_ks, a.part && a.part_tickets);
-    if (tn.prompt_tile == 256 || (tn.prompt_tile == 0 && tn.prompt_ks == 0 && tn.prompt_cus == 0)) {
-        const double other = gemm_prompt_256_cost(a, mode, cus);
-        if (tn.prompt_tile == 256 ? other < HUGE_VAL : other < prompt_cost(mode, n_stages, cus, sp)) return launch_gemm_prompt_256(a, mode, cus, s, n_groups);
+    const bool parts = a.part && a.part_tickets;
+    if (mode == MODE_QKV_ROPE && (a.hd != 128 || !a.ssq_in || !a.col_at || !a.rope_cs || (a.kv_dtype != 0 && a.kv_dtype != 2))) return (int)hipErrorInvalidValue;
+    if (split_in_lines(a.x_form, a.K)) {
+        const PromptCosts cost = prompt_costs(mode, a.total_rows, a.K, a.ncols, parts ? a.part_bytes : 0, cus, tn);
+        if (cost.large < cost.small && (mode == MODE_RESID || a.ssq_in)) return launch_gemm_prompt_256(a, mode, cus, s, n_groups);
     }
+    const PromptSplit sp = prompt_split(tiles_wg, n_stages, cus, tn.prompt_ks, parts);
     if (mode == MODE_STORE) return launch_prompt<MODE_STORE>(a, n_rb, n_cb, sp, s);
     if (mode == MODE_QKV_ROPE) return launch_prompt<MODE_QKV_ROPE>(a, n_rb, n_cb, sp, s);
     if (mode == MODE_SWIGLU) return launch_prompt<MODE_SWIGLU>(a, n_rb, n_cb, sp, s);

@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_256_kernel(Args256) {
     // (l % 8) ^ ((slab row / 2) % 8) of that row.  They run ahead of the arithmetic and into the next unit: activations (32 k at a time) two k-steps,
     // weights (64 k) three slabs.  Past the last unit nothing is fetched (a range of zero bytes). ----
     const int prow = lane >> 3, pseg = (lane & 7) ^ ((lane >> 4) | (4 * (wave8 & 1)));
-    const int pitch_x = 2 * (int)split_pitch(K), voff_w = 2 * (prow * K + pseg * 8), voff_x = (8 * wave8 + prow) * pitch_x + pseg * 16;
+    const int pitch_x = 4 * K, voff_w = 2 * (prow * K + pseg * 8), voff_x = (8 * wave8 + prow) * pitch_x + pseg * 16;
     __amdgpu_buffer_rsrc_t src_w[kLoads], src_x;
     int at_w, at_x, step_w, step_x, rows_x;            // byte offsets into the rows, what they advance by; 64 columns
     auto point_w = [&](const Args256& args, const Unit& u, bool live) {
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_256_kernel(Args256) {
     auto point_x = [&](const Args256& args, const Unit& u, bool live) {
         int rb, cb;
         place(args.order, u.tile, rb, cb);
-        src_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(args.a.x_split) + cb * kTileN * split_pitch(K), 0, live ? kTileN * pitch_x : 0, 0x00027000);
+        src_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(args.a.x_split) + (size_t)(cb * kTileN) * 2 * K, 0, live ? kTileN * pitch_x : 0, 0x00027000);
         at_x = live ? u.s0 * 2 * kPitch : 0;
         step_x = live ? kPitch : 0;
         rows_x = live ? 64 * pitch_x : 0;
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_256_kernel(Args256) {
                             if (a.out_split) {         // a normalised projection reads it next: hand it x * gain (and sum(x^2) below)
                                 const float4 gn = gain[hf];
                                 const float w[4] = {v[0] * gn.x, v[1] * gn.y, v[2] * gn.z, v[3] * gn.w};
-                                store_split4(a.out_split + column(tt, i) * split_pitch(a.out_stride), row_w + 64 * hf, w);
+                                store_split4(a.out_split + (size_t)column(tt, i) * a.out_form.pitch, row_w + 64 * hf, w, a.out_form.lo);
                             }
                         }
                     }
@@ -552,32 +552,32 @@ int launch_256(const GemvArgs& a, const Order256& o, hipStream_t s) {
 namespace {
 
 // The launch's order; false: not for this kernel.
-bool plan_256(const GemvArgs& a, int mode, int n_cu, Order256* o) {
-    if (mode == MODE_STORE || (mode != MODE_RESID && !a.ssq_in) || a.K % kBK != 0 || a.K < kMinPart * kBK) return false;
-    const int tiles = a.total_rows / 16, ot = mode == MODE_SWIGLU ? 8 : 16;
-    const int n_rb = (tiles + ot - 1) / ot, n_cb = (a.ncols + kTileN - 1) / kTileN, stages = a.K / kBK, n_wg = n_cu < 8 ? 8 : n_cu & ~7;
+bool plan_256(int mode, int total_rows, int K, int ncols, size_t part_bytes, int n_cu, Order256* o) {
+    if (mode == MODE_STORE || K % kBK != 0 || K < kMinPart * kBK) return false;
+    const int tiles = total_rows / 16, ot = mode == MODE_SWIGLU ? 8 : 16;
+    const int n_rb = (tiles + ot - 1) / ot, n_cb = (ncols + kTileN - 1) / kTileN, stages = K / kBK, n_wg = n_cu < 8 ? 8 : n_cu & ~7;
     // What is left after the full rounds is cut where each main has more than a seventh of its tile (a tile has at most kPromptMaxParts parts) and both
     // sides more than the exchange of a part costs.
     const int rest = n_rb * n_cb % n_wg, main = Order256::main_share(rest, stages, n_wg);
-    const bool split = a.part && a.part_tickets && rest > 0 && 7 * main >= stages + 7 * kMinPart && main >= kPromptCutK / 2 / kBK && stages - main >= kPromptCutK / 2 / kBK && rest * kPromptMaxParts <= kGemmPartTickets &&
-                       (long long)rest * stages * n_wg < (1ll << 31) && (size_t)(rest + n_wg) * kPartBytes <= a.part_bytes;
+    const bool split = rest > 0 && 7 * main >= stages + 7 * kMinPart && main >= kPromptCutK / 2 / kBK && stages - main >= kPromptCutK / 2 / kBK && rest * kPromptMaxParts <= kGemmPartTickets &&
+                       (long long)rest * stages * n_wg < (1ll << 31) && (size_t)(rest + n_wg) * kPartBytes <= part_bytes;
     *o = Order256(n_rb, n_cb, stages, n_wg, split);
     return true;
 }
 
 }  // namespace
 
-double gemm_prompt_256_cost(const GemvArgs& a, int mode, int n_cu) {
+double gemm_prompt_256_cost(int mode, int total_rows, int K, int ncols, size_t part_bytes, int n_cu) {
     Order256 o;
-    if (!plan_256(a, mode, n_cu, &o)) return HUGE_VAL;
+    if (!plan_256(mode, total_rows, K, ncols, part_bytes, n_cu, &o)) return HUGE_VAL;
     const double tile = mode == MODE_RESID ? 32 : 10, cut = mode == MODE_SWIGLU ? 34 : 64, stage = 1.9;
     return o.rounds * (stage * o.stages + tile) + (o.rest ? stage * o.main + cut : 0);
 }
 
-// Requirements: those of launch_gemm_prompt and a finite cost; x_split holds ncols rounded up to 256 rows.
+// Requirements: those of launch_gemm_prompt and a finite cost; x_split in lines, of ncols columns rounded up to 256; ssq_in, unless MODE_RESID.
 int launch_gemm_prompt_256(const GemvArgs& a, int mode, int n_cu, hipStream_t s, int* n_groups) {
     Order256 o;
-    if (!plan_256(a, mode, n_cu, &o)) return (int)hipErrorInvalidValue;
+    if (!split_in_lines(a.x_form, a.K) || (mode != MODE_RESID && !a.ssq_in) || !plan_256(mode, a.total_rows, a.K, a.ncols, a.part && a.part_tickets ? a.part_bytes : 0, n_cu, &o)) return (int)hipErrorInvalidValue;
     if (n_groups) *n_groups = o.n_rb;
     if (mode == MODE_QKV_ROPE) return launch_256<MODE_QKV_ROPE>(a, o, s);
     if (mode == MODE_SWIGLU) return launch_256<MODE_SWIGLU>(a, o, s);

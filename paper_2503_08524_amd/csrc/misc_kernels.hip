@@ -56,7 +56,7 @@ __device__ __forceinline__ void embed_column(const W* __restrict__ emb, int tok,
                         ss += f[e] * f[e];
                         w[e] = f[e] * g[e];
                     }
-                    store_split8(split.split + c * split_pitch(d), j, w, split.lo);
+                    store_split8(split.split + (size_t)c * split.form.pitch, j, w, split.form.lo);
                 }
             }
         }
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256) void pick_rows_kernel(const float* __restrict_
 __global__ __launch_bounds__(256) void gain_split_kernel(const float* __restrict__ x, int x_stride,
                                                          const float* __restrict__ gain, int K,
                                                          bf16_t* __restrict__ split,
-                                                         float* __restrict__ ssq, int lo) {
+                                                         float* __restrict__ ssq, SplitForm form) {
     constexpr int R = 8;
     __shared__ float red[4];
     const int c = blockIdx.x, tid = threadIdx.x;
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void gain_split_kernel(const float* __restrict
     auto emit = [&](int i4, const float4& t, const float4& gg) {
         const float f[4] = {t.x * gg.x, t.y * gg.y, t.z * gg.z, t.w * gg.w};
         ss += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
-        store_split4(split + c * split_pitch(K), i4 * 4, f, lo);
+        store_split4(split + (size_t)c * form.pitch, i4 * 4, f, form.lo);
     };
     float4 v[R], g[R];
 #pragma unroll
@@ -324,8 +324,8 @@ int launch_pick_rows(const float* x, int d, const RowPick& pick, float* dst, hip
 }
 
 int launch_gain_split(const float* x, int x_stride, const float* gain, int K, int ncols,
-                      bf16_t* split, float* ssq, bool planar, hipStream_t s) {
-    hipLaunchKernelGGL(gain_split_kernel, dim3(ncols), dim3(256), 0, s, x, x_stride, gain, K, split, ssq, split_lo(planar, K));
+                      bf16_t* split, float* ssq, SplitForm form, hipStream_t s) {
+    hipLaunchKernelGGL(gain_split_kernel, dim3(ncols), dim3(256), 0, s, x, x_stride, gain, K, split, ssq, form);
     return (int)hipGetLastError();
 }
 

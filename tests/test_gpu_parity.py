@@ -400,6 +400,14 @@ def test_prompt_tiles_of_256_columns(monkeypatch, cus, d, F, P, kv):
         helpers.compare(gpu, gens, 2)
 
 
+# passes in lines by the estimate, whose other projections take the smaller tiles: of 128 columns, and head_dim 64, whose QKV rotates in a launch of its own
+@pytest.mark.parametrize("d,H,H_kv,hd,F,P", [(1024, 8, 8, 128, 2816, 1536), (2048, 32, 8, 64, 8192, 812)])
+def test_passes_with_tiles_of_both_sizes(d, H, H_kv, hd, F, P):
+    s = ModelShape("both-tiles", L=1, d=d, H=H, H_kv=H_kv, hd=hd, F=F, V=512, dtype="bf16")
+    gpu, gens = _run(s, 1, P, 2, 1.0, 0, forced_seed=19, kv_dtype="f16")
+    helpers.compare(gpu, gens, 2)
+
+
 def test_prompt_tiles_of_256_columns_replay_from_a_graph(monkeypatch):
     # tiles in parts leave their arrival counters zero: each replay, on new tokens in between, equals the eager call bit for bit; two sequences that share passes
     import torch

@@ -9,6 +9,7 @@ from paper_2503_08524_amd import build as d3_build
 
 PROGRAM = r"""
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include "d3_common.h"
 using namespace d3;
@@ -35,6 +36,11 @@ static int refused(const char* what) {
 
 int main(int argc, char** argv) {
     if (argc > 2 && !strcmp(argv[1], "refused")) printf("%d\n", refused(argv[2]));
+    if (argc > 1 && !strcmp(argv[1], "lines")) {             // d_model, q rows, q + k + v rows, d_ffn, rotating QKV; then any number of columns
+        const PromptDims dims{atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]) != 0};
+        Tuning tn;
+        for (int i = 7; i < argc; ++i) printf("%d\n", (int)prompt_pass_in_lines(dims, atoi(argv[i]), kPromptPartBytes256, 256, tn));
+    }
 }
 """
 
@@ -62,3 +68,15 @@ def ask(tmp_path_factory):
 def test_rotating_projection_refuses_what_its_epilogue_cannot_do(ask, what):
     # whichever of the two kernels the launch would take
     assert ask("refused", what) == ["1"]
+
+
+WIDTHS = {"7b": (4096, 4096, 12288, 11008, 1), "13b": (5120, 5120, 15360, 13824, 1), "70b": (8192, 8192, 10240, 28672, 1),
+          "hd64": (2048, 2048, 3072, 8192, 0), "2048": (2048, 2048, 6144, 8192, 1)}
+
+
+@pytest.mark.parametrize("width,planes,lines", [("7b", (9, 64, 65, 128, 129, 200, 256, 300), (2048, 4096)), ("13b", (65, 128, 129, 200, 256), (2048, 4096)),
+                                                ("70b", (65, 77, 100, 128), (2048, 4096)), ("hd64", (65, 128, 256, 300, 500), (2048, 4096)), ("2048", (128, 256, 300, 512), (4096,))])
+def test_form_of_the_split_activations_follows_the_pass(ask, width, planes, lines):
+    # rows of lines, 32 k with both halves, are twice as far apart: only where tiles of 256 columns gain more by them (the calls of a few hundred columns are those that lost)
+    assert ask("lines", *WIDTHS[width], *planes) == ["0"] * len(planes)
+    assert ask("lines", *WIDTHS[width], *lines) == ["1"] * len(lines)
