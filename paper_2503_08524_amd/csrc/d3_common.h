@@ -287,6 +287,8 @@ bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn);   // laun
 // gemm_prompt_256.hip, which launch_gemm_prompt chooses by this estimate (in its own unit; infinite: not for that kernel); part_bytes: 0 without part buffer
 double gemm_prompt_256_cost(int mode, int total_rows, int K, int ncols, size_t part_bytes, int n_cu);
 int launch_gemm_prompt_256(const GemvArgs& a, int mode, int n_cu, hipStream_t s, int* n_groups);
+// The choice of a launch whose activations are in lines: tiles of 256 columns.
+bool prompt_takes_large_tiles(int mode, int total_rows, int K, int ncols, size_t part_bytes, int n_cu, const Tuning& tn);
 // Whether a prompt pass keeps its split activations in lines, because its projections then take less (launch_gemm_prompt).
 struct PromptDims { int d_model, q_dim, qkv_rows, d_ffn; bool rope_in_qkv; };
 bool prompt_pass_in_lines(const PromptDims& d, int ncols, size_t part_bytes, int n_cu, const Tuning& tn);

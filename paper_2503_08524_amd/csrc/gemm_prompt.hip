@@ -666,17 +666,21 @@ PromptSplit prompt_split(int tiles_wg, int n_stages, int n_cu, int forced, bool 
     return best;
 }
 
-// What a launch of this kernel costs, in stages with few compute units busy, to compare with gemm_prompt_256_cost.  Both are fitted to kernel traces of the four
-// projections at the 7B, 13B and 70B widths, 256 to 4096 columns (14 widths; the fit takes the slower kernel nowhere by more than 4.5 %, by 0.3 % on
-// average).  Beside its stages a whole tile costs its start and its epilogue, most of all where it reads and writes the residual.  A stage of the other kernel
+// What a launch of this kernel costs, in stages with few compute units busy, to compare with gemm_prompt_256_cost.  Both were fitted to kernel traces of the four
+// projections at the 7B, 13B and 70B widths, and checked on nine widths of 1024 to 8192, 200 to 4096 columns, 700 launches timed with either kernel: the choice, which wants
+// kPromptLargeGain, is nowhere the larger tiles where they are slower by more than 0.7 %, stays with the smaller where the others are up to 15 % faster (down projections of
+// 2048 and 3072 wide models at 2500 columns and more, of the 70B widths at 812), and costs 0.3 % on average.  Beside its stages a whole tile costs its start and its epilogue, most of all where it reads
+// and writes the residual.  A stage of the other kernel
 // is 64 k of 256 columns: 1.9 of this one's, which is where that kernel gains; its tiles are twice as large, so it loses where they leave compute units
 // idle or K parts have to be exchanged.  Measured, this kernel / the other, us: 7B gate/up 183 / 295 (616 columns), 274 / 267 (1024), 526 / 492 (2048), 1031 / 947
-// (4096), down 100 / 143, 138 / 165, 257 / 274, 523 / 480; 70B gate/up 649 / 644 (512), 2482 / 2341 (2048), 5154 / 4697 (4096), down 358 / 355, 1334 / 1210, 2691 / 2432.
+// (4096), down 100 / 143, 138 / 165, 257 / 274, 523 / 480; 70B gate/up 649 / 644 (512), 2482 / 2341 (2048), 5154 / 4697 (4096), down 358 / 355, 1334 / 1210, 2691 / 2432; 2048 wide
+// QKV 87 / 99 (1800, 192 of the larger tiles), 169 / 174 (4096), gate/up 87 / 91 (700), 102 / 94 (1024), 397 / 357 (4096).
 double prompt_cost(int mode, int n_stages, int n_cu, const PromptSplit& sp) {
     const double tile = mode == MODE_SWIGLU ? 9 : mode == MODE_RESID ? 14 : 11, stage = mode == MODE_RESID ? 1.08 : 1.04;
     return (sp.n_whole + n_cu - 1) / n_cu * (stage * n_stages + tile) + stage * sp.cut_cost;
 }
 
+constexpr double kPromptLargeGain = 0.985;     // of the smaller tiles' cost: the estimate is no better than that
 // Both kernels' costs of a launch; the measurements' overrides make one of them infinite.
 struct PromptCosts { double small, large; };
 PromptCosts prompt_costs(int mode, int total_rows, int K, int ncols, size_t part_bytes, int n_cu, const Tuning& tn) {
@@ -713,6 +717,11 @@ bool gemm_prompt_takes(const GemvArgs& a, int mode, const Tuning& tn) {
     return a.K >= 2 * kBK && a.part && tn.mfma_wide && (a.ncols > 128 || (a.ncols > 64 && row_blocks >= tn.prompt_row_blocks));
 }
 
+bool prompt_takes_large_tiles(int mode, int total_rows, int K, int ncols, size_t part_bytes, int n_cu, const Tuning& tn) {
+    const PromptCosts c = prompt_costs(mode, total_rows, K, ncols, part_bytes, n_cu, tn);
+    return c.large < kPromptLargeGain * c.small;
+}
+
 bool prompt_pass_in_lines(const PromptDims& d, int ncols, size_t part_bytes, int n_cu, const Tuning& tn) {
     if (!tn.mfma_wide || ncols <= 128 || std::min(std::min(d.d_model, d.q_dim), d.d_ffn) < 2 * kBK) return false;      // all of its projections have to read this form
     const struct { int mode, rows, K; } launches[] = {{d.rope_in_qkv ? MODE_QKV_ROPE : MODE_STORE, d.qkv_rows, d.d_model}, {MODE_RESID, d.d_model, d.q_dim},
@@ -721,9 +730,9 @@ bool prompt_pass_in_lines(const PromptDims& d, int ncols, size_t part_bytes, int
     for (const auto& l : launches) {
         const PromptCosts c = prompt_costs(l.mode, l.rows, l.K, ncols, part_bytes, tn.prompt_cus ? tn.prompt_cus : n_cu, tn);
         small += c.small;
-        best += std::min(c.small, c.large);
+        best += c.large < kPromptLargeGain * c.small ? c.large : c.small;
     }
-    return best < 0.99 * small;
+    return best < kPromptLargeGain * small;
 }
 
 int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipStream_t s, int* n_groups) {
@@ -739,8 +748,8 @@ int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, 
     const bool parts = a.part && a.part_tickets;
     if (mode == MODE_QKV_ROPE && (a.hd != 128 || !a.ssq_in || !a.col_at || !a.rope_cs || (a.kv_dtype != 0 && a.kv_dtype != 2))) return (int)hipErrorInvalidValue;
     if (split_in_lines(a.x_form, a.K)) {
-        const PromptCosts cost = prompt_costs(mode, a.total_rows, a.K, a.ncols, parts ? a.part_bytes : 0, cus, tn);
-        if (cost.large < cost.small && (mode == MODE_RESID || a.ssq_in)) return launch_gemm_prompt_256(a, mode, cus, s, n_groups);
+        if ((mode == MODE_RESID || a.ssq_in) && prompt_takes_large_tiles(mode, a.total_rows, a.K, a.ncols, parts ? a.part_bytes : 0, cus, tn))
+            return launch_gemm_prompt_256(a, mode, cus, s, n_groups);
     }
     const PromptSplit sp = prompt_split(tiles_wg, n_stages, cus, tn.prompt_ks, parts);
     if (mode == MODE_STORE) return launch_prompt<MODE_STORE>(a, n_rb, n_cb, sp, s);

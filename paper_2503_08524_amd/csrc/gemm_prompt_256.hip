@@ -570,8 +570,8 @@ bool plan_256(int mode, int total_rows, int K, int ncols, size_t part_bytes, int
 double gemm_prompt_256_cost(int mode, int total_rows, int K, int ncols, size_t part_bytes, int n_cu) {
     Order256 o;
     if (!plan_256(mode, total_rows, K, ncols, part_bytes, n_cu, &o)) return HUGE_VAL;
-    const double tile = mode == MODE_RESID ? 32 : 10, cut = mode == MODE_SWIGLU ? 34 : 64, stage = 1.9;
-    return o.rounds * (stage * o.stages + tile) + (o.rest ? stage * o.main + cut : 0);
+    const double tile = mode == MODE_RESID ? 32 : 10, cut = mode == MODE_SWIGLU ? 34 : 64, idle = 8, stage = 1.9;       // idle: the last round leaves compute units without a tile
+    return o.rounds * (stage * o.stages + tile) + (o.rest ? stage * o.main + cut : o.n_rb * o.n_cb % o.n_wg ? idle : 0);
 }
 
 // Requirements: those of launch_gemm_prompt and a finite cost; x_split in lines, of ncols columns rounded up to 256; ssq_in, unless MODE_RESID.

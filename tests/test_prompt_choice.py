@@ -36,6 +36,7 @@ static int refused(const char* what) {
 
 int main(int argc, char** argv) {
     if (argc > 2 && !strcmp(argv[1], "refused")) printf("%d\n", refused(argv[2]));
+    if (argc > 5 && !strcmp(argv[1], "large")) printf("%d\n", (int)prompt_takes_large_tiles(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), kPromptPartBytes256, 256, Tuning()));
     if (argc > 1 && !strcmp(argv[1], "lines")) {             // d_model, q rows, q + k + v rows, d_ffn, rotating QKV; then any number of columns
         const PromptDims dims{atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]) != 0};
         Tuning tn;
@@ -68,6 +69,15 @@ def ask(tmp_path_factory):
 def test_rotating_projection_refuses_what_its_epilogue_cannot_do(ask, what):
     # whichever of the two kernels the launch would take
     assert ask("refused", what) == ["1"]
+
+
+@pytest.mark.parametrize("mode,rows,K,ncols,large", [
+    # measured, the smaller tiles / the larger, us: 87 / 99, 90 / 101, 87 / 91, 445 / 458, 142 / 149: few tiles of a short contraction, a last round that leaves compute units idle
+    (3, 6144, 2048, 1800, 0), (3, 6144, 2048, 2048, 0), (2, 8192, 2048, 700, 0), (2, 14336, 4096, 1400, 0), (2, 8192, 2048, 1400, 0),
+    # 526 / 492, 2482 / 2341, 1334 / 1210, 143 / 134, 397 / 357
+    (2, 11008, 4096, 2048, 1), (2, 28672, 8192, 2048, 1), (1, 8192, 28672, 2048, 1), (2, 8192, 3072, 1024, 1), (2, 8192, 2048, 4096, 1)])
+def test_estimate_between_the_two_tiles(ask, mode, rows, K, ncols, large):
+    assert ask("large", mode, rows, K, ncols) == [str(large)]
 
 
 WIDTHS = {"7b": (4096, 4096, 12288, 11008, 1), "13b": (5120, 5120, 15360, 13824, 1), "70b": (8192, 8192, 10240, 28672, 1),
