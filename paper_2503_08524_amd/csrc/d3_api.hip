@@ -65,6 +65,13 @@ bool shares_passes(const d3_model_desc& d) {
     return mfma_fits(d) && d.head_dim == 128 && (grp == 1 || grp == 2 || grp == 4 || grp == 8);
 }
 
+// Prompt passes may take tiles of 256 columns: an fp16 cache.  Their sums over K are in one accumulator where the smaller tiles have two for half of K each, i.e. twice as many
+// roundings in a row.  The rounding of fp16 rows hides that (7.16e-4 with either, 13B widths, 4 x 1024 tokens, 4
+// blocks); on an fp32 cache it shows (keys and values against float64, 70B widths, 8 x 1024 tokens, 2
+// blocks, 8.81e-6 with the smaller tiles, 9.02e-6 with these; 13B widths, 4 x 1024, 3 blocks, 1.057e-5, 1.075e-5), so there the smaller ones stay though they are 7 % slower.  Not kept: each
+// k-step's two products summed by themselves and added (8.67e-6, but 14 to 16 % slower), the sums of the first half of K put aside in memory (8.81e-6, 4 to 5 % slower).
+bool takes_large_tiles(const d3_model_desc& d) { return mfma_fits(d) && d.kv_dtype == D3_F16; }
+
 // Partial accumulators of K-sliced projections: of the panel kernel, and of the prompt pass's tiles (all of a small model's cut
 // into the most parts, at most what a launch may publish).  The head's columns, one per sequence, are too few for that kernel.
 size_t gemm_part_bytes(const d3_model_desc& d, size_t C, bool prompt_passes) {
@@ -74,7 +81,7 @@ size_t gemm_part_bytes(const d3_model_desc& d, size_t C, bool prompt_passes) {
     const size_t row_blocks = std::max(std::max((qkv + 255) / 256, (residual + 255) / 256), (pairs + 127) / 128);
     const size_t parts = std::min(std::max(row_blocks * ((C + 127) / 128) * kPromptMaxParts * kPromptPartTile, kGemmPartBytes), kPromptPartBytes);
     const int longest = std::max(std::max(d.d_model, d.d_ffn), d.n_heads * d.head_dim);
-    return C > 128 && longest >= kPromptCutK ? kPromptPartBytes256 : parts;
+    return C > 128 && longest >= kPromptCutK && takes_large_tiles(d) ? kPromptPartBytes256 : parts;
 }
 
 // C columns of fp32 activations, CS columns of bf16 hi/lo splits (the matrix-core projections read whole column tiles:
@@ -119,8 +126,8 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
 // vector ALUs always); never more than the cache can hold.
 int pass_cols(const d3_model_desc& d) {
     const long long rows = (long long)d.max_seq * (shares_passes(d) || !mfma_fits(d) ? d.max_batch : 1);
-    const long long need = (rows + 127) / 128 * 128;
-    return (int)(need < kPassCols ? need : kPassCols);
+    const long long need = (rows + 127) / 128 * 128, most = takes_large_tiles(d) ? kPassCols : kPassCols / 2;
+    return (int)(need < most ? need : most);
 }
 // The caller's workspace serves prompt chunks of up to pass_cols() columns.
 Layout make_layout(const d3_model_desc& d) { return make_layout(d, pass_cols(d), (size_t)(pass_cols(d) + 255) / 256 * 256, true, true); }
@@ -478,7 +485,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     const SeqRuns& runs = shared ? *shared : one;
     // the form of the pass's split activations
     const PromptDims dims{dm, qdim, qkv_dim, F, qtile};
-    const bool lines = ncols <= 8 || (mfma && prompt_pass_in_lines(dims, ncols, c->lay.gemm_part_bytes, c->n_cu, c->tn));
+    const bool lines = ncols <= 8 || (mfma && (takes_large_tiles(d) || c->tn.prompt_tile == 256) && prompt_pass_in_lines(dims, ncols, c->lay.gemm_part_bytes, c->n_cu, c->tn));
     auto form = [&](int K) { return lines ? split_lines(K) : split_planes(K, c->lay.split_cols); };
     const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_split, ssq, form(dm)};
     int2* col_at = qtile ? c->at<int2>(c->lay.col_at) : nullptr;

@@ -259,7 +259,7 @@ inline bool gemm_rounds(int K) { return K % 4096 == 0 && K >= 8192; }
 // and K slices of the panel kernel; D3_WIDE_SPLIT_MB: matrix size above which a pass of more than 64 columns runs as
 // two 64-column launches; D3_ATTN_MFMA=0: grouped-query and query-tile attention on the vector ALUs;
 // D3_ATTN_MIN_SPLIT: shortest context split; D3_PREFILL_COLS: columns per prompt chunk (a multiple of 64, at most kPassCols); D3_PROMPT_KS: K parts of the projections of the prompt pass (1..8; a contraction without two stages for every part stays whole);
-// D3_PROMPT_TILE: 128 or 256, columns of a tile of the prompt pass's projections (default: the launcher's estimate; D3_PROMPT_KS and D3_PROMPT_CUS mean tiles of 128 unless it says 256);
+// D3_PROMPT_TILE: 128 or 256, columns of a tile of the prompt pass's projections (default: the launcher's estimate with an fp16 cache, 128 with an fp32 one; D3_PROMPT_KS and D3_PROMPT_CUS mean tiles of 128 unless it says 256);
 // D3_PROMPT_ROW_BLOCKS: fewest blocks of 256 rows for which 65..128 columns take the LDS-tiled kernel;
 // D3_PROMPT_CUS: compute units a round of its tiles is taken to have;
 // D3_PROMPT_ATTN_WGS: fewest workgroups (128 (query, head) pairs each) for which a prompt pass, shared or not, takes the whole-context attention kernel; D3_GEMV_WGS_PER_CU: workgroups

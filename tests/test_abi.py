@@ -105,6 +105,13 @@ def test_workspace_size_and_shape_checks(lib):
     assert "D3_BF16" in lib.d3_last_error().decode()
 
 
+def test_workspace_of_an_fp32_cache_is_that_of_passes_of_2048_columns(lib):
+    # wider passes pay with tiles of 256 columns, which an fp32 cache does not take
+    for s in (d3_inputs.LLAMA_7B, d3_inputs.LLAMA_70B):
+        assert d3.d3_workspace_size(s, "f32", 1, 2048) == d3.d3_workspace_size(s, "f32", 1, 4096) == d3.d3_workspace_size(s, "f32", 8, 4096)
+        assert d3.d3_workspace_size(s, "f16", 1, 2048) < d3.d3_workspace_size(s, "f16", 1, 4096)
+
+
 def test_workspace_holds_partial_sums_only_where_a_kernel_can_write_them(lib):
     MiB = 1 << 20
     shape = d3_inputs.ModelShape("small", L=2, d=256, H=4, H_kv=4, hd=64, F=704, V=1024, dtype="bf16")

@@ -408,6 +408,25 @@ def test_passes_with_tiles_of_both_sizes(d, H, H_kv, hd, F, P):
     helpers.compare(gpu, gens, 2)
 
 
+def test_fp32_caches_keep_the_tiles_that_sum_in_two_accumulators(monkeypatch):
+    # the pass above with an fp32 cache, whose rounding does not hide twice as many roundings in a row: bit for bit what the smaller tiles give
+    import torch
+    from paper_2503_08524_amd import binding
+    s = ModelShape("fp32-cache", L=2, d=1024, H=8, H_kv=8, hd=128, F=2816, V=512, dtype="bf16")
+    w, toks = binding.random_weights_on_device(s, 5), torch.from_numpy(d3_inputs.make_prompt(1, 1536, s.V, seed=1)).to("cuda:0")
+    got = []
+    print("case fp32 cache", flush=True)
+    for tile in (None, "128", "256"):
+        monkeypatch.setenv("D3_PROMPT_TILE", tile) if tile else monkeypatch.delenv("D3_PROMPT_TILE", raising=False)
+        dec, logits = binding.Decoder(s, w, 1, 1536, kv_dtype="f32"), torch.zeros(1, s.V, device="cuda:0")
+        dec.prefill(toks, logits=logits)
+        torch.cuda.synchronize()
+        got.append((logits, dec.k_cache.clone(), dec.v_cache.clone()))
+        dec.close()
+    assert all(torch.equal(a, b) for a, b in zip(got[0], got[1]))
+    assert not torch.equal(got[1][1], got[2][1])       # the larger tiles' sums do differ
+
+
 def test_prompt_tiles_of_256_columns_replay_from_a_graph(monkeypatch):
     # tiles in parts leave their arrival counters zero: each replay, on new tokens in between, equals the eager call bit for bit; two sequences that share passes
     import torch
