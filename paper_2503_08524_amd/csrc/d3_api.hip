@@ -97,19 +97,20 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
     l.x = take(C * d.d_model * 4);
     l.qkv = take(C * qkv_dim * 4);
     l.attn_o = take(C * qdim * 4);
-    l.act = take(C * (size_t)d.d_ffn * 4);
+    const bool mfma = mfma_fits(d);
     const size_t PC = C < (size_t)kMaxCols ? C : (size_t)kMaxCols;   // a pass has at most kMaxCols * kMaxSplits (column, split) pairs
+    l.act = take((mfma ? PC : C) * (size_t)d.d_ffn * 4);              // of the vector-ALU projections, which beside the matrix cores take a column of each sequence
     l.part_o = take(PC * d.n_heads * kMaxSplits * (size_t)d.head_dim * 4);
     l.part_ml = take(PC * d.n_heads * kMaxSplits * 2 * 4);
     l.tickets = take(C * d.n_heads * 4);
     l.logits = take(PC * (size_t)d.vocab * 4);                        // one row per sequence
-    l.split_cols = CS;
-    l.s_split = take(CS * s_dim * 4);
-    l.f_split = take(CS * (size_t)d.d_ffn * 4);
+    l.split_cols = mfma ? CS : 0;
+    l.s_split = take(l.split_cols * s_dim * 4);
+    l.f_split = take(l.split_cols * (size_t)d.d_ffn * 4);
     l.inv_freq = take((size_t)d.head_dim / 2 * 8);
     l.rope_cs = take(C * (size_t)d.head_dim / 2 * 8);
-    l.n_split = take(CS * (size_t)d.d_model * 4);
-    l.ssq = take(C * kSsqStride * 4);
+    l.n_split = take(l.split_cols * (size_t)d.d_model * 4);
+    l.ssq = take(mfma ? C * kSsqStride * 4 : 0);
     l.h_skip = take(PC * d.d_model * 4);                              // decode passes only
     l.gemm_part_bytes = with_gemm_part ? gemm_part_bytes(d, C, prompt_passes) : 0;
     l.gemm_part = take(l.gemm_part_bytes);

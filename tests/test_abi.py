@@ -112,6 +112,16 @@ def test_workspace_of_an_fp32_cache_is_that_of_passes_of_2048_columns(lib):
         assert d3.d3_workspace_size(s, "f16", 1, 2048) < d3.d3_workspace_size(s, "f16", 1, 4096)
 
 
+def test_workspace_of_the_vector_alus_holds_no_split_activations(lib):
+    # x, q k v, attention, MLP and rotary rows of 4096 / 2 columns and little else: the bf16 halves and sums of squares belong to the matrix cores, whose MLP rows are 32
+    d, F, C = 4096, 11008, 2048
+    f32 = d3_inputs.ModelShape("f32", L=2, d=d, H=32, H_kv=32, hd=128, F=F, V=32000, dtype="f32")
+    small = 32 * 32 * 32 * 130 * 4 + 32 * (32000 + d) * 4 + C * (32 * 4 + 64 * 8) + (1 << 16)
+    assert C * 4 * (d + 3 * d + d + F) < d3.d3_workspace_size(f32, "f32", 32, 128) < C * 4 * (d + 3 * d + d + F) + small
+    parts, split = 64 << 20, C * 4 * (d + F + d)
+    assert d3.d3_workspace_size(d3_inputs.LLAMA_7B, "f32", 32, 128) < C * 4 * (5 * d) + split + parts + small + C * (2048 + 8) + 32 * (F + d) * 4
+
+
 def test_workspace_holds_partial_sums_only_where_a_kernel_can_write_them(lib):
     MiB = 1 << 20
     shape = d3_inputs.ModelShape("small", L=2, d=256, H=4, H_kv=4, hd=64, F=704, V=1024, dtype="bf16")
@@ -122,7 +132,7 @@ def test_workspace_holds_partial_sums_only_where_a_kernel_can_write_them(lib):
     assert 16 * MiB < small < 16 * MiB + 12 * MiB
     # in sixteen column blocks: 6 x 16 tiles in 8 parts are more than a launch may publish, 64 MiB
     long = d3.d3_workspace_size(shape, "f16", 1, 2048)
-    activations = lambda C: C * (4 * (256 + 768 + 256 + 704) + 2 * 2 * (256 + 704 + 256) + 8 * 32 + 4 * 512 + 4 * 4)
+    activations = lambda C: C * (4 * (256 + 768 + 256) + 2 * 2 * (256 + 704 + 256) + 8 * 32 + 4 * 512 + 4 * 4)
     assert abs((long - small) - (48 * MiB + activations(2048) - activations(128))) < MiB
     # 7B widths, 48 QKV and 86 gate/up row blocks: one column block can already publish 64 MiB (86 x 8 parts)
     assert d3.d3_workspace_size(d3_inputs.LLAMA_7B, "f16", 1, 64) > 64 * MiB
