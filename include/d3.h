@@ -109,13 +109,15 @@ int d3_plan_depth_linear(int32_t L, int32_t keep_first, int32_t keep_last, int32
 int d3_plan_from_table(int32_t L, int32_t n_steps, const int32_t *keep, const int32_t *drop_begin,
                        int32_t *layer_ids);
 
-/* Bytes of device workspace d3_create needs for this model (0 on a bad desc). */
+/* Bytes of device workspace with which d3_create's context runs fastest (0 on a bad desc). */
 size_t d3_workspace_size(const d3_model_desc *desc);
 
 /* Build a context around caller-owned device buffers.  k_cache / v_cache: dev,
- * [L][max_batch][H_kv][max_seq][head_dim] of kv_dtype.  workspace: dev, at least
+ * [L][max_batch][H_kv][max_seq][head_dim] of kv_dtype.  workspace: dev,
  * d3_workspace_size() bytes, 256-byte aligned; the library keeps the residual
- * stream, activations, attention partials and the layer-index table there.
+ * stream, activations, attention partials and the layer-index table there.  With
+ * fewer bytes prompt passes are narrower (prompts take longer); D3_EINVAL, with the
+ * fewest that will do in the message, only below those.
  * D3_ESHAPE unless head_dim in {64,128}, n_heads % n_kv_heads == 0,
  * d_model % 8 == 0, d_ffn % 8 == 0, 1 <= max_batch <= 32. */
 int d3_create(d3_ctx **out, const d3_model_desc *desc, const d3_weights *weights, void *k_cache,

@@ -22,7 +22,8 @@ constexpr size_t kAlign = 256;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-struct Layout {          // byte offsets into the workspace
+struct Layout {          // byte offsets into the workspace, for passes of up to cols columns
+    int cols;
     size_t x, qkv, attn_o, act, part_o, part_ml, tickets, logits, s_split, f_split, split_cols, inv_freq, rope_cs, n_split, ssq, h_skip, gemm_part, gemm_part_bytes, gemm_tickets, row0, col_at, h_last, total;
 };
 
@@ -74,24 +75,25 @@ bool takes_large_tiles(const d3_model_desc& d) { return mfma_fits(d) && d.kv_dty
 
 // Partial accumulators of K-sliced projections: of the panel kernel, and of the prompt pass's tiles (all of a small model's cut
 // into the most parts, at most what a launch may publish).  The head's columns, one per sequence, are too few for that kernel.
-size_t gemm_part_bytes(const d3_model_desc& d, size_t C, bool prompt_passes) {
+size_t gemm_part_bytes(const d3_model_desc& d, size_t C, bool prompt_passes, bool large_parts) {
     if (!mfma_fits(d)) return 0;
     if (!prompt_passes) return kGemmPartBytes;
     const size_t qkv = (size_t)(d.n_heads + 2 * d.n_kv_heads) * d.head_dim, residual = d.d_model, pairs = d.d_ffn;
     const size_t row_blocks = std::max(std::max((qkv + 255) / 256, (residual + 255) / 256), (pairs + 127) / 128);
     const size_t parts = std::min(std::max(row_blocks * ((C + 127) / 128) * kPromptMaxParts * kPromptPartTile, kGemmPartBytes), kPromptPartBytes);
     const int longest = std::max(std::max(d.d_model, d.d_ffn), d.n_heads * d.head_dim);
-    return C > 128 && longest >= kPromptCutK && takes_large_tiles(d) ? kPromptPartBytes256 : parts;
+    return large_parts && C > 128 && longest >= kPromptCutK && takes_large_tiles(d) ? kPromptPartBytes256 : parts;
 }
 
 // C columns of fp32 activations, CS columns of bf16 hi/lo splits (the matrix-core projections read whole column tiles:
 // at least 32 of them must exist), the K-slice partials of the panel kernel only when a pass can have more than 16 columns,
 // what only prompt passes use only for those.
-Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_part, bool prompt_passes) {
+Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_part, bool prompt_passes, bool large_parts = true) {
     const size_t qdim = (size_t)d.n_heads * d.head_dim;
     const size_t qkv_dim = (size_t)(d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
     const size_t s_dim = qdim > (size_t)d.d_model ? qdim : (size_t)d.d_model;
     Layout l{};
+    l.cols = (int)C;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes); return at; };
     l.x = take(C * d.d_model * 4);
@@ -112,7 +114,7 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
     l.n_split = take(l.split_cols * (size_t)d.d_model * 4);
     l.ssq = take(mfma ? C * kSsqStride * 4 : 0);
     l.h_skip = take(PC * d.d_model * 4);                              // decode passes only
-    l.gemm_part_bytes = with_gemm_part ? gemm_part_bytes(d, C, prompt_passes) : 0;
+    l.gemm_part_bytes = with_gemm_part ? gemm_part_bytes(d, C, prompt_passes, large_parts) : 0;
     l.gemm_part = take(l.gemm_part_bytes);
     l.gemm_tickets = take((size_t)kGemmPartTickets * 4);
     l.row0 = take(kMaxCols * 4);
@@ -125,13 +127,25 @@ Layout make_layout(const d3_model_desc& d, size_t C, size_t CS, bool with_gemm_p
 // Columns of a prompt chunk: a whole sequence if it fits kPassCols (one pass over the weights per sequence, and enough
 // column blocks for the 4096-row projections to fill the chip), or several sequences that share it (on the matrix cores, where their attention takes runs; on the
 // vector ALUs always); never more than the cache can hold.
-int pass_cols(const d3_model_desc& d) {
-    const long long rows = (long long)d.max_seq * (shares_passes(d) || !mfma_fits(d) ? d.max_batch : 1);
-    const long long need = (rows + 127) / 128 * 128, most = takes_large_tiles(d) ? kPassCols : kPassCols / 2;
+int pass_cols(const d3_model_desc& d, int sequences, int most) {
+    const long long need = ((long long)d.max_seq * sequences + 127) / 128 * 128;
     return (int)(need < most ? need : most);
 }
-// The caller's workspace serves prompt chunks of up to pass_cols() columns.
-Layout make_layout(const d3_model_desc& d) { return make_layout(d, pass_cols(d), (size_t)(pass_cols(d) + 255) / 256 * 256, true, true); }
+// The layout of the caller's workspace: with the most columns that pay, or the first of these that `bytes` hold, or the last.  Half as many columns, the smaller part buffer (fewer of
+// the large tiles are then cut) and, on the vector ALUs, a single sequence's columns cost speed and nothing else; a workspace of the size that was asked for when passes were that wide is
+// still enough.
+Layout make_layout(const d3_model_desc& d, size_t bytes = ~(size_t)0) {
+    const int most = takes_large_tiles(d) ? kPassCols : kPassCols / 2, half = std::min(most, kPassCols / 2);
+    const int all = shares_passes(d) || !mfma_fits(d) ? d.max_batch : 1, fewest = shares_passes(d) ? all : 1;
+    const struct { int cols; bool large_parts; } choices[] = {{pass_cols(d, all, most), true}, {pass_cols(d, all, half), true}, {pass_cols(d, all, half), false}, {pass_cols(d, fewest, half), false}};
+    Layout l{};
+    for (const auto& c : choices) {
+        const size_t split_cols = c.cols > 128 ? (size_t)(c.cols + 255) / 256 * 256 : c.cols;       // whole column tiles
+        l = make_layout(d, c.cols, split_cols, true, true, c.large_parts);
+        if (l.total <= bytes) break;
+    }
+    return l;
+}
 
 }  // namespace
 
@@ -240,7 +254,7 @@ extern "C" int d3_create(d3_ctx** out, const d3_model_desc* desc, const d3_weigh
     }
     if (!k_cache || !v_cache || !workspace) return fail(D3_EINVAL, "d3_create: cache or workspace is NULL");
     if (reinterpret_cast<uintptr_t>(workspace) % kAlign != 0) return fail(D3_EINVAL, "d3_create: workspace must be %zu-byte aligned", kAlign);
-    const Layout lay = make_layout(*desc);
+    const Layout lay = make_layout(*desc, workspace_bytes);
     if (workspace_bytes < lay.total) return fail(D3_EINVAL, "d3_create: workspace has %zu bytes, %zu needed", workspace_bytes, lay.total);
 
     int dev = 0;
@@ -291,7 +305,7 @@ extern "C" int d3_create(d3_ctx** out, const d3_model_desc* desc, const d3_weigh
     inv.resize(desc->head_dim / 2);
     for (int j = 0; j < desc->head_dim / 2; ++j) inv[j] = std::pow((double)desc->rope_base, -2.0 * j / desc->head_dim);
     hipError_t e = hipMemcpy(c->at<double>(lay.inv_freq), inv.data(), inv.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(c->at<int>(lay.tickets), 0, (size_t)pass_cols(*desc) * desc->n_heads * sizeof(int));   // arrival counters start at 0
+    if (e == hipSuccess) e = hipMemset(c->at<int>(lay.tickets), 0, (size_t)lay.cols * desc->n_heads * sizeof(int));   // arrival counters start at 0
     if (e == hipSuccess) e = hipMemset(c->at<int>(lay.gemm_tickets), 0, (size_t)kGemmPartTickets * sizeof(int));
     if (e != hipSuccess) { delete c; return fail(D3_EDEVICE, "d3_create: hipMemcpy/hipMemset failed: %s", hipGetErrorString(e)); }
     *out = c;
@@ -744,11 +758,11 @@ int prefill_impl(d3_ctx* ctx, const int32_t* tokens, int32_t B, int32_t P, int32
     std::vector<int32_t> all(d.n_layers);
     for (int l = 0; l < d.n_layers; ++l) all[l] = l;
     float* lg = logits ? logits : ctx->at<float>(ctx->lay.logits);
-    const int fit = pass_cols(d);
+    const int fit = ctx->lay.cols;
     const int wide_cols = ctx->tn.prefill_cols && ctx->tn.prefill_cols < fit ? ctx->tn.prefill_cols : fit;
     if ((ctx->prefill_by_seq && ctx->mfma_ok) || (ctx->ragged && pos_begin == 0)) {
         // consecutive positions of a sequence per pass: the attention of such a chunk reads every cache row once per tile of
-        // queries instead of once per query.  The matrix-core path takes pass_cols() columns (the weights are streamed once per
+        // queries instead of once per query.  The matrix-core path takes as many columns as the workspace (the weights are streamed once per
         // pass), of several sequences if its attention kernel can; else one sequence at a time
         const int chunk_cols = ctx->mfma_ok && !ctx->tn.mfma_wide ? kMaxCols : wide_cols;
         if (B > 1 && ctx->prefill_by_seq && shares_passes(d) && ctx->tn.mfma_wide && ctx->tn.attn_mfma) {

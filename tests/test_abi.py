@@ -112,6 +112,37 @@ def test_workspace_of_an_fp32_cache_is_that_of_passes_of_2048_columns(lib):
         assert d3.d3_workspace_size(s, "f16", 1, 2048) < d3.d3_workspace_size(s, "f16", 1, 4096)
 
 
+SMALLER = [  # (shape, cache, max_batch, max_seq, bytes that d3_workspace_size gave when passes were at most 2048 columns and those of the vector ALUs of one sequence)
+    (d3_inputs.TINY, "f32", 8, 512, 8929792), (d3_inputs.TINY, "f32", 32, 128, 3172864),
+    (d3_inputs.LLAMA_7B, "f16", 1, 64, 115599104), (d3_inputs.LLAMA_7B, "f16", 1, 300, 168193792), (d3_inputs.LLAMA_7B, "f16", 8, 512, 510059264),
+    (d3_inputs.LLAMA_13B, "f16", 32, 2048, 619504384), (d3_inputs.LLAMA_70B, "f32", 8, 2048, 935256832), (d3_inputs.LLAMA_70B, "f16", 8, 2048, 935256832),
+    (d3_inputs.ModelShape("f32", L=2, d=2048, H=16, H_kv=16, hd=128, F=5504, V=32000, dtype="f32"), "f32", 32, 128, 26198784),
+    (d3_inputs.ModelShape("hd64", L=3, d=2048, H=32, H_kv=8, hd=64, F=8192, V=32000, dtype="bf16"), "f16", 1, 300, 123527680),
+    (d3_inputs.ModelShape("odd", L=3, d=264, H=4, H_kv=2, hd=64, F=696, V=1000, dtype="bf16"), "f16", 32, 128, 3060224)]
+
+
+@pytest.mark.parametrize("shape,kv,B,n,size", SMALLER)
+def test_smaller_workspaces_are_accepted(lib, shape, kv, B, n, size):
+    """The sizes above, with which contexts used to be made, are enough still; a tenth is refused.  Without a GPU d3_create stops at the device, behind the workspace's check."""
+    import ctypes as C
+    import torch
+    from paper_2503_08524_amd import binding
+    if torch.cuda.is_available():
+        pytest.skip("the buffers below are not the GPU's")
+    word = np.zeros(1024, np.uint8)
+    at = (word.ctypes.data + 255) // 256 * 256
+    layers = (binding._LayerWeights * shape.L)(*[binding._LayerWeights(*[at] * 9) for _ in range(shape.L)])
+    desc, w, ctx = binding._desc(shape, kv, B, n), binding._Weights(at, layers, at, at), C.c_void_p()
+
+    def create(bytes_):
+        return lib.d3_create(C.byref(ctx), C.byref(desc), C.byref(w), at, at, at, bytes_), lib.d3_last_error().decode()
+    device = create(binding.d3_workspace_size(shape, kv, B, n))[0]
+    status, message = create(size)
+    assert status == device, message
+    status, message = create(size // 10)
+    assert status == -1 and "workspace" in message and status != device
+
+
 def test_workspace_of_the_vector_alus_holds_no_split_activations(lib):
     # x, q k v, attention, MLP and rotary rows of 4096 / 2 columns and little else: the bf16 halves and sums of squares belong to the matrix cores, whose MLP rows are 32
     d, F, C = 4096, 11008, 2048

@@ -121,6 +121,33 @@ def test_groups_of_columns_on_the_vector_alus(B, P, d, F, dtype, kv, lengths):
         helpers.compare(gpu, gens, 3, logit_atol=1e-4, hidden_tol=1e-5)
 
 
+@pytest.mark.parametrize("shape,kv,B,P,size", [
+    (ModelShape("smaller-ws", L=1, d=1536, H=12, H_kv=12, hd=128, F=2048, V=512, dtype="bf16"), "f16", 2, 590, 153336576),      # the smaller part buffer, 1280 columns
+    (d3_inputs.TINY, "f32", 8, 505, 8929792), (d3_inputs.TINY, "f32", 32, 120, 3172864)])       # passes of one sequence's columns, of all of them
+def test_prompts_in_a_workspace_of_an_earlier_size(monkeypatch, shape, kv, B, P, size):
+    # max_seq 600, 512 and 128: what d3_workspace_size gave for them when it asked for less
+    import torch
+    from paper_2503_08524_amd import binding
+    w, toks = binding.weights_to_device(shape, d3_inputs.make_weights(shape, 0), "cuda:0"), torch.from_numpy(d3_inputs.make_prompt(B, P, shape.V, seed=1)).to("cuda:0")
+    rows = {590: 600, 505: 512, 120: 128}[P]
+    print(f"case smaller workspace {shape.name} B={B} P={P}", flush=True)
+
+    def run():
+        dec, logits = binding.Decoder(shape, w, B, rows, kv_dtype=kv), torch.zeros(B, shape.V, device="cuda:0")
+        dec.prefill(toks, logits=logits)
+        torch.cuda.synchronize()
+        got = logits.double(), dec.k_cache.double(), dec.v_cache.double(), dec.workspace.numel()
+        dec.close()
+        return got
+    full = run()
+    monkeypatch.setattr(binding.load_library(), "d3_workspace_size", lambda desc: size)
+    less = run()
+    assert less[3] == size < full[3]
+    # another cut of the passes moves sums by their rounding: an ulp of an fp16 row (4.9e-4, and a row in a hundred), a few of fp32
+    for a, b in zip(less[:3], full[:3]):
+        assert (a - b).norm() / b.norm() < (1e-3 if kv == "f16" else 2e-6)
+
+
 def test_batch_on_the_vector_alus_equals_its_sequences_one_at_a_time():
     # the sums of a column do not depend on the group it is in: logits and cache rows of a batch, prompt and decode step, bit for bit those of each sequence alone
     # (16 rows: attention cuts neither context)
