@@ -460,11 +460,12 @@ int alu_projection(d3_ctx* c, GemvArgs g, int first, int count, int mode, bool n
 // shared: a prompt pass whose columns are runs of several sequences (cm then gives P and
 // pos_begin only, and there is no head); picks: its last positions, which hidden_dump takes.
 // fp32_projections: fp32 activations on the vector ALUs also where the pass has several columns.
+// cut_len > 0: the context's splits are so many rows long, instead of as the pass's columns would have them.
 // save_before >= 0: the residual that enters the first listed block >= save_before (the one after the last, if none)
 // is copied to the workspace's h_skip: it is what the blocks of the drop window would have seen.
 int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_t* ids, int n_ids,
             float* hidden_dump, int dump_first, int dump_cols, const HeadOut* head, hipStream_t s, int save_before = -1,
-            int dump_total = -1, int dump_dst = 0, const SeqRuns* shared = nullptr, const RowPick* picks = nullptr, bool fp32_projections = false) {
+            int dump_total = -1, int dump_dst = 0, const SeqRuns* shared = nullptr, const RowPick* picks = nullptr, bool fp32_projections = false, int cut_len = 0) {
     const d3_model_desc& d = c->desc;
     const int dm = d.d_model, hd = d.head_dim, qdim = d.n_heads * hd, kvdim = d.n_kv_heads * hd, qkv_dim = qdim + 2 * kvdim, F = d.d_ffn;
     float* x = c->at<float>(c->lay.x);
@@ -519,7 +520,9 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
 
     const bool prompt_attn = qtile && whole_context_attention(c, runs, shared != nullptr);
     int split_len = 0, n_splits = 0;
-    if (!prompt_attn && !shared) pick_splits(c, ncols, cm.pos(ncols - 1) + 1, c->attn_wgs_per_cu * c->n_cu, &split_len, &n_splits, qtile);
+    const int context = cm.pos(ncols - 1) + 1;
+    if (cut_len > 0) { split_len = cut_len; n_splits = (context + cut_len - 1) / cut_len; }
+    else if (!prompt_attn && !shared) pick_splits(c, ncols, context, c->attn_wgs_per_cu * c->n_cu, &split_len, &n_splits, qtile);
 
     bool saved = save_before < 0;
     auto save_skip = [&]() -> int {
@@ -725,6 +728,29 @@ int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin
     return D3_OK;
 }
 
+// A prompt pass on the vector ALUs, from prompt position `at` on: how many positions of each of `sequences` sequences, and how its contexts are cut.  Wide passes would leave the
+// contexts whole (their columns fill the chip), which sums longer chains: 2 x 3000 tokens of the tiny model, keys against float64 1.947e-7 -> 1.978e-7, logits 2.346e-7 ->
+// 2.393e-7.  So 32 positions at a time are cut as a pass of those alone is, a pass takes groups that are cut alike, as many columns as the partials have room for, and what a
+// sequence gives depends neither on the width of its passes nor on what shares them.
+int alu_prompt_pass(const d3_ctx* c, int first, int at, int end, int pos_begin, int sequences, int most, int* cut_len) {
+    auto cut = [&](int begin) {                        // rows of a split of the group that begins here; 0: whole contexts
+        const int n = std::min(kMaxCols, end - begin), rows = pos_begin + begin + n;
+        int len, splits;
+        pick_splits(c, n, rows, c->attn_wgs_per_cu * c->n_cu, &len, &splits);
+        return splits > 1 ? len : 0;
+    };
+    int alike = at - (at - first) % kMaxCols;          // end of the groups that are cut alike
+    const int len = cut(alike);
+    const int reach = (int)std::min<long long>(end, (long long)at + most / sequences);
+    do alike += kMaxCols; while (alike <= reach && alike < end && cut(alike) == len);
+    alike = std::min(alike, end);
+    int to = std::min(alike, reach);
+    *cut_len = len ? len : pos_begin + to;
+    if (len) to = std::min(to, at + kMaxCols * kMaxSplits / ((pos_begin + to + len - 1) / len * sequences));
+    if (to == alike - 1 && to > at + 1) --to;          // not one position by itself: that would be rotated by the attention kernel, with other roundings
+    return to - at;
+}
+
 // Prompt pass.  lengths (host, optional): a left-padded batch, sequence b holds lengths[b] tokens in columns
 // [P - lengths[b], P) of its row of `tokens` and in the cache rows of the same numbers.
 int prefill_impl(d3_ctx* ctx, const int32_t* tokens, int32_t B, int32_t P, int32_t pos_begin, const int32_t* lengths,
@@ -769,13 +795,15 @@ int prefill_impl(d3_ctx* ctx, const int32_t* tokens, int32_t B, int32_t P, int32
             const int rc = prefill_shared(ctx, tokens, B, P, pos_begin, chunk_cols, all, next_tok, lg, hidden_dump, s);
             if (rc != D3_OK) return rc;
         } else for (int b = 0; b < B; ++b) {
-            for (int base = pos_begin == 0 ? ctx->row0[b] : 0; base < P;) {     // padding columns are not computed
-                const int ncols = P - base < chunk_cols ? P - base : chunk_cols;
+            const int first = pos_begin == 0 ? ctx->row0[b] : 0;                // padding columns are not computed
+            for (int base = first; base < P;) {
+                int ncols = P - base < chunk_cols ? P - base : chunk_cols, cut_len = 0;
+                if (!ctx->mfma_ok) ncols = alu_prompt_pass(ctx, first, base, P, pos_begin, 1, chunk_cols, &cut_len);
                 const bool last = base + ncols == P;
                 ColMap cm{base, 1, P, pos_begin, b};
                 HeadOut head{ncols - 1, 1, lg + (size_t)b * d.vocab, next_tok + b};
                 int rc = forward(ctx, tokens, cm, ncols, all.data(), d.n_layers, last ? hidden_dump : nullptr, ncols - 1, 1,
-                                 last ? &head : nullptr, s, -1, B, b);
+                                 last ? &head : nullptr, s, -1, B, b, nullptr, nullptr, false, cut_len);
                 if (rc != D3_OK) return rc;
                 base += ncols;
             }
@@ -788,12 +816,13 @@ int prefill_impl(d3_ctx* ctx, const int32_t* tokens, int32_t B, int32_t P, int32
         // position-major columns in chunks that are multiples of B: the last B columns of the last
         // chunk are the last prompt position of every sequence
         for (int base = 0; base < total;) {
-            const int ncols = total - base < chunk ? total - base : chunk;
+            int ncols = total - base < chunk ? total - base : chunk, cut_len = 0;
+            if (!ctx->mfma_ok) ncols = B * alu_prompt_pass(ctx, 0, base / B, P, pos_begin, B, chunk, &cut_len);
             const bool last = base + ncols == total;
             ColMap cm{base, B, P, pos_begin};
             HeadOut head{ncols - B, B, lg, next_tok};
             int rc = forward(ctx, tokens, cm, ncols, all.data(), d.n_layers, last ? hidden_dump : nullptr, ncols - B, B,
-                             last ? &head : nullptr, s);
+                             last ? &head : nullptr, s, -1, -1, 0, nullptr, nullptr, false, cut_len);
             if (rc != D3_OK) return rc;
             base += ncols;
         }

@@ -148,6 +148,33 @@ def test_prompts_in_a_workspace_of_an_earlier_size(monkeypatch, shape, kv, B, P,
         assert (a - b).norm() / b.norm() < (1e-3 if kv == "f16" else 2e-6)
 
 
+@pytest.mark.parametrize("B,P,past", [(1, 700, 0), (3, 1100, 0), (8, 300, 0), (5, 70, 1500), (2, 1032, 40)])
+def test_contexts_of_vector_alu_prompts_are_cut_as_passes_of_32_columns_cut_them(monkeypatch, B, P, past):
+    # long contexts: logits and cache rows of a batch in wide passes, bit for bit those in passes of 64 columns and those of each sequence alone
+    import torch
+    from paper_2503_08524_amd import binding
+    s = d3_inputs.TINY
+    w = binding.weights_to_device(s, d3_inputs.make_weights(s, 3), "cuda:0")
+    toks = torch.from_numpy(d3_inputs.make_prompt(B, past + P, s.V, seed=4)).to("cuda:0")
+    print(f"case cut contexts B={B} P={P} past={past}", flush=True)
+
+    def run(t):
+        dec, lg = binding.Decoder(s, w, t.shape[0], past + P, kv_dtype="f32"), torch.zeros(t.shape[0], s.V, device="cuda:0")
+        if past:
+            dec.prefill(t[:, :past].contiguous())
+        dec.prefill(t[:, past:].contiguous(), pos_begin=past, logits=lg)
+        torch.cuda.synchronize()
+        got = lg, dec.k_cache.clone(), dec.v_cache.clone()
+        dec.close()
+        return got
+    lg, k, v = run(toks)
+    for b in range(B):
+        one = run(toks[b:b + 1].contiguous())
+        assert torch.equal(one[0][0], lg[b]) and torch.equal(one[1][:, 0], k[:, b]) and torch.equal(one[2][:, 0], v[:, b])
+    monkeypatch.setenv("D3_PREFILL_COLS", "64")
+    assert all(torch.equal(a, b) for a, b in zip(run(toks), (lg, k, v)))
+
+
 def test_batch_on_the_vector_alus_equals_its_sequences_one_at_a_time():
     # the sums of a column do not depend on the group it is in: logits and cache rows of a batch, prompt and decode step, bit for bit those of each sequence alone
     # (16 rows: attention cuts neither context)
