@@ -335,6 +335,25 @@ def test_left_padded_continuation_on_shared_passes(monkeypatch, P2, wgs):
     print(f"  logit abs err {wl:.3e}, hidden {wh:.3e}", flush=True)
 
 
+@pytest.mark.parametrize("d,F,dtype,P2", [(256, 688, "f32", 1), (256, 688, "f32", 45), (264, 696, "bf16", 33)])
+def test_left_padded_continuation_on_the_vector_alus(d, F, dtype, P2):
+    """Equal tails behind a ragged batch where all sequences share passes of vector-ALU projections: their rows begin at different places, also behind cut contexts."""
+    shape = ModelShape("ragged-tail-alu", L=2, d=d, H=4, H_kv=2, hd=64, F=F, V=1000, dtype=dtype)
+    lengths = np.array([140, 2, 77], np.int32)
+    B, P, G2 = 3, 140, 2
+    w = d3_inputs.make_weights(shape, 2)
+    prompts, prompts2 = d3_inputs.make_prompt(B, P, shape.V, seed=1), d3_inputs.make_prompt(B, P2, shape.V, seed=5)
+    forced2 = d3_inputs.make_prompt(B, G2 - 1, shape.V, seed=6)
+    max_seq = P + P2 + G2
+    print(f"case ragged tail of {P2} on the vector ALUs, {dtype}", flush=True)
+    gpu = helpers.gpu_generate(shape, w, prompts, 1, 1.0, 1, kv_dtype="f32", max_seq=max_seq, lengths=lengths)
+    model, gens = helpers.oracle_generate(shape, w, prompts, 1, 1.0, 1, max_seq=max_seq, lengths=lengths)
+    gpu2 = helpers.gpu_generate(shape, w, prompts2, G2, 1.0, 1, forced=forced2, decoder=gpu["decoder"], pos_begin=P)
+    gens2 = [oracle.generate(model, prompts2[b], G2, 1.0, 1, seq=gen.seq, pos_begin=int(lengths[b]), forced=forced2[b]) for b, gen in enumerate(gens)]
+    wl, wh = helpers.compare(gpu2, gens2, G2, logit_atol=1e-4, hidden_tol=1e-5)
+    print(f"  logit abs err {wl:.3e}, hidden {wh:.3e}", flush=True)
+
+
 @pytest.mark.parametrize("name,B", [("llama-7b", 1), ("llama-70b", 2)])
 def test_recompute_fill_at_real_widths(name, B):
     import torch

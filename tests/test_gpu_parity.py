@@ -108,7 +108,7 @@ def test_tiny_fp32_batches_use_the_alu_path(B):
 
 
 # Groups of columns in one launch of the vector-ALU projections: 4, 2 and 1 columns a workgroup (rows of up to 15 KB, 30 KB and 60 KB of fp32 activations), batches that fill their
-# last group and that do not, group by group in decode and in prompt passes of several sequences (of 15 to 340 columns, of more than one chunk, beside a ragged batch, which stays
+# last group and that do not, group by group in decode and in prompt passes of several sequences (15 to 350 columns in one pass, beside a ragged batch, which stays
 # one sequence a pass), fp32 and bf16 rows (bf16: widths that the matrix cores do not take), a cache of 16 bits
 @pytest.mark.parametrize("B,P,d,F,dtype,kv,lengths", [
     (5, 3, 256, 688, "f32", "f32", None), (8, 40, 256, 688, "f32", "f32", None), (9, 33, 256, 688, "f32", "f16", None), (32, 5, 256, 688, "f32", "f32", None), (3, 97, 256, 688, "f32", "f32", None),
@@ -119,6 +119,21 @@ def test_groups_of_columns_on_the_vector_alus(B, P, d, F, dtype, kv, lengths):
     gpu, gens = _run(s, B, P, 3, 0.8, 1, kv_dtype=kv, forced_seed=6, **kw)
     if kv == "f32":
         helpers.compare(gpu, gens, 3, logit_atol=1e-4, hidden_tol=1e-5)
+
+
+ODD_BF16 = ModelShape("odd-bf16", L=2, d=264, H=4, H_kv=2, hd=64, F=696, V=1000, dtype="bf16")
+
+
+# prompts in more than one pass: 40 positions of 5 sequences in passes of 12, 12, 12 and 4 (64 columns, which 5 does not divide), 130 of one in three, 70 of a ragged batch in
+# passes of 64 and 6; 1200 columns of 3 sequences, whose contexts are cut from 128 rows on, in the passes that the partials leave
+@pytest.mark.parametrize("shape,B,P,cols,lengths", [(d3_inputs.TINY, 5, 40, 64, None), (ODD_BF16, 5, 40, 64, None), (d3_inputs.TINY, 1, 130, 64, None), (ODD_BF16, 3, 70, 64, (70, 1, 41)),
+                                                    (d3_inputs.TINY, 3, 400, 0, None), (ODD_BF16, 1, 1100, 0, None)])
+def test_prompts_of_several_passes_on_the_vector_alus(monkeypatch, shape, B, P, cols, lengths):
+    if cols:
+        monkeypatch.setenv("D3_PREFILL_COLS", str(cols))
+    kw = {} if lengths is None else {"lengths": np.array(lengths, np.int32)}
+    gpu, gens = _run(shape, B, P, 3, 0.8, 1, kv_dtype="f32", forced_seed=6, **kw)
+    helpers.compare(gpu, gens, 3, logit_atol=1e-4, hidden_tol=1e-5)
 
 
 @pytest.mark.parametrize("shape,kv,B,P,size", [
