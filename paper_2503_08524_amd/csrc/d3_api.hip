@@ -174,7 +174,8 @@ Tuning tuning_from_env() {
     t.prefill_cols = pc % 64 == 0 ? pc : 0;
     t.prompt_ks = env_int("D3_PROMPT_KS", 1, kPromptMaxParts, 0);
     t.prompt_row_blocks = env_int("D3_PROMPT_ROW_BLOCKS", 1, 1 << 20, t.prompt_row_blocks);
-    t.prompt_tile = env_int("D3_PROMPT_TILE", 128, 256, 0);
+    const int tile = env_int("D3_PROMPT_TILE", 128, 256, 0);
+    t.prompt_tile = tile == 128 || tile == 256 ? tile : 0;
     t.prompt_cus = env_int("D3_PROMPT_CUS", 1, 4096, 0);
     t.prompt_attn_wgs = env_int("D3_PROMPT_ATTN_WGS", 1, 1 << 20, 0);
     return t;

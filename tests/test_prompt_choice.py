@@ -37,6 +37,7 @@ static int refused(const char* what) {
 int main(int argc, char** argv) {
     if (argc > 2 && !strcmp(argv[1], "refused")) printf("%d\n", refused(argv[2]));
     if (argc > 5 && !strcmp(argv[1], "large")) printf("%d\n", (int)prompt_takes_large_tiles(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), kPromptPartBytes256, 256, Tuning()));
+    if (argc > 1 && !strcmp(argv[1], "tile")) printf("%d\n", tuning_from_env().prompt_tile);
     if (argc > 1 && !strcmp(argv[1], "lines")) {             // d_model, q rows, q + k + v rows, d_ffn, rotating QKV; then any number of columns
         const PromptDims dims{atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]) != 0};
         Tuning tn;
@@ -78,6 +79,12 @@ def test_rotating_projection_refuses_what_its_epilogue_cannot_do(ask, what):
     (2, 11008, 4096, 2048, 1), (2, 28672, 8192, 2048, 1), (1, 8192, 28672, 2048, 1), (2, 8192, 3072, 1024, 1), (2, 8192, 2048, 4096, 1)])
 def test_estimate_between_the_two_tiles(ask, mode, rows, K, ncols, large):
     assert ask("large", mode, rows, K, ncols) == [str(large)]
+
+
+@pytest.mark.parametrize("value,tile", [("128", "128"), ("256", "256"), ("129", "0"), ("192", "0"), ("255", "0"), ("64", "0"), ("512", "0")])
+def test_tile_override_is_one_of_the_two_or_none(ask, monkeypatch, value, tile):
+    monkeypatch.setenv("D3_PROMPT_TILE", value)
+    assert ask("tile") == [tile]
 
 
 WIDTHS = {"7b": (4096, 4096, 12288, 11008, 1), "13b": (5120, 5120, 15360, 13824, 1), "70b": (8192, 8192, 10240, 28672, 1),
