@@ -447,15 +447,6 @@ bool whole_context_attention(const d3_ctx* c, const SeqRuns& runs, bool shared) 
     return std::max(2.85 * longest, 3.3 * steps / c->n_cu) <= tiles_us;
 }
 
-// ALU path: the columns [first, first + count) of a pass
-int alu_projection(d3_ctx* c, GemvArgs g, int first, int count, int mode, bool norm, hipStream_t s) {
-    g.x += (size_t)first * g.x_stride;
-    g.out += (size_t)first * g.out_stride;
-    g.ncols = count;
-    g.col0 = first;
-    return launch_gemv_alu(g, c->desc.weight_dtype, mode, norm, c->n_cu * c->tn.gemv_wgs_per_cu, s);
-}
-
 // One pass of `ncols` columns through the listed blocks.  hidden_dump (or NULL): dev
 // [(n_ids+1)][dump_cols][d], fed from columns [dump_first, dump_first + dump_cols).
 // shared: a prompt pass whose columns are runs of several sequences (cm then gives P and
@@ -517,7 +508,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     };
     D3_HIP(dump(0));
 
-    auto alu = [&](GemvArgs g, int first, int count, int mode, bool norm) -> int { return alu_projection(c, g, first, count, mode, norm, s); };
+    auto alu = [&](const GemvArgs& g, int mode, bool norm) -> int { return launch_gemv_alu(g, d.weight_dtype, mode, norm, c->n_cu * c->tn.gemv_wgs_per_cu, s); };
 
     const bool prompt_attn = qtile && whole_context_attention(c, runs, shared != nullptr);
     int split_len = 0, n_splits = 0;
@@ -566,7 +557,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
             g.rope_cs = rope_cs; g.k_cache = k_layer; g.v_cache = v_layer; g.cm = cm;
             g.H = d.n_heads; g.H_kv = d.n_kv_heads; g.hd = hd; g.max_seq = d.max_seq; g.kv_dtype = d.kv_dtype;
             Timed t(c, D3_K_QKV, s);
-            D3_HIP(alu(g, 0, ncols, rope_in_attn ? MODE_STORE : MODE_QKV_ROPE, true));
+            D3_HIP(alu(g, rope_in_attn ? MODE_STORE : MODE_QKV_ROPE, true));
         }
         AttnArgs at{};
         at.q = qkv; at.q_stride = qkv_dim; at.k_cache = k_layer; at.v_cache = v_layer; at.cm = cm;
@@ -605,7 +596,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
                 o.out_split = n_split; o.out_form = form(dm); o.gain_next = static_cast<const float*>(w.mlp_norm); o.ssq_out = ssq;
                 D3_HIP(launch_gemm_mfma(o, MODE_RESID, c->n_cu, c->tn, s, &ssq_parts));
             }
-            else { o.x = attn_o; o.x_stride = qdim; D3_HIP(alu(o, 0, ncols, MODE_RESID, false)); }
+            else { o.x = attn_o; o.x_stride = qdim; D3_HIP(alu(o, MODE_RESID, false)); }
         }
 
         // --- SwiGLU half: x += Wd (silu(Wg m) * (Wu m)) with m = RMSNorm(x) ---
@@ -626,10 +617,10 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
             { Timed t(c, D3_K_DOWN, s); D3_HIP(launch_gemm_mfma(dn, MODE_RESID, c->n_cu, c->tn, s, &ssq_parts)); }
         } else {
             u.x = x; u.x_stride = dm; u.gain = static_cast<const float*>(w.mlp_norm); u.out = act;
-            { Timed t(c, D3_K_GATE_UP, s); D3_HIP(alu(u, 0, ncols, MODE_SWIGLU, true)); }
+            { Timed t(c, D3_K_GATE_UP, s); D3_HIP(alu(u, MODE_SWIGLU, true)); }
             dn.x = act; dn.x_stride = F;
             { Timed t(c, D3_K_EMPTY, s); }
-            { Timed t(c, D3_K_DOWN, s); D3_HIP(alu(dn, 0, ncols, MODE_RESID, false)); }
+            { Timed t(c, D3_K_DOWN, s); D3_HIP(alu(dn, MODE_RESID, false)); }
         }
         D3_HIP(dump(e + 1));
     }
@@ -648,7 +639,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         } else {
             g.x = x + (size_t)head->first_col * dm; g.x_stride = dm; g.gain = static_cast<const float*>(c->final_norm);
             Timed t(c, D3_K_LM_HEAD, s);
-            D3_HIP(alu(g, 0, head->n_cols, MODE_STORE, true));
+            D3_HIP(alu(g, MODE_STORE, true));
         }
         D3_HIP(launch_argmax(head->logits, d.vocab, head->n_cols, head->tok_out, s));
     }
@@ -958,7 +949,7 @@ int fill_recompute(d3_ctx* c, int pos_begin, int pos_end, hipStream_t s) {
             g.x = h; g.x_stride = dm; g.gain = static_cast<const float*>(w.attn_norm);
             g.rope_cs = rope_cs; g.k_cache = k_layer; g.v_cache = v_layer; g.cm = cm;
             g.H = 0; g.H_kv = d.n_kv_heads; g.hd = hd; g.max_seq = d.max_seq; g.kv_dtype = d.kv_dtype;
-            D3_HIP(alu_projection(c, g, 0, B, MODE_QKV_ROPE, true, s));
+            D3_HIP(launch_gemv_alu(g, d.weight_dtype, MODE_QKV_ROPE, true, c->n_cu * c->tn.gemv_wgs_per_cu, s));
         }
     }
     return D3_OK;

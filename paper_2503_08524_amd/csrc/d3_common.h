@@ -185,7 +185,7 @@ struct GemvArgs {
     const bf16_t* x_split;
     SplitForm x_form;
     size_t part_bytes;   // what part holds
-    int x_stride;
+    int x_stride;        // ALU path
     const float* gain;   // RMSNorm gain [K] when the norm is fused (ALU path), else nullptr
     float eps;
     int K;

@@ -147,8 +147,22 @@ def test_fragments_in_flight_are_left_alone(compiled):
         assert set(re.findall(rf"\.{what}:\s+(\d+)", text)) == {"0"}, what
 
 
+def step_loops(lines):
+    """The innermost loops that multiply: (lines of the body)."""
+    labels = {raw.split(":")[0]: i for i, (_, raw) in enumerate(lines) if re.match(r"\.LBB\w+:", raw)}
+    loops = []
+    for i, (_, raw) in enumerate(lines):
+        m = re.search(r"s_c?branch\w* (\.LBB\w+)", raw)
+        if m and labels.get(m.group(1), i) < i:
+            loops.append([t for _, t in lines[labels[m.group(1)]:i]])
+    loops = [b for b in loops if any("v_mfma" in t for t in b)]
+    return [b for b in loops if not any(len(o) < len(b) and set(o) <= set(b) for o in loops)]
+
+
 def test_fragments_in_flight_are_left_alone_in_the_kernel_of_the_larger_tiles(tmp_path):
-    # the same for the tiles of 256 columns: four steps of 16 reads each are written out (the last one of 6), and the first reads of a tile
+    # the same for the tiles of 256 columns: four steps of 16 reads each are written out (the last one of 6), and the first reads of a tile.  No vector register is spilled, but
+    # all of them are taken and scalars (buffer descriptors, the plan of the next tile) are kept in lanes of a few of them: between tiles, and in the loop over steps only QKV's
+    # descriptors of three matrices, four times each way in 128 MFMAs
     out = str(tmp_path / "gemm_prompt_256.s")
     src = os.path.join(d3_build.CSRC, "gemm_prompt_256.hip")
     r = subprocess.run([d3_build.HIPCC] + d3_build.FLAGS + ["-x", "hip", "--cuda-device-only", "-S", src, "-o", out], capture_output=True, text=True)
@@ -163,5 +177,9 @@ def test_fragments_in_flight_are_left_alone_in_the_kernel_of_the_larger_tiles(tm
         print(name, n_reads, "reads")
         assert n_reads >= 60, name
         assert not found, f"{name}:\n" + "\n".join(found)
+        loops = step_loops(lines[i + 1:end])
+        assert len(loops) == 1 and sum("v_mfma" in t for t in loops[0]) == 128, name
+        lanes = sum("v_readlane" in t or "v_writelane" in t for t in loops[0])
+        assert lanes <= (8 if "ILi3E" in name else 0), f"{name}: {lanes}"
     for what in ("vgpr_spill_count", "private_segment_fixed_size"):
         assert set(re.findall(rf"\.{what}:\s+(\d+)", text)) == {"0"}, what
