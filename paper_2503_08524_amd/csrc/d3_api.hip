@@ -659,8 +659,8 @@ namespace {
 // chunk_cols and one) is not shared: a single column runs on the fp32 projections, as it does at batch 1, and joining a pass of
 // bf16 hi + lo activations would cost it precision (7B widths, fp32 cache, two prompts of one token: logits 5.7e-7 off float64 on
 // the fp32 projections, 7.6e-6 in a shared pass).  Where every sequence has such a token they go through in one pass, which those
-// projections take 2 or 4 columns at a time (one token a sequence behind 128 rows, 7B widths, a block and head, one sequence at a time ->
-// together: 2 sequences 271 -> 161 us, 4 537 -> 297, 16 2154 -> 1132; in a shared pass 158, 159 and 189).
+// projections take in one launch each, 4 columns a workgroup or fewer (one token a sequence behind 128 rows, 7B widths, a block and head: 2 sequences 137 us, 4 239, 16 742,
+// 32 845; two tokens a sequence, in a shared pass, 155, 156, 194 and 247).
 int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin, int chunk_cols, const std::vector<int32_t>& all, int32_t* next_tok,
                    float* logits, float* hidden_dump, hipStream_t s) {
     const d3_model_desc& d = c->desc;
