@@ -650,6 +650,16 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
 
 namespace {
 
+// Columns of the next prompt pass on the matrix cores, of `left` that are to come.  As many as there is room for, but up to 16 columns behind kPassCols / 2 wait for the next pass:
+// the narrow kernel takes them for a stream of the weights, another column of tiles costs more or as much (2 blocks, us, together / kPassCols / 2 of them and the rest: 2048 wide, 2049
+// columns 1201 / 1103, 2056 1193 / 1147, 2064 1190 / 1166; 7B widths 2762 / 2643, 2779 / 2711, 2811 / 2726; 13B 4098 / 4009, 4114 / 4114, 4124 / 4161; 70B, a block, 5222 / 4893,
+// 5280 / 4907, 5291 / 4956).
+int prompt_pass_cols(int left, int most) {
+    constexpr int half = kPassCols / 2;
+    if (most > half && left > half && left <= half + 16) return half;
+    return std::min(left, most);
+}
+
 // Prompts of several sequences, their tokens laid end to end and cut into passes of chunk_cols columns: the weights are streamed
 // once per pass and not once per sequence, and short prompts fill the projections' column tiles together (8 x 77 tokens at the 7B
 // shape, 8 blocks: eight passes 17.4 ms, one pass 4.2 ms;
@@ -670,19 +680,20 @@ int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin
     auto first_of = [&](int b) { return pos_begin == 0 ? c->row0[b] : 0; };          // padding columns are not computed
     auto last_alone = [&](int b) { return c->alu_ok && (P - first_of(b)) % chunk_cols == 1; };
     auto end_of = [&](int b) { return last_alone(b) ? P - 1 : P; };
-    int n_alone = 0;
-    for (int b = 0; b < B; ++b) n_alone += last_alone(b);
+    int n_alone = 0, to_come = 0;
+    for (int b = 0; b < B; ++b) { n_alone += last_alone(b); to_come += end_of(b) - first_of(b); }
     int b = 0, at = first_of(0);                       // next token: sequence b, prompt column `at`
     auto skip_done = [&] { while (b < B && at == end_of(b)) if (++b < B) at = first_of(b); };
     for (skip_done(); b < B;) {
         SeqRuns runs{};
         RowPick picks{};
         int ncols = 0;
-        while (b < B && ncols < chunk_cols) {
-            const int left = end_of(b) - at, n = left < chunk_cols - ncols ? left : chunk_cols - ncols;
+        const int pass = prompt_pass_cols(to_come, chunk_cols);
+        while (b < B && ncols < pass) {
+            const int left = end_of(b) - at, n = left < pass - ncols ? left : pass - ncols;
             runs.seq[runs.n] = b; runs.pos[runs.n] = pos_begin + at;
             runs.n += 1;
-            ncols += n; at += n;
+            ncols += n; at += n; to_come -= n;
             runs.col[runs.n] = ncols;
             if (at == P) {
                 picks.col[picks.n] = ncols - 1; picks.row[picks.n] = b;
@@ -789,7 +800,7 @@ int prefill_impl(d3_ctx* ctx, const int32_t* tokens, int32_t B, int32_t P, int32
         } else for (int b = 0; b < B; ++b) {
             const int first = pos_begin == 0 ? ctx->row0[b] : 0;                // padding columns are not computed
             for (int base = first; base < P;) {
-                int ncols = P - base < chunk_cols ? P - base : chunk_cols, cut_len = 0;
+                int ncols = prompt_pass_cols(P - base, chunk_cols), cut_len = 0;
                 if (!ctx->mfma_ok) ncols = alu_prompt_pass(ctx, first, base, P, pos_begin, 1, chunk_cols, &cut_len);
                 const bool last = base + ncols == P;
                 ColMap cm{base, 1, P, pos_begin, b};

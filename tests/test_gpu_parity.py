@@ -477,6 +477,26 @@ def test_passes_with_tiles_of_both_sizes(d, H, H_kv, hd, F, P):
     helpers.compare(gpu, gens, 2)
 
 
+# one prompt, a last token by itself, prompts that share passes, unequal ones
+@pytest.mark.parametrize("B,P,lengths", [(1, 2056, None), (1, 2049, None), (2, 1030, None), (2, 1100, (1100, 950))])
+def test_few_columns_behind_2048_are_a_pass_of_their_own(monkeypatch, B, P, lengths):
+    # bit for bit what passes of 2048 columns give
+    import torch
+    from paper_2503_08524_amd import binding
+    s = ModelShape("few-behind", L=2, d=256, H=2, H_kv=2, hd=128, F=512, V=512, dtype="bf16")
+    w, toks = binding.random_weights_on_device(s, 5), torch.from_numpy(d3_inputs.make_prompt(B, P, s.V, seed=1)).to("cuda:0")
+    got = []
+    print(f"case few columns behind 2048, B={B} P={P}", flush=True)
+    for cols in (None, "2048"):
+        monkeypatch.setenv("D3_PREFILL_COLS", cols) if cols else monkeypatch.delenv("D3_PREFILL_COLS", raising=False)
+        dec, logits = binding.Decoder(s, w, B, P, kv_dtype="f16"), torch.zeros(B, s.V, device="cuda:0")
+        dec.prefill_ragged(toks, list(lengths), logits=logits) if lengths else dec.prefill(toks, logits=logits)
+        torch.cuda.synchronize()
+        got.append((logits, dec.k_cache.clone(), dec.v_cache.clone()))
+        dec.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 def test_fp32_caches_keep_the_tiles_that_sum_in_two_accumulators(monkeypatch):
     # the pass above with an fp32 cache, whose rounding does not hide twice as many roundings in a row: bit for bit what the smaller tiles give
     import torch
