@@ -132,15 +132,16 @@ int pass_cols(const d3_model_desc& d, int sequences, int most) {
     return (int)(need < most ? need : most);
 }
 // The layout of the caller's workspace: with the most columns that pay, or the first of these that `bytes` hold, or the last.  Half as many columns, the smaller part buffer (fewer of
-// the large tiles are then cut) and, on the vector ALUs, a single sequence's columns cost speed and nothing else; a workspace of the size that was asked for when passes were that wide is
-// still enough.
+// the large tiles are then cut), on the vector ALUs a single sequence's columns, and split activations of no more columns than there are (passes whose last large tile would read past them
+// take the small ones) cost speed and nothing else; a workspace of the size that was asked for when passes were that wide is still enough.
 Layout make_layout(const d3_model_desc& d, size_t bytes = ~(size_t)0) {
     const int most = takes_large_tiles(d) ? kPassCols : kPassCols / 2, half = std::min(most, kPassCols / 2);
     const int all = shares_passes(d) || !mfma_fits(d) ? d.max_batch : 1, fewest = shares_passes(d) ? all : 1;
-    const struct { int cols; bool large_parts; } choices[] = {{pass_cols(d, all, most), true}, {pass_cols(d, all, half), true}, {pass_cols(d, all, half), false}, {pass_cols(d, fewest, half), false}};
+    const struct { int cols; bool large_parts, whole_tiles; } choices[] = {{pass_cols(d, all, most), true, true}, {pass_cols(d, all, half), true, true}, {pass_cols(d, all, half), false, true},
+                                                                           {pass_cols(d, fewest, half), false, true}, {pass_cols(d, fewest, half), false, false}};
     Layout l{};
     for (const auto& c : choices) {
-        const size_t split_cols = c.cols > 128 ? (size_t)(c.cols + 255) / 256 * 256 : c.cols;       // whole column tiles
+        const size_t split_cols = c.whole_tiles && c.cols > 128 ? (size_t)(c.cols + 255) / 256 * 256 : c.cols;       // whole column tiles
         l = make_layout(d, c.cols, split_cols, true, true, c.large_parts);
         if (l.total <= bytes) break;
     }
@@ -493,7 +494,8 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     const SeqRuns& runs = shared ? *shared : one;
     // the form of the pass's split activations
     const PromptDims dims{dm, qdim, qkv_dim, F, qtile};
-    const bool lines = ncols <= 8 || (mfma && (takes_large_tiles(d) || c->tn.prompt_tile == 256) && prompt_pass_in_lines(dims, ncols, c->lay.gemm_part_bytes, c->n_cu, c->tn));
+    const bool whole_tiles = (size_t)(ncols + 255) / 256 * 256 <= c->lay.split_cols;
+    const bool lines = ncols <= 8 || (mfma && whole_tiles && (takes_large_tiles(d) || c->tn.prompt_tile == 256) && prompt_pass_in_lines(dims, ncols, c->lay.gemm_part_bytes, c->n_cu, c->tn));
     auto form = [&](int K) { return lines ? split_lines(K) : split_planes(K, c->lay.split_cols); };
     const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_split, ssq, form(dm)};
     int2* col_at = qtile ? c->at<int2>(c->lay.col_at) : nullptr;

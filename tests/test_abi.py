@@ -118,7 +118,11 @@ SMALLER = [  # (shape, cache, max_batch, max_seq, bytes that d3_workspace_size g
     (d3_inputs.LLAMA_13B, "f16", 32, 2048, 619504384), (d3_inputs.LLAMA_70B, "f32", 8, 2048, 935256832), (d3_inputs.LLAMA_70B, "f16", 8, 2048, 935256832),
     (d3_inputs.ModelShape("f32", L=2, d=2048, H=16, H_kv=16, hd=128, F=5504, V=32000, dtype="f32"), "f32", 32, 128, 26198784),
     (d3_inputs.ModelShape("hd64", L=3, d=2048, H=32, H_kv=8, hd=64, F=8192, V=32000, dtype="bf16"), "f16", 1, 300, 123527680),
-    (d3_inputs.ModelShape("odd", L=3, d=264, H=4, H_kv=2, hd=64, F=696, V=1000, dtype="bf16"), "f16", 32, 128, 3060224)]
+    (d3_inputs.ModelShape("odd", L=3, d=264, H=4, H_kv=2, hd=64, F=696, V=1000, dtype="bf16"), "f16", 32, 128, 3060224),
+    # few MLP rows, and passes whose columns are no multiple of 256
+    (d3_inputs.ModelShape("narrow-mlp", L=1, d=1536, H=12, H_kv=12, hd=128, F=128, V=512, dtype="bf16"), "f16", 1, 320, 81393408),
+    (d3_inputs.ModelShape("wide", L=1, d=8192, H=16, H_kv=8, hd=128, F=1088, V=32000, dtype="bf16"), "f32", 2, 146, 133369600),
+    (d3_inputs.ModelShape("hd64-narrow", L=1, d=2048, H=16, H_kv=2, hd=64, F=128, V=32000, dtype="bf16"), "f32", 16, 1658, 137675264)]
 
 
 @pytest.mark.parametrize("shape,kv,B,n,size", SMALLER)

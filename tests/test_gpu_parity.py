@@ -136,15 +136,21 @@ def test_prompts_of_several_passes_on_the_vector_alus(monkeypatch, shape, B, P, 
     helpers.compare(gpu, gens, 3, logit_atol=1e-4, hidden_tol=1e-5)
 
 
-@pytest.mark.parametrize("shape,kv,B,P,size", [
-    (ModelShape("smaller-ws", L=1, d=1536, H=12, H_kv=12, hd=128, F=2048, V=512, dtype="bf16"), "f16", 2, 590, 153336576),      # the smaller part buffer, 1280 columns
-    (d3_inputs.TINY, "f32", 8, 505, 8929792), (d3_inputs.TINY, "f32", 32, 120, 3172864)])       # passes of one sequence's columns, of all of them
-def test_prompts_in_a_workspace_of_an_earlier_size(monkeypatch, shape, kv, B, P, size):
-    # max_seq 600, 512 and 128: what d3_workspace_size gave for them when it asked for less
+NARROW_MLP = ModelShape("narrow-mlp", L=1, d=1536, H=12, H_kv=12, hd=128, F=128, V=512, dtype="bf16")
+
+
+@pytest.mark.parametrize("shape,kv,B,P,size,tile", [
+    (ModelShape("smaller-ws", L=1, d=1536, H=12, H_kv=12, hd=128, F=2048, V=512, dtype="bf16"), "f16", 2, 590, 153336576, None),      # the smaller part buffer, 1280 columns
+    (d3_inputs.TINY, "f32", 8, 505, 8929792, None), (d3_inputs.TINY, "f32", 32, 120, 3172864, None),       # passes of one sequence's columns, of all of them
+    (NARROW_MLP, "f16", 1, 310, 81393408, None), (NARROW_MLP, "f16", 1, 310, 81393408, "256")])            # split activations of 384 columns, which tiles of 256 would read 512 of
+def test_prompts_in_a_workspace_of_an_earlier_size(monkeypatch, shape, kv, B, P, size, tile):
+    # max_seq 600, 512, 128 and 320: what d3_workspace_size gave for them when it asked for less
     import torch
     from paper_2503_08524_amd import binding
     w, toks = binding.weights_to_device(shape, d3_inputs.make_weights(shape, 0), "cuda:0"), torch.from_numpy(d3_inputs.make_prompt(B, P, shape.V, seed=1)).to("cuda:0")
-    rows = {590: 600, 505: 512, 120: 128}[P]
+    rows = {590: 600, 505: 512, 120: 128, 310: 320}[P]
+    if tile:
+        monkeypatch.setenv("D3_PROMPT_TILE", tile)
     print(f"case smaller workspace {shape.name} B={B} P={P}", flush=True)
 
     def run():
@@ -223,12 +229,12 @@ def test_small_bf16_matrix_core_path(B, P):
     _run(SMALL_BF16, B, P, 8, 0.9, 2, forced_seed=7)
 
 
-# planar split: decode and prompt passes of 9 to 16 columns, heads of as many and of fewer columns behind them, heads of 9 to 16 columns behind a wider pass (hi and lo
-# in one line), contractions whose last turn is ragged, grouped queries
+# split activations in planes: decode and prompt passes of 9 to 16 columns, heads of as many and of fewer columns behind them, heads of 9 to 16 columns behind a wider
+# pass, contractions whose last turn is ragged, grouped queries
 @pytest.mark.parametrize("B,P,d,F,H_kv,kv", [(9, 1, 96, 160, 2, "f32"), (16, 1, 256, 416, 1, "f16"), (1, 13, 96, 160, 1, "f32"), (3, 4, 160, 96, 2, "f32"), (8, 2, 256, 224, 2, "f32"),
                                              (12, 3, 160, 288, 1, "f32"), (16, 9, 256, 512, 2, "f32"), (1, 75, 96, 160, 2, "f32"), (11, 5, 32, 32, 1, "f16")])
 def test_nine_to_sixteen_columns(B, P, d, F, H_kv, kv):
-    s = ModelShape("planar", L=3, d=d, H=2, H_kv=H_kv, hd=64, F=F, V=512, dtype="bf16")
+    s = ModelShape("planes", L=3, d=d, H=2, H_kv=H_kv, hd=64, F=F, V=512, dtype="bf16")
     gpu, gens = _run(s, B, P, 4, 0.97, 2, forced_seed=19, kv_dtype=kv)
     helpers.compare(gpu, gens, 4, **({} if kv == "f16" else {"logit_atol": 2e-4, "hidden_tol": 1e-4}))
 
