@@ -38,7 +38,7 @@ __device__ __forceinline__ float group_sum(float v) {
 // What the first loads need of the arguments, requested together: read as they come up, each is a round trip to memory that the next one waits behind.
 __device__ __forceinline__ void attn_take_args(const AttnArgs& a) {
     asm volatile("" :: "s"(a.q), "s"(a.rope_cs), "s"(a.row0), "s"(a.q_stride), "s"(a.k_cache), "s"(a.v_cache), "s"(a.cm.base), "s"(a.cm.pos_begin),
-                       "s"(a.cm.seq0), "s"(a.H), "s"(a.H_kv), "s"(a.max_seq), "s"(a.split_len), "s"(a.by_b.d), "s"(a.by_b.m), "s"(a.by_group.m), "s"(a.by_split.m), "s"(a.out_form.pitch), "s"(a.out_form.lo));
+                       "s"(a.cm.seq0), "s"(a.H), "s"(a.H_kv), "s"(a.max_seq), "s"(a.split_len), "s"(a.by_b.d), "s"(a.by_b.m), "s"(a.by_group.m), "s"(a.by_split.m), "s"(a.out_form.lo));
 }
 // position of column c of the pass, counted from the start of the pass, and its sequence (ColMap's, without its division)
 __device__ __forceinline__ int attn_step_of(const AttnArgs& a, int c) { return a.by_b.of(a.cm.base + c); }
@@ -82,7 +82,7 @@ __device__ __forceinline__ void attn_merge_publish(const AttnArgs& a, int split,
             const float r = o / L;
             const size_t oi = (size_t)ce * a.H * HD + (size_t)he * HD + t;
             if (FUSED) st_agent(&a.out[oi], r); else a.out[oi] = r;
-            if (a.out_split) store_split1(a.out_split + ce * (size_t)a.out_form.pitch, he * HD + t, r, a.out_form.lo);
+            if (a.out_split) store_split1(a.out_split + ce * a.out_form.pitch(a.H * HD), he * HD + t, r, a.out_form.lo);
             continue;
         }
         const size_t pidx = ((size_t)ce * a.H + he) * a.n_splits + split;
@@ -152,7 +152,7 @@ __device__ __forceinline__ void attn_merge_publish(const AttnArgs& a, int split,
         const float r = o[i] / L[i];
         const size_t oi = (size_t)ce * a.H * HD + (size_t)(h0 + ge % GH) * HD + idx % HD;
         if (FUSED) st_agent(&a.out[oi], r); else a.out[oi] = r;
-        if (a.out_split) store_split1(a.out_split + ce * (size_t)a.out_form.pitch, (h0 + ge % GH) * HD + idx % HD, r, a.out_form.lo);
+        if (a.out_split) store_split1(a.out_split + ce * a.out_form.pitch(a.H * HD), (h0 + ge % GH) * HD + idx % HD, r, a.out_form.lo);
     }
 }
 

@@ -301,7 +301,7 @@ __global__ __launch_bounds__(512, 2) void attn_prompt_kernel(AttnArgs a, SeqRuns
         if (c >= c_end) continue;
         const float4 u = o[en * 32 + ((2 * part) ^ en)], w = o[en * 32 + ((2 * part + 1) ^ en)];
         const float f[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
-        store_split8(a.out_split + c * (size_t)a.out_form.pitch, (size_t)(h0 + (32 * wave + en) % GH) * HD + 8 * part, f, a.out_form.lo);
+        store_split8(a.out_split + c * a.out_form.pitch(a.H * HD), (size_t)(h0 + (32 * wave + en) % GH) * HD + 8 * part, f, a.out_form.lo);
     }
 }
 

@@ -496,7 +496,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     const PromptDims dims{dm, qdim, qkv_dim, F, qtile};
     const bool whole_tiles = (size_t)(ncols + 255) / 256 * 256 <= c->lay.split_cols;
     const bool lines = ncols <= 8 || (mfma && whole_tiles && (takes_large_tiles(d) || c->tn.prompt_tile == 256) && prompt_pass_in_lines(dims, ncols, c->lay.gemm_part_bytes, c->n_cu, c->tn));
-    auto form = [&](int K) { return lines ? split_lines(K) : split_planes(K, c->lay.split_cols); };
+    auto form = [&](int K) { return lines ? split_lines() : split_planes(K, c->lay.split_cols); };
     const EmbedSplit split{mfma ? gain_after(-1) : nullptr, n_split, ssq, form(dm)};
     int2* col_at = qtile ? c->at<int2>(c->lay.col_at) : nullptr;
     if (qtile) D3_HIP(launch_embed_runs(c->tok_emb, tokens, runs, cm.P, cm.pos_begin, ncols, dm, d.vocab, x, c->at<double>(c->lay.inv_freq), hd / 2, rope_cs, row0, col_at, split, s));
@@ -529,7 +529,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         if (!saved && l >= save_before) D3_HIP(save_skip());
         // --- attention half: x += Wo . attention(RoPE(Wq a), cache) with a = RMSNorm(x) ---
         GemvArgs g{};
-        g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = (unsigned)c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
         g.K = dm; g.eps = d.rms_eps;
         g.w[0] = w.wq; g.w[1] = w.wk; g.w[2] = w.wv;
         g.rows[0] = qdim; g.rows[1] = kvdim; g.rows[2] = kvdim; g.total_rows = qkv_dim;
@@ -577,7 +577,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
                 own.ncols = runs.col[r + 1] - col;
                 own.cm = ColMap{0, 1, own.ncols, runs.pos[r], runs.seq[r]};
                 own.q += (size_t)col * qkv_dim;
-                own.out += (size_t)col * qdim; own.out_split += (size_t)col * at.out_form.pitch;
+                own.out += (size_t)col * qdim; own.out_split += col * at.out_form.pitch(qdim);
                 pick_splits(c, own.ncols, runs.pos[r] + own.ncols, c->attn_wgs_per_cu * c->n_cu, &own.split_len, &own.n_splits, true);
                 Timed t(c, D3_K_ATTN, s);
                 D3_HIP(launch_attention(own, d.kv_dtype, true, s));
@@ -589,7 +589,7 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
         }
 
         GemvArgs o{};
-        o.part = c->at<float>(c->lay.gemm_part); o.part_bytes = c->lay.gemm_part_bytes; o.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        o.part = c->at<float>(c->lay.gemm_part); o.part_bytes = (unsigned)c->lay.gemm_part_bytes; o.part_tickets = c->at<int>(c->lay.gemm_tickets);
         o.K = qdim; o.w[0] = w.wo; o.rows[0] = dm; o.total_rows = dm; o.out = x; o.out_stride = dm; o.ncols = ncols;
         {
             Timed t(c, D3_K_OPROJ, s);
@@ -603,11 +603,11 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
 
         // --- SwiGLU half: x += Wd (silu(Wg m) * (Wu m)) with m = RMSNorm(x) ---
         GemvArgs u{};
-        u.part = c->at<float>(c->lay.gemm_part); u.part_bytes = c->lay.gemm_part_bytes; u.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        u.part = c->at<float>(c->lay.gemm_part); u.part_bytes = (unsigned)c->lay.gemm_part_bytes; u.part_tickets = c->at<int>(c->lay.gemm_tickets);
         u.K = dm; u.eps = d.rms_eps; u.w[0] = w.w_gate; u.w[1] = w.w_up; u.rows[0] = F; u.rows[1] = F; u.total_rows = F;
         u.out_stride = F; u.ncols = ncols;
         GemvArgs dn{};
-        dn.part = c->at<float>(c->lay.gemm_part); dn.part_bytes = c->lay.gemm_part_bytes; dn.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        dn.part = c->at<float>(c->lay.gemm_part); dn.part_bytes = (unsigned)c->lay.gemm_part_bytes; dn.part_tickets = c->at<int>(c->lay.gemm_tickets);
         dn.K = F; dn.w[0] = w.w_down; dn.rows[0] = dm; dn.total_rows = dm; dn.out = x; dn.out_stride = dm; dn.ncols = ncols;
         if (mfma) {
             u.x_split = n_split; u.x_form = form(dm); u.ssq_in = ssq; u.ssq_parts = ssq_parts;
@@ -630,11 +630,11 @@ int forward(d3_ctx* c, const int32_t* tokens, ColMap cm, int ncols, const int32_
     if (!saved) D3_HIP(save_skip());
     if (head) {
         GemvArgs g{};
-        g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = (unsigned)c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
         g.K = dm; g.eps = d.rms_eps; g.w[0] = c->lm_head; g.rows[0] = d.vocab; g.total_rows = d.vocab;
         g.out = head->logits; g.out_stride = d.vocab; g.ncols = head->n_cols;
         if (mfma) {
-            g.x_form = form(dm); g.x_split = n_split + (size_t)head->first_col * g.x_form.pitch;
+            g.x_form = form(dm); g.x_split = n_split + head->first_col * g.x_form.pitch(dm);
             g.ssq_in = ssq + (size_t)head->first_col * kSsqStride; g.ssq_parts = ssq_parts;
             Timed t(c, D3_K_LM_HEAD, s);
             D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s));
@@ -715,9 +715,9 @@ int prefill_shared(d3_ctx* c, const int32_t* tokens, int B, int P, int pos_begin
     bf16_t* n_split = c->at<bf16_t>(c->lay.n_split);
     float* ssq = c->at<float>(c->lay.ssq);
     GemvArgs g{};
-    g.x_form = B <= 8 ? split_lines(dm) : split_planes(dm, c->lay.split_cols);
+    g.x_form = B <= 8 ? split_lines() : split_planes(dm, c->lay.split_cols);
     D3_HIP(launch_gain_split(h_last, dm, static_cast<const float*>(c->final_norm), dm, B, n_split, ssq, g.x_form, s));
-    g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
+    g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = (unsigned)c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
     g.K = dm; g.eps = d.rms_eps; g.w[0] = c->lm_head; g.rows[0] = d.vocab; g.total_rows = d.vocab;
     g.out = logits; g.out_stride = d.vocab; g.ncols = B;
     g.x_split = n_split; g.ssq_in = ssq; g.ssq_parts = 1;
@@ -944,13 +944,13 @@ int fill_recompute(d3_ctx* c, int pos_begin, int pos_end, hipStream_t s) {
         void* k_layer = c->k_cache + (size_t)l * c->kv_layer_bytes();
         void* v_layer = c->v_cache + (size_t)l * c->kv_layer_bytes();
         GemvArgs g{};
-        g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
+        g.part = c->at<float>(c->lay.gemm_part); g.part_bytes = (unsigned)c->lay.gemm_part_bytes; g.part_tickets = c->at<int>(c->lay.gemm_tickets);
         g.K = dm; g.eps = d.rms_eps; g.w[0] = w.wk; g.w[1] = w.wv; g.rows[0] = kvdim; g.rows[1] = kvdim; g.total_rows = 2 * kvdim;
         g.out = kv; g.out_stride = 2 * kvdim; g.ncols = B;
         if (mfma) {
             bf16_t* n_split = c->at<bf16_t>(c->lay.n_split);
             float* ssq = c->at<float>(c->lay.ssq);
-            g.x_form = B <= 8 ? split_lines(dm) : split_planes(dm, c->lay.split_cols);
+            g.x_form = B <= 8 ? split_lines() : split_planes(dm, c->lay.split_cols);
             D3_HIP(launch_gain_split(h, dm, static_cast<const float*>(w.attn_norm), dm, B, n_split, ssq, g.x_form, s));
             g.x_split = n_split; g.ssq_in = ssq; g.ssq_parts = 1;
             D3_HIP(launch_gemm_mfma(g, MODE_STORE, c->n_cu, c->tn, s));

@@ -8,7 +8,7 @@ namespace d3 {
 
 constexpr int kWave = 64;          // CDNA wavefront
 constexpr int kMaxCols = 32;       // largest batch; columns of a decode pass
-// Most columns of a prompt pass on the matrix-core path (a context holds min(this, n rounded up to 128), n = the cache rows of one sequence, or of all where they share
+// Most columns of a prompt pass (a context holds min(this, n rounded up to 128), half of this with an fp32 cache or on the vector ALUs, n = the cache rows of one sequence, or of all where they share
 // passes).  The 7B widths' O and down projections are 128 of the large tiles at 2048 columns, a full round of compute units at 4096: 32 x 2048 tokens, 2 blocks, 79.0 ms in
 // passes of 2048, 74.7 of 4096, 74.9 of 8192.
 constexpr int kPassCols = 4096;
@@ -93,12 +93,16 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
 //    by shorter pieces.  Lines / planes, us: a block's four projections at 14 columns of the 7B shape 98.5 / 96.5; prompts: 2048 wide, head_dim 64, 256 columns 554 / 541 (its down
 //    projection 52 / 41), 70B widths, 128 columns, 1179 / 1154, 13B widths, 129 columns, 708 / 693, 7B shape, 128 columns, 492 / 488; decode steps of 17 to 32 columns equal to 0.5 %.
 //    Rows of lines padded by 128 to 1152 bytes mend the first and the third and cost the second 2 to 7 %.
-// pitch: halves from column to column; lo: halves from a value's hi half to its lo half.
-struct SplitForm { int pitch; size_t lo; };
+// lo: halves from a value's hi half to its lo half, which in planes is far more than in lines; pitch: halves from column to column.  (Kept in the arguments of every launch, so no larger
+// than a pointer: with the pitch beside it small launches took 0.1 us more, 1024 wide, 5 prompts of 2 tokens, 2 blocks, 339.5 -> 336 us.)
 constexpr int kSplitLo = 32;
-inline SplitForm split_lines(int K) { return SplitForm{2 * K, kSplitLo}; }
-inline SplitForm split_planes(int K, size_t columns) { return SplitForm{K, columns * K}; }     // columns: of the whole plane, 32 or more
-__host__ __device__ __forceinline__ bool split_in_lines(const SplitForm& f, int K) { return f.pitch == 2 * K; }
+struct SplitForm {
+    size_t lo;
+    __host__ __device__ __forceinline__ bool lines() const { return lo == kSplitLo; }
+    __host__ __device__ __forceinline__ size_t pitch(size_t K) const { return lines() ? 2 * K : K; }
+};
+inline SplitForm split_lines() { return SplitForm{kSplitLo}; }
+inline SplitForm split_planes(int K, size_t columns) { return SplitForm{columns * K}; }     // columns: of the whole plane, 32 or more
 // where in its row value k's hi half is (k, k + 1, ... of one run of 32 are adjacent); a kernel that knows the form says so
 enum { SPLIT_ANY, SPLIT_LINES, SPLIT_PLANES };
 template <int FORM = SPLIT_ANY>
@@ -184,8 +188,8 @@ struct GemvArgs {
     const float* x;
     const bf16_t* x_split;
     SplitForm x_form;
-    size_t part_bytes;   // what part holds
     int x_stride;        // ALU path
+    unsigned part_bytes; // what part holds (kPromptPartBytes256 at most)
     const float* gain;   // RMSNorm gain [K] when the norm is fused (ALU path), else nullptr
     float eps;
     int K;

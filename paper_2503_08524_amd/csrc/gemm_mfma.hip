@@ -325,8 +325,8 @@ int launch_gemm_mfma(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hi
     const int nt = a.ncols > 16 ? 2 : 1;
     if (gemm_prompt_takes(a, mode, tn)) return launch_gemm_prompt(a, mode, n_cu, tn, s, n_groups);
     if (mode == MODE_QKV_ROPE) return (int)hipErrorInvalidValue;
-    const bool lines = split_in_lines(a.x_form, a.K);
-    if (lines ? a.ncols > 8 : a.x_form.pitch != a.K) return (int)hipErrorInvalidValue;      // lines: the packed kernel alone
+    const bool lines = a.x_form.lines();
+    if (lines && a.ncols > 8) return (int)hipErrorInvalidValue;      // lines: the packed kernel alone
     if (nt == 2 && a.part && tn.mfma_wide) return launch_gemm_mfma_wide(a, mode, n_cu, tn, s, n_groups);
     if (a.ncols > kMaxCols) return (int)hipErrorInvalidValue;
     const int sw = mode == MODE_SWIGLU ? 2 : 1;

@@ -389,9 +389,9 @@ int launch_config(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, hipSt
 GemvArgs columns_of(const GemvArgs& a, int first, int n) {
     GemvArgs g = a;
     g.ncols = n;
-    g.x_split += (size_t)first * a.x_form.pitch;
+    g.x_split += first * a.x_form.pitch(a.K);
     if (g.out) g.out += (size_t)first * a.out_stride;
-    if (g.out_split) g.out_split += (size_t)first * a.out_form.pitch;
+    if (g.out_split) g.out_split += first * a.out_form.pitch(a.out_stride);
     if (g.ssq_in) g.ssq_in += (size_t)first * kSsqStride;
     if (g.ssq_out) g.ssq_out += (size_t)first * kSsqStride;
     return g;

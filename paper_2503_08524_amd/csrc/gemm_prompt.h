@@ -83,8 +83,8 @@ __device__ __forceinline__ void store_row4(f16_t* p, const float (&v)[4]) {
 
 // ---- epilogues of the projections that only store, from the summed accumulators of one column tile: lane (i, g) holds column i, rows 4g..4g+3 of each
 // row tile.  units: which units to store, bit r for row tiles r and r + 4; sc: the column's RMSNorm scale. ----
-// otile0: the wave's first output row tile of `tiles`
-template <int MODE>
+// otile0: the wave's first output row tile of `tiles`; FORM: of the split output (its column pitch is out_form's, or known)
+template <int MODE, int FORM = SPLIT_ANY>
 __device__ __forceinline__ void store_tiles(const GemvArgs& a, const f32x4 (&acc)[RW], unsigned units, int otile0, int tiles, int col, float sc) {
     constexpr int SW = (MODE == MODE_SWIGLU) ? 2 : 1;
     const int lg = (threadIdx.x & 63) >> 4;
@@ -100,7 +100,7 @@ __device__ __forceinline__ void store_tiles(const GemvArgs& a, const f32x4 (&acc
         }
         if (otile < tiles && col < a.ncols) {
             if (a.out) *reinterpret_cast<float4*>(a.out + (size_t)col * a.out_stride + row) = make_float4(v[0], v[1], v[2], v[3]);
-            if (a.out_split) store_split4(a.out_split + (size_t)col * a.out_form.pitch, row, v, a.out_form.lo);
+            if (a.out_split) store_split4<FORM>(a.out_split + col * (FORM == SPLIT_LINES ? 2 * (size_t)a.out_stride : a.out_form.pitch(a.out_stride)), row, v, a.out_form.lo);
         }
     }
 }

@@ -126,7 +126,7 @@ __device__ __forceinline__ void add_residual(const GemvArgs& a, char* lds, int r
             store_row4(a.out + oi, v);
             if (a.out_split) {                         // a normalised projection reads it next: hand it x * gain (and sum(x^2) below)
                 const float w[4] = {v[0] * gain.x, v[1] * gain.y, v[2] * gain.z, v[3] * gain.w};
-                store_split4(a.out_split + (size_t)(cb * kTileN + column(i)) * a.out_form.pitch, row, w, a.out_form.lo);
+                store_split4(a.out_split + (cb * kTileN + column(i)) * a.out_form.pitch(a.out_stride), row, w, a.out_form.lo);
             }
         }
     }
@@ -747,7 +747,7 @@ int launch_gemm_prompt(const GemvArgs& a, int mode, int n_cu, const Tuning& tn, 
     const int cus = tn.prompt_cus ? tn.prompt_cus : n_cu;
     const bool parts = a.part && a.part_tickets;
     if (mode == MODE_QKV_ROPE && (a.hd != 128 || !a.ssq_in || !a.col_at || !a.rope_cs || (a.kv_dtype != 0 && a.kv_dtype != 2))) return (int)hipErrorInvalidValue;
-    if (split_in_lines(a.x_form, a.K)) {
+    if (a.x_form.lines()) {
         if ((mode == MODE_RESID || a.ssq_in) && prompt_takes_large_tiles(mode, a.total_rows, a.K, a.ncols, parts ? a.part_bytes : 0, cus, tn))
             return launch_gemm_prompt_256(a, mode, cus, s, n_groups);
     }

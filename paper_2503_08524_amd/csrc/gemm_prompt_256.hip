@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_256_kernel(Args256) {
                             if (a.out_split) {         // a normalised projection reads it next: hand it x * gain (and sum(x^2) below)
                                 const float4 gn = gain[hf];
                                 const float w[4] = {v[0] * gn.x, v[1] * gn.y, v[2] * gn.z, v[3] * gn.w};
-                                store_split4(a.out_split + (size_t)column(tt, i) * a.out_form.pitch, row_w + 64 * hf, w, a.out_form.lo);
+                                store_split4<SPLIT_LINES>(a.out_split + (size_t)column(tt, i) * 2 * a.out_stride, row_w + 64 * hf, w, kSplitLo);
                             }
                         }
                     }
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_prompt_256_kernel(Args256) {
                     f32x4 sum[RW];
 #pragma unroll
                     for (int r = 0; r < RW; ++r) sum[r] = acc[r][tt];
-                    store_tiles<MODE>(a, sum, 15u, rb * OT + wy * (RW / SW), tiles, col0 + 16 * tt + li, __shfl(inv, 16 * tt + li, 64));
+                    store_tiles<MODE, SPLIT_LINES>(a, sum, 15u, rb * OT + wy * (RW / SW), tiles, col0 + 16 * tt + li, __shfl(inv, 16 * tt + li, 64));
                 }
             }
         }
@@ -574,10 +574,10 @@ double gemm_prompt_256_cost(int mode, int total_rows, int K, int ncols, size_t p
     return o.rounds * (stage * o.stages + tile) + (o.rest ? stage * o.main + cut : o.n_rb * o.n_cb % o.n_wg ? idle : 0);
 }
 
-// Requirements: those of launch_gemm_prompt and a finite cost; x_split in lines, of ncols columns rounded up to 256; ssq_in, unless MODE_RESID.
+// Requirements: those of launch_gemm_prompt and a finite cost; x_split in lines, of ncols columns rounded up to 256, out_split in lines; ssq_in, unless MODE_RESID.
 int launch_gemm_prompt_256(const GemvArgs& a, int mode, int n_cu, hipStream_t s, int* n_groups) {
     Order256 o;
-    if (!split_in_lines(a.x_form, a.K) || (mode != MODE_RESID && !a.ssq_in) || !plan_256(mode, a.total_rows, a.K, a.ncols, a.part && a.part_tickets ? a.part_bytes : 0, n_cu, &o)) return (int)hipErrorInvalidValue;
+    if (!a.x_form.lines() || (a.out_split && !a.out_form.lines()) || (mode != MODE_RESID && !a.ssq_in) || !plan_256(mode, a.total_rows, a.K, a.ncols, a.part && a.part_tickets ? a.part_bytes : 0, n_cu, &o)) return (int)hipErrorInvalidValue;
     if (n_groups) *n_groups = o.n_rb;
     if (mode == MODE_QKV_ROPE) return launch_256<MODE_QKV_ROPE>(a, o, s);
     if (mode == MODE_SWIGLU) return launch_256<MODE_SWIGLU>(a, o, s);

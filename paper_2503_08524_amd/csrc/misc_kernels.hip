@@ -56,7 +56,7 @@ __device__ __forceinline__ void embed_column(const W* __restrict__ emb, int tok,
                         ss += f[e] * f[e];
                         w[e] = f[e] * g[e];
                     }
-                    store_split8(split.split + (size_t)c * split.form.pitch, j, w, split.form.lo);
+                    store_split8(split.split + c * split.form.pitch(d), j, w, split.form.lo);
                 }
             }
         }
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void gain_split_kernel(const float* __restrict
     auto emit = [&](int i4, const float4& t, const float4& gg) {
         const float f[4] = {t.x * gg.x, t.y * gg.y, t.z * gg.z, t.w * gg.w};
         ss += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
-        store_split4(split + (size_t)c * form.pitch, i4 * 4, f, form.lo);
+        store_split4(split + c * form.pitch(K), i4 * 4, f, form.lo);
     };
     float4 v[R], g[R];
 #pragma unroll
