@@ -212,7 +212,7 @@ def test_recompute_fill_matches_oracle_and_continuation_reads_it(B, start, kv):
 
 @pytest.mark.parametrize("B", [9, 16])
 def test_recompute_fill_of_nine_to_sixteen_columns(B):
-    # the kept residual, split in the planar form that the projections of so many columns read
+    # the kept residual, split into the planes that the projections of so many columns read
     from paper_2503_08524_amd import binding
     shape, P, G, alpha, start = SHAPE, 6, 9, 0.8, 2
     w = d3_inputs.make_weights(shape, 2)
